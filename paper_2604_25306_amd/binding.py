@@ -1,4 +1,5 @@
-"""ctypes binding of the C ABI in include/qflash.h (same names, argument marshalling only)."""
+"""Python binding of the C ABI in include/qflash.h (same names, argument marshalling only).  The calls
+that enqueue work go through a small compiled module (csrc/qflash_py.cpp), the rest through ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -177,24 +178,25 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
-def _marshal(Q, K, V, O, bias, stream):
-    import torch
-    for name, t in (("Q", Q), ("K", K), ("V", V), ("O", O)):
-        if t.dtype != torch.int8 or not t.is_cuda or not t.is_contiguous() or t.dim() != 4:
-            raise ValueError("%s must be a contiguous int8 CUDA tensor [B,H,N,d]" % name)
-        if t.shape != Q.shape:
-            raise ValueError("Q, K, V, O must share one shape")
-    B, H, N, d = Q.shape
-    bias_B = bias_H = 0
-    if bias is not None:
-        if bias.dtype != torch.int32 or not bias.is_cuda or not bias.is_contiguous() \
-                or bias.dim() != 4 or tuple(bias.shape[2:]) != (N, N):
-            raise ValueError("bias must be a contiguous int32 CUDA tensor [bias_B,bias_H,N,N]")
-        bias_B, bias_H = int(bias.shape[0]), int(bias.shape[1])
-    if stream is None:
-        stream = torch.cuda.current_stream(Q.device).cuda_stream
-    return (_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(bias), bias_B, bias_H,
-            int(B), int(H), int(N), int(d)), ctypes.c_void_p(stream)
+_native_mod = None
+
+
+def _native():
+    """The compiled half of this binding (csrc/qflash_py.cpp): tensor checks and the call itself."""
+    global _native_mod
+    if _native_mod is None:
+        load_library()
+        import torch  # noqa: F401  (its libraries have to be loaded first)
+        try:
+            from . import _qflash_native
+        except ImportError as e:
+            raise RuntimeError("_qflash_native.so is missing or stale: build it with "
+                               "`python -m paper_2604_25306_amd.build`.") from e
+        _native_mod = _qflash_native
+    return _native_mod
+
+
+_PER_TENSOR, _STATIC, _PER_HEAD = 0, 1, 2       # first argument of _qflash_native.attention
 
 
 def qflash_attention(ctx: int, Q, K, V, O, params: QFlashParams, kv_tile: int, bias=None,
@@ -202,8 +204,7 @@ def qflash_attention(ctx: int, Q, K, V, O, params: QFlashParams, kv_tile: int, b
     """Enqueue one forward pass.  Q, K, V, O: contiguous int8 CUDA tensors [B,H,N,d];
     bias: None or contiguous int32 CUDA tensor [bias_B,bias_H,N,N].  ``stream`` is a raw
     hipStream_t value (default: torch's current stream on the tensors' device)."""
-    args, st = _marshal(Q, K, V, O, bias, stream)
-    rc = load_library().qflash_attention(ctypes.c_void_p(ctx), *args, int(kv_tile), ctypes.byref(params), st)
+    rc = (_native_mod or _native()).attention(_PER_TENSOR, ctx, Q, K, V, O, params, kv_tile, bias, stream)
     if rc != 0:
         raise QFlashError(rc, "qflash_attention")
 
@@ -211,9 +212,7 @@ def qflash_attention(ctx: int, Q, K, V, O, params: QFlashParams, kv_tile: int, b
 def qflash_attention_static(ctx: int, Q, K, V, O, params: QFlashParams, kv_tile: int, bias=None,
                             stream: Optional[int] = None) -> None:
     """``qflash_attention`` through the entry point that allocates no device memory."""
-    args, st = _marshal(Q, K, V, O, bias, stream)
-    rc = load_library().qflash_attention_static(ctypes.c_void_p(ctx), *args, int(kv_tile),
-                                                ctypes.byref(params), st)
+    rc = (_native_mod or _native()).attention(_STATIC, ctx, Q, K, V, O, params, kv_tile, bias, stream)
     if rc != 0:
         raise QFlashError(rc, "qflash_attention_static")
 
@@ -228,12 +227,8 @@ def params_array(params):
 def qflash_attention_per_head(ctx: int, Q, K, V, O, params, kv_tile: int, bias=None,
                               stream: Optional[int] = None) -> None:
     """The same with one ``QFlashParams`` per head (a sequence of H of them, or ``params_array`` of it)."""
-    args, st = _marshal(Q, K, V, O, bias, stream)
     arr = params if isinstance(params, ctypes.Array) else params_array(params)
-    if len(arr) != args[8]:
-        raise ValueError("need one QFlashParams per head")
-    rc = load_library().qflash_attention_per_head(
-        ctypes.c_void_p(ctx), *args, int(kv_tile), ctypes.cast(arr, ctypes.POINTER(QFlashParams)), st)
+    rc = (_native_mod or _native()).attention(_PER_HEAD, ctx, Q, K, V, O, arr, kv_tile, bias, stream)
     if rc != 0:
         raise QFlashError(rc, "qflash_attention_per_head")
 
@@ -264,21 +259,9 @@ def qflash_attention_packed_bias(ctx: int, Q, K, V, O, params, kv_tile: int, pac
                                  bias_H: int, stream: Optional[int] = None) -> None:
     """The forward pass with a bias packed by ``qflash_pack_bias`` for the same bias_B, bias_H, N.
     ``params``: one QFlashParams or a sequence of H."""
-    import torch
-    args, st = _marshal(Q, K, V, O, None, stream)
-    if packed.dtype != torch.int32 or not packed.is_cuda or not packed.is_contiguous():
-        raise ValueError("packed must be a contiguous int32 CUDA tensor")
-    # same figure as qflash_packed_bias_bytes, without a call into the library per launch
-    if packed.numel() < int(bias_B) * int(bias_H) * ((args[9] + 31) // 32) ** 2 * 1024:
-        raise ValueError("packed is smaller than qflash_packed_bias_bytes(bias_B, bias_H, N)")
-    if isinstance(params, QFlashParams):
-        pp, n_p = ctypes.byref(params), 1
-    else:
-        arr = params if isinstance(params, ctypes.Array) else params_array(params)
-        pp, n_p = ctypes.cast(arr, ctypes.POINTER(QFlashParams)), len(arr)
-    rc = load_library().qflash_attention_packed_bias(
-        ctypes.c_void_p(ctx), args[0], args[1], args[2], args[3], _ptr(packed), int(bias_B), int(bias_H),
-        args[7], args[8], args[9], args[10], int(kv_tile), pp, n_p, st)
+    if not isinstance(params, (QFlashParams, ctypes.Array)):
+        params = params_array(params)
+    rc = (_native_mod or _native()).attention_packed_bias(ctx, Q, K, V, O, params, kv_tile, packed, bias_B, bias_H, stream)
     if rc != 0:
         raise QFlashError(rc, "qflash_attention_packed_bias")
 
@@ -322,45 +305,11 @@ def qflash_attention_dynamic(ctx: int, Qf, Kf, Vf, O, kv_tile: int, workspace, i
     ``info``: None or a uint8 CUDA tensor of ``ctypes.sizeof(DynamicInfo)`` bytes;
     ``bias_real`` / ``excluded``: None, or float32 / uint8 CUDA tensors [bias_B,bias_H,N,N] (a bias in
     real units and an exclusion mask: qflash_attention_dynamic_bias)."""
-    import torch
-    ref = bias_real if bias_real is not None else excluded
-    if ref is not None:
-        if bias_real is not None and (bias_real.dtype != torch.float32 or not bias_real.is_cuda
-                                      or not bias_real.is_contiguous() or bias_real.dim() != 4):
-            raise ValueError("bias_real must be a contiguous float32 CUDA tensor [bias_B,bias_H,N,N]")
-        if excluded is not None and (excluded.dtype != torch.uint8 or not excluded.is_cuda
-                                     or not excluded.is_contiguous() or excluded.shape != ref.shape):
-            raise ValueError("excluded must be a contiguous uint8 CUDA tensor of the bias shape")
-        if tuple(ref.shape[2:]) != (Qf.shape[2], Qf.shape[2]):
-            raise ValueError("bias must be [bias_B,bias_H,N,N]")
-    for name, t in (("Qf", Qf), ("Kf", Kf), ("Vf", Vf)):
-        if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous() or t.dim() != 4 \
-                or t.shape != Qf.shape:
-            raise ValueError("%s must be a contiguous float32 CUDA tensor [B,H,N,d]" % name)
-    if O.dtype != torch.int8 or not O.is_cuda or not O.is_contiguous() or O.shape != Qf.shape:
-        raise ValueError("O must be a contiguous int8 CUDA tensor [B,H,N,d]")
-    if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
-        raise ValueError("workspace must be a contiguous uint8 CUDA tensor")
-    if info is not None and (info.dtype != torch.uint8 or not info.is_cuda
-                             or info.numel() < ctypes.sizeof(DynamicInfo)):
-        raise ValueError("info must be a uint8 CUDA tensor of sizeof(DynamicInfo) bytes")
-    B, H, N, d = Qf.shape
-    if stream is None:
-        stream = torch.cuda.current_stream(Qf.device).cuda_stream
-    if ref is not None:
-        rc = load_library().qflash_attention_dynamic_bias(
-            ctypes.c_void_p(ctx), _ptr(Qf), _ptr(Kf), _ptr(Vf), _ptr(O), _ptr(bias_real), _ptr(excluded),
-            int(ref.shape[0]), int(ref.shape[1]), int(B), int(H), int(N), int(d), int(kv_tile), int(out_round),
-            _ptr(info), _ptr(workspace), int(workspace.numel()), ctypes.c_void_p(stream))
-        if rc != 0:
-            raise QFlashError(rc, "qflash_attention_dynamic_bias")
-        return
-    rc = load_library().qflash_attention_dynamic(
-        ctypes.c_void_p(ctx), _ptr(Qf), _ptr(Kf), _ptr(Vf), _ptr(O), int(B), int(H), int(N), int(d),
-        int(kv_tile), int(out_round), _ptr(info), _ptr(workspace), int(workspace.numel()),
-        ctypes.c_void_p(stream))
+    rc = (_native_mod or _native()).attention_dynamic(ctx, Qf, Kf, Vf, O, kv_tile, workspace, info, out_round, stream,
+                                                      bias_real, excluded)
     if rc != 0:
-        raise QFlashError(rc, "qflash_attention_dynamic")
+        raise QFlashError(rc, "qflash_attention_dynamic" if bias_real is None and excluded is None
+                          else "qflash_attention_dynamic_bias")
 
 
 def qflash_peaks_mfma_i8(workgroups: int, iters: int, out, stream: Optional[int] = None) -> float:

@@ -1,4 +1,4 @@
-"""Builds libqflash.so (gfx950 only) in-tree with hipcc.
+"""Builds libqflash.so (gfx950 only, hipcc) and the compiled half of the Python binding (g++) in-tree.
 
     python -m paper_2604_25306_amd.build            # compile every source, link
     python -m paper_2604_25306_amd.build --changed  # recompile only sources older than their object
@@ -16,6 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqflash.so")
+NATIVE = os.path.join(HERE, "_qflash_native.so")
 SOURCES = ["qflash_api.cpp", "qflash_plan.cpp", "qflash_kernels.hip", "qflash_qmax.hip", "qflash_cu.hip", "qflash_win.hip", "qflash_ring.hip", "qflash_dynamic.hip", "qflash_peaks.hip"]
 
 HIPCC_FLAGS = [
@@ -59,7 +60,25 @@ def build(verbose: bool = True, only_changed: bool = False) -> str:
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wno-unused-command-line-argument"]
          + [os.path.join(OBJ, s + ".o") for s in SOURCES] + ["-o", tmp], verbose)
     os.replace(tmp, LIB)
+    _build_native(verbose)
     return LIB
+
+
+def _build_native(verbose: bool) -> None:
+    """The extension module over libqflash.so: host code only, against the installed torch."""
+    import sysconfig
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+          "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(tdir, "include"),
+          "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "qflash_py.cpp"), "-o", tmp,
+          "-L", HERE, "-l:libqflash.so", "-L", os.path.join(tdir, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+          "-ltorch_python", "-Wl,-rpath,$ORIGIN"], verbose)
+    os.replace(tmp, NATIVE)
 
 
 if __name__ == "__main__":
