@@ -106,7 +106,8 @@ int qflash_configure(qflash_ctx* ctx, int key, int value);
  *   slots_total, slots_in_use, slots_pinned (read by a captured graph: never rebuilt), evictions
  *   (slots rebuilt for other constants so far); last_weight_mode: QFLASH_WEIGHTS_ARITHMETIC, _TABLE
  *   (every head read its table) or _MIXED (per-head constants of which only some had a table) of the
- *   last qflash_attention / _per_head / _packed_bias call; last_kernel: as qflash_plan_info.kernel.
+ *   last qflash_attention / _per_head / _packed_bias call; last_kernel: as qflash_plan_info.kernel (the
+ *   family of the shape, also where qflash_plan_info.key_waves says that the keys are shared out).
  * Errors: NULL, CTX.
  */
 #define QFLASH_WEIGHTS_ARITHMETIC 0
@@ -334,6 +335,10 @@ int qflash_attention_dynamic_bias(qflash_ctx* ctx,
  *   units (pieces of work = workgroups that have rows), workgroups (launched; a few may be idle),
  *   tile_by_tile (1: KV tiles staged one ahead of their use), bias_period_units (0, or the number of
  *   units after which the bias slices repeat and by which workgroups are dealt to the 8 XCDs).
+ *   key_waves        0, or the number of wavefronts that share out the keys of a block of 32 query rows: a
+ *                    launch too small to fill the chip is decomposed that way instead, one workgroup per
+ *                    (batch, head, block of 32 query rows), whatever its kernel family; the other fields
+ *                    then say what a larger launch of the shape would do.
  * qflash_plan_unit: the unit that workgroup `workgroup` of such a launch takes, or -1 if it is one
  * of the idle ones (or out of range).  Every unit in [0, units) is taken by exactly one workgroup.
  * Errors: NULL, CTX, SHAPE, TILE.
@@ -341,7 +346,7 @@ int qflash_attention_dynamic_bias(qflash_ctx* ctx,
 typedef struct {
     int32_t kernel, pairs_per_workgroup, wavefronts_per_pair, query_blocks;
     int32_t units, workgroups, tile_by_tile, bias_period_units;
-    int32_t units_per_xcd, reserved[3];
+    int32_t units_per_xcd, key_waves, reserved[2];
 } qflash_plan_info;
 
 int qflash_plan_query(qflash_ctx* ctx /* or NULL */, int B, int H, int N, int d, int kv_tile,

@@ -70,7 +70,7 @@ class PlanInfo(ctypes.Structure):
     """Mirror of ``qflash_plan_info`` (how a call would be laid out on the GPU)."""
     _fields_ = [(n, ctypes.c_int32) for n in (
         "kernel", "pairs_per_workgroup", "wavefronts_per_pair", "query_blocks", "units", "workgroups",
-        "tile_by_tile", "bias_period_units", "units_per_xcd")] + [("reserved", ctypes.c_int32 * 3)]
+        "tile_by_tile", "bias_period_units", "units_per_xcd", "key_waves")] + [("reserved", ctypes.c_int32 * 2)]
 
 
 def library_path() -> str:

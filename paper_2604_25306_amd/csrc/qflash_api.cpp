@@ -162,8 +162,13 @@ extern "C" void qflash_debug_trace(void* buf) { g_trace = (unsigned long long*)b
 
 namespace {
 
+// Largest score difference (negated) with a weight above 0: x_p = ceil(8 s_inv / 2^k), 8 octaves; size of the table.
+int64_t table_span(const qflash_params& p) { return (8 * (int64_t)p.s_inv + ((int64_t)1 << p.x_shift) - 1) >> p.x_shift; }
+int table_bytes(int64_t x_p) { return ((int)x_p + 1 + 15) & ~15; }
+
 // The kernel family the plan chose.
 int launch_attention(QflashKernelArgs& a, int d, int kv_tile, int lds_limit, void* hip_stream) {
+    if (a.split_waves) return qflash_launch_fwd_split(a, d, lds_limit, hip_stream);
     if (a.win_mode) return qflash_launch_fwd_win(a, lds_limit, hip_stream);
     if (a.cu_mode) return qflash_launch_fwd_cu(a, lds_limit, hip_stream);
     if (a.ring_dma) {
@@ -175,6 +180,7 @@ int launch_attention(QflashKernelArgs& a, int d, int kv_tile, int lds_limit, voi
 
 // Whether the planned launch can hold a weight table of table_bytes in LDS and copying it pays.
 bool table_fits(const QflashKernelArgs& a, int d, int table_bytes, int lds_limit) {
+    if (a.split_waves) return table_bytes <= a.split_table_lds;
     if (a.win_mode) return table_bytes <= a.win_table_lds;      // staged once per compute unit
     if (a.cu_mode) return table_bytes <= a.cu_table_lds && 4ll * a.cu_heads * a.N * d >= (long long)table_bytes;
     return qflash_table_fits(a, d, table_bytes, lds_limit) != 0;
@@ -217,11 +223,11 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     // constants whose table is larger than that are refused, not silently run another way.
     int static_xp = 0, static_np = 0;
     if (static_table && table_wanted) {
-        const int64_t x_p = (8 * (int64_t)p[0].s_inv + ((int64_t)1 << p[0].x_shift) - 1) >> p[0].x_shift;
+        const int64_t x_p = table_span(p[0]);
         if (x_p + 16 > kScratchBytes) return QFLASH_ERR_SCRATCH;
         if (!scratch_ptr) return QFLASH_ERR_DEVICE;
         static_xp = (int)x_p;
-        static_np = ((int)x_p + 1 + 15) & ~15;
+        static_np = table_bytes(x_p);
     }
 
     static_assert(QFLASH_MAX_PARAM_HEADS == kQflashMaxParamHeads, "header and kernel arguments disagree");
@@ -249,17 +255,18 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     a.lut_bytes_max = 0;
     if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &a) != 0) return QFLASH_ERR_SHAPE;
     a.ring_table_lds = 0;
-    // The kernel that gives a whole compute unit to one workgroup, where the shape allows it: its LDS
-    // budget depends on the size of the weight table the call would use.
+    a.split_waves = 0;
+    // The kernels whose plan depends on the size of the weight table the call would use: the largest of all heads
+    // (the windowed and the whole-compute-unit kernel take one set of constants only).
     {
         int table_hint = 0;
         if (hc_dev) {
             table_hint = (table_wanted && dyn_table) ? kTableMaxBytes : 0;
-        } else if (static_table) {
-            table_hint = static_np;
-        } else if (table_wanted && !per_head) {
-            const int64_t x_p = (8 * (int64_t)p[0].s_inv + ((int64_t)1 << p[0].x_shift) - 1) >> p[0].x_shift;
-            if (x_p + 16 <= kTableMaxBytes) table_hint = ((int)x_p + 1 + 15) & ~15;
+        } else if (table_wanted) {
+            for (int h = 0; h < n_p; ++h) {
+                const int64_t x_p = table_span(p[h]);
+                if (x_p + 16 <= kTableMaxBytes && table_bytes(x_p) > table_hint) table_hint = table_bytes(x_p);
+            }
         }
         // a table only pays while it is smaller than the Q, K, V, O bytes of the workgroup
         a.win_mode = 0;
@@ -268,6 +275,8 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         if (qmax || a.win_mode) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
         else if (!qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table_hint, &a) && table_hint > 0)
             qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, 0, &a);
+        // attention_static would have to build its table ahead of a launch no longer than that takes
+        qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     }
     // wave priority by dispatch round: only for launches of two to four rounds (0 = off)
     if (a.n_units <= n_cu || a.n_units > 4 * n_cu) a.n_cu = 0;
@@ -289,7 +298,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // the stream, which also decides whether there is one (mode 3 reads that decision per
         // workgroup; without mode 3 the table is simply not looked at).
         const bool use_table = table_wanted;
-        if (use_table && dyn_table && a.resident && table_fits(a, d, kTableMaxBytes, lds_limit)) {
+        if (use_table && dyn_table && (a.resident || a.split_waves) && table_fits(a, d, kTableMaxBytes, lds_limit)) {
             a.exp_mode = 3;
             a.lut_bytes_max = kTableMaxBytes;
         }
@@ -297,7 +306,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // One table, rebuilt by every call in the static device array ahead of the attention kernel
         // on the same stream (the array keeps the last call's table and every byte the kernel
         // stages, [0, static_np), is rewritten).  No lock: nothing of the context is touched.
-        if (static_np > 0 && a.resident && table_fits(a, d, static_np, lds_limit)) {
+        if (static_np > 0 && (a.resident || a.split_waves) && table_fits(a, d, static_np, lds_limit)) {
             rc = qflash_launch_build_table(scratch_ptr, static_xp + 1, static_np, static_xp, a.hc[0], hip_stream);
             a.hc[0].lut = scratch_ptr;
             a.hc[0].lut_bytes = static_np;
@@ -309,7 +318,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // The context's lock is held until the attention kernel has been enqueued: a slot this launch
         // reads must not be handed to other constants by another host thread in between.
         std::unique_lock<std::mutex> lk(ctx->mu);
-        const bool allowed = ctx->use_table && ctx->tables && a.resident && !(per_head && a.heads_per_wg > 1 && !a.same_head);
+        const bool allowed = ctx->use_table && ctx->tables && (a.split_waves || (a.resident && !(per_head && a.heads_per_wg > 1 && !a.same_head)));
         // A stream under capture records the kernels instead of running them: a table built now would
         // be read, by eager launches with the same constants, before it has ever been written.  Such a
         // call only uses tables that already exist (and pins them, since the graph keeps reading them).
@@ -323,10 +332,9 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         int xp[kQflashMaxParamHeads], np_[kQflashMaxParamHeads], max_bytes = 0, n_with = 0;
         bool has[kQflashMaxParamHeads];
         for (int h = 0; h < n_p; ++h) {
-            // weight is 0 at and below -8 octaves: x_p = ceil(8 s_inv / 2^k)
-            const int64_t x_p = (8 * (int64_t)p[h].s_inv + ((int64_t)1 << p[h].x_shift) - 1) >> p[h].x_shift;
+            const int64_t x_p = table_span(p[h]);
             xp[h] = (int)x_p;
-            np_[h] = ((int)x_p + 1 + 15) & ~15;
+            np_[h] = table_bytes(x_p);
             has[h] = allowed && x_p + 16 <= kTableMaxBytes;
             if (has[h] && np_[h] > max_bytes) max_bytes = np_[h];
         }
@@ -436,10 +444,14 @@ extern "C" int qflash_attention_per_head(qflash_ctx* ctx, const int8_t* Q, const
     return attention_impl(ctx, Q, K, V, O, bias, bias_B, bias_H, B, H, N, d, kv_tile, p, true, hip_stream);
 }
 
-extern "C" int qflash_plan_query(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, int bias_B,
-                                 int bias_H, qflash_plan_info* out) {
+namespace {
+
+// The kernel family of a shape and its decomposition (*lds_limit: 160 KiB on entry).
+int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, int bias_B, int bias_H,
+                      qflash_plan_info* out, QflashKernelArgs* args, int* lds_limit_io) {
     if (!out) return QFLASH_ERR_NULL;
-    int lds_limit = 160 * 1024, n_cu = 256;
+    int& lds_limit = *lds_limit_io;
+    int n_cu = 256;
     bool qmax = false;
     if (ctx) {
         {
@@ -457,7 +469,7 @@ extern "C" int qflash_plan_query(qflash_ctx* ctx, int B, int H, int N, int d, in
     if (kv_tile != 64 && kv_tile != 128) return QFLASH_ERR_TILE;
     const bool has_bias = bias_B != 0 || bias_H != 0;
     if (has_bias && (bias_B < 1 || bias_H < 1)) return QFLASH_ERR_SHAPE;
-    QflashKernelArgs a;
+    QflashKernelArgs& a = *args;
     std::memset(&a, 0, sizeof a);
     static const int32_t some_bias = 0;
     a.bias = has_bias ? &some_bias : nullptr;    // the plan only asks whether there is one
@@ -497,6 +509,17 @@ extern "C" int qflash_plan_query(qflash_ctx* ctx, int B, int H, int N, int d, in
     out->bias_period_units = a.xcd_period;
     out->units_per_xcd = a.units_per_xcd;
     return QFLASH_OK;
+}
+
+}  // namespace
+
+extern "C" int qflash_plan_query(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, int bias_B,
+                                 int bias_H, qflash_plan_info* out) {
+    QflashKernelArgs a;
+    int lds_limit = 160 * 1024;
+    const int rc = plan_query_family(ctx, B, H, N, d, kv_tile, bias_B, bias_H, out, &a, &lds_limit);
+    if (rc == QFLASH_OK) out->key_waves = qflash_plan_split(d, lds_limit, kPlanQueryTableBytes, &a);
+    return rc;
 }
 
 extern "C" int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out) {

@@ -37,19 +37,7 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_cu[];
 
-typedef __attribute__((address_space(3))) void* lds_void;
-typedef const __attribute__((address_space(1))) void* glb_void;
 typedef __attribute__((address_space(3))) int lds_int;
-
-// One direct load: the 64 lanes fetch 16 bytes each from g + lane_off (their own offset from a
-// uniform address) and the 1 KiB lands at lds_addr + 16 * lane (lds_addr uniform).
-// (Spelled out as instructions: for loads it knows to write LDS, the compiler makes the next LDS
-// access of the wavefront wait for all of them, while this kernel counts them itself, tile by tile.
-// M0 holds the LDS address of such a load; one idle cycle separates writing it from using it.)
-__device__ __forceinline__ void load_1k_to_lds(const int8_t* g /* uniform */, int lane_off, int lds_addr /* uniform */) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"((glb_void)g) : "memory", "m0");
-}
 
 // Wait until the counter at flag_addr (LDS) has reached target.  The LDS serves the requests of a
 // wavefront in order, so the reads that follow in program order see what was written before the

@@ -61,6 +61,11 @@ struct QflashKernelArgs {
     int win_chunk;           // consecutive pairs (in slice-major order) each pair of wavefronts works through
     int win_groups;          // workgroups
     int win_table_lds;       // LDS bytes reserved for the weight table (a multiple of 1 KiB)
+    // kernel that shares out the keys of 32 query rows (qflash_plan_split): wavefronts per workgroup, 0 if not taken
+    int split_waves;
+    int split_blocks;        // 32-key blocks per wavefront: 1 or 2
+    unsigned split_qtiles_inv;   // ceil(2^32 / n_qtiles): unit / n_qtiles is the high word of the product
+    int split_table_lds;     // LDS bytes reserved for the weight table (a multiple of 1 KiB)
 #ifdef QF_TRACE
     unsigned long long* trace;   // instrumented builds only: [workgroup][wavefront][16] timestamps
 #endif
@@ -132,6 +137,15 @@ int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stre
 int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
 int qflash_launch_fwd_win(const QflashKernelArgs& args, int lds_limit, void* stream);
 size_t qflash_win_lds_bytes(int streams, int table_bytes);
+
+// The kernel for launches that leave the chip idle, whose wavefronts share out the keys of 32 query rows:
+// decides whether the launch, already planned for the other kernels, takes it, and then sets split_waves
+// and replaces the work decomposition (n_qtiles, n_units, units_per_xcd, xcd_period).  table_bytes: weight
+// table the call would use; split_table_lds says whether it is worth its room (0: compute the
+// weights).  Reads B, H, N, n_cu, qmax and win_mode.  Returns split_waves.
+int qflash_plan_split(int d, int lds_limit, int table_bytes, QflashKernelArgs* args);
+int qflash_launch_fwd_split(const QflashKernelArgs& args, int d, int lds_limit, void* stream);
+size_t qflash_split_lds_bytes(int d, int waves, int table_bytes);
 
 // The two-tile ring with direct global-to-LDS loads (long sequences, d = 64, no bias, both
 // Algorithm 1 and the quantised-maximum variant; work decomposition as for the ring of the resident kernel, four wavefronts per workgroup).

@@ -240,3 +240,41 @@ int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKe
     a->win_table_lds = (table_bytes + 1023) & ~1023;
     return 1;
 }
+
+// LDS bytes of the kernel that shares out the keys: the table (rounded up to 1 KiB), one part of P V
+// per wavefront, row maxima, row sums and alpha (32 x 20 words each).
+size_t qflash_split_lds_bytes(int d, int waves, int table_bytes) {
+    return (((size_t)table_bytes + 1023) & ~(size_t)1023) + (size_t)waves * 128 * (size_t)d + 4 * 32 * 3 * 20;
+}
+
+int qflash_plan_split(int d, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+    a->split_waves = 0;
+    if (a->qmax) return 0;
+    const int nblk = (a->N + 31) / 32;
+    const long long units = (long long)a->B * a->H * nblk;
+    const int cus = a->n_cu > 0 ? a->n_cu : 256;
+    // Where the line lies (d = 64, one image to a small batch, us per launch here against the other kernels):
+    // N = 197: 336 units 5.7 / 8.1, 672 units 8.3 / 8.2; N = 577: 456 units 10.1 / 12.7, 912 units 17.7 / 12.9;
+    // N = 1025: 396 units 14.8 / 19.6, 792 units 26.5 / 19.8.  One KV tile (N = 64) has no chain to cut:
+    // 192 units 3.7 / 3.9, 384 units 4.2 / 3.9.  The windowed kernel is as fast from the start.
+    if (a->win_mode || units > (nblk > 2 ? 2ll : 1ll) * cus) return 0;
+    // Two blocks per wavefront make one KV tile of 64 keys local to it and halve what the chain reads; one
+    // tile in all is spread over two wavefronts (49 tokens with a bias: 3.8 against 4.5 us).  Eight
+    // wavefronts while every workgroup has a compute unit to itself, else four so that two fit one
+    // (N = 577, 456 units: 10.1 against 13.2 us); parts of 32 features are half the size.
+    const int kb = nblk > 2 ? 2 : 1;
+    const int parts = (nblk + kb - 1) / kb;
+    const int waves = parts > 4 && units * d <= 64ll * cus ? 8 : 4;
+    // The table (up to 40 KiB per workgroup) pays once a wavefront looks up more than it fetches.
+    const int table = nblk > 2 ? (table_bytes + 1023) & ~1023 : 0;
+    if (qflash_split_lds_bytes(d, waves, table) > (size_t)lds_limit) return 0;
+    a->split_waves = waves;
+    a->split_blocks = kb;
+    a->split_table_lds = table;
+    a->split_qtiles_inv = (unsigned)((((unsigned long long)1 << 32) + nblk - 1) / nblk);   // (not used where nblk is 1)
+    a->n_qtiles = nblk;
+    a->n_units = (int)units;
+    a->units_per_xcd = (int)((units + 7) / 8);
+    a->xcd_period = 0;
+    return waves;
+}

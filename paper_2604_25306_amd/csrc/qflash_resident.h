@@ -69,23 +69,6 @@ extern __shared__ __align__(16) int8_t smem[];
 template <bool NARROW>
 constexpr int resident_max_waves() { return NARROW ? kResidentMaxWavesNarrow : kResidentMaxWavesWide; }
 
-// Where this lane's bias values start.  Plain layout [bias_B,bias_H,N,N]: the lane's row (lanes
-// beyond the sequence read row 0; their results are never stored).  Packed layout
-// [bias_B*bias_H][ceil(N/32) row blocks][ceil(N/32) column blocks][4 groups][64 lanes][4]: the
-// 16-byte word of lane (li, g) in group a4 of column block cb holds
-// bias[32*rb + li][32*cb + 8*a4 + 4*g + 0..3], which is exactly what the lane adds to its four
-// scores of that group, so one instruction of the wavefront reads 1 KiB in a row.
-__device__ __forceinline__ const int32_t* bias_lane_base(const QflashKernelArgs& a, int bh, int row0, int i,
-                                                        int li, int g) {
-    const int b = bh / a.H, h = bh % a.H, N = a.N;
-    const size_t slice = (size_t)(b % a.bias_B) * a.bias_H + (size_t)(h % a.bias_H);
-    if (a.bias_packed) {
-        const int nb = (N + 31) / 32;
-        return a.bias + ((slice * nb + (size_t)min(row0 / 32, nb - 1)) * nb) * 1024 + 4 * (32 * g + li);
-    }
-    return a.bias + slice * N * N + (size_t)(i < N ? i : 0) * N;
-}
-
 template <int D, int BC, int BIAS, bool NARROW, int XM, bool QMAX>
 __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     constexpr int KSTEPS = D / 32;

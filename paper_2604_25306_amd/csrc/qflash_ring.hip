@@ -31,15 +31,6 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_ring[];
 
-typedef __attribute__((address_space(3))) void* lds_void_r;
-typedef const __attribute__((address_space(1))) void* glb_void_r;
-
-// 64 lanes fetch 16 bytes each from g + lane_off; the 1 KiB lands at lds_addr + 16 * lane.
-__device__ __forceinline__ void ring_load_1k(const int8_t* g /* uniform */, int lane_off, int lds_addr /* uniform */) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"((glb_void_r)g) : "memory", "m0");
-}
-
 template <int BC, int XM, bool QMAX>
 __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     constexpr int D = 64;
@@ -60,7 +51,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
 
     // ---- LDS: [weight table][slot 0][slot 1]; the dynamic LDS is the only LDS of the kernel, so the
     //      table index is its address
-    const int lds0 = (int)(size_t)(lds_void_r)smem_ring;
+    const int lds0 = (int)(size_t)(lds_void)smem_ring;
     const int tbytes = XM == kExpTable ? a.ring_table_lds : 0;
     const int ring_base = lds0 + tbytes;
 
@@ -80,7 +71,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
         const int slot = ring_base + kRingTileBytes * (j & 1);
         for (int x = wave; x < kPieces; x += n_waves) {
             const int b = x % (kPieces / 2);
-            ring_load_1k(x < kPieces / 2 ? Kh : Vh, block_off(BC * j + 16 * b), slot + 1024 * x);
+            load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, block_off(BC * j + 16 * b), slot + 1024 * x);
         }
     };
 
@@ -91,7 +82,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     //      them would mean waiting for the tile in flight.
     if (XM == kExpTable)
         for (int it = wave; it < (tbytes >> 10); it += n_waves)
-            ring_load_1k((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
+            load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
     issue_tile(0);
     v4i qreg[2];
     {

@@ -186,8 +186,30 @@ __device__ __forceinline__ int smax3(int a, int b, int c) {
 enum { kLayPadded = 0, kLaySwizzled = 1 };
 
 typedef int v2i_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void* lds_void;
+typedef const __attribute__((address_space(1))) void* glb_void;
+
+// One direct load: the 64 lanes fetch 16 bytes each from g + lane_off (their own offset from a
+// uniform address) and the 1 KiB lands at lds_addr + 16 * lane (lds_addr uniform).
+// (Spelled out as instructions: for loads it knows to write LDS, the compiler makes the next LDS
+// access of the wavefront wait for all of them, while the kernels count them themselves.
+// M0 holds the LDS address of such a load; one idle cycle separates writing it from using it.)
+__device__ __forceinline__ void load_1k_to_lds(const int8_t* g /* uniform */, int lane_off, int lds_addr /* uniform */) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"((glb_void)g) : "memory", "m0");
+}
+
 typedef __attribute__((address_space(3))) v2i_t lds_v2i;
 typedef const __attribute__((address_space(3))) v4i lds_v4i;
+
+// Four of them for consecutive KiB under one setting of M0 (the offset of the instruction counts on both
+// sides): a wavefront issues a direct load per 45 ns when it sets M0 anew each time, per 10 ns when not.
+__device__ __forceinline__ void load_4k_to_lds(const int8_t* g /* uniform */, int lane_off, int lds_addr /* uniform */) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:1024\n\tglobal_load_lds_dwordx4 %1, %2 offset:2048\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:3072"
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"((glb_void)g) : "memory", "m0");
+}
 
 // ds_read_b64_tr_b8 works on blocks of 16 lanes: lane i of a block receives, as byte j, byte i % 8 of
 // the 8 bytes that lane 2 j + i / 8 of the block points to.  With even lanes pointing at features
@@ -531,6 +553,27 @@ __device__ __forceinline__ void normalise_words(const RowState<D>& st, bool roun
         out[q] = v4i{(int)ev[2 * q], (int)od[2 * q], (int)ev[2 * q + 1], (int)od[2 * q + 1]};
 }
 
+// The same for n quads of four features of one row (accumulators with their offset).
+template <int L, int NQ>
+__device__ __forceinline__ void normalise_quads(const v4i* acc, int l, bool round_nearest, unsigned* out) {
+    const int rs = round_nearest ? 1 : 0;
+    const bool empty = l == 0;
+    const unsigned dsafe = empty ? 1u : ((unsigned)l << rs);
+    const int z = L - (32 - __clz((int)(dsafe - 1)));
+    const unsigned dn = dsafe << z;
+    const unsigned R = recip_ceil<L>(dn);
+    const int u_max = (int)(256u * dn) - 1, zz = z + rs;
+    const int bias_z = (int)(((128u * dsafe + (round_nearest ? (unsigned)l : 0u)) << z) - ((unsigned)kAccBias << zz));
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        unsigned hi[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) hi[b] = __umulhi((unsigned)clamp_0((acc[q][b] << zz) + bias_z, u_max), R);
+        const unsigned w = pack_byte<(2 * L + 8 - 32) / 8>(hi[0], hi[1], hi[2], hi[3]) ^ 0x80808080u;
+        out[q] = empty ? 0u : w;
+    }
+}
+
 template <int D, int L>
 __device__ __forceinline__ void normalise_store(const RowState<D>& st, int8_t* Orow, int g, bool round_nearest) {
     v4i w[D / 32];
@@ -570,5 +613,22 @@ __device__ __forceinline__ QflashHeadConsts head_consts(const QflashKernelArgs& 
 static_assert(offsetof(QflashHeadConsts, x_floor) == 24 && offsetof(QflashHeadConsts, lut_xp) == 28 &&
               offsetof(QflashHeadConsts, lut_bytes) == 32 && offsetof(QflashHeadConsts, lut) == 40,
               "field order read by head_consts");
+
+// Where this lane's bias values start.  Plain layout [bias_B,bias_H,N,N]: the lane's row (lanes
+// beyond the sequence read row 0; their results are never stored).  Packed layout
+// [bias_B*bias_H][ceil(N/32) row blocks][ceil(N/32) column blocks][4 groups][64 lanes][4]: the
+// 16-byte word of lane (li, g) in group a4 of column block cb holds
+// bias[32*rb + li][32*cb + 8*a4 + 4*g + 0..3], which is exactly what the lane adds to its four
+// scores of that group, so one instruction of the wavefront reads 1 KiB in a row.
+__device__ __forceinline__ const int32_t* bias_lane_base(const QflashKernelArgs& a, int bh, int row0, int i,
+                                                        int li, int g) {
+    const int b = bh / a.H, h = bh % a.H, N = a.N;
+    const size_t slice = (size_t)(b % a.bias_B) * a.bias_H + (size_t)(h % a.bias_H);
+    if (a.bias_packed) {
+        const int nb = (N + 31) / 32;
+        return a.bias + ((slice * nb + (size_t)min(row0 / 32, nb - 1)) * nb) * 1024 + 4 * (32 * g + li);
+    }
+    return a.bias + slice * N * N + (size_t)(i < N ? i : 0) * N;
+}
 
 }  // namespace

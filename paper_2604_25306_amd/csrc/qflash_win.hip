@@ -36,15 +36,6 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_win[];
 
-typedef __attribute__((address_space(3))) void* lds_void_w;
-typedef const __attribute__((address_space(1))) void* glb_void_w;
-
-// 64 lanes fetch 16 bytes each from g + lane_off; the 1 KiB lands at lds_addr + 16 * lane.
-__device__ __forceinline__ void win_load_1k(const int8_t* g /* uniform */, int lane_off, int lds_addr /* uniform */) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"((glb_void_w)g) : "memory", "m0");
-}
-
 constexpr int kWinSetBytes = 5 * 1024;     // V, K and 32 query rows of one pair
 constexpr int kWinExcluded = -(1 << 29);   // stands for "takes no part" in the offset representation
 
@@ -68,11 +59,11 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
 
     // ---- LDS: [weight table, a.win_table_lds bytes][wavefront w: two sets of V (2 KiB), K (2 KiB),
     //      Q (1 KiB)]; the dynamic LDS is the only LDS of the kernel, so the table index is its address
-    const int lds0 = (int)(size_t)(lds_void_w)smem_win;
+    const int lds0 = (int)(size_t)(lds_void)smem_win;
     const int tbytes = XM == kExpTable ? a.win_table_lds : 0;
     if (XM == kExpTable) {
         for (int it = wave; it < (tbytes >> 10); it += n_waves)
-            win_load_1k((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
+            load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();          // the only barrier: the table is in place
@@ -130,11 +121,11 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     auto issue_loads = [&](const WinPair& q, int parity) {
         const size_t off = (size_t)pair_index(q) * pair_bytes;
         const int set = wbuf + kWinSetBytes * parity;
-        win_load_1k(a.K + off, voff0, set + 2048);
-        win_load_1k(a.Q + off, qoff, set + 4096);
-        win_load_1k(a.K + off, voff1, set + 3072);
-        win_load_1k(a.V + off, voff0, set);
-        win_load_1k(a.V + off, voff1, set + 1024);
+        load_1k_to_lds(a.K + off, voff0, set + 2048);
+        load_1k_to_lds(a.Q + off, qoff, set + 4096);
+        load_1k_to_lds(a.K + off, voff1, set + 3072);
+        load_1k_to_lds(a.V + off, voff0, set);
+        load_1k_to_lds(a.V + off, voff1, set + 1024);
     };
 
     // ---- accumulator input of the score product: bias (or 0) + 2^30, excluded / beyond the sequence: -2^29 + 2^30
