@@ -142,10 +142,8 @@ int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out /* host */);
  *            computes its weights arithmetically there because the look-up variant is slower
  *            still); on long sequences with d = 64 the two are within 1 % (N = 577: 43.7 against
  *            43.9 us).  A d = 32 sequence
- *            too long for LDS (N above about 1000) takes the streamed kernel, which stages one
- *            tile at a time with two barriers per tile and computes weights arithmetically:
- *            about 0.65 of the ring kernel's rate per score with tile 64 (B*H = 64, N = 2100:
- *            150 us), 0.43 with tile 128 (228 us).
+ *            with a bias that is too long for LDS (N above about 1000) takes a kernel that stages one
+ *            tile at a time with two barriers per tile and computes weights arithmetically.
  *   p        host; validated on every call.
  *   hip_stream  a hipStream_t of the context's device (NULL = the default stream).
  *
@@ -314,7 +312,9 @@ int qflash_attention_dynamic_bias(qflash_ctx* ctx,
  * own choice and does not change a single output bit.
  *
  *   bias_B, bias_H   extents of the bias the call would be given, or 0, 0 for none.
- *   kernel           0: KV tiles streamed through LDS, 128 query rows per workgroup;
+ *   kernel           0: KV tiles streamed through LDS (d = 32: every sequence of more than 64 keys
+ *                    without a bias, fed by direct global-to-LDS loads, up to 256 query rows per
+ *                    workgroup; with a bias those too long for LDS, 128 query rows per workgroup);
  *                    1: K and V of a (batch, head) pair resident in LDS; 2: two KV tiles in LDS (long
  *                    sequences with d = 64; without a bias they are fed by direct global-to-LDS loads and
  *                    workgroups are four wavefronts);

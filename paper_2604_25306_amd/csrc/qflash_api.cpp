@@ -173,7 +173,7 @@ int launch_attention(QflashKernelArgs& a, int d, int kv_tile, int lds_limit, voi
     if (a.cu_mode) return qflash_launch_fwd_cu(a, lds_limit, hip_stream);
     if (a.ring_dma) {
         a.ring_table_lds = (a.lut_bytes_max + 1023) & ~1023;
-        return qflash_launch_fwd_ring(a, lds_limit, hip_stream);
+        return qflash_launch_fwd_ring(a, d, lds_limit, hip_stream);
     }
     return qflash_launch_fwd(a, d, kv_tile, lds_limit, hip_stream);
 }
@@ -272,12 +272,14 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         a.win_mode = 0;
         if (!qmax && qflash_plan_win(d, kv_tile, lds_limit, table_hint, &a) == 0 && table_hint > 0)
             qflash_plan_win(d, kv_tile, lds_limit, 0, &a);
+        qflash_plan_ring(d, lds_limit, table_hint, &a);
         if (qmax || a.win_mode) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
         else if (!qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table_hint, &a) && table_hint > 0)
             qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, 0, &a);
         // attention_static would have to build its table ahead of a launch no longer than that takes
         qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     }
+    const bool takes_table = a.resident || a.ring_dma || a.split_waves;
     // wave priority by dispatch round: only for launches of two to four rounds (0 = off)
     if (a.n_units <= n_cu || a.n_units > 4 * n_cu) a.n_cu = 0;
 
@@ -298,7 +300,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // the stream, which also decides whether there is one (mode 3 reads that decision per
         // workgroup; without mode 3 the table is simply not looked at).
         const bool use_table = table_wanted;
-        if (use_table && dyn_table && (a.resident || a.split_waves) && table_fits(a, d, kTableMaxBytes, lds_limit)) {
+        if (use_table && dyn_table && takes_table && table_fits(a, d, kTableMaxBytes, lds_limit)) {
             a.exp_mode = 3;
             a.lut_bytes_max = kTableMaxBytes;
         }
@@ -306,7 +308,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // One table, rebuilt by every call in the static device array ahead of the attention kernel
         // on the same stream (the array keeps the last call's table and every byte the kernel
         // stages, [0, static_np), is rewritten).  No lock: nothing of the context is touched.
-        if (static_np > 0 && (a.resident || a.split_waves) && table_fits(a, d, static_np, lds_limit)) {
+        if (static_np > 0 && takes_table && table_fits(a, d, static_np, lds_limit)) {
             rc = qflash_launch_build_table(scratch_ptr, static_xp + 1, static_np, static_xp, a.hc[0], hip_stream);
             a.hc[0].lut = scratch_ptr;
             a.hc[0].lut_bytes = static_np;
@@ -318,7 +320,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // The context's lock is held until the attention kernel has been enqueued: a slot this launch
         // reads must not be handed to other constants by another host thread in between.
         std::unique_lock<std::mutex> lk(ctx->mu);
-        const bool allowed = ctx->use_table && ctx->tables && (a.split_waves || (a.resident && !(per_head && a.heads_per_wg > 1 && !a.same_head)));
+        const bool allowed = ctx->use_table && ctx->tables && takes_table && (a.split_waves || !(per_head && a.heads_per_wg > 1 && !a.same_head));
         // A stream under capture records the kernels instead of running them: a table built now would
         // be read, by eager launches with the same constants, before it has ever been written.  Such a
         // call only uses tables that already exist (and pins them, since the graph keeps reading them).
@@ -499,6 +501,7 @@ int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, 
         out->workgroups = a.cu_groups;
         return QFLASH_OK;
     }
+    qflash_plan_ring(d, lds_limit, kPlanQueryTableBytes, &a);
     out->kernel = !a.resident ? 0 : a.ring ? 2 : 1;
     out->pairs_per_workgroup = a.heads_per_wg;
     out->wavefronts_per_pair = a.waves_per_head;

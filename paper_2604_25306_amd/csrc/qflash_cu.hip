@@ -103,7 +103,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 
     // ---- loop-invariant registers
     const ExpConst c = make_exp_const(hc);
-    const SwizzledLane sl = swizzled_lane_offsets(lane);
+    const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
     const int nb16 = rows16 >> 4;                   // 1 KiB loads per tensor of a pair
     const int nt = tbytes >> 10;                    // 1 KiB loads of the table
 

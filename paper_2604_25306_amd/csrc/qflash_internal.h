@@ -52,7 +52,7 @@ struct QflashKernelArgs {
     int cu_groups;           // workgroups
     int cu_waves;            // wavefronts per workgroup (at most 16)
     int cu_table_lds;        // LDS bytes reserved for the weight table (a multiple of 1 KiB)
-    // two-tile ring fed by direct global-to-LDS loads (d = 64, no bias; set by qflash_plan_fwd): 1 if the launch takes it
+    // two-tile ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
     int ring_dma;
     int ring_table_lds;      // LDS bytes reserved for the weight table (a multiple of 1 KiB)
     // windowed-attention kernel (qflash_plan_win): 1 if the launch takes it
@@ -147,10 +147,15 @@ int qflash_plan_split(int d, int lds_limit, int table_bytes, QflashKernelArgs* a
 int qflash_launch_fwd_split(const QflashKernelArgs& args, int d, int lds_limit, void* stream);
 size_t qflash_split_lds_bytes(int d, int waves, int table_bytes);
 
-// The two-tile ring with direct global-to-LDS loads (long sequences, d = 64, no bias, both
-// Algorithm 1 and the quantised-maximum variant; work decomposition as for the ring of the resident kernel, four wavefronts per workgroup).
-int qflash_launch_fwd_ring(const QflashKernelArgs& args, int lds_limit, void* stream);
-size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes);
+// The two-tile ring with direct global-to-LDS loads (long sequences, no bias, both Algorithm 1 and the
+// quantised-maximum variant; work decomposition as for the ring of the resident kernel).
+constexpr int kRingMaxWaves = 8;
+int qflash_launch_fwd_ring(const QflashKernelArgs& args, int d, int lds_limit, void* stream);
+size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d = 64);
+// Completes the plan of qflash_plan_fwd for that kernel: takes every sequence of 32 features without a bias and
+// with more than one KV tile (planned as resident or streamed so far), and chooses the number of wavefronts
+// per workgroup for a weight table of table_bytes.  Returns ring_dma.
+int qflash_plan_ring(int d, int lds_limit, int table_bytes, QflashKernelArgs* args);
 
 // GPUs per process for which per-device launch set-up is remembered.
 constexpr int kQflashMaxDevices = 64;

@@ -165,7 +165,7 @@ int qflash_table_fits(const QflashKernelArgs& a, int d, int table_bytes, int lds
     // the bytes of Q, K, V, O the workgroup moves anyway.
     const long long io = 4ll * a.heads_per_wg * a.N * d;
     if (io < (long long)table_bytes) return 0;
-    if (a.ring_dma) return qflash_ring_lds_bytes(a.waves_per_head, a.kv_tile, table_bytes) <= (size_t)lds_limit / 2;
+    if (a.ring_dma) return qflash_ring_lds_bytes(a.waves_per_head, a.kv_tile, table_bytes, d) <= (size_t)lds_limit / 2;
     // Short sequences with the wide tile: that variant is out of registers with the table's
     // addressing on top (ViT-B/16 B=64: 34 us with the table, 25.5 us without).
     if (d == 64 && a.kv_tile == 128 && a.N <= 256) return 0;
@@ -200,11 +200,59 @@ int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_b
     return 1;
 }
 
-// LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and two KV tiles (K and V,
-// 64-byte rows).
-size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes) {
+// LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and two KV tiles of K and V.
+size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
     (void)waves;
-    return (((size_t)table_bytes + 1023) & ~(size_t)1023) + 2 * (size_t)kv_tile * 128;
+    return (((size_t)table_bytes + 1023) & ~(size_t)1023) + 2 * (size_t)kv_tile * 2 * (size_t)d;
+}
+
+// Wavefronts per workgroup of the ring.  More of them share one weight table and one staged tile, fewer
+// are dealt out more evenly.  Cost of a choice: wavefronts on the busiest compute unit times the time each
+// of them adds, (2200 + 230 x) / x cycles per KV tile with x wavefronts on the unit (fitted to 12 to
+// 20: DeiT-B/384, N(0,1), 12 resident: 414; N(0,1.5^2), small table, 20 resident: 341), x limited by LDS and
+// registers.  Measured against the fixed four (us): d = 64, 96 pairs of 1025 tokens 47.4 -> 39.7 (seven),
+// 32 features, 64 pairs of 2100 tokens 81.2 -> 76.9 (six), 96 pairs of 1200 tokens 41.2 -> 39.9 (three).
+static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKernelArgs& a, int want, int* waves, int* qtiles) {
+    const int nblk = (a.N + 31) / 32, cus = a.n_cu > 0 ? a.n_cu : 256;
+    *qtiles = (nblk + want - 1) / want;
+    const int w = *waves = (nblk + *qtiles - 1) / *qtiles;                        // balanced
+    // (at 64 features the SIMDs are busy enough for an uneven workgroup to cost its fullest SIMD's share)
+    const int eff = d == 64 ? (w + 3) & ~3 : w;
+    const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 3) : a.kv_tile == 64 ? 6 : 4;   // by registers
+    const long long units = (long long)a.B * a.H * *qtiles, per_cu = (units + cus - 1) / cus;
+    long long fit = (long long)((size_t)lds_limit / qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d));
+    if (fit > 4 * per_simd / w) fit = 4 * per_simd / w;
+    if (fit > per_cu) fit = per_cu;
+    if (fit < 1) return 1e30;
+    const double x = (double)fit * eff;
+    return (double)per_cu * eff * (2200.0 + 230.0 * x) / x;
+}
+
+int qflash_plan_ring(int d, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+    if (a->bias || a->win_mode || (!a->ring_dma && (d != 32 || a->N <= 64))) return 0;
+    const int wants[2][3] = {{4, 8, 4}, {4, 3, 6}};
+    double best = 0.0;
+    int waves = 0, qtiles = 0;
+    for (int i = 0; i < 3; ++i) {
+        int w, t;
+        const double cost = ring_cost(d, lds_limit, table_bytes, *a, wants[d == 32][i], &w, &t);
+        if (waves == 0 || cost < 0.97 * best) { best = cost; waves = w; qtiles = t; }
+    }
+    const long long units = (long long)a->B * a->H * qtiles;
+    if (units >= (1ll << 30)) return 0;
+    a->waves_per_head = waves;
+    a->rows_per_wg = 32 * waves;
+    a->n_qtiles = qtiles;
+    if (d == 32) a->resident = 0;          // (whatever the plan was before: K and V are streamed now)
+    a->ring = 1;
+    a->ring_dma = 1;
+    a->pipelined = d == 64;
+    a->heads_per_wg = 1;
+    a->same_head = 0;
+    a->n_units = (int)units;
+    a->units_per_xcd = (a->n_units + 7) / 8;
+    a->xcd_period = 0;
+    return 1;
 }
 
 // LDS bytes of the windowed-attention kernel: the table (rounded up to 1 KiB) and, per wavefront

@@ -1,15 +1,21 @@
 // gfx950 kernel of the integer-only fused attention forward pass (Algorithm 1) for long sequences
-// with 64 features per head and no bias: the two-tile ring, fed by direct
-// global-to-LDS loads.
+// without a bias: the two-tile ring, fed by direct global-to-LDS loads.
 //
-// A workgroup of up to 8 wavefronts (4 where the sequence allows it) serves 32 query rows per wavefront of one (batch, head) pair and
-// walks over all KV tiles of the pair.  LDS holds the weight table and two KV tiles: the one in use and the one on its way.  K and V tiles arrive row-major as they lie
-// in memory (64-byte rows, 16-byte pieces permuted by the row so that operand reads are free of bank
-// conflicts), put there by `global_load_lds_dwordx4`; the K/Q operands are plain 16-byte LDS reads
+// A workgroup of up to 8 wavefronts serves 32 query rows per wavefront of one (batch, head) pair and
+// walks over all KV tiles of the pair.  LDS holds the weight table and two KV tiles: the one in use
+// and the one on its way.  K and V tiles arrive row-major as they lie in memory (16-byte pieces
+// permuted by the row so that operand reads are free of bank conflicts), put there by `global_load_lds_dwordx4`; the K/Q operands are plain 16-byte LDS reads
 // and the V^T operand is read with the transposing 8-bit LDS read (see qflash_tile.h).  Compared with
 // staging through registers (qflash_resident.h) there are no staging registers, no byte transposes
 // in the vector ALU and no LDS write instructions: about a third of that kernel's vector
 // instructions on these shapes.
+//
+// What bounds it: the LDS (a byte look-up costs the compute unit 7 cycles, its lanes meeting 3.5 to a bank)
+// and vector issue, both at two thirds to nine tenths: 290 LDS and 250 vector cycles of the compute unit
+// per KV tile of 64 and wavefront at 64 features, 340 to 414 measured, depending on how many wavefronts
+// the weight table leaves room for.  32 features against the streamed kernel that staged one tile at a
+// time through registers and computed the weights: B*H = 64, N = 2100 145.6 -> 76.0 us with tiles of 64,
+// 202 -> 79.5 us with tiles of 128; against whole sequences in LDS: B*H = 96, N = 1200 56.8 -> 39.6 us.
 //
 // Synchronisation: the wavefronts share the loads of a tile (1 KiB pieces, dealt round robin).
 // While tile j is computed, tile j+1 lands in the other slot; after its arithmetic a wavefront waits
@@ -31,11 +37,12 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_ring[];
 
-template <int BC, int XM, bool QMAX>
+template <int D, int BC, int XM, bool QMAX>
 __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
-    constexpr int D = 64;
-    constexpr int kRingTileBytes = 2 * BC * D;      // one KV tile in LDS: K (BC rows x 64 bytes), then V
-    constexpr int kPieces = 2 * BC / 16;            // 1 KiB pieces of a tile: K blocks of 16 rows, then V blocks
+    constexpr int kRingTileBytes = 2 * BC * D;      // one KV tile in LDS: K (BC rows of D bytes), then V
+    constexpr int kRows = 1024 / D;                 // rows of a 1 KiB piece
+    constexpr int kPieces = 2 * BC / kRows;         // pieces of a tile: K, then V
+    constexpr int kRowPieces = D / 16;              // 16-byte pieces of a row
     constexpr bool SB = XM == kExpTable;
     const int N = a.N;
     const int unit = qflash_unit_of_workgroup(blockIdx.x, a.units_per_xcd, a.xcd_period);
@@ -47,7 +54,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, bh);
     const ExpConst c = make_exp_const(hc);
-    const SwizzledLane sl = swizzled_lane_offsets(lane);
+    const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
 
     // ---- LDS: [weight table][slot 0][slot 1]; the dynamic LDS is the only LDS of the kernel, so the
     //      table index is its address
@@ -62,16 +69,16 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const bool active = row0 < N;
     const int n_tiles = (N + BC - 1) / BC;
 
-    // Lane part of the address of a 16-row block: row lane / 4, 16-byte piece (lane % 4) permuted by the
-    // row.  Rows beyond the sequence are clamped to the last row (what lands there is never used).
-    const int lrow = lane >> 2, piece = ((lane & 3) ^ ((lane >> 4) & 3)) << 4;
+    // Lane part of the address of a 1 KiB piece: row lane / (D / 16), 16-byte piece lane % (D / 16) permuted
+    // by the row.  Rows beyond the sequence are clamped to the last row (what lands there is never used).
+    const int lrow = lane / kRowPieces, piece = ((lane ^ (lrow >> 2)) & (kRowPieces - 1)) << 4;
     auto block_off = [&](int first_row) { return min(first_row + lrow, N - 1) * D + piece; };
     // The 1 KiB pieces of tile j (the K blocks, then the V blocks), dealt round robin to the wavefronts.
     auto issue_tile = [&](int j) {
         const int slot = ring_base + kRingTileBytes * (j & 1);
         for (int x = wave; x < kPieces; x += n_waves) {
             const int b = x % (kPieces / 2);
-            load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, block_off(BC * j + 16 * b), slot + 1024 * x);
+            load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, block_off(BC * j + kRows * b), slot + 1024 * x);
         }
     };
 
@@ -84,15 +91,15 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
         for (int it = wave; it < (tbytes >> 10); it += n_waves)
             load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
     issue_tile(0);
-    v4i qreg[2];
+    v4i qreg[D / 32];
     {
         const int8_t* Qrow = a.Q + head_off + (size_t)min(row0 + li, N - 1) * D + 16 * g;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) qreg[s] = *(const v4i*)(Qrow + 32 * s);
+        for (int s = 0; s < D / 32; ++s) qreg[s] = *(const v4i*)(Qrow + 32 * s);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int s = 0; s < 2; ++s) asm volatile("" : "+v"(qreg[s]));
+    for (int s = 0; s < D / 32; ++s) asm volatile("" : "+v"(qreg[s]));
     __syncthreads();
 
     RowState<D> st;
@@ -128,25 +135,32 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     normalise_store<D, 20>(st, a.O + head_off + (size_t)i * D, g, a.out_round != 0);
 }
 
-// Wavefronts per SIMD the register allocation has to allow: with KV tiles of 64, 5 for the look-up
-// variant (94 registers) and 4 for the others (which would spill at 96); 3 with tiles of 128 (137
-// registers; held to 128 it spills a dozen and is a sixth slower).
+// Wavefronts per SIMD the register allocation has to allow.  64 features: with KV tiles of 64, 5 for the
+// look-up variant (94 registers) and 4 for the others (which would spill at 96); 3 with tiles of 128 (137
+// registers; held to 128 it spills a dozen and is a sixth slower).  32 features: 5 and 4 (72 and 104
+// registers).
+template <int D, int BC, int XM>
+constexpr int ring_min_waves() {
+    if (D == 32) return BC == 128 ? 4 : 5;
+    return BC == 128 ? 3 : XM == kExpTable ? 5 : 4;
+}
+
 // QMAX: the quantised-maximum variant (not Algorithm 1 as printed; see process_tile).
-template <int BC, int XM, bool QMAX>
-__global__ __launch_bounds__(512, (BC == 128 ? 3 : XM == kExpTable ? 5 : 4)) void qflash_fwd_ring(const QflashKernelArgs a) {
+template <int D, int BC, int XM, bool QMAX>
+__global__ __launch_bounds__(64 * kRingMaxWaves, (ring_min_waves<D, BC, XM>())) void qflash_fwd_ring(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
         const int unit = qflash_unit_of_workgroup(blockIdx.x, a.units_per_xcd, a.xcd_period);
         if (unit >= a.n_units) return;
-        if (head_consts(a, unit / a.n_qtiles).lut_bytes > 0) ring_body<BC, kExpTable, QMAX>(a);
-        else ring_body<BC, kExpShift, QMAX>(a);
+        if (head_consts(a, unit / a.n_qtiles).lut_bytes > 0) ring_body<D, BC, kExpTable, QMAX>(a);
+        else ring_body<D, BC, kExpShift, QMAX>(a);
     } else {
-        ring_body<BC, XM, QMAX>(a);
+        ring_body<D, BC, XM, QMAX>(a);
     }
 }
 
-template <int BC, int XM, bool QMAX>
+template <int D, int BC, int XM, bool QMAX>
 int launch_ring(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    auto kern = qflash_fwd_ring<BC, XM, QMAX>;
+    auto kern = qflash_fwd_ring<D, BC, XM, QMAX>;
     // once per process and device: raise the dynamic LDS limit, and make sure that the kernel has no
     // static LDS in front of the dynamic one (the table index is used as an LDS address)
     static std::once_flag once[kQflashMaxDevices];
@@ -168,31 +182,30 @@ int launch_ring(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_
 }  // namespace
 
 namespace {
+template <int D, int BC, bool QMAX>
+int launch_mode(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
+    if (a.exp_mode == kExpAuto) return launch_ring<D, BC, kExpAuto, QMAX>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpTable) return launch_ring<D, BC, kExpTable, QMAX>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpShift0) return launch_ring<D, BC, kExpShift0, QMAX>(a, lds, lds_limit, st);
+    return launch_ring<D, BC, kExpShift, QMAX>(a, lds, lds_limit, st);
+}
 template <bool QMAX>
-int launch_variant(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    if (a.kv_tile == 64) {
-        if (a.exp_mode == kExpAuto) return launch_ring<64, kExpAuto, QMAX>(a, lds, lds_limit, st);
-        if (a.exp_mode == kExpTable) return launch_ring<64, kExpTable, QMAX>(a, lds, lds_limit, st);
-        if (a.exp_mode == kExpShift0) return launch_ring<64, kExpShift0, QMAX>(a, lds, lds_limit, st);
-        return launch_ring<64, kExpShift, QMAX>(a, lds, lds_limit, st);
-    }
-    if (a.exp_mode == kExpAuto) return launch_ring<128, kExpAuto, QMAX>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpTable) return launch_ring<128, kExpTable, QMAX>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpShift0) return launch_ring<128, kExpShift0, QMAX>(a, lds, lds_limit, st);
-    return launch_ring<128, kExpShift, QMAX>(a, lds, lds_limit, st);
+int launch_variant(const QflashKernelArgs& a, int d, size_t lds, int lds_limit, hipStream_t st) {
+    if (d == 64) return a.kv_tile == 64 ? launch_mode<64, 64, QMAX>(a, lds, lds_limit, st) : launch_mode<64, 128, QMAX>(a, lds, lds_limit, st);
+    return a.kv_tile == 64 ? launch_mode<32, 64, QMAX>(a, lds, lds_limit, st) : launch_mode<32, 128, QMAX>(a, lds, lds_limit, st);
 }
 }  // namespace
 
-int qflash_launch_fwd_ring(const QflashKernelArgs& a, int lds_limit, void* stream) {
+int qflash_launch_fwd_ring(const QflashKernelArgs& a, int d, int lds_limit, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     // everything the kernel's indexing assumes, checked once more where it is launched
-    if (!a.ring_dma || !a.ring || a.bias || a.heads_per_wg != 1 || (a.kv_tile != 64 && a.kv_tile != 128))
+    if (!a.ring_dma || !a.ring || a.bias || a.heads_per_wg != 1 || (a.kv_tile != 64 && a.kv_tile != 128) || (d != 32 && d != 64))
         return (int)hipErrorInvalidValue;
-    if (a.waves_per_head < 1 || a.waves_per_head > 8 || a.rows_per_wg != 32 * a.waves_per_head) return (int)hipErrorInvalidValue;
+    if (a.waves_per_head < 1 || a.waves_per_head > kRingMaxWaves || a.rows_per_wg != 32 * a.waves_per_head) return (int)hipErrorInvalidValue;
     if ((long long)a.rows_per_wg * a.n_qtiles < a.N) return (int)hipErrorInvalidValue;
     const bool table = a.exp_mode == kExpTable || a.exp_mode == kExpAuto;
     if (table && a.lut_bytes_max > a.ring_table_lds) return (int)hipErrorInvalidValue;
-    const size_t lds = qflash_ring_lds_bytes(a.waves_per_head, a.kv_tile, table ? a.ring_table_lds : 0);
+    const size_t lds = qflash_ring_lds_bytes(a.waves_per_head, a.kv_tile, table ? a.ring_table_lds : 0, d);
     if (lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
-    return a.qmax ? launch_variant<true>(a, lds, lds_limit, st) : launch_variant<false>(a, lds, lds_limit, st);
+    return a.qmax ? launch_variant<true>(a, d, lds, lds_limit, st) : launch_variant<false>(a, d, lds, lds_limit, st);
 }

@@ -133,24 +133,17 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
     int* maxs = (int*)(parts + W * kPart);                                     // [32 rows][kRowPitch]
     int* sums = maxs + 32 * kRowPitch;                                         // likewise
     int* alphas = sums + 32 * kRowPitch;                                       // [32 rows][kRowPitch]
-    // Where the pieces of V go in LDS, and where the transposing reads of the V^T operand start.  64-byte
-    // rows: pieces permuted by the row as everywhere (swizzled_lane_offsets); 32-byte rows: as in memory.
+    // Where the pieces of V go in LDS: permuted by the row as everywhere (swizzled_lane_offsets).
     auto store_v = [&]() {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int s = 0; s < TB; ++s) {
                 const int x = 64 * s + lane, r = x / (D / 16), pc = x % (D / 16);
-                *(v4i*)(part + 32 * D * kb + r * D + 16 * (D == 64 ? pc ^ ((r >> 2) & 3) : pc)) = vreg[kb][s];
+                *(v4i*)(part + 32 * D * kb + r * D + 16 * (pc ^ ((r >> 2) & (D / 16 - 1)))) = vreg[kb][s];
             }
     };
-    int v_lane;
-    if (D == 64) {
-        v_lane = swizzled_lane_offsets(lane).v_off;
-    } else {
-        const int li_hi = (lane >> 4) & 1, s = lane & 15, odd = s & 1, jj = s >> 1, aa = jj >> 2, bb = jj & 3;
-        v_lane = (8 * aa + 4 * g + bb) * D + 16 * li_hi + 8 * odd;
-    }
+    const int v_lane = swizzled_lane_offsets<D>(lane).v_off;
     const int part_addr = lds0 + tbytes + wave * kPart;
 
     const int32_t* bias_row = nullptr;
@@ -293,7 +286,7 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int t = 0; t < TB; ++t) {
-                    const int va_addr = part_addr + 32 * D * kb + (D == 64 ? v_lane ^ (32 * t) : v_lane);
+                    const int va_addr = part_addr + 32 * D * kb + (v_lane ^ (32 * t));
                     const v2i_t lo2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(size_t)va_addr);
                     const v2i_t hi2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(size_t)(va_addr + 16 * D));
                     const v4i va = __builtin_shufflevector(lo2, hi2, 0, 1, 2, 3);

@@ -178,7 +178,7 @@ __device__ __forceinline__ int smax3(int a, int b, int c) {
 //
 // LAY selects where the MFMA A operands come from.  kLayPadded: K rows with pitch KROW at sK and V^T
 // (columns in result order) with pitch VROW at sV, both written by the staging code of the kernel.
-// kLaySwizzled: K and V tiles row-major in LDS exactly as in memory (64-byte rows, the four 16-byte
+// kLaySwizzled: K and V tiles row-major in LDS exactly as in memory (for 64-byte rows: the four 16-byte
 // pieces of row r stored at piece index p ^ ((r >> 2) & 3), which is what keeps both kinds of read
 // free of bank conflicts), put there by direct global-to-LDS loads; kx / vx are then this lane's LDS
 // byte addresses inside the tile (see swizzled_lane_offsets) and sK, KROW, sV, VROW are unused.
@@ -217,16 +217,19 @@ __device__ __forceinline__ void load_4k_to_lds(const int8_t* g /* uniform */, in
 // the eight keys kappa(0..7): a 16 x 8 piece of V^T.  Two such reads (keys 16 apart) are the 16
 // bytes of the A operand of O^T += V^T P^T, with kappa chosen as the row order of the score block
 // (k-slot 16 g + 4 a + b  <->  key 8 a + 4 g + b).
+// (32 features: 32-byte rows of two pieces, piece p of row r stored at p ^ ((r >> 2) & 1).)
 struct SwizzledLane {
     int k_off;   // K / Q operand: row li, 16-byte piece g (k-step 0; k-step 1 is this ^ 32)
-    int v_off;   // V^T operand: first transposing read of feature block 0 (block 1 is this ^ 32; keys +16: + 1024)
+    int v_off;   // V^T operand: first transposing read of feature block 0 (block 1 is this ^ 32; keys +16: + 16 rows)
 };
+template <int D>
 __device__ __forceinline__ SwizzledLane swizzled_lane_offsets(int lane) {
+    constexpr int M = D / 16 - 1;
     const int li = lane & 31, g = lane >> 5;
     SwizzledLane o;
-    o.k_off = li * 64 + ((g ^ ((li >> 2) & 3)) << 4);
+    o.k_off = li * D + ((g ^ ((li >> 2) & M)) << 4);
     const int li_hi = (lane >> 4) & 1, s = lane & 15, odd = s & 1, j = s >> 1, a = j >> 2, b = j & 3;
-    o.v_off = (8 * a + 4 * g + b) * 64 + ((li_hi ^ ((2 * a + g) & 3)) << 4) + 8 * odd;
+    o.v_off = (8 * a + 4 * g + b) * D + ((li_hi ^ ((2 * a + g) & M)) << 4) + 8 * odd;
     return o;
 }
 
@@ -240,7 +243,6 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                                             const ExpConst& c, int a_mul, int li, int g,
                                             int kx = 0, int vx = 0) {
     const v16i zb = offset_block();
-    static_assert(LAY == kLayPadded || D == 64, "the swizzled layout is for 64-byte rows");
     constexpr int KSTEPS = D / 32, TB = D / 32, KB = BC / 32;
     constexpr bool KZ = XM == kExpShift0;
     static_assert(!SB || (XM == kExpTable && !BIAS), "biased scores: table mode without bias only");
@@ -253,12 +255,20 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     auto blk_on = [&](int kb) { return NG ? 4 * kb < NG : 32 * kb < n_valid; };
     auto grp_on = [&](int kb, int a4) { return NG ? 4 * kb + a4 < NG : 32 * kb + 8 * a4 < n_valid; };
     auto grp_cut = [&](int kb, int a4) { return NG ? 4 * kb + a4 == NG - 1 : 32 * kb + 8 * a4 + 8 > n_valid; };
+    // Look-up mode with 32 features: one group of four scores in eight is computed instead of looked up.  A
+    // look-up costs the LDS of the compute unit 7 cycles (64 random bytes, two passes of 32 lanes that
+    // meet 3.5 to a bank; 2.5 cycles without conflicts), its arithmetic the vector units 5.  At 32
+    // features a tile has half the vector work per look-up and the LDS is what runs out first
+    // (B*H = 64, N = 2100: 88.0 us with every weight looked up, 81.2 with 7 of 8, 79.8 with 6 of 8 but
+    // 105 with larger workgroups: registers); at 64 features it only costs (40.5 -> 45 us, N = 577).
+    constexpr bool MIX = XM == kExpTable && D == 32 && LAY == kLaySwizzled && FULL;   // (a ragged tile would spill)
+    auto computed = [&](int kb, int a4) { return MIX && (kb & 1) == 1 && a4 == 3; };
     // ---- step 1: S^T blocks (32 kv rows x 32 queries each)
     v16i s[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
         if (blk_on(kb)) {
-            const v4i ka0 = LAY == kLaySwizzled ? *(lds_v4i*)(size_t)(kx + 2048 * kb)
+            const v4i ka0 = LAY == kLaySwizzled ? *(lds_v4i*)(size_t)(kx + 32 * D * kb)
                                                 : *(const v4i*)(sK + (32 * kb + li) * KROW + 16 * g);
             const v16i zs = kb == 0 ? score_offset_block<0>() : kb == 1 ? score_offset_block<1>()
                           : kb == 2 ? score_offset_block<2>() : score_offset_block<3>();
@@ -266,7 +276,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                        : __builtin_amdgcn_mfma_i32_32x32x32_i8(ka0, qreg[0], v16i{0}, 0, 0, 0);
 #pragma unroll
             for (int ks = 1; ks < KSTEPS; ++ks) {
-                const v4i ka = LAY == kLaySwizzled ? *(lds_v4i*)(size_t)((kx ^ (32 * ks)) + 2048 * kb)
+                const v4i ka = LAY == kLaySwizzled ? *(lds_v4i*)(size_t)((kx ^ (32 * ks)) + 32 * D * kb)
                                                    : *(const v4i*)(sK + (32 * kb + li) * KROW + 32 * ks + 16 * g);
                 s[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka, qreg[ks], s[kb], 0, 0, 0);
             }
@@ -406,11 +416,27 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                         const unsigned sv = (unsigned)s[kb][4 * a4 + b];
                         const unsigned idx = SB ? __builtin_elementwise_sub_sat(sv, edge_kb)
                                                 : __builtin_elementwise_sub_sat(x_p_v, (unsigned)m_new - sv);
-                        s[kb][4 * a4 + b] = table_weight(idx);
+                        s[kb][4 * a4 + b] = computed(kb, a4) ? (int)idx : table_weight(idx);
                     }
                 }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (MIX) {
+            const int xpk = x_p << c.k;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int a4 = 0; a4 < 4; ++a4)
+                    if (computed(kb, a4) && grp_on(kb, a4)) {
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const int xs = (s[kb][4 * a4 + b] << c.k) - xpk, xs2 = xs + c.two_s_inv_v;
+                            const int q = mulhi24(xs, c.M_v);
+                            const int y = (int)((unsigned)(__mul24(q, c.s_inv) + xs2) >> (q + 1));
+                            s[kb][4 * a4 + b] = __mul24(y, c.p_mul_hi_v);
+                        }
+                    }
+        }
         if (!FIRST) release_past();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -419,8 +445,9 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
 #pragma unroll
             for (int a4 = 0; a4 < 4; ++a4)
                 if (grp_on(kb, a4)) {
-                    const unsigned w = pack_byte<0>((unsigned)s[kb][4 * a4], (unsigned)s[kb][4 * a4 + 1],
-                                                    (unsigned)s[kb][4 * a4 + 2], (unsigned)s[kb][4 * a4 + 3]);
+                    const unsigned p0 = (unsigned)s[kb][4 * a4], p1 = (unsigned)s[kb][4 * a4 + 1];
+                    const unsigned p2 = (unsigned)s[kb][4 * a4 + 2], p3 = (unsigned)s[kb][4 * a4 + 3];
+                    const unsigned w = computed(kb, a4) ? pack_byte3(p0, p1, p2, p3) : pack_byte<0>(p0, p1, p2, p3);
                     pk[kb][a4] = (int)w;
                     rowsum = __builtin_amdgcn_sdot4((int)w, 0x01010101, rowsum, false);   // step 7
                 }
@@ -473,9 +500,9 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
             if (blk_on(kb)) {
                 v4i va;
                 if (LAY == kLaySwizzled) {
-                    const int va_addr = (vx ^ (32 * t)) + 2048 * kb;
+                    const int va_addr = (vx ^ (32 * t)) + 32 * D * kb;
                     const v2i_t lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(size_t)va_addr);
-                    const v2i_t hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(size_t)(va_addr + 1024));
+                    const v2i_t hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(size_t)(va_addr + 16 * D));
                     va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
                 } else {
                     va = *(const v4i*)(sV + (32 * t + li) * VROW + 32 * kb + 16 * g);

@@ -1,0 +1,28 @@
+"""GPU parity of the direct-load ring with 32 features per head: edges of tiles and row blocks, every
+workgroup size the plan can choose, look-ups mixed with computed weights (full tiles) and ragged tails."""
+import pytest
+
+import oracle
+from tests.test_gpu_parity import gpu, rand_case, run_gpu, assert_same  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, N): more than two workgroups of 32 rows per compute unit, so that the keys are not shared out
+SHAPES = [(60, 4, 65), (60, 4, 96), (45, 4, 128), (45, 4, 129), (30, 4, 191), (30, 4, 256), (24, 4, 257),
+          (12, 8, 320), (8, 12, 577), (5, 8, 513), (4, 6, 1000)]
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("bhn", SHAPES)
+def test_ring32(gpu, bhn, tile):  # noqa: F811
+    torch, qf, ctx = gpu
+    B, H, N = bhn
+    plan = qf.qflash_plan_query(ctx.handle, B, H, N, 32, tile)
+    assert plan.kernel == 0 and plan.key_waves == 0 and plan.query_blocks * plan.wavefronts_per_pair * 32 >= N, bhn
+    Q, K, V, sQ, sK, _ = rand_case((B, H, N, 32), 5000 + N, q_gain=1.0 + (N % 3) * 0.4)
+    for scale in (1.0, 40.0):                                # 40: coarse scores, x_shift > 0
+        p = oracle.derive_params(sQ * scale, sK * scale, 32, out_round=N % 2)
+        assert_same(run_gpu(gpu, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "%s x%g" % (bhn, scale))
+    if N in (129, 577):
+        ps = [oracle.derive_params(sQ * g, sK, 32) for g in ([0.2, 1.0, 30.0] + [1.3] * H)[:H]]
+        assert_same(run_gpu(gpu, Q, K, V, ps, tile), oracle.qflash_attention(Q, K, V, ps, tile), "%s per head" % (bhn,))
