@@ -162,8 +162,8 @@ extern "C" void qflash_debug_trace(void* buf) { g_trace = (unsigned long long*)b
 
 namespace {
 
-// Largest score difference (negated) with a weight above 0: x_p = ceil(8 s_inv / 2^k), 8 octaves; size of the table.
-int64_t table_span(const qflash_params& p) { return (8 * (int64_t)p.s_inv + ((int64_t)1 << p.x_shift) - 1) >> p.x_shift; }
+// x_p of the weight table of a set of constants; size of the table.
+int64_t table_span(const qflash_params& p) { return qflash_table_span(p.s_inv, p.x_shift, p.p_mul, p.p_shift); }
 int table_bytes(int64_t x_p) { return ((int)x_p + 1 + 15) & ~15; }
 
 // The kernel family the plan chose.
@@ -223,8 +223,9 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     // constants whose table is larger than that are refused, not silently run another way.
     int static_xp = 0, static_np = 0;
     if (static_table && table_wanted) {
+        // (refused by the size the header states, 8 s_inv / 2^k, not by the eighth less that is used)
+        if (((8 * (int64_t)p[0].s_inv + ((int64_t)1 << p[0].x_shift) - 1) >> p[0].x_shift) + 16 > kScratchBytes) return QFLASH_ERR_SCRATCH;
         const int64_t x_p = table_span(p[0]);
-        if (x_p + 16 > kScratchBytes) return QFLASH_ERR_SCRATCH;
         if (!scratch_ptr) return QFLASH_ERR_DEVICE;
         static_xp = (int)x_p;
         static_np = table_bytes(x_p);

@@ -105,7 +105,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     const ExpConst c = make_exp_const(hc);
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
     const int nb16 = rows16 >> 4;                   // 1 KiB loads per tensor of a pair
-    const int nt = tbytes >> 10;                    // 1 KiB loads of the table
+    const int nt = XM == kExpTable ? (hc.lut_bytes + 1023) >> 10 : 0;   // 1 KiB loads of the table
 
     // ---- the loads.  The wavefronts whose first unit belongs to pair g (its group) share the loads of
     //      that pair: member m of a group of n takes the pieces of the table (group 0 only), the 16-row

@@ -94,3 +94,16 @@ QF_HD inline bool qflash_fill_head_consts(const qflash_params& p, QflashHeadCons
     h->lut = nullptr; h->lut_bytes = 0; h->lut_xp = 0;
     return true;
 }
+
+// x_p of the weight table: the int8 weight of a score difference x is 0 for every x <= -x_p.
+// Eight octaves always suffice.  Exactly, a weight is 1 or more from y1 = ceil(2^r / M_r) (Eq. 10) on, and y
+// reaches it inside octave 6 (q = 6, y = (x + 8 s_inv) >> 7): the last x with weight 0 is the one below
+// 128 y1 - 8 s_inv, about 6.99 octaves down.  In octave 7 and beyond x + q s_inv stays below 0.008 s_inv
+// (M s_inv is -2^32 to 0.1 %), so y < 2.008 s_inv / 256 = s_inv / 127.49: below y1 if that is at least
+// s_inv / 127.4, which is checked (constants from real scales have y1 >= s_inv / 127.25).  An eighth less
+// table means an eighth less LDS: a fourth workgroup per compute unit for unit-variance inputs of 64 features.
+QF_HD inline int64_t qflash_table_span(int s_inv, int x_shift, int p_mul, int p_shift) {
+    const int64_t s = s_inv, y1 = (((int64_t)1 << p_shift) + p_mul - 1) / p_mul;
+    if (1274 * y1 >= 10 * s && 128 * y1 <= 2 * s) return ((8 * s - 128 * y1) >> x_shift) + 1;
+    return (8 * s + ((int64_t)1 << x_shift) - 1) >> x_shift;
+}

@@ -216,8 +216,8 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     const int nblk = (a.N + 31) / 32, cus = a.n_cu > 0 ? a.n_cu : 256;
     *qtiles = (nblk + want - 1) / want;
     const int w = *waves = (nblk + *qtiles - 1) / *qtiles;                        // balanced
-    // (at 64 features the SIMDs are busy enough for an uneven workgroup to cost its fullest SIMD's share)
-    const int eff = d == 64 ? (w + 3) & ~3 : w;
+    // (at 64 features the SIMDs are busy enough for an uneven workgroup to cost part of its fullest SIMD's share)
+    const double eff = d == 64 ? 0.5 * (w + ((w + 3) & ~3)) : w;
     const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 3) : a.kv_tile == 64 ? 6 : 4;   // by registers
     const long long units = (long long)a.B * a.H * *qtiles, per_cu = (units + cus - 1) / cus;
     long long fit = (long long)((size_t)lds_limit / qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d));

@@ -88,7 +88,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     //      loads the compiler counts, and it must not find them pending later, when waiting for
     //      them would mean waiting for the tile in flight.
     if (XM == kExpTable)
-        for (int it = wave; it < (tbytes >> 10); it += n_waves)
+        for (int it = wave; it < ((hc.lut_bytes + 1023) >> 10); it += n_waves)
             load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
     issue_tile(0);
     v4i qreg[D / 32];
