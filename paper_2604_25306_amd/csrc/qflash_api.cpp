@@ -413,7 +413,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         }
         if (rc == 0) rc = launch_attention(a, d, kv_tile, lds_limit, hip_stream);
         ctx->last_mode = a.exp_mode == 2 ? QFLASH_WEIGHTS_TABLE : a.exp_mode == 3 ? QFLASH_WEIGHTS_MIXED : QFLASH_WEIGHTS_ARITHMETIC;
-        ctx->last_kernel = a.win_mode ? 4 : a.cu_mode ? 3 : !a.resident ? 0 : a.ring ? 2 : 1;   // (2 also for the direct-load ring)
+        ctx->last_kernel = a.win_mode ? (a.bias && !a.bias_packed ? 1 : 4) : a.cu_mode ? 3 : !a.resident ? 0 : a.ring ? 2 : 1;   // (2 also for the direct-load ring)
         lk.unlock();
         if (cur != device) (void)hipSetDevice(cur);
         if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }

@@ -265,7 +265,7 @@ int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKe
     (void)kv_tile;                      // a single KV tile either way: 64 and 128 give the same result
     a->win_mode = 0;
     if (d != 32 || a->N <= 32 || a->N > 64 || a->per_head || a->qmax) return 0;
-    if (a->bias && (!a->bias_packed || a->bias_B < 1 || a->bias_H < 1 || a->B % a->bias_B != 0 || a->H % a->bias_H != 0)) return 0;
+    if (a->bias && (a->bias_B < 1 || a->bias_H < 1 || a->B % a->bias_B != 0 || a->H % a->bias_H != 0)) return 0;
     const long long T = (long long)a->B * a->H;
     const int cus = a->n_cu > 0 ? a->n_cu : 256;
     // as many runs as there are pairs, up to eight per compute unit (fewer where the table leaves

@@ -193,6 +193,13 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
 #pragma unroll
                         for (int v = 0; v < 16; ++v) s[kb][v] = kExcluded;
                     }
+                } else if (BIAS == kBiasPlain && n_valid >= 32) {
+#pragma unroll
+                    for (int a4 = 0; a4 < 4; ++a4) {
+                        const v4i_a4 bv = *(const v4i_a4*)(bias_row + 32 * (blk + kb) + 8 * a4 + 4 * g);
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) s[kb][4 * a4 + b] = __builtin_elementwise_add_sat(s[kb][4 * a4 + b], bv[b]);
+                    }
                 } else if (BIAS == kBiasPlain) {
 #pragma unroll
                     for (int a4 = 0; a4 < 4; ++a4)

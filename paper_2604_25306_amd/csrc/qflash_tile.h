@@ -12,6 +12,7 @@
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 namespace {
 
@@ -300,6 +301,12 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                     for (int b = 0; b < 4; ++b)
                         s[kb][4 * a4 + b] = __builtin_elementwise_add_sat(s[kb][4 * a4 + b], bv[b]);
                 }
+            } else if (BIAS == kBiasPlain && grp_on(kb, a4) && (FULL || !grp_cut(kb, a4))) {
+                // plain bias, a group inside the sequence: one load of four dwords (rows need not start on 16
+                // bytes; such a load asks for dword alignment only) instead of four loads
+                const v4i_a4 bv = *(const v4i_a4*)(bias_row + cb + 4 * g);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s[kb][4 * a4 + b] = __builtin_elementwise_add_sat(s[kb][4 * a4 + b], bv[b]);
             } else if (grp_on(kb, a4) && (BIAS || grp_cut(kb, a4))) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {

@@ -45,7 +45,7 @@ struct WinPair {      // where a run stands: pair t of the launch order
     int i, j;         // replica of the slice: batch step, head step
 };
 
-template <int XM>
+template <int XM, bool PLAIN>
 __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     constexpr int D = 32;
     constexpr bool KZ = XM == kExpShift0;
@@ -62,7 +62,7 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     const int lds0 = (int)(size_t)(lds_void)smem_win;
     const int tbytes = XM == kExpTable ? a.win_table_lds : 0;
     if (XM == kExpTable) {
-        for (int it = wave; it < (tbytes >> 10); it += n_waves)
+        for (int it = wave; it < ((hc.lut_bytes + 1023) >> 10); it += n_waves)
             load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
@@ -131,7 +131,27 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     // ---- accumulator input of the score product: bias (or 0) + 2^30, excluded / beyond the sequence: -2^29 + 2^30
     v16i cb[2];
     auto load_slice = [&](int s_idx) {
-        if (has_bias) {
+        if (PLAIN) {
+            // Plain [N,N] layout: every lane reads its own row, 8 loads of four columns that each touch 32 rows'
+            // lines; but once per run and slice, not once per pair.  (Buffer loads over the slice: one lane
+            // offset for all of them, and dwords past the last row read 0 instead of leaving the tensor.
+            // Rows need not start on 16 bytes: a load of four dwords asks for dword alignment only.)
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(a.bias + (size_t)s_idx * N * N), 0, 4 * N * N, 0x00020000);
+            const int lane_off = 4 * (min(row, N - 1) * N + 4 * g);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int a4 = 0; a4 < 4; ++a4) {
+                    const auto w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, 4 * (32 * kb + 8 * a4), 0);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) cb[kb][4 * a4 + b] = (int)w[b];
+                }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    cb[kb][v] = (32 * kb + 8 * (v >> 2) + 4 * g + (v & 3) < N ? max(cb[kb][v], kWinExcluded) : kWinExcluded) + kAccBias;
+        } else if (has_bias) {
             const int nb = (N + 31) / 32;                               // 2
             const int32_t* base = a.bias + (((size_t)s_idx * nb + half) * nb) * 1024 + 4 * lane;
 #pragma unroll
@@ -264,19 +284,20 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     if (have_prev && row < N) *(v4i*)(a.O + o_prev_off + o_lane) = o_prev;
 }
 
-template <int XM>
+// PLAIN: a bias in the plain [N,N] layout; else a packed one or none.
+template <int XM, bool PLAIN>
 __global__ __launch_bounds__(1024) void qflash_fwd_win(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
-        if (head_consts_or_dev(a, a.hc[0]).lut_bytes > 0) win_body<kExpTable>(a);
-        else win_body<kExpShift>(a);
+        if (head_consts_or_dev(a, a.hc[0]).lut_bytes > 0) win_body<kExpTable, PLAIN>(a);
+        else win_body<kExpShift, PLAIN>(a);
     } else {
-        win_body<XM>(a);
+        win_body<XM, PLAIN>(a);
     }
 }
 
-template <int XM>
+template <int XM, bool PLAIN>
 int launch_win(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    auto kern = qflash_fwd_win<XM>;
+    auto kern = qflash_fwd_win<XM, PLAIN>;
     // once per process and device: raise the dynamic LDS limit, and make sure that the kernel has no
     // static LDS in front of the dynamic one (the table index is used as an LDS address)
     static std::once_flag once[kQflashMaxDevices];
@@ -295,6 +316,14 @@ int launch_win(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t
     return (int)hipGetLastError();
 }
 
+template <bool PLAIN>
+int launch_mode(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
+    if (a.exp_mode == kExpAuto) return launch_win<kExpAuto, PLAIN>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpTable) return launch_win<kExpTable, PLAIN>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpShift0) return launch_win<kExpShift0, PLAIN>(a, lds, lds_limit, st);
+    return launch_win<kExpShift, PLAIN>(a, lds, lds_limit, st);
+}
+
 }  // namespace
 
 int qflash_launch_fwd_win(const QflashKernelArgs& a, int lds_limit, void* stream) {
@@ -303,15 +332,12 @@ int qflash_launch_fwd_win(const QflashKernelArgs& a, int lds_limit, void* stream
     if (!a.win_mode || a.N <= 32 || a.N > 64 || a.win_streams < 1 || a.win_streams > 8 || a.win_chunk < 1 || a.win_groups < 1)
         return (int)hipErrorInvalidValue;
     if ((long long)a.win_groups * a.win_streams * a.win_chunk < (long long)a.B * a.H) return (int)hipErrorInvalidValue;
-    if (a.bias && (!a.bias_packed || a.bias_B < 1 || a.bias_H < 1 || a.B % a.bias_B != 0 || a.H % a.bias_H != 0))
+    if (a.bias && (a.bias_B < 1 || a.bias_H < 1 || a.B % a.bias_B != 0 || a.H % a.bias_H != 0))
         return (int)hipErrorInvalidValue;
     if (a.per_head || a.qmax) return (int)hipErrorInvalidValue;
     const bool table = a.exp_mode == kExpTable || a.exp_mode == kExpAuto;
     if (table && a.lut_bytes_max > a.win_table_lds) return (int)hipErrorInvalidValue;
     const size_t lds = qflash_win_lds_bytes(a.win_streams, table ? a.win_table_lds : 0);
     if (lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
-    if (a.exp_mode == kExpAuto) return launch_win<kExpAuto>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpTable) return launch_win<kExpTable>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpShift0) return launch_win<kExpShift0>(a, lds, lds_limit, st);
-    return launch_win<kExpShift>(a, lds, lds_limit, st);
+    return a.bias && !a.bias_packed ? launch_mode<true>(a, lds, lds_limit, st) : launch_mode<false>(a, lds, lds_limit, st);
 }
