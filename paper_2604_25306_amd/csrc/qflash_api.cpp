@@ -597,7 +597,7 @@ extern "C" int qflash_attention_packed_bias(qflash_ctx* ctx, const int8_t* Q, co
 // Workspace layout of the dynamic entry point: [int8 Q | int8 K | int8 V | constants | abs-max scratch | weight table]
 namespace {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-size_t dyn_scratch_bytes(size_t n) {     // partial maxima of the abs-max kernel
+size_t dyn_scratch_bytes(size_t n) {     // score unit (a double), partial maxima of the abs-max kernel
     return align256(sizeof(float) * (4 + 3 * (size_t)qflash_dynamic_partials((long long)n)));
 }
 }
@@ -623,6 +623,7 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         n_cu = ctx->n_cu;
     }
     const bool with_bias = bias_real || excluded;
+    bool wants_table = true;
     if (!Qf || !Kf || !Vf || !O || !workspace) return QFLASH_ERR_NULL;
     if (d != 32 && d != 64) return QFLASH_ERR_SHAPE;
     if (B < 1 || H < 1 || N < 1 || N > QFLASH_MAX_N) return QFLASH_ERR_SHAPE;
@@ -651,6 +652,10 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         probe.bias_B = with_bias ? bias_B : 1;
         probe.bias_H = with_bias ? bias_H : 1;
         if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &probe) != 0) return QFLASH_ERR_SHAPE;
+        // a launch whose keys are shared out computes its weights (building a table takes longer than it saves)
+        probe.bias_packed = with_bias;
+        (void)qflash_plan_win(d, kv_tile, lds_limit, 0, &probe);
+        wants_table = qflash_plan_split(d, lds_limit, 0, &probe) == 0;
     }
 
     const size_t n = (size_t)B * H * N * d;        // a multiple of 32
@@ -659,8 +664,9 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
     int8_t* Ko = Qo + align256(n);
     int8_t* Vo = Ko + align256(n);
     QflashHeadConsts* hc_dev = (QflashHeadConsts*)(Vo + align256(n));
-    float* scratch = (float*)((int8_t*)hc_dev + align256(sizeof(QflashHeadConsts)));
-    uint8_t* dyn_table = (uint8_t*)scratch + dyn_scratch_bytes(n);    // kTableMaxBytes: a weight table made on the GPU
+    double* unit = (double*)((int8_t*)hc_dev + align256(sizeof(QflashHeadConsts)));
+    float* scratch = (float*)(unit + 2);
+    uint8_t* dyn_table = wants_table ? (uint8_t*)unit + dyn_scratch_bytes(n) : nullptr;    // kTableMaxBytes: a weight table made on the GPU
     int32_t* packed = (int32_t*)(ws + qflash_dynamic_workspace_bytes(B, H, N, d));   // with_bias only
 
     int cur = -1;
@@ -670,10 +676,9 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         return QFLASH_ERR_DEVICE;
     }
     int rc = qflash_launch_dynamic_front(Qf, Kf, Vf, Qo, Ko, Vo, (long long)n, std::sqrt((double)d), out_round,
-                                         scratch, hc_dev, info, dyn_table, kTableMaxBytes, hip_stream);
+                                         scratch, hc_dev, unit, info, dyn_table, kTableMaxBytes, hip_stream);
     if (rc == 0 && with_bias)
-        rc = qflash_launch_dynamic_bias(bias_real, excluded, bias_B * bias_H, N, packed, scratch, (long long)n,
-                                        std::sqrt((double)d), hip_stream);
+        rc = qflash_launch_dynamic_bias(bias_real, excluded, bias_B * bias_H, N, packed, unit, hip_stream);
     if (cur != device) (void)hipSetDevice(cur);
     if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }
     return attention_impl(ctx, Qo, Ko, Vo, O, with_bias ? packed : nullptr, with_bias ? bias_B : 0, with_bias ? bias_H : 0,

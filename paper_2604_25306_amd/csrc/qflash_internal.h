@@ -173,17 +173,18 @@ int qflash_launch_pack_bias(const int32_t* bias, int slices, int N, int32_t* pac
 
 // Enqueue the front end of the dynamic pipeline: abs-max of the three float32 tensors of n elements
 // each (n a multiple of 4), derivation of the scales and constants into *hc_dev (and *info if not
-// null), quantisation into Qo, Ko, Vo.  scratch: 3 * qflash_dynamic_partials(n) device floats.
+// null) and of the real value of one score unit into *unit, quantisation into Qo, Ko, Vo.
+// scratch: 3 * qflash_dynamic_partials(n) device floats.
 int qflash_dynamic_partials(long long n);
 // table (may be null): room for a weight table of up to table_max bytes; if the table of the
-// derived constants fits, the quantising kernel also builds it (one workgroup more, beside the
+// derived constants fits, the quantising kernel also builds it (a few workgroups more, beside the
 // streaming ones) and records it in *hc_dev (lut, lut_bytes, lut_xp); lut_bytes == 0 says "none".
 int qflash_launch_dynamic_front(const float* Qf, const float* Kf, const float* Vf, int8_t* Qo, int8_t* Ko, int8_t* Vo,
                                 long long n, double sqrt_d, int out_round, float* scratch,
-                                QflashHeadConsts* hc_dev, qflash_dynamic_info* info, uint8_t* table, int table_max,
+                                QflashHeadConsts* hc_dev, double* unit, qflash_dynamic_info* info, uint8_t* table, int table_max,
                                 void* stream);
-// Enqueue (after qflash_launch_dynamic_front on the same stream, same scratch and n) the kernel that
+// Enqueue (after qflash_launch_dynamic_front on the same stream, same unit) the kernel that
 // converts a real bias (float32 [slices,N,N] or null) and exclusion mask (uint8, same shape, or
 // null) into the packed int32 bias of the scales found by the abs-max step.
 int qflash_launch_dynamic_bias(const float* bias, const uint8_t* mask, int slices, int N, int32_t* packed,
-                               const float* scratch, long long n, double sqrt_d, void* stream);
+                               const double* unit, void* stream);
