@@ -365,13 +365,17 @@ class Context:
 
     def attention(self, Q, K, V, O, params, kv_tile, bias=None, stream=None):
         """``params``: one QFlashParams (per-tensor scales) or a sequence of H (per-head scales)."""
-        if isinstance(params, QFlashParams):
-            qflash_attention(self.handle, Q, K, V, O, params, kv_tile, bias, stream)
+        if isinstance(params, QFlashParams):        # (the compiled call directly: one Python frame less)
+            rc = (_native_mod or _native()).attention(_PER_TENSOR, self.handle, Q, K, V, O, params, kv_tile, bias, stream)
+            if rc != 0:
+                raise QFlashError(rc, "qflash_attention")
         else:
             qflash_attention_per_head(self.handle, Q, K, V, O, params, kv_tile, bias, stream)
 
     def attention_static(self, Q, K, V, O, params, kv_tile, bias=None, stream=None):
-        qflash_attention_static(self.handle, Q, K, V, O, params, kv_tile, bias, stream)
+        rc = (_native_mod or _native()).attention(_STATIC, self.handle, Q, K, V, O, params, kv_tile, bias, stream)
+        if rc != 0:
+            raise QFlashError(rc, "qflash_attention_static")
 
     def pack_bias(self, bias, stream=None):
         """Returns the packed copy of ``bias`` (a new int32 CUDA tensor) for ``attention_packed_bias``."""

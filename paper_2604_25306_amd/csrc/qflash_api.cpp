@@ -29,13 +29,13 @@ struct TableSlot {
 
 constexpr int kPlanQueryTableBytes = 32 * 1024;   // table size qflash_plan_query assumes (it is not given constants)
 constexpr int kTableSlots = 32;
-constexpr int kTableMaxBytes = 40 * 1024;
 
 // Device memory of the entry point that allocates nothing (qflash_attention_static): room for one
 // weight table.  Every GPU the library runs on holds its own copy until the process ends.  In host
 // code this name is only a stand-in for the symbol: the address that kernels and copies may use is
 // the one hipGetSymbolAddress reports for the current device (qflash_create, kept in the context).
 constexpr int kScratchBytes = QFLASH_STATIC_TABLE_BYTES;
+static_assert(kTableSlots <= 256, "a slot number is packed into eight bits");
 static_assert(kScratchBytes % 256 == 0 && kScratchBytes <= kTableMaxBytes, "one table at most");
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
@@ -164,7 +164,7 @@ namespace {
 
 // x_p of the weight table of a set of constants; size of the table.
 int64_t table_span(const qflash_params& p) { return qflash_table_span(p.s_inv, p.x_shift, p.p_mul, p.p_shift); }
-int table_bytes(int64_t x_p) { return ((int)x_p + 1 + 15) & ~15; }
+int table_bytes(int64_t x_p) { return qflash_table_bytes((int)x_p); }
 
 // The kernel family the plan chose.
 int launch_attention(QflashKernelArgs& a, int d, int kv_tile, int lds_limit, void* hip_stream) {
@@ -247,9 +247,12 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
 #ifdef QF_TRACE
     a.trace = g_trace;
 #endif
+    a.device = device;
+    a.lut_base = nullptr;
+    QflashHeadConsts hc[kQflashMaxParamHeads];
     bool all_k0 = hc_dev == nullptr;
     for (int h = 0; h < n_p; ++h) {
-        if (!qflash_fill_head_consts(p[h], &a.hc[h])) return QFLASH_ERR_PARAM;
+        if (!qflash_fill_head_consts(p[h], &hc[h])) return QFLASH_ERR_PARAM;
         all_k0 = all_k0 && p[h].x_shift == 0;
     }
     a.exp_mode = all_k0 ? 1 : 0;
@@ -310,10 +313,10 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // on the same stream (the array keeps the last call's table and every byte the kernel
         // stages, [0, static_np), is rewritten).  No lock: nothing of the context is touched.
         if (static_np > 0 && takes_table && table_fits(a, d, static_np, lds_limit)) {
-            rc = qflash_launch_build_table(scratch_ptr, static_xp + 1, static_np, static_xp, a.hc[0], hip_stream);
-            a.hc[0].lut = scratch_ptr;
-            a.hc[0].lut_bytes = static_np;
-            a.hc[0].lut_xp = static_xp;
+            rc = qflash_launch_build_table(scratch_ptr, static_xp + 1, static_np, static_xp, hc[0], hip_stream);
+            a.lut_base = scratch_ptr;
+            hc[0].lut_bytes = static_np;
+            hc[0].lut_xp = static_xp;
             a.exp_mode = 2;
             a.lut_bytes_max = static_np;
         }
@@ -383,7 +386,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
                     // The builder is enqueued under the lock, so no other host thread can enqueue a
                     // reader of this slot on the same stream ahead of it.
                     uint8_t* tbl = ctx->tables + (size_t)victim * kTableMaxBytes;
-                    rc = qflash_launch_build_table(tbl, xp[h] + 1, np_[h], xp[h], a.hc[h], hip_stream);
+                    rc = qflash_launch_build_table(tbl, xp[h] + 1, np_[h], xp[h], hc[h], hip_stream);
                     if (rc == 0) {
                         slot = victim;
                         if (victim == ctx->n_slots) ++ctx->n_slots;
@@ -397,9 +400,9 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             if (slot < 0) { has[h] = false; continue; }     // no slot to be had: this head computes
             ctx->slots[slot].last_use = now;
             if (capturing) ctx->slots[slot].pinned = true;
-            a.hc[h].lut = ctx->tables + (size_t)slot * kTableMaxBytes;
-            a.hc[h].lut_bytes = np_[h];
-            a.hc[h].lut_xp = xp[h];
+            hc[h].lut_bytes = np_[h];
+            hc[h].lut_xp = xp[h];
+            a.hw[h] = qflash_pack_head(hc[h], slot);
             ++n_with;
         }
         if (rc == 0 && n_with == n_p) {
@@ -409,8 +412,11 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             a.exp_mode = 3;
             a.lut_bytes_max = max_bytes;
         } else {
-            for (int h = 0; h < n_p; ++h) { a.hc[h].lut = nullptr; a.hc[h].lut_bytes = 0; a.hc[h].lut_xp = 0; }
+            for (int h = 0; h < n_p; ++h) hc[h].lut_bytes = 0;
         }
+        a.lut_base = ctx->tables;
+        for (int h = 0; h < n_p; ++h)
+            if (hc[h].lut_bytes == 0) a.hw[h] = qflash_pack_head(hc[h], 0);
         if (rc == 0) rc = launch_attention(a, d, kv_tile, lds_limit, hip_stream);
         ctx->last_mode = a.exp_mode == 2 ? QFLASH_WEIGHTS_TABLE : a.exp_mode == 3 ? QFLASH_WEIGHTS_MIXED : QFLASH_WEIGHTS_ARITHMETIC;
         ctx->last_kernel = a.win_mode ? (a.bias && !a.bias_packed ? 1 : 4) : a.cu_mode ? 3 : !a.resident ? 0 : a.ring ? 2 : 1;   // (2 also for the direct-load ring)
@@ -419,6 +425,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }
         return QFLASH_OK;
     }
+    if (!hc_dev) a.hw[0] = qflash_pack_head(hc[0], 0);
     if (rc == 0) rc = launch_attention(a, d, kv_tile, lds_limit, hip_stream);
     if (cur != device) (void)hipSetDevice(cur);
     if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }

@@ -25,8 +25,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <mutex>
-
+#include "qflash_launch.h"
 #include "qflash_tile.h"
 
 // (M0 is written by the direct loads below and declared as clobbered; the compiler's remark that it
@@ -99,7 +98,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     if (wave >= n_waves) return;
     QF_T(1);
 
-    const QflashHeadConsts hc = head_consts_or_dev(a, a.hc[0]);   // one set of constants per launch
+    const QflashHeadConsts hc = head_consts(a, 0);   // one set of constants per launch
 
     // ---- loop-invariant registers
     const ExpConst c = make_exp_const(hc);
@@ -278,7 +277,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 template <int XM>
 __global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
-        if (head_consts_or_dev(a, a.hc[0]).lut_bytes > 0) cu_body<kExpTable>(a);
+        if (head_consts(a, 0).lut_bytes > 0) cu_body<kExpTable>(a);
         else cu_body<kExpShift>(a);
     } else {
         cu_body<XM>(a);
@@ -287,23 +286,7 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) 
 
 template <int XM>
 int launch_cu(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    auto kern = qflash_fwd_cu<XM>;
-    // once per process and device: raise the dynamic LDS limit, and make sure that the kernel has no
-    // static LDS in front of the dynamic one (the table index is used as an LDS address)
-    static std::once_flag once[kQflashMaxDevices];
-    static int status[kQflashMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kQflashMaxDevices) return (int)hipErrorInvalidDevice;
-    std::call_once(once[dev], [&] {
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
-        if (e == hipSuccess && fa.sharedSizeBytes != 0) e = hipErrorInvalidValue;
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-        status[dev] = (int)e;
-    });
-    if (status[dev] != 0) return status[dev];
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.cu_groups), dim3((unsigned)(64 * a.cu_waves)), lds, st, a);
-    return (int)hipGetLastError();
+    return qflash_launch_kernel<qflash_fwd_cu<XM>>(a, (unsigned)a.cu_groups, (unsigned)(64 * a.cu_waves), lds, lds_limit, st);
 }
 
 }  // namespace

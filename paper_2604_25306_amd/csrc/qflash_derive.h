@@ -90,7 +90,7 @@ QF_HD inline bool qflash_fill_head_consts(const qflash_params& p, QflashHeadCons
     h->p_mul = p.p_mul; h->p_shift = p.p_shift; h->a_mul = p.a_mul;
     const int64_t x0 = (41 * (int64_t)p.s_inv + ((int64_t)2 << p.x_shift) - 1) >> (p.x_shift + 1);
     if ((x0 << p.x_shift) * 2 > 57 * (int64_t)p.s_inv) return false;
-    h->x_floor = (int)-x0;
+    h->x_floor = qflash_x_floor(p.s_inv, p.x_shift);        // -x0
     h->lut = nullptr; h->lut_bytes = 0; h->lut_xp = 0;
     return true;
 }

@@ -1,8 +1,15 @@
 // Internal interface between the host side of the C ABI and the gfx950 kernels.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #include "qflash.h"
+
+#if defined(__HIPCC__)
+#define QF_UNIT_HD __host__ __device__
+#else
+#define QF_UNIT_HD
+#endif
 
 // Integer constants of Algorithm 1 / 2 for one head, or for the whole tensor (see qflash_params).
 struct QflashHeadConsts {
@@ -16,8 +23,14 @@ struct QflashHeadConsts {
     const uint8_t* lut;      // nullptr = none
 };
 
-// Per-head constants travel in the kernel arguments (at most 4 KB in all).
+// Per-head constants travel in the kernel arguments, which the host copies on every launch: packed, 20
+// bytes per head (the unpacked structures made it 3.9 KB and 0.3 us).
 constexpr int kQflashMaxParamHeads = 64;
+constexpr int kTableMaxBytes = 40 * 1024;    // largest weight table, and the distance of two in the context's cache
+
+struct QflashHeadWords {
+    uint32_t w[5];   // s_inv | x_shift << 18 | p_shift << 22 | has table << 27; exp_mul; p_mul; a_mul; table slot | lut_xp << 8
+};
 
 struct QflashKernelArgs {
     const int8_t* Q;
@@ -70,12 +83,46 @@ struct QflashKernelArgs {
     unsigned long long* trace;   // instrumented builds only: [workgroup][wavefront][16] timestamps
 #endif
     int qmax;                // 1: the quantised-maximum variant (not Algorithm 1 as printed; every x_shift must be 0)
-    int per_head;            // 0: hc[0] serves every head; 1: head h uses hc[h] (H <= kQflashMaxParamHeads)
+    int per_head;            // 0: hw[0] serves every head; 1: head h uses hw[h] (H <= kQflashMaxParamHeads)
     // Constants computed on the GPU (dynamic quantisation): if set, the kernel reads this device
-    // structure instead of hc[]; exp_mode is then 0 (the host does not know the constants).
+    // structure instead of hw[]; exp_mode is then 0 (the host does not know the constants).
     const QflashHeadConsts* hc_dev;
-    QflashHeadConsts hc[kQflashMaxParamHeads];
+    const uint8_t* lut_base;                 // table slot 0
+    int device;                              // the GPU of the launch (current when it is made)
+    QflashHeadWords hw[kQflashMaxParamHeads];
 };
+
+// Number of bytes of a weight table that reaches down to -x_p (multiple of 16).
+QF_UNIT_HD inline int qflash_table_bytes(int x_p) { return (x_p + 1 + 15) & ~15; }
+
+// The constants of one head packed for the kernel arguments, and unpacked in the kernel.
+inline QflashHeadWords qflash_pack_head(const QflashHeadConsts& h, int table_slot /* used if h has a table */) {
+    QflashHeadWords r;
+    const bool has = h.lut_bytes > 0;
+    r.w[0] = (uint32_t)h.s_inv | (uint32_t)h.x_shift << 18 | (uint32_t)h.p_shift << 22 | (has ? 1u << 27 : 0u);
+    r.w[1] = (uint32_t)h.exp_mul;
+    r.w[2] = (uint32_t)h.p_mul;
+    r.w[3] = (uint32_t)h.a_mul;
+    r.w[4] = has ? (uint32_t)table_slot | (uint32_t)h.lut_xp << 8 : 0u;
+    return r;
+}
+// x_floor of a set of constants: the smallest multiple of 2^-k at or below -20.5 octaves (qflash_fill_head_consts).
+QF_UNIT_HD inline int qflash_x_floor(int s_inv, int x_shift) { return -((41 * s_inv + (2 << x_shift) - 1) >> (x_shift + 1)); }
+QF_UNIT_HD inline QflashHeadConsts qflash_unpack_head(const QflashHeadWords& r, const uint8_t* lut_base) {
+    QflashHeadConsts h;
+    h.s_inv = (int)(r.w[0] & 0x3ffffu);
+    h.x_shift = (int)(r.w[0] >> 18 & 15u);
+    h.p_shift = (int)(r.w[0] >> 22 & 31u);
+    h.exp_mul = (int)r.w[1];
+    h.p_mul = (int)r.w[2];
+    h.a_mul = (int)r.w[3];
+    h.x_floor = qflash_x_floor(h.s_inv, h.x_shift);
+    const bool has = (r.w[0] >> 27 & 1u) != 0;
+    h.lut_xp = (int)(r.w[4] >> 8);
+    h.lut_bytes = has ? qflash_table_bytes(h.lut_xp) : 0;
+    h.lut = has ? lut_base + (size_t)(r.w[4] & 255u) * kTableMaxBytes : nullptr;
+    return h;
+}
 
 // Which unit of work a workgroup takes (host and device: the kernels use it, qflash_plan_unit
 // reports it).  Consecutive workgroup indices go to consecutive XCDs (each with its own L2), so XCD
@@ -83,11 +130,6 @@ struct QflashKernelArgs {
 // L2.  With a bias whose slices repeat every xcd_period units (windowed attention: the same windows
 // in every image) XCD x instead takes the x-th eighth of every period, so that each L2 only ever
 // sees an eighth of the bias.  The result may be >= n_units: such a workgroup has nothing to do.
-#if defined(__HIPCC__)
-#define QF_UNIT_HD __host__ __device__
-#else
-#define QF_UNIT_HD
-#endif
 QF_UNIT_HD inline int qflash_unit_of_workgroup(int wg, int units_per_xcd, int xcd_period) {
     const int x = wg & 7, k = wg >> 3;
     if (xcd_period == 0) return x * units_per_xcd + k;

@@ -7,10 +7,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <mutex>
-
 #include "qflash_internal.h"
 #include "qflash_device.h"
+#include "qflash_launch.h"
 #include "qflash_tile.h"
 
 namespace {
@@ -522,25 +521,8 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
 
 template <int D, int BC, int BIAS, bool NARROW, int XM, bool QMAX>
 int launch_resident(const QflashKernelArgs& a, size_t lds_bytes, int lds_limit, int threads, hipStream_t stream) {
-    const dim3 grid((unsigned)(8 * a.units_per_xcd));
-    auto kern = qflash_fwd_resident<D, BC, BIAS, NARROW, XM, QMAX>;
-    // once per process and device: raise the dynamic LDS limit of this kernel, and make sure that it
-    // has no static LDS in front of the dynamic one (the index into the weight table is used as an
-    // LDS address)
-    static std::once_flag once[kQflashMaxDevices];
-    static int status[kQflashMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kQflashMaxDevices) return (int)hipErrorInvalidDevice;
-    std::call_once(once[dev], [&] {
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
-        if (e == hipSuccess && fa.sharedSizeBytes != 0) e = hipErrorInvalidValue;
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-        status[dev] = (int)e;
-    });
-    if (status[dev] != 0) return status[dev];
-    hipLaunchKernelGGL(kern, grid, dim3((unsigned)threads), lds_bytes, stream, a);
-    return (int)hipGetLastError();
+    return qflash_launch_kernel<qflash_fwd_resident<D, BC, BIAS, NARROW, XM, QMAX>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)threads,
+                                                                                  lds_bytes, lds_limit, stream);
 }
 
 template <int D, int BC, int BIAS, bool NARROW, bool QMAX>
@@ -554,9 +536,8 @@ int launch_mode(const QflashKernelArgs& a, size_t lds, int lds_limit, int thread
 template <int D, int BC, int BIAS, bool QMAX>
 int launch_dbc_bias(const QflashKernelArgs& a, bool resident, size_t lds, int lds_limit, int threads, hipStream_t st) {
     if (!resident) {
-        const dim3 grid((unsigned)(8 * a.units_per_xcd));
-        hipLaunchKernelGGL((qflash_fwd_stream<D, BC, BIAS, QMAX>), grid, dim3(kStreamThreads), 0, st, a);
-        return (int)hipGetLastError();
+        return qflash_launch_kernel<qflash_fwd_stream<D, BC, BIAS, QMAX>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)kStreamThreads, 0,
+                                                                         lds_limit, st, true);
     }
     return a.N <= 256 ? launch_mode<D, BC, BIAS, true, QMAX>(a, lds, lds_limit, threads, st)
                       : launch_mode<D, BC, BIAS, false, QMAX>(a, lds, lds_limit, threads, st);

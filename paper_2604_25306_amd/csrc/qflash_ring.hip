@@ -26,8 +26,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <mutex>
-
+#include "qflash_launch.h"
 #include "qflash_tile.h"
 
 // (M0 is written by the direct loads below and declared as clobbered)
@@ -160,23 +159,7 @@ __global__ __launch_bounds__(64 * kRingMaxWaves, (ring_min_waves<D, BC, XM>())) 
 
 template <int D, int BC, int XM, bool QMAX>
 int launch_ring(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    auto kern = qflash_fwd_ring<D, BC, XM, QMAX>;
-    // once per process and device: raise the dynamic LDS limit, and make sure that the kernel has no
-    // static LDS in front of the dynamic one (the table index is used as an LDS address)
-    static std::once_flag once[kQflashMaxDevices];
-    static int status[kQflashMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kQflashMaxDevices) return (int)hipErrorInvalidDevice;
-    std::call_once(once[dev], [&] {
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
-        if (e == hipSuccess && fa.sharedSizeBytes != 0) e = hipErrorInvalidValue;
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-        status[dev] = (int)e;
-    });
-    if (status[dev] != 0) return status[dev];
-    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * a.units_per_xcd)), dim3((unsigned)(64 * a.waves_per_head)), lds, st, a);
-    return (int)hipGetLastError();
+    return qflash_launch_kernel<qflash_fwd_ring<D, BC, XM, QMAX>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)(64 * a.waves_per_head), lds, lds_limit, st);
 }
 
 }  // namespace

@@ -31,8 +31,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <mutex>
-
+#include "qflash_launch.h"
 #include "qflash_tile.h"
 
 namespace {
@@ -373,23 +372,7 @@ __global__ __launch_bounds__(KB == 1 ? 1024 : 512) void qflash_fwd_split(const Q
 
 template <int D, int BC, int BIAS, int XM, int KB>
 int launch_split(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    auto kern = qflash_fwd_split<D, BC, BIAS, XM, KB>;
-    // once per process and device: raise the dynamic LDS limit, and make sure that the kernel has no
-    // static LDS in front of the dynamic one (the table index is used as an LDS address)
-    static std::once_flag once[kQflashMaxDevices];
-    static int status[kQflashMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kQflashMaxDevices) return (int)hipErrorInvalidDevice;
-    std::call_once(once[dev], [&] {
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
-        if (e == hipSuccess && fa.sharedSizeBytes != 0) e = hipErrorInvalidValue;
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-        status[dev] = (int)e;
-    });
-    if (status[dev] != 0) return status[dev];
-    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * a.units_per_xcd)), dim3((unsigned)(64 * a.split_waves)), lds, st, a);
-    return (int)hipGetLastError();
+    return qflash_launch_kernel<qflash_fwd_split<D, BC, BIAS, XM, KB>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)(64 * a.split_waves), lds, lds_limit, st);
 }
 
 template <int D, int BC, int BIAS, int KB>

@@ -642,7 +642,7 @@ __device__ __forceinline__ QflashHeadConsts head_consts_or_dev(const QflashKerne
     return h;
 }
 __device__ __forceinline__ QflashHeadConsts head_consts(const QflashKernelArgs& a, int bh) {
-    return head_consts_or_dev(a, a.hc[a.per_head ? bh % a.H : 0]);
+    return head_consts_or_dev(a, qflash_unpack_head(a.hw[a.per_head ? bh % a.H : 0], a.lut_base));
 }
 static_assert(offsetof(QflashHeadConsts, x_floor) == 24 && offsetof(QflashHeadConsts, lut_xp) == 28 &&
               offsetof(QflashHeadConsts, lut_bytes) == 32 && offsetof(QflashHeadConsts, lut) == 40,

@@ -25,8 +25,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <mutex>
-
+#include "qflash_launch.h"
 #include "qflash_tile.h"
 
 // (M0 is written by the direct loads below and declared as clobbered)
@@ -54,7 +53,7 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
-    const QflashHeadConsts hc = head_consts_or_dev(a, a.hc[0]);
+    const QflashHeadConsts hc = head_consts(a, 0);
     const ExpConst c = make_exp_const(hc);
 
     // ---- LDS: [weight table, a.win_table_lds bytes][wavefront w: two sets of V (2 KiB), K (2 KiB),
@@ -288,7 +287,7 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
 template <int XM, bool PLAIN>
 __global__ __launch_bounds__(1024) void qflash_fwd_win(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
-        if (head_consts_or_dev(a, a.hc[0]).lut_bytes > 0) win_body<kExpTable, PLAIN>(a);
+        if (head_consts(a, 0).lut_bytes > 0) win_body<kExpTable, PLAIN>(a);
         else win_body<kExpShift, PLAIN>(a);
     } else {
         win_body<XM, PLAIN>(a);
@@ -297,23 +296,7 @@ __global__ __launch_bounds__(1024) void qflash_fwd_win(const QflashKernelArgs a)
 
 template <int XM, bool PLAIN>
 int launch_win(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    auto kern = qflash_fwd_win<XM, PLAIN>;
-    // once per process and device: raise the dynamic LDS limit, and make sure that the kernel has no
-    // static LDS in front of the dynamic one (the table index is used as an LDS address)
-    static std::once_flag once[kQflashMaxDevices];
-    static int status[kQflashMaxDevices];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kQflashMaxDevices) return (int)hipErrorInvalidDevice;
-    std::call_once(once[dev], [&] {
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
-        if (e == hipSuccess && fa.sharedSizeBytes != 0) e = hipErrorInvalidValue;
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_limit);
-        status[dev] = (int)e;
-    });
-    if (status[dev] != 0) return status[dev];
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.win_groups), dim3((unsigned)(128 * a.win_streams)), lds, st, a);
-    return (int)hipGetLastError();
+    return qflash_launch_kernel<qflash_fwd_win<XM, PLAIN>>(a, (unsigned)a.win_groups, (unsigned)(128 * a.win_streams), lds, lds_limit, st);
 }
 
 template <bool PLAIN>
