@@ -280,6 +280,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         if (qmax || a.win_mode) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
         else if (!qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table_hint, &a) && table_hint > 0)
             qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, 0, &a);
+        if (per_head && !qmax && !a.win_mode) qflash_plan_cu_heads(B * H, N, d, kv_tile, lds_limit, &a);
         // attention_static would have to build its table ahead of a launch no longer than that takes
         qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     }
@@ -324,7 +325,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // The context's lock is held until the attention kernel has been enqueued: a slot this launch
         // reads must not be handed to other constants by another host thread in between.
         std::unique_lock<std::mutex> lk(ctx->mu);
-        const bool allowed = ctx->use_table && ctx->tables && takes_table && (a.split_waves || !(per_head && a.heads_per_wg > 1 && !a.same_head));
+        const bool allowed = ctx->use_table && ctx->tables && takes_table && (a.split_waves || a.cu_mode || !(per_head && a.heads_per_wg > 1 && !a.same_head));
         // A stream under capture records the kernels instead of running them: a table built now would
         // be read, by eager launches with the same constants, before it has ever been written.  Such a
         // call only uses tables that already exist (and pins them, since the graph keeps reading them).
@@ -341,7 +342,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             const int64_t x_p = table_span(p[h]);
             xp[h] = (int)x_p;
             np_[h] = table_bytes(x_p);
-            has[h] = allowed && x_p + 16 <= kTableMaxBytes;
+            has[h] = allowed && x_p + 16 <= kTableMaxBytes && !(per_head && a.cu_mode && !a.split_waves && np_[h] > a.cu_table_lds);
             if (has[h] && np_[h] > max_bytes) max_bytes = np_[h];
         }
         if (max_bytes == 0 || !table_fits(a, d, max_bytes, lds_limit))
@@ -413,6 +414,12 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             a.lut_bytes_max = max_bytes;
         } else {
             for (int h = 0; h < n_p; ++h) hc[h].lut_bytes = 0;
+        }
+        if (per_head && a.cu_mode) {
+            // (heads with a table first)
+            a.cu_table_heads = n_with;
+            int with = 0, without = n_with;
+            for (int h = 0; h < n_p; ++h) a.cu_order[hc[h].lut_bytes > 0 ? with++ : without++] = (uint8_t)h;
         }
         a.lut_base = ctx->tables;
         for (int h = 0; h < n_p; ++h)

@@ -38,6 +38,8 @@ extern __shared__ __align__(1024) int8_t smem_cu[];
 
 typedef __attribute__((address_space(3))) int lds_int;
 
+template <int XM> struct WeightMode { static constexpr int value = XM; };
+
 // Wait until the counter at flag_addr (LDS) has reached target.  The LDS serves the requests of a
 // wavefront in order, so the reads that follow in program order see what was written before the
 // counter was; the empty statement only keeps the compiler from moving them up.
@@ -62,10 +64,12 @@ __device__ __forceinline__ void count_up(int flag_addr) {
 #define QF_T(K_) do {} while (0)
 #endif
 
-template <int XM>
+// PH: one set of constants per head.  The pairs are then dealt out so that every workgroup gets its share of
+// those with a table and of those without, the former one head after the other: a workgroup stages
+// the table of its first pair's head, and a unit of a pair of another head computes its weights.
+template <int XM, bool PH>
 __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     constexpr int D = 64, BC = 64;
-    constexpr bool SB = XM == kExpTable;
     const int N = a.N;
     const int rows16 = (N + 15) & ~15;
     const int slot = rows16 * D;                    // LDS bytes of one tensor of one pair
@@ -73,6 +77,19 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     const int hpw = a.cu_heads;
     const int head0 = blockIdx.x * hpw;
     const int n_heads = min(hpw, a.B * a.H - head0);
+    // PH: lane h < n_heads holds pair and head of slot h.  Slots [p0, p0 + n_heads) of the launch: T of the P
+    // pairs have a table, so slot position p stands behind p T / P of them (rounded down).
+    [[maybe_unused]] int pair_l = 0, head_l = 0, table_head = -1;
+    if constexpr (PH) {
+        const int P = a.B * a.H, T = a.cu_table_heads * a.B;
+        const int t0 = (int)((long long)head0 * T / P), n_t = (int)((long long)(head0 + n_heads) * T / P) - t0;
+        const int h = min((int)(threadIdx.x & 63), n_heads - 1);
+        const int x = h < n_t ? t0 + h : T + (head0 - t0) + (h - n_t);          // position in head order
+        head_l = a.cu_order[x / a.B];
+        pair_l = (x % a.B) * a.H + head_l;
+        if (n_t > 0) table_head = __builtin_amdgcn_readfirstlane(head_l);
+    }
+    auto pair_of = [&](int h) { return PH ? __builtin_amdgcn_readlane(pair_l, h) : head0 + h; };
     const int units = n_heads * nblk;
     const int n_waves = min((int)(blockDim.x >> 6), units);   // the last workgroup may have fewer pairs: extra wavefronts leave
     const int lane = threadIdx.x & 63;
@@ -98,13 +115,14 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     if (wave >= n_waves) return;
     QF_T(1);
 
-    const QflashHeadConsts hc = head_consts(a, 0);   // one set of constants per launch
+    // constants of the launch; PH: of the table's head, each unit then takes those of its own
+    const QflashHeadConsts hc0 = PH ? head_consts(a, max(table_head, 0)) : head_consts(a, 0);
 
     // ---- loop-invariant registers
-    const ExpConst c = make_exp_const(hc);
+    const ExpConst c0 = make_exp_const(hc0);
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
     const int nb16 = rows16 >> 4;                   // 1 KiB loads per tensor of a pair
-    const int nt = XM == kExpTable ? (hc.lut_bytes + 1023) >> 10 : 0;   // 1 KiB loads of the table
+    const int nt = XM == kExpTable && (!PH || table_head >= 0) ? (hc0.lut_bytes + 1023) >> 10 : 0;   // 1 KiB loads of the table
 
     // ---- the loads.  The wavefronts whose first unit belongs to pair g (its group) share the loads of
     //      that pair: member m of a group of n takes the pieces of the table (group 0 only), the 16-row
@@ -142,16 +160,16 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
         if (my_group > 0) wait_count(cnt_base, nblk);
         if (XM == kExpTable && my_group == 0)
             for (int it = member; it < nt; it += group_size)
-                load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
+                load_1k_to_lds((const int8_t*)hc0.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
         const int x0 = min(8, 2 * nb16);                            // K/V block numbers of the first tile
         auto load_q = [&](int h, int mi, int np) {
-            const size_t head_off = (size_t)(head0 + h) * N * D;
+            const size_t head_off = (size_t)pair_of(h) * N * D;
             for (int b = mi; b < nb16; b += np)
                 load_1k_to_lds(a.Q + head_off + 1024 * b, b == nb16 - 1 ? off_last : off_norm,
                                kv_base + (3 * h + 2) * slot + 1024 * b);
         };
         auto load_kv = [&](int h, int x_lo, int x_hi, int mi, int np) {
-            const size_t head_off = (size_t)(head0 + h) * N * D;
+            const size_t head_off = (size_t)pair_of(h) * N * D;
             const int first = x_lo + ((mi - x_lo) % np + np) % np;
             for (int x = first; x < x_hi; x += np) {
                 const int b = x >> 1;
@@ -201,8 +219,9 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
         const int row0 = 32 * blk, i = row0 + li;
         RowState<D> st;
         st.l = 0;
-        st.m = SB ? (int)((unsigned)kMInit + (unsigned)kAccBias) : kMInit;
         v4i qreg[2];
+        const QflashHeadConsts hc = PH ? head_consts(a, __builtin_amdgcn_readlane(head_l, h)) : hc0;
+        const ExpConst c = PH ? make_exp_const(hc) : c0;
 #define QF_TILE(FULL_, FIRST_, J_, NV_, NG_)                                                               \
         if (first_unit && (J_) == (n_tiles > 1 ? 1 : 0)) {                                                 \
             /* second tile of the first unit (or its only one): all own loads have had a tile's time */   \
@@ -221,7 +240,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
             _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                  \
                 qreg[s] = *(lds_v4i*)(size_t)(Qb + row0 * D + (sl.k_off ^ (32 * s)));                      \
         }                                                                                                  \
-        process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_>(                          \
+        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_>(                          \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,      \
             Kb + 4096 * (J_) + sl.k_off, Vb + 4096 * (J_) + sl.v_off);                                     \
         if (tk == 6) QF_T(9 + (J_))
@@ -237,12 +256,22 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
             case 7: { QF_TILE(false, FIRST_, J_, rem, 7); } break;                                         \
             default: { QF_TILE(false, FIRST_, J_, rem, 8); } break;                                        \
         }
-        if (n_full > 0) {
-            QF_TILE(true, true, 0, BC, 0);
-            for (int j = 1; j < n_full; ++j) { QF_TILE(true, false, j, BC, 0); }
-            if (rem > 0) { QF_RAGGED(false, n_full) }
+        auto walk = [&](auto mode) {
+            constexpr int UM = decltype(mode)::value;          // weight mode of this unit
+            st.m = UM == kExpTable ? (int)((unsigned)kMInit + (unsigned)kAccBias) : kMInit;
+            if (n_full > 0) {
+                QF_TILE(true, true, 0, BC, 0);
+                for (int j = 1; j < n_full; ++j) { QF_TILE(true, false, j, BC, 0); }
+                if (rem > 0) { QF_RAGGED(false, n_full) }
+            } else {
+                QF_RAGGED(true, 0)
+            }
+        };
+        if constexpr (PH && XM == kExpTable) {
+            if (__builtin_amdgcn_readlane(head_l, h) == table_head) walk(WeightMode<kExpTable>{});
+            else walk(WeightMode<kExpShift>{});
         } else {
-            QF_RAGGED(true, 0)
+            walk(WeightMode<XM>{});
         }
 #undef QF_RAGGED
 #undef QF_TILE
@@ -253,7 +282,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
             // the unit loop would be held in registers across all the tile code, or spilled)
             v4i w[2];
             normalise_words<D, 16>(st, a.out_round != 0, w);
-            int8_t* Ob = a.O + (size_t)(head0 + h) * N * D;
+            int8_t* Ob = a.O + (size_t)pair_of(h) * N * D;
             unsigned o_lane = (unsigned)(i * D + g * (D / 2));
             asm volatile("" : "+v"(o_lane));
             *(v4i*)(Ob + o_lane) = w[0];
@@ -274,19 +303,19 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 #endif
 }
 
-template <int XM>
+template <int XM, bool PH>
 __global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
-        if (head_consts(a, 0).lut_bytes > 0) cu_body<kExpTable>(a);
-        else cu_body<kExpShift>(a);
+        if (head_consts(a, 0).lut_bytes > 0) cu_body<kExpTable, PH>(a);
+        else cu_body<kExpShift, PH>(a);
     } else {
-        cu_body<XM>(a);
+        cu_body<XM, PH>(a);
     }
 }
 
-template <int XM>
+template <int XM, bool PH>
 int launch_cu(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    return qflash_launch_kernel<qflash_fwd_cu<XM>>(a, (unsigned)a.cu_groups, (unsigned)(64 * a.cu_waves), lds, lds_limit, st);
+    return qflash_launch_kernel<qflash_fwd_cu<XM, PH>>(a, (unsigned)a.cu_groups, (unsigned)(64 * a.cu_waves), lds, lds_limit, st);
 }
 
 }  // namespace
@@ -299,8 +328,14 @@ int qflash_launch_fwd_cu(const QflashKernelArgs& a, int lds_limit, void* stream)
     if (table && a.lut_bytes_max > a.cu_table_lds) return (int)hipErrorInvalidValue;
     const size_t lds = qflash_cu_lds_bytes(a.N, a.cu_heads, table ? a.cu_table_lds : 0);
     if (lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
-    if (a.exp_mode == kExpAuto) return launch_cu<kExpAuto>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpTable) return launch_cu<kExpTable>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0>(a, lds, lds_limit, st);
-    return launch_cu<kExpShift>(a, lds, lds_limit, st);
+    if (a.per_head) {
+        if (a.hc_dev || a.cu_table_heads < 0 || a.cu_table_heads > a.H || a.H > kQflashMaxParamHeads) return (int)hipErrorInvalidValue;
+        if (table) return launch_cu<kExpTable, true>(a, lds, lds_limit, st);
+        if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, true>(a, lds, lds_limit, st);
+        return launch_cu<kExpShift, true>(a, lds, lds_limit, st);
+    }
+    if (a.exp_mode == kExpAuto) return launch_cu<kExpAuto, false>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpTable) return launch_cu<kExpTable, false>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, false>(a, lds, lds_limit, st);
+    return launch_cu<kExpShift, false>(a, lds, lds_limit, st);
 }

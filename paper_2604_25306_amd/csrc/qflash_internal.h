@@ -65,6 +65,8 @@ struct QflashKernelArgs {
     int cu_groups;           // workgroups
     int cu_waves;            // wavefronts per workgroup (at most 16)
     int cu_table_lds;        // LDS bytes reserved for the weight table (a multiple of 1 KiB)
+    int cu_table_heads;      // per-head constants: number of heads with a table, and
+    uint8_t cu_order[kQflashMaxParamHeads];   // the heads, those with a table first
     // two-tile ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
     int ring_dma;
     int ring_table_lds;      // LDS bytes reserved for the weight table (a multiple of 1 KiB)
@@ -170,6 +172,9 @@ int qflash_plan_fwd(int BH, int N, int d, int kv_tile, int lds_limit, QflashKern
 // no bias, one set of constants): decides whether the launch takes it, assuming a weight table of
 // table_bytes (0: none), and fills the cu_* fields.  Reads bias, per_head, n_cu (0: 256).  Returns cu_mode.
 int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
+// The same kernel for per-head constants: heads whose table is at most cu_table_lds bytes (what is left of LDS)
+// look their weights up, the others compute them.
+int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* args);
 int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stream);
 
 // The persistent kernel for windowed attention (33 to 64 tokens, 32 features, one KV tile, no bias or a

@@ -200,6 +200,23 @@ int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_b
     return 1;
 }
 
+int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* a) {
+    QflashKernelArgs one = *a;
+    one.per_head = 0;
+    a->cu_mode = 0;
+    if (!a->per_head || N <= 64 || !qflash_plan_cu(BH, N, d, kv_tile, lds_limit, 0, &one)) return 0;
+    // (with one pair per compute unit, or one KV tile, the resident kernel is as fast: 10.6 us for 192 pairs of
+    // 197 tokens against 10.9, 7.8 for 768 pairs of 64 against 8.1; 768 pairs of 197: 24.4 against 22.7)
+    if (one.cu_heads < 2) return 0;
+    a->cu_mode = 1;
+    a->cu_heads = one.cu_heads;
+    a->cu_groups = one.cu_groups;
+    a->cu_waves = one.cu_waves;
+    const int left = lds_limit - (int)qflash_cu_lds_bytes(N, one.cu_heads, 0);
+    a->cu_table_lds = left < kTableMaxBytes ? left & ~1023 : kTableMaxBytes;
+    return 1;
+}
+
 // LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and two KV tiles of K and V.
 size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
     (void)waves;
