@@ -248,14 +248,14 @@ int qflash_attention_packed_bias(qflash_ctx* ctx,
  *               or QFLASH_ERR_PARAM when the scales fall outside the supported window (O is then
  *               all zeros, with or without info).
  *   workspace   device scratch of at least qflash_dynamic_workspace_bytes(B,H,N,d) bytes, 16-byte
- *               aligned, caller-owned; it holds the int8 copies of Q, K, V among other things and
- *               must stay untouched until the stream has executed the work.  The call allocates
- *               nothing.
+ *               aligned, caller-owned; it holds the int8 copies of Q, K, V among other things (where
+ *               the attention kernel does not quantise by itself) and must stay untouched until the
+ *               stream has executed the work.  The call allocates nothing.
  *   out_round, kv_tile, hip_stream  as for qflash_attention.  No integer bias in these entry
  *               points (it is expressed in a score unit that is only known on the GPU here);
  *               qflash_attention_dynamic_bias takes one in real units.
  * The weight table of the look-up mode, if the constants allow one, is built on the GPU as well
- * (in the workspace).
+ * (in the workspace, or by the attention kernel in its own memory).
  * Errors: CTX, NULL, SHAPE (also: workspace too small), TILE, PARAM (out_round), ALIGN, DEVICE,
  * LAUNCH.
  */

@@ -193,7 +193,8 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
                    const int32_t* bias, int bias_B, int bias_H, int B, int H, int N, int d, int kv_tile,
                    const qflash_params* p, bool per_head, void* hip_stream,
                    QflashHeadConsts* hc_dev = nullptr, int out_round_dev = 0, bool bias_packed = false,
-                   uint8_t* dyn_table = nullptr, bool static_table = false) {
+                   uint8_t* dyn_table = nullptr, bool static_table = false, const float* dyn_partial = nullptr,
+                   qflash_dynamic_info* dyn_info = nullptr) {
     if (!ctx) return QFLASH_ERR_NULL;
     int device, lds_limit, n_cu;
     uint8_t* scratch_ptr;
@@ -243,6 +244,10 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     a.per_head = per_head ? 1 : 0;
     a.qmax = qmax ? 1 : 0;
     a.hc_dev = hc_dev;
+    a.dyn_partial = dyn_partial;
+    a.dyn_partials = dyn_partial ? qflash_dynamic_partials((long long)B * H * N * d) : 0;
+    a.dyn_sqrt_d = std::sqrt((double)d);
+    a.dyn_info = dyn_info;
     a.n_cu = n_cu;
 #ifdef QF_TRACE
     a.trace = g_trace;
@@ -277,13 +282,15 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         if (!qmax && qflash_plan_win(d, kv_tile, lds_limit, table_hint, &a) == 0 && table_hint > 0)
             qflash_plan_win(d, kv_tile, lds_limit, 0, &a);
         qflash_plan_ring(d, lds_limit, table_hint, &a);
-        if (qmax || a.win_mode) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
+        if (dyn_partial) (void)qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &a);
+        else if (qmax || a.win_mode || hc_dev) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
         else if (!qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table_hint, &a) && table_hint > 0)
             qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, 0, &a);
         if (per_head && !qmax && !a.win_mode) qflash_plan_cu_heads(B * H, N, d, kv_tile, lds_limit, &a);
         // attention_static would have to build its table ahead of a launch no longer than that takes
         qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     }
+    if (dyn_partial && (!a.cu_mode || a.split_waves || a.win_mode)) return QFLASH_ERR_SHAPE;    // (the caller planned the same launch)
     const bool takes_table = a.resident || a.ring_dma || a.split_waves;
     // wave priority by dispatch round: only for launches of two to four rounds (0 = off)
     if (a.n_units <= n_cu || a.n_units > 4 * n_cu) a.n_cu = 0;
@@ -305,7 +312,12 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // the stream, which also decides whether there is one (mode 3 reads that decision per
         // workgroup; without mode 3 the table is simply not looked at).
         const bool use_table = table_wanted;
-        if (use_table && dyn_table && takes_table && table_fits(a, d, kTableMaxBytes, lds_limit)) {
+        if (dyn_partial) {
+            // the kernel makes the table itself, in every workgroup: worth it from two scores per entry on (24.7 K entries: 48.4 us
+            // against 52.3 with 116 K scores per workgroup, even with 20 to 34 K, 17.0 against 14.1 with 13 K)
+            const long long half = (long long)a.cu_heads * N * N / 2;
+            a.lut_bytes_max = !table_wanted ? 0 : half < a.cu_table_lds ? (int)half : a.cu_table_lds;
+        } else if (use_table && dyn_table && takes_table && table_fits(a, d, kTableMaxBytes, lds_limit)) {
             a.exp_mode = 3;
             a.lut_bytes_max = kTableMaxBytes;
         }
@@ -637,7 +649,7 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         n_cu = ctx->n_cu;
     }
     const bool with_bias = bias_real || excluded;
-    bool wants_table = true;
+    bool wants_table = true, fused = false;
     if (!Qf || !Kf || !Vf || !O || !workspace) return QFLASH_ERR_NULL;
     if (d != 32 && d != 64) return QFLASH_ERR_SHAPE;
     if (B < 1 || H < 1 || N < 1 || N > QFLASH_MAX_N) return QFLASH_ERR_SHAPE;
@@ -670,6 +682,8 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         probe.bias_packed = with_bias;
         (void)qflash_plan_win(d, kv_tile, lds_limit, 0, &probe);
         wants_table = qflash_plan_split(d, lds_limit, 0, &probe) == 0;
+        // ... and one that gives whole compute units to a workgroup quantises on the way in
+        fused = wants_table && qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &probe) != 0;
     }
 
     const size_t n = (size_t)B * H * N * d;        // a multiple of 32
@@ -689,12 +703,16 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         (void)hipGetLastError();
         return QFLASH_ERR_DEVICE;
     }
-    int rc = qflash_launch_dynamic_front(Qf, Kf, Vf, Qo, Ko, Vo, (long long)n, std::sqrt((double)d), out_round,
+    int rc = fused ? qflash_launch_absmax(Qf, Kf, Vf, (long long)n, scratch, hip_stream) :
+             qflash_launch_dynamic_front(Qf, Kf, Vf, Qo, Ko, Vo, (long long)n, std::sqrt((double)d), out_round,
                                          scratch, hc_dev, unit, info, dyn_table, kTableMaxBytes, hip_stream);
     if (rc == 0 && with_bias)
         rc = qflash_launch_dynamic_bias(bias_real, excluded, bias_B * bias_H, N, packed, unit, hip_stream);
     if (cur != device) (void)hipSetDevice(cur);
     if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }
+    if (fused)
+        return attention_impl(ctx, (const int8_t*)Qf, (const int8_t*)Kf, (const int8_t*)Vf, O, nullptr, 0, 0, B, H, N, d, kv_tile,
+                              nullptr, false, hip_stream, hc_dev, out_round, false, nullptr, false, scratch, info);
     return attention_impl(ctx, Qo, Ko, Vo, O, with_bias ? packed : nullptr, with_bias ? bias_B : 0, with_bias ? bias_H : 0,
                           B, H, N, d, kv_tile, nullptr, false, hip_stream, hc_dev, out_round, with_bias, dyn_table);
 }

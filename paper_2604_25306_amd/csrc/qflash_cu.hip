@@ -25,6 +25,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "qflash_derive_device.h"
 #include "qflash_launch.h"
 #include "qflash_tile.h"
 
@@ -64,6 +65,108 @@ __device__ __forceinline__ void count_up(int flag_addr) {
 #define QF_T(K_) do {} while (0)
 #endif
 
+// The units of a workgroup, from unit u0 of this wavefront on.  ready(pair, tile, first tile of the unit, first unit of the
+// wavefront) returns when the tile (and what goes with the first one of a unit) is in LDS; next_unit: LDS
+// address of the counter; PH: hc0 are the constants of the table's head, otherwise of the launch.
+template <int XM, bool PH, class Ready, class PairOf, class HeadOf>
+__device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const QflashHeadConsts& hc0, int table_head, int u0, int units,
+                                         int nblk, int kv_base, int slot, int next_unit, int wave, int trace_base,
+                                         Ready ready, PairOf pair_of, HeadOf head_of) {
+    constexpr int D = 64, BC = 64;
+    const int N = a.N;
+    const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
+    const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
+    const ExpConst c0 = make_exp_const(hc0);
+    const int n_tiles = (N + BC - 1) / BC;
+    [[maybe_unused]] int tk = 3;
+
+    // Units: wavefront w starts with unit w; all further ones come from the counter.
+    bool first_unit = true;
+    int u = u0;
+    while (u < units) {
+        // (the sequence length through an opaque copy: the compiler would otherwise evaluate every
+        // "is this group of keys inside the sequence" test of the ragged tile once, ahead of the loop,
+        // and keep the answers in more scalar registers than there are)
+        int N_ = N;
+        asm volatile("" : "+s"(N_));
+        // (likewise the lane's half: the key indices of the ragged tile derive from it, two dozen
+        // registers' worth if they are prepared ahead of the loop)
+        int g_ = g;
+        asm volatile("" : "+v"(g_));
+        const int n_full = N_ / BC, rem = N_ - n_full * BC;
+        const int h = u / nblk, blk = u - h * nblk;
+        const int Kb = kv_base + 3 * h * slot, Vb = Kb + slot, Qb = Vb + slot;
+        const int row0 = 32 * blk, i = row0 + li;
+        RowState<D> st;
+        st.l = 0;
+        v4i qreg[2];
+        const QflashHeadConsts hc = PH ? head_consts(a, head_of(h)) : hc0;
+        const ExpConst c = PH ? make_exp_const(hc) : c0;
+#define QF_TILE(FULL_, FIRST_, J_, NV_, NG_)                                                               \
+        ready(h, J_, FIRST_, first_unit);                                                                  \
+        if (FIRST_) QF_T(tk);                                                                              \
+        if (FIRST_) {                                                                                      \
+            _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                  \
+                qreg[s] = *(lds_v4i*)(size_t)(Qb + row0 * D + (sl.k_off ^ (32 * s)));                      \
+        }                                                                                                  \
+        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_>(                          \
+            st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,      \
+            Kb + 4096 * (J_) + sl.k_off, Vb + 4096 * (J_) + sl.v_off);                                     \
+        if (tk == 6) QF_T(9 + (J_))
+        // the ragged tile, with its number of groups of 8 keys as a compile-time constant
+#define QF_RAGGED(FIRST_, J_)                                                                              \
+        switch ((rem + 7) >> 3) {                                                                          \
+            case 1: { QF_TILE(false, FIRST_, J_, rem, 1); } break;                                         \
+            case 2: { QF_TILE(false, FIRST_, J_, rem, 2); } break;                                         \
+            case 3: { QF_TILE(false, FIRST_, J_, rem, 3); } break;                                         \
+            case 4: { QF_TILE(false, FIRST_, J_, rem, 4); } break;                                         \
+            case 5: { QF_TILE(false, FIRST_, J_, rem, 5); } break;                                         \
+            case 6: { QF_TILE(false, FIRST_, J_, rem, 6); } break;                                         \
+            case 7: { QF_TILE(false, FIRST_, J_, rem, 7); } break;                                         \
+            default: { QF_TILE(false, FIRST_, J_, rem, 8); } break;                                        \
+        }
+        auto walk = [&](auto mode) {
+            constexpr int UM = decltype(mode)::value;          // weight mode of this unit
+            st.m = UM == kExpTable ? (int)((unsigned)kMInit + (unsigned)kAccBias) : kMInit;
+            if (n_full > 0) {
+                QF_TILE(true, true, 0, BC, 0);
+                for (int j = 1; j < n_full; ++j) { QF_TILE(true, false, j, BC, 0); }
+                if (rem > 0) { QF_RAGGED(false, n_full) }
+            } else {
+                QF_RAGGED(true, 0)
+            }
+        };
+        if constexpr (PH && XM == kExpTable) {
+            if (head_of(h) == table_head) walk(WeightMode<kExpTable>{});
+            else walk(WeightMode<kExpShift>{});
+        } else {
+            walk(WeightMode<XM>{});
+        }
+#undef QF_RAGGED
+#undef QF_TILE
+        first_unit = false;
+        QF_T(tk + 1);
+        if (i < N) {
+            // (uniform base plus a 32-bit lane offset made here: a per-lane 64-bit pointer prepared ahead of
+            // the unit loop would be held in registers across all the tile code, or spilled)
+            v4i w[2];
+            normalise_words<D, 16>(st, a.out_round != 0, w);
+            int8_t* Ob = a.O + (size_t)pair_of(h) * N * D;
+            unsigned o_lane = (unsigned)(i * D + g * (D / 2));
+            asm volatile("" : "+v"(o_lane));
+            *(v4i*)(Ob + o_lane) = w[0];
+            *(v4i*)(Ob + o_lane + 16) = w[1];
+        }
+        // next unit
+        int nxt = 0;
+        if (lane == 0) nxt = __hip_atomic_fetch_add((lds_int*)(size_t)(next_unit), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        u = __builtin_amdgcn_readfirstlane(nxt);
+        QF_T(tk + 2);
+        tk += 3;
+    }
+    QF_T(15);
+}
+
 // PH: one set of constants per head.  The pairs are then dealt out so that every workgroup gets its share of
 // those with a table and of those without, the former one head after the other: a workgroup stages
 // the table of its first pair's head, and a unit of a pair of another head computes its weights.
@@ -94,7 +197,6 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     const int n_waves = min((int)(blockDim.x >> 6), units);   // the last workgroup may have fewer pairs: extra wavefronts leave
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = lane >> 5, li = lane & 31;
 
     // LDS map (dynamic LDS is the only LDS of this kernel, so it starts at address 0 and the index
     // into the weight table is its address): [table][pair 0: K, V, Q][pair 1: ...] ... [1 KiB that
@@ -119,8 +221,6 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
     const QflashHeadConsts hc0 = PH ? head_consts(a, max(table_head, 0)) : head_consts(a, 0);
 
     // ---- loop-invariant registers
-    const ExpConst c0 = make_exp_const(hc0);
-    const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
     const int nb16 = rows16 >> 4;                   // 1 KiB loads per tensor of a pair
     const int nt = XM == kExpTable && (!PH || table_head >= 0) ? (hc0.lut_bytes + 1023) >> 10 : 0;   // 1 KiB loads of the table
 
@@ -194,108 +294,29 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
             load_kv(last_group, 0, x0, member, nblk + last_size);
         }
     }
-    const int n_tiles = (N + BC - 1) / BC;
-    [[maybe_unused]] int tk = 3;
     QF_T(2);
-
-    // Units: wavefront w starts with unit w; all further ones come from the counter.
-    bool first_unit = true;
-    int u = wave;
-    while (u < units) {
-        // (the sequence length through an opaque copy: the compiler would otherwise evaluate every
-        // "is this group of keys inside the sequence" test of the ragged tile once, ahead of the loop,
-        // and keep the answers in more scalar registers than there are)
-        int N_ = N;
-        asm volatile("" : "+s"(N_));
-        // (likewise the lane's half: the key indices of the ragged tile derive from it, two dozen
-        // registers' worth if they are prepared ahead of the loop)
-        int g_ = g;
-        asm volatile("" : "+v"(g_));
-        const int n_full = N_ / BC, rem = N_ - n_full * BC;
-        const int h = u / nblk, blk = u - h * nblk;
+    const int n_tiles = (N + BC - 1) / BC;
+    auto ready = [&](int h, int j, bool first, bool first_unit) {
+        if (first_unit && j == (n_tiles > 1 ? 1 : 0)) {
+            // second tile of the first unit (or its only one): all own loads have had a tile's time
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) {
+                if (helper) count_up(cnt_base + 4 * (4 * last_group));
+                for (int s = 1; s < n_tiles; ++s) count_up(cnt_base + 4 * (4 * my_group + s));
+                for (int e = my_group + 1; e <= my_group + n_extra; ++e)
+                    for (int s = 0; s < n_tiles; ++s) count_up(cnt_base + 4 * (4 * e + s));
+            }
+        }
+        if (first && XM == kExpTable && h != 0) wait_count(cnt_base, min(nblk, n_waves));
         const int owner = min(h, last_group);
         const int target = min(nblk, n_waves - owner * nblk);
-        const int Kb = kv_base + 3 * h * slot, Vb = Kb + slot, Qb = Vb + slot;
-        const int row0 = 32 * blk, i = row0 + li;
-        RowState<D> st;
-        st.l = 0;
-        v4i qreg[2];
-        const QflashHeadConsts hc = PH ? head_consts(a, __builtin_amdgcn_readlane(head_l, h)) : hc0;
-        const ExpConst c = PH ? make_exp_const(hc) : c0;
-#define QF_TILE(FULL_, FIRST_, J_, NV_, NG_)                                                               \
-        if (first_unit && (J_) == (n_tiles > 1 ? 1 : 0)) {                                                 \
-            /* second tile of the first unit (or its only one): all own loads have had a tile's time */   \
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                               \
-            if (lane == 0) {                                                                               \
-                if (helper) count_up(cnt_base + 4 * (4 * last_group));                                     \
-                for (int s = 1; s < n_tiles; ++s) count_up(cnt_base + 4 * (4 * my_group + s));             \
-                for (int e = my_group + 1; e <= my_group + n_extra; ++e)                                   \
-                    for (int s = 0; s < n_tiles; ++s) count_up(cnt_base + 4 * (4 * e + s));                \
-            }                                                                                              \
-        }                                                                                                  \
-        if ((FIRST_) && XM == kExpTable && h != 0) wait_count(cnt_base, min(nblk, n_waves));               \
-        wait_count(cnt_base + 4 * (4 * h + (J_)), (J_) == 0 && small_last && h == last_group ? target + nblk : target); \
-        if (FIRST_) QF_T(tk);                                                                              \
-        if (FIRST_) {                                                                                      \
-            _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                  \
-                qreg[s] = *(lds_v4i*)(size_t)(Qb + row0 * D + (sl.k_off ^ (32 * s)));                      \
-        }                                                                                                  \
-        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_>(                          \
-            st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,      \
-            Kb + 4096 * (J_) + sl.k_off, Vb + 4096 * (J_) + sl.v_off);                                     \
-        if (tk == 6) QF_T(9 + (J_))
-        // the ragged tile, with its number of groups of 8 keys as a compile-time constant
-#define QF_RAGGED(FIRST_, J_)                                                                              \
-        switch ((rem + 7) >> 3) {                                                                          \
-            case 1: { QF_TILE(false, FIRST_, J_, rem, 1); } break;                                         \
-            case 2: { QF_TILE(false, FIRST_, J_, rem, 2); } break;                                         \
-            case 3: { QF_TILE(false, FIRST_, J_, rem, 3); } break;                                         \
-            case 4: { QF_TILE(false, FIRST_, J_, rem, 4); } break;                                         \
-            case 5: { QF_TILE(false, FIRST_, J_, rem, 5); } break;                                         \
-            case 6: { QF_TILE(false, FIRST_, J_, rem, 6); } break;                                         \
-            case 7: { QF_TILE(false, FIRST_, J_, rem, 7); } break;                                         \
-            default: { QF_TILE(false, FIRST_, J_, rem, 8); } break;                                        \
-        }
-        auto walk = [&](auto mode) {
-            constexpr int UM = decltype(mode)::value;          // weight mode of this unit
-            st.m = UM == kExpTable ? (int)((unsigned)kMInit + (unsigned)kAccBias) : kMInit;
-            if (n_full > 0) {
-                QF_TILE(true, true, 0, BC, 0);
-                for (int j = 1; j < n_full; ++j) { QF_TILE(true, false, j, BC, 0); }
-                if (rem > 0) { QF_RAGGED(false, n_full) }
-            } else {
-                QF_RAGGED(true, 0)
-            }
-        };
-        if constexpr (PH && XM == kExpTable) {
-            if (__builtin_amdgcn_readlane(head_l, h) == table_head) walk(WeightMode<kExpTable>{});
-            else walk(WeightMode<kExpShift>{});
-        } else {
-            walk(WeightMode<XM>{});
-        }
-#undef QF_RAGGED
-#undef QF_TILE
-        first_unit = false;
-        QF_T(tk + 1);
-        if (i < N) {
-            // (uniform base plus a 32-bit lane offset made here: a per-lane 64-bit pointer prepared ahead of
-            // the unit loop would be held in registers across all the tile code, or spilled)
-            v4i w[2];
-            normalise_words<D, 16>(st, a.out_round != 0, w);
-            int8_t* Ob = a.O + (size_t)pair_of(h) * N * D;
-            unsigned o_lane = (unsigned)(i * D + g * (D / 2));
-            asm volatile("" : "+v"(o_lane));
-            *(v4i*)(Ob + o_lane) = w[0];
-            *(v4i*)(Ob + o_lane + 16) = w[1];
-        }
-        // next unit
-        int nxt = 0;
-        if (lane == 0) nxt = __hip_atomic_fetch_add((lds_int*)(size_t)(cnt_base + 4 * 4 * hpw), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        u = __builtin_amdgcn_readfirstlane(nxt);
-        QF_T(tk + 2);
-        tk += 3;
-    }
-    QF_T(15);
+        wait_count(cnt_base + 4 * (4 * h + j), j == 0 && small_last && h == last_group ? target + nblk : target);
+    };
+#ifndef QF_TRACE
+    const int trace_base = 0;
+#endif
+    cu_units<XM, PH>(a, hc0, table_head, wave, units, nblk, kv_base, slot, cnt_base + 4 * 4 * hpw, wave, trace_base, ready,
+                     pair_of, [&](int h) { return __builtin_amdgcn_readlane(head_l, h); });
 #ifdef QF_TRACE
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (a.trace && lane < 16)
@@ -305,12 +326,196 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 
 template <int XM, bool PH>
 __global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) {
-    if constexpr (XM == kExpAuto) {
-        if (head_consts(a, 0).lut_bytes > 0) cu_body<kExpTable, PH>(a);
-        else cu_body<kExpShift, PH>(a);
+    cu_body<XM, PH>(a);
+}
+
+// ---- the same from float32 tensors (dynamic quantisation): the kernel quantises on the way into LDS
+//
+// After the abs-max pass the tensors are read once more and neither the int8 copies nor the constants
+// travel through memory: 12 B read + 1 B written per element triple instead of 12 + 3 and 3 + 1 in two
+// launches, and all but the last pair's attention runs while floats are still arriving.  Bound by that
+// read (from the last-level cache where the tensors fit it).  Whole call, abs-max included: 768 pairs of 197
+// tokens 64.8 -> 48.4 us, 384 35.6 -> 29.4, 480 of 256 52.5 -> 40.8, 2048 of 50 40.0 -> 29.9.
+//
+// Wavefront 0 derives the constants (double precision on one lane, 3 us); the others quantise the
+// first pairs, 4 KiB of floats (16 rows) at a time with two pieces of loads in flight each (with one
+// or two 48 us, with three or four 51).  Then the first `workers` wavefronts build the weight table
+// in LDS and start on the units, while the others go on quantising pair after pair and join them at
+// the end (8 workers: with 4 to 12 of the 16 within 3 %).  Nobody waits for anything but loads, the
+// constants (wavefront 0 waits for no other) and the table and tiles that the former two lead to, so
+// every wavefront reaches its exit.
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kCuDynWaves = 16;
+constexpr int kCuDynWorkers = 8;      // at most: wavefronts that start on the units while the others quantise
+
+__global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs a) {
+    constexpr int D = 64;
+    constexpr int kDepth = 2;                       // pieces in flight per wavefront
+    const int N = a.N;
+    const int nb16 = (N + 15) >> 4;                 // pieces per tensor of a pair
+    const int slot = 16 * nb16 * D;
+    const int nblk = (N + 31) >> 5;
+    const int hpw = a.cu_heads;
+    const int head0 = blockIdx.x * hpw;
+    const int n_heads = min(hpw, a.B * a.H - head0);
+    const int units = n_heads * nblk;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int early = min(n_heads, max(1, kCuDynWorkers / nblk));     // pairs that everybody quantises first
+    const int workers = min(early * nblk, kCuDynWorkers);
+
+    // LDS map: as above, then [constants ready][wavefronts done with the table][the constants]
+    const int lds0 = (int)(size_t)(lds_void)smem_cu;
+    const int kv_base = lds0 + a.cu_table_lds;
+    const int cnt_base = kv_base + hpw * 3 * slot + 1024;
+    const int next_unit = cnt_base + 16 * hpw, hc_ready = next_unit + 4, table_ready = next_unit + 8, hc_base = next_unit + 12;
+    for (int t = threadIdx.x; t < 4 * hpw + 3; t += blockDim.x) *(lds_int*)(size_t)(cnt_base + 4 * t) = t == 4 * hpw ? workers : 0;
+    __syncthreads();
+
+    // ---- partial maxima of the three tensors (at most 256 each)
+    float part[3][4];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part[t][k] = a.dyn_partial[t * a.dyn_partials + min(lane + 64 * k, a.dyn_partials - 1)];
+    auto maximum = [&](int t) {
+        float m = fmaxf(fmaxf(part[t][0], part[t][1]), fmaxf(part[t][2], part[t][3]));
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+        return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));
+    };
+
+    if (wave == 0) {
+        const float am[3] = {maximum(0), maximum(1), maximum(2)};
+        if (lane == 0) {
+            QflashHeadConsts h;
+            derive_on_device(am, a.dyn_sqrt_d, a.out_round, &h, blockIdx.x == 0 ? a.dyn_info : nullptr, nullptr);
+            reserve_table(&h, nullptr, a.lut_bytes_max);
+            const int w[9] = {h.x_shift, h.s_inv, h.exp_mul, h.p_mul, h.p_shift, h.a_mul, h.x_floor, h.lut_xp, h.lut_bytes};
+#pragma unroll
+            for (int k = 0; k < 9; ++k) *(lds_int*)(size_t)(hc_base + 4 * k) = w[k];
+            count_up(hc_ready);
+        }
     } else {
-        cu_body<XM, PH>(a);
+        // ---- pieces: index x of the launch's share -> pair x / per; inside a pair the blocks of Q, then
+        //      those of K and V in turn
+        const int per = 3 * nb16;
+        const unsigned per_inv = (unsigned)(0x100000000ull / (unsigned)per) + 1u;
+        struct Piece { int x, h, y; };               // h < 0: none left
+        const int first_end = early * per, end = n_heads * per;
+        auto place = [&](int x) {
+            Piece p;
+            p.x = x;
+            p.h = x < end ? (int)__umulhi((unsigned)x, per_inv) : -1;
+            p.y = x - p.h * per;
+            return p;
+        };
+        auto next = [&](int x) {
+            if (x < first_end) {
+                x += kCuDynWaves - 1;
+                if (x >= first_end) x = wave >= workers ? first_end + wave - workers : end;
+            } else {
+                x += kCuDynWaves - workers;
+            }
+            return place(x);
+        };
+        v4f buf[kDepth][4];
+        Piece pc[kDepth];
+        // loads of a piece: lane l takes 16 bytes of row 4 u + l / 16; what lies beyond the sequence (or a
+        // piece that does not exist) reads as zero
+        auto issue = [&](int s) {
+            const Piece p = pc[s];
+            const int h = max(p.h, 0), z = p.y - nb16, b = z < 0 ? p.y : z >> 1;
+            const float* base = (const float*)(z < 0 ? a.Q : (z & 1) ? a.V : a.K) + (size_t)(head0 + h) * N * D + 1024 * b;
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, p.h < 0 ? 0 : 4 * (N * D - 1024 * b), 0x00020000);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                buf[s][u] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, 16 * lane + 1024 * u, 0, 0));
+        };
+        const int x0 = wave - 1;
+        pc[0] = place(x0 < first_end ? x0 : wave >= workers ? first_end + wave - workers : end);
+        issue(0);
+#pragma unroll
+        for (int s = 1; s < kDepth; ++s) { pc[s] = next(pc[s - 1].x); issue(s); }
+        float r[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const float am = maximum(t);
+            r[t] = am == 0.0f ? 0.0f : __fdiv_rn(127.0f, am);
+        }
+        // byte of row 4 u + lane / 16: the 16-byte pieces of a row are permuted by (row / 4) & 3 = u
+        const int w_lane = 64 * (lane >> 4) + 16 * ((lane & 15) >> 2) + 4 * (lane & 3);
+        // (no way out of the middle of a trip: the compiler would have every trip wait for all its loads)
+        while (pc[0].h >= 0) {
+#pragma unroll
+            for (int s = 0; s < kDepth; ++s) {
+                const Piece p = pc[s];
+                const int z = p.y - nb16, b = z < 0 ? p.y : z >> 1;
+                const float rr = z < 0 ? r[0] : (z & 1) ? r[2] : r[1];
+                const int dst = kv_base + (3 * p.h + (z < 0 ? 2 : z & 1)) * slot + 1024 * b;
+                int packed[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    // clip, then round half to even by adding 1.5 * 2^23: the low byte of the sum is the integer
+                    unsigned q[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float c = __builtin_amdgcn_fmed3f(__fmul_rn(buf[s][u][e], rr), -127.0f, 127.0f);
+                        q[e] = __float_as_uint(__fadd_rn(c, 12582912.0f));
+                    }
+                    packed[u] = (int)(__builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u) | __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu));
+                }
+                // (converted before the registers are loaded again, not in the branch below)
+                asm volatile("" : "+v"(packed[0]), "+v"(packed[1]), "+v"(packed[2]), "+v"(packed[3]));
+                pc[s] = next(pc[(s + kDepth - 1) % kDepth].x);
+                issue(s);
+                if (p.h >= 0) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) *(lds_int*)(size_t)(dst + (w_lane ^ (16 * u)) + 256 * u) = packed[u];
+                    // (the LDS serves a wavefront's requests in order: the count is seen after the bytes)
+                    if (lane == 0) count_up(cnt_base + 4 * (4 * p.h + (z < 0 ? 0 : b >> 2)));
+                }
+            }
+        }
     }
+
+    // ---- constants; the weight table
+    wait_count(hc_ready, 1);
+    QflashHeadConsts hc;
+    {
+        int w[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) w[k] = __builtin_amdgcn_readfirstlane(*(lds_int*)(size_t)(hc_base + 4 * k));
+        hc.x_shift = w[0]; hc.s_inv = w[1]; hc.exp_mul = w[2]; hc.p_mul = w[3]; hc.p_shift = w[4]; hc.a_mul = w[5];
+        hc.x_floor = w[6]; hc.lut_xp = w[7]; hc.lut_bytes = w[8];
+        hc.lut = nullptr;
+    }
+    if (wave < workers && hc.lut_bytes > 0) {
+        const ExpConst c = make_exp_const(hc);
+        for (int i = 4 * (64 * wave + lane); i < hc.lut_bytes; i += 4 * 64 * workers) {
+            unsigned w = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w |= (i + e <= hc.lut_xp ? table_entry(i + e, hc.lut_xp, hc, c) : 0u) << (8 * e);
+            *(lds_int*)(size_t)(lds0 + i) = (int)w;
+        }
+        if (lane == 0) count_up(table_ready);
+    }
+    int u0 = wave;
+    if (wave >= workers) {
+        int nxt = 0;
+        if (lane == 0) nxt = __hip_atomic_fetch_add((lds_int*)(size_t)next_unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        u0 = __builtin_amdgcn_readfirstlane(nxt);
+    }
+    auto ready = [&](int h, int j, bool first, bool first_unit) {
+        if (first && first_unit && hc.lut_bytes > 0) wait_count(table_ready, workers);
+        wait_count(cnt_base + 4 * (4 * h + j), 2 * (min(4 * j + 4, nb16) - 4 * j) + (j == 0 ? nb16 : 0));
+    };
+    auto pair_of = [&](int h) { return head0 + h; };
+    auto head_of = [](int) { return 0; };
+    if (hc.lut_bytes > 0)
+        cu_units<kExpTable, false>(a, hc, 0, u0, units, nblk, kv_base, slot, next_unit, wave, 0, ready, pair_of, head_of);
+    else
+        cu_units<kExpShift, false>(a, hc, 0, u0, units, nblk, kv_base, slot, next_unit, wave, 0, ready, pair_of, head_of);
 }
 
 template <int XM, bool PH>
@@ -324,17 +529,22 @@ int launch_cu(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t 
 int qflash_launch_fwd_cu(const QflashKernelArgs& a, int lds_limit, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     if (!a.cu_mode || a.cu_heads < 1 || a.cu_waves < 1 || a.cu_waves > 16 || a.N > 256 || a.bias) return (int)hipErrorInvalidValue;
-    const bool table = a.exp_mode == kExpTable || a.exp_mode == kExpAuto;
+    if (a.dyn_partial) {
+        const size_t lds = qflash_cu_lds_bytes(a.N, a.cu_heads, a.cu_table_lds) + kCuDynExtraLds;
+        if (a.per_head || a.lut_bytes_max > a.cu_table_lds || a.dyn_partials > 256 || lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
+        return qflash_launch_kernel<qflash_fwd_cu_dyn>(a, (unsigned)a.cu_groups, 64 * kCuDynWaves, lds, lds_limit, st);
+    }
+    if (a.hc_dev) return (int)hipErrorInvalidValue;
+    const bool table = a.exp_mode == kExpTable || (a.exp_mode == kExpAuto && a.per_head);      // (some heads have one)
     if (table && a.lut_bytes_max > a.cu_table_lds) return (int)hipErrorInvalidValue;
     const size_t lds = qflash_cu_lds_bytes(a.N, a.cu_heads, table ? a.cu_table_lds : 0);
     if (lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
     if (a.per_head) {
-        if (a.hc_dev || a.cu_table_heads < 0 || a.cu_table_heads > a.H || a.H > kQflashMaxParamHeads) return (int)hipErrorInvalidValue;
+        if (a.cu_table_heads < 0 || a.cu_table_heads > a.H || a.H > kQflashMaxParamHeads) return (int)hipErrorInvalidValue;
         if (table) return launch_cu<kExpTable, true>(a, lds, lds_limit, st);
         if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, true>(a, lds, lds_limit, st);
         return launch_cu<kExpShift, true>(a, lds, lds_limit, st);
     }
-    if (a.exp_mode == kExpAuto) return launch_cu<kExpAuto, false>(a, lds, lds_limit, st);
     if (a.exp_mode == kExpTable) return launch_cu<kExpTable, false>(a, lds, lds_limit, st);
     if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, false>(a, lds, lds_limit, st);
     return launch_cu<kExpShift, false>(a, lds, lds_limit, st);

@@ -13,6 +13,7 @@
 //   2b. bias      (optional) a bias in real units and an exclusion mask are brought to the integer
 //                 score unit of the scales just found and written in the packed layout
 //   3. attention  the usual kernel, reading its constants from the device structure of step 2
+// (The whole-compute-unit kernel, see qflash_cu.hip, takes over steps 2 and 3 from the partial maxima on.)
 //
 // Steps 1 and 2 stream the float32 tensors once each and are bound by HBM: 12 B read in step 1
 // and 12 B read + 3 B written in step 2 per (q, k, v) element triple.
@@ -21,8 +22,7 @@
 
 #include "qflash.h"
 #include "qflash_internal.h"
-#include "qflash_derive.h"
-#include "qflash_device.h"
+#include "qflash_derive_device.h"
 
 namespace {
 
@@ -63,35 +63,6 @@ __device__ __forceinline__ float wg_max(const float* partial, int n_partial, flo
     return wg_reduce_max((int)threadIdx.x < n_partial ? partial[threadIdx.x] : 0.0f, wmax);
 }
 
-// Scales and constants from the three maxima (one thread).  *unit: real value of one integer score unit.
-__device__ void derive_on_device(const float am[3], double sqrt_d, int out_round, QflashHeadConsts* hc,
-                                 qflash_dynamic_info* info, double* unit) {
-    double s[3];
-    for (int t = 0; t < 3; ++t) s[t] = am[t] == 0.0f ? 1.0 : (double)am[t] / 127.0;   // all-zero tensor: scale 1
-    if (unit) *unit = __ddiv_rn(__dmul_rn(s[0], s[1]), sqrt_d);
-    qflash_params p;
-    int status = qflash_derive_params(s[0], s[1], sqrt_d, &p);
-    if (status == QFLASH_OK) {
-        p.out_round = out_round;
-        if (!qflash_fill_head_consts(p, hc)) status = QFLASH_ERR_PARAM;
-    }
-    if (status != QFLASH_OK) {
-        // Scales outside the supported window: the attention kernel runs on safe constants (those
-        // of a mid-range scale) with the requantisation multiplier set to 0, so that every weight is
-        // 0, every denominator is 0 and the output is all zeros (Algorithm 1 with l = 0); the status
-        // says why.
-        (void)qflash_derive_params(0.03, 0.03, sqrt_d, &p);
-        p.out_round = out_round;
-        (void)qflash_fill_head_consts(p, hc);
-        hc->p_mul = 0;
-    }
-    if (info) {
-        info->sQ = s[0]; info->sK = s[1]; info->sV = s[2];
-        info->params = p;
-        info->status = status;
-    }
-}
-
 // grid.y = tensor, grid.x = n_partial streaming workgroups + those that make the constants; 4 elements per
 // thread and iteration: 16 B in, 4 B out.  Every streaming workgroup first finishes the abs-max
 // reduction of its tensor from the per-workgroup partial maxima (1 KB, L2-resident).
@@ -114,13 +85,7 @@ __global__ __launch_bounds__(kDynThreads) void qflash_dyn_quantize(const float* 
         for (int t = 0; t < 3; ++t) a3[t] = wg_max(partial + t * n_partial, n_partial, wmax);
         if (threadIdx.x == 0) {
             derive_on_device(a3, sqrt_d, out_round, &sh_hc, part == 0 ? info : nullptr, part == 0 ? unit : nullptr);
-            // table of x_p + 1 entries (the host's rule), padded to 16
-            const long long x_p = qflash_table_span(sh_hc.s_inv, sh_hc.x_shift, max(sh_hc.p_mul, 1), sh_hc.p_shift);
-            const long long n_padded = (x_p + 1 + 15) & ~15ll;
-            const bool fits = table != nullptr && n_padded <= (long long)table_max;
-            sh_hc.lut = fits ? table : nullptr;
-            sh_hc.lut_bytes = fits ? (int)n_padded : 0;
-            sh_hc.lut_xp = fits ? (int)x_p : 0;
+            reserve_table(&sh_hc, table, table ? table_max : 0);
             if (part == 0) *hc = sh_hc;
         }
         __syncthreads();
@@ -220,6 +185,12 @@ int qflash_dynamic_partials(long long n) {
     return (int)wgs;
 }
 
+int qflash_launch_absmax(const float* Qf, const float* Kf, const float* Vf, long long n, float* scratch, void* stream) {
+    hipLaunchKernelGGL(qflash_dyn_absmax, dim3((unsigned)qflash_dynamic_partials(n), 3), dim3(kDynThreads), 0, (hipStream_t)stream, Qf, Kf, Vf,
+                       n / 4, scratch);
+    return (int)hipGetLastError();
+}
+
 int qflash_launch_dynamic_front(const float* Qf, const float* Kf, const float* Vf, int8_t* Qo, int8_t* Ko, int8_t* Vo,
                                 long long n, double sqrt_d, int out_round, float* scratch,
                                 QflashHeadConsts* hc_dev, double* unit, qflash_dynamic_info* info, uint8_t* table, int table_max,
@@ -228,7 +199,8 @@ int qflash_launch_dynamic_front(const float* Qf, const float* Kf, const float* V
     const long long n4 = n / 4;
     const int wgs = qflash_dynamic_partials(n);
     float* partial = scratch;         // 3 * wgs words
-    hipLaunchKernelGGL(qflash_dyn_absmax, dim3((unsigned)wgs, 3), dim3(kDynThreads), 0, st, Qf, Kf, Vf, n4, partial);
+    const int rc = qflash_launch_absmax(Qf, Kf, Vf, n, partial, stream);
+    if (rc != 0) return rc;
     hipLaunchKernelGGL(qflash_dyn_quantize, dim3((unsigned)wgs + (table ? kTableWgs : 1), 3), dim3(kDynThreads), 0, st, Qf, Kf, Vf,
                        Qo, Ko, Vo, n4, (const float*)partial, wgs, sqrt_d, out_round, hc_dev, unit, info, table, table_max);
     return (int)hipGetLastError();

@@ -92,6 +92,12 @@ struct QflashKernelArgs {
     const uint8_t* lut_base;                 // table slot 0
     int device;                              // the GPU of the launch (current when it is made)
     QflashHeadWords hw[kQflashMaxParamHeads];
+    // where the attention kernel itself quantises (cu_mode and hc_dev only; nullptr: it does not): Q, K and V are float32, these
+    // are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
+    const float* dyn_partial;
+    int dyn_partials;
+    double dyn_sqrt_d;
+    qflash_dynamic_info* dyn_info;           // may be null
 };
 
 // Number of bytes of a weight table that reaches down to -x_p (multiple of 16).
@@ -175,6 +181,9 @@ int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_b
 // The same kernel for per-head constants: heads whose table is at most cu_table_lds bytes (what is left of LDS)
 // look their weights up, the others compute them.
 int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* args);
+// The same kernel fed with float32 tensors (dynamic quantisation).
+int qflash_plan_cu_dynamic(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* args);
+constexpr int kCuDynExtraLds = 64;           // LDS of that variant beyond qflash_cu_lds_bytes
 int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stream);
 
 // The persistent kernel for windowed attention (33 to 64 tokens, 32 features, one KV tile, no bias or a
@@ -221,8 +230,9 @@ int qflash_launch_pack_bias(const int32_t* bias, int slices, int N, int32_t* pac
 // Enqueue the front end of the dynamic pipeline: abs-max of the three float32 tensors of n elements
 // each (n a multiple of 4), derivation of the scales and constants into *hc_dev (and *info if not
 // null) and of the real value of one score unit into *unit, quantisation into Qo, Ko, Vo.
-// scratch: 3 * qflash_dynamic_partials(n) device floats.
+// scratch: 3 * qflash_dynamic_partials(n) device floats.  The first step alone: qflash_launch_absmax.
 int qflash_dynamic_partials(long long n);
+int qflash_launch_absmax(const float* Qf, const float* Kf, const float* Vf, long long n, float* scratch, void* stream);
 // table (may be null): room for a weight table of up to table_max bytes; if the table of the
 // derived constants fits, the quantising kernel also builds it (a few workgroups more, beside the
 // streaming ones) and records it in *hc_dev (lut, lut_bytes, lut_xp); lut_bytes == 0 says "none".

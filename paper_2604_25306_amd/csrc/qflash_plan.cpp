@@ -217,6 +217,14 @@ int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, Qflas
     return 1;
 }
 
+int qflash_plan_cu_dynamic(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* a) {
+    if (!qflash_plan_cu(BH, N, d, kv_tile, lds_limit, 0, a)) return 0;
+    const int left = lds_limit - (int)qflash_cu_lds_bytes(N, a->cu_heads, 0) - kCuDynExtraLds;
+    if (left < 0) { a->cu_mode = 0; return 0; }
+    a->cu_table_lds = left < kTableMaxBytes ? left & ~1023 : kTableMaxBytes;
+    return 1;
+}
+
 // LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and two KV tiles of K and V.
 size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
     (void)waves;
