@@ -283,7 +283,7 @@ int qflash_attention_dynamic(qflash_ctx* ctx,
  *   unit = (s_Q * s_K) / sqrt(d),   b_hat = clip(floor(double(b) / unit + 0.5), -(2^20-1), 2^20-1)
  * in float64, one rounding per operation; excluded pairs take no part in the maximum and get
  * weight 0 (QFLASH_EXCLUDED).  The converted bias is written to the workspace in the packed layout
- * (see qflash_pack_bias) and the attention kernel reads it from there.
+ * (see qflash_pack_bias) and the attention kernel reads it from there, unless that converts it itself.
  *
  *   bias_real  device or NULL, float32 [bias_B,bias_H,N,N] contiguous, 4-byte aligned, finite;
  *              NULL means a bias of zeros (mask only).

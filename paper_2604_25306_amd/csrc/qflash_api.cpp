@@ -186,6 +186,16 @@ bool table_fits(const QflashKernelArgs& a, int d, int table_bytes, int lds_limit
     return qflash_table_fits(a, d, table_bytes, lds_limit) != 0;
 }
 
+// Dynamic quantisation inside the attention kernel (Q, K and V of the call are float32 then): the partial maxima, and the
+// bias in real units and exclusion mask of a windowed launch.
+struct DynSource {
+    const float* partial;
+    qflash_dynamic_info* info;
+    const float* bias;
+    const uint8_t* mask;
+    int bias_B, bias_H;
+};
+
 // Shared by the per-tensor and the per-head entry points: n_p = 1 (p[0] serves every head) or H.
 // hc_dev != nullptr: the constants are computed on the GPU (dynamic quantisation); p is then not
 // used and out_round_dev gives the rounding mode.
@@ -193,8 +203,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
                    const int32_t* bias, int bias_B, int bias_H, int B, int H, int N, int d, int kv_tile,
                    const qflash_params* p, bool per_head, void* hip_stream,
                    QflashHeadConsts* hc_dev = nullptr, int out_round_dev = 0, bool bias_packed = false,
-                   uint8_t* dyn_table = nullptr, bool static_table = false, const float* dyn_partial = nullptr,
-                   qflash_dynamic_info* dyn_info = nullptr) {
+                   uint8_t* dyn_table = nullptr, bool static_table = false, const DynSource* dyn = nullptr) {
     if (!ctx) return QFLASH_ERR_NULL;
     int device, lds_limit, n_cu;
     uint8_t* scratch_ptr;
@@ -244,10 +253,16 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     a.per_head = per_head ? 1 : 0;
     a.qmax = qmax ? 1 : 0;
     a.hc_dev = hc_dev;
-    a.dyn_partial = dyn_partial;
-    a.dyn_partials = dyn_partial ? qflash_dynamic_partials((long long)B * H * N * d) : 0;
+    a.dyn_partial = dyn ? dyn->partial : nullptr;
+    a.dyn_partials = dyn ? qflash_dynamic_partials((long long)B * H * N * d) : 0;
     a.dyn_sqrt_d = std::sqrt((double)d);
-    a.dyn_info = dyn_info;
+    a.dyn_info = dyn ? dyn->info : nullptr;
+    a.dyn_mask = dyn ? dyn->mask : nullptr;
+    if (dyn && (dyn->bias || dyn->mask)) {
+        a.bias = (const int32_t*)dyn->bias;
+        a.bias_B = dyn->bias_B;
+        a.bias_H = dyn->bias_H;
+    }
     a.n_cu = n_cu;
 #ifdef QF_TRACE
     a.trace = g_trace;
@@ -279,10 +294,13 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         }
         // a table only pays while it is smaller than the Q, K, V, O bytes of the workgroup
         a.win_mode = 0;
-        if (!qmax && qflash_plan_win(d, kv_tile, lds_limit, table_hint, &a) == 0 && table_hint > 0)
+        if (dyn) {
+            if (dyn->bias || dyn->mask) (void)qflash_plan_win_dynamic(d, kv_tile, lds_limit, &a);
+        } else if (!qmax && qflash_plan_win(d, kv_tile, lds_limit, table_hint, &a) == 0 && table_hint > 0) {
             qflash_plan_win(d, kv_tile, lds_limit, 0, &a);
+        }
         qflash_plan_ring(d, lds_limit, table_hint, &a);
-        if (dyn_partial) (void)qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &a);
+        if (dyn && !a.win_mode) (void)qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &a);
         else if (qmax || a.win_mode || hc_dev) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
         else if (!qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table_hint, &a) && table_hint > 0)
             qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, 0, &a);
@@ -290,7 +308,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // attention_static would have to build its table ahead of a launch no longer than that takes
         qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     }
-    if (dyn_partial && (!a.cu_mode || a.split_waves || a.win_mode)) return QFLASH_ERR_SHAPE;    // (the caller planned the same launch)
+    if (dyn && ((!a.cu_mode && !a.win_mode) || a.split_waves)) return QFLASH_ERR_SHAPE;    // (the caller planned the same launch)
     const bool takes_table = a.resident || a.ring_dma || a.split_waves;
     // wave priority by dispatch round: only for launches of two to four rounds (0 = off)
     if (a.n_units <= n_cu || a.n_units > 4 * n_cu) a.n_cu = 0;
@@ -312,11 +330,12 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // the stream, which also decides whether there is one (mode 3 reads that decision per
         // workgroup; without mode 3 the table is simply not looked at).
         const bool use_table = table_wanted;
-        if (dyn_partial) {
+        if (dyn) {
             // the kernel makes the table itself, in every workgroup: worth it from two scores per entry on (24.7 K entries: 48.4 us
             // against 52.3 with 116 K scores per workgroup, even with 20 to 34 K, 17.0 against 14.1 with 13 K)
-            const long long half = (long long)a.cu_heads * N * N / 2;
-            a.lut_bytes_max = !table_wanted ? 0 : half < a.cu_table_lds ? (int)half : a.cu_table_lds;
+            const long long pairs = a.win_mode ? (long long)a.win_streams * a.win_chunk : a.cu_heads, half = pairs * N * N / 2;
+            const int room = a.win_mode ? a.win_table_lds : a.cu_table_lds;
+            a.lut_bytes_max = !table_wanted ? 0 : half < room ? (int)half : room;
         } else if (use_table && dyn_table && takes_table && table_fits(a, d, kTableMaxBytes, lds_limit)) {
             a.exp_mode = 3;
             a.lut_bytes_max = kTableMaxBytes;
@@ -680,10 +699,11 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &probe) != 0) return QFLASH_ERR_SHAPE;
         // a launch whose keys are shared out computes its weights (building a table takes longer than it saves)
         probe.bias_packed = with_bias;
-        (void)qflash_plan_win(d, kv_tile, lds_limit, 0, &probe);
+        fused = with_bias && qflash_plan_win_dynamic(d, kv_tile, lds_limit, &probe) != 0;
+        if (!fused) (void)qflash_plan_win(d, kv_tile, lds_limit, 0, &probe);
         wants_table = qflash_plan_split(d, lds_limit, 0, &probe) == 0;
-        // ... and one that gives whole compute units to a workgroup quantises on the way in
-        fused = wants_table && qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &probe) != 0;
+        // Windows with a bias and short sequences (one that gives whole compute units to a workgroup) are quantised on the way in.
+        fused = fused || (wants_table && qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &probe) != 0);
     }
 
     const size_t n = (size_t)B * H * N * d;        // a multiple of 32
@@ -706,13 +726,15 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
     int rc = fused ? qflash_launch_absmax(Qf, Kf, Vf, (long long)n, scratch, hip_stream) :
              qflash_launch_dynamic_front(Qf, Kf, Vf, Qo, Ko, Vo, (long long)n, std::sqrt((double)d), out_round,
                                          scratch, hc_dev, unit, info, dyn_table, kTableMaxBytes, hip_stream);
-    if (rc == 0 && with_bias)
+    if (rc == 0 && with_bias && !fused)
         rc = qflash_launch_dynamic_bias(bias_real, excluded, bias_B * bias_H, N, packed, unit, hip_stream);
     if (cur != device) (void)hipSetDevice(cur);
     if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }
-    if (fused)
+    if (fused) {
+        const DynSource src = {scratch, info, bias_real, excluded, bias_B, bias_H};
         return attention_impl(ctx, (const int8_t*)Qf, (const int8_t*)Kf, (const int8_t*)Vf, O, nullptr, 0, 0, B, H, N, d, kv_tile,
-                              nullptr, false, hip_stream, hc_dev, out_round, false, nullptr, false, scratch, info);
+                              nullptr, false, hip_stream, hc_dev, out_round, false, nullptr, false, &src);
+    }
     return attention_impl(ctx, Qo, Ko, Vo, O, with_bias ? packed : nullptr, with_bias ? bias_B : 0, with_bias ? bias_H : 0,
                           B, H, N, d, kv_tile, nullptr, false, hip_stream, hc_dev, out_round, with_bias, dyn_table);
 }

@@ -25,6 +25,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "qflash_counters.h"
 #include "qflash_derive_device.h"
 #include "qflash_launch.h"
 #include "qflash_tile.h"
@@ -37,25 +38,8 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_cu[];
 
-typedef __attribute__((address_space(3))) int lds_int;
-
 template <int XM> struct WeightMode { static constexpr int value = XM; };
 
-// Wait until the counter at flag_addr (LDS) has reached target.  The LDS serves the requests of a
-// wavefront in order, so the reads that follow in program order see what was written before the
-// counter was; the empty statement only keeps the compiler from moving them up.
-__device__ __forceinline__ void wait_count(int flag_addr, int target) {
-    lds_int* f = (lds_int*)(size_t)flag_addr;
-    while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target) __builtin_amdgcn_s_sleep(2);
-    asm volatile("" ::: "memory");
-}
-// Add 1 to a counter after the loads it stands for have landed (the caller has waited for them).
-// Written as an instruction of its own: the compiler would otherwise make every LDS access that it
-// cannot tell apart from the destination of a direct load wait for all direct loads still in flight.
-__device__ __forceinline__ void count_up(int flag_addr) {
-    const int one = 1;
-    asm volatile("ds_add_u32 %0, %1" ::"v"(flag_addr), "v"(one) : "memory");
-}
 #ifdef QF_TRACE
 // timestamps go to LDS (an instruction the compiler does not count, like the counters) and are copied out at the end
 #define QF_T(K_) do { if ((K_) < 16) { const unsigned long long t_ = __builtin_amdgcn_s_memrealtime(); \
@@ -344,7 +328,6 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) 
 // the end (8 workers: with 4 to 12 of the 16 within 3 %).  Nobody waits for anything but loads, the
 // constants (wavefront 0 waits for no other) and the table and tiles that the former two lead to, so
 // every wavefront reaches its exit.
-typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kCuDynWaves = 16;
 constexpr int kCuDynWorkers = 8;      // at most: wavefronts that start on the units while the others quantise
 
@@ -372,28 +355,13 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
     for (int t = threadIdx.x; t < 4 * hpw + 3; t += blockDim.x) *(lds_int*)(size_t)(cnt_base + 4 * t) = t == 4 * hpw ? workers : 0;
     __syncthreads();
 
-    // ---- partial maxima of the three tensors (at most 256 each)
-    float part[3][4];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) part[t][k] = a.dyn_partial[t * a.dyn_partials + min(lane + 64 * k, a.dyn_partials - 1)];
-    auto maximum = [&](int t) {
-        float m = fmaxf(fmaxf(part[t][0], part[t][1]), fmaxf(part[t][2], part[t][3]));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-        return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));
-    };
+    PartialMaxima pm;
+    pm.load(a);
 
     if (wave == 0) {
-        const float am[3] = {maximum(0), maximum(1), maximum(2)};
+        const float am[3] = {pm.maximum(0), pm.maximum(1), pm.maximum(2)};
         if (lane == 0) {
-            QflashHeadConsts h;
-            derive_on_device(am, a.dyn_sqrt_d, a.out_round, &h, blockIdx.x == 0 ? a.dyn_info : nullptr, nullptr);
-            reserve_table(&h, nullptr, a.lut_bytes_max);
-            const int w[9] = {h.x_shift, h.s_inv, h.exp_mul, h.p_mul, h.p_shift, h.a_mul, h.x_floor, h.lut_xp, h.lut_bytes};
-#pragma unroll
-            for (int k = 0; k < 9; ++k) *(lds_int*)(size_t)(hc_base + 4 * k) = w[k];
+            derive_to_lds(a, am, hc_base);
             count_up(hc_ready);
         }
     } else {
@@ -437,12 +405,7 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
         issue(0);
 #pragma unroll
         for (int s = 1; s < kDepth; ++s) { pc[s] = next(pc[s - 1].x); issue(s); }
-        float r[3];
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            const float am = maximum(t);
-            r[t] = am == 0.0f ? 0.0f : __fdiv_rn(127.0f, am);
-        }
+        const float r[3] = {pm.factor(0), pm.factor(1), pm.factor(2)};
         // byte of row 4 u + lane / 16: the 16-byte pieces of a row are permuted by (row / 4) & 3 = u
         const int w_lane = 64 * (lane >> 4) + 16 * ((lane & 15) >> 2) + 4 * (lane & 3);
         // (no way out of the middle of a trip: the compiler would have every trip wait for all its loads)
@@ -455,16 +418,7 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
                 const int dst = kv_base + (3 * p.h + (z < 0 ? 2 : z & 1)) * slot + 1024 * b;
                 int packed[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    // clip, then round half to even by adding 1.5 * 2^23: the low byte of the sum is the integer
-                    unsigned q[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float c = __builtin_amdgcn_fmed3f(__fmul_rn(buf[s][u][e], rr), -127.0f, 127.0f);
-                        q[e] = __float_as_uint(__fadd_rn(c, 12582912.0f));
-                    }
-                    packed[u] = (int)(__builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u) | __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu));
-                }
+                for (int u = 0; u < 4; ++u) packed[u] = quantise4(buf[s][u], rr);
                 // (converted before the registers are loaded again, not in the branch below)
                 asm volatile("" : "+v"(packed[0]), "+v"(packed[1]), "+v"(packed[2]), "+v"(packed[3]));
                 pc[s] = next(pc[(s + kDepth - 1) % kDepth].x);
@@ -481,23 +435,9 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
 
     // ---- constants; the weight table
     wait_count(hc_ready, 1);
-    QflashHeadConsts hc;
-    {
-        int w[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) w[k] = __builtin_amdgcn_readfirstlane(*(lds_int*)(size_t)(hc_base + 4 * k));
-        hc.x_shift = w[0]; hc.s_inv = w[1]; hc.exp_mul = w[2]; hc.p_mul = w[3]; hc.p_shift = w[4]; hc.a_mul = w[5];
-        hc.x_floor = w[6]; hc.lut_xp = w[7]; hc.lut_bytes = w[8];
-        hc.lut = nullptr;
-    }
+    const QflashHeadConsts hc = consts_from_lds(hc_base);
     if (wave < workers && hc.lut_bytes > 0) {
-        const ExpConst c = make_exp_const(hc);
-        for (int i = 4 * (64 * wave + lane); i < hc.lut_bytes; i += 4 * 64 * workers) {
-            unsigned w = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w |= (i + e <= hc.lut_xp ? table_entry(i + e, hc.lut_xp, hc, c) : 0u) << (8 * e);
-            *(lds_int*)(size_t)(lds0 + i) = (int)w;
-        }
+        table_to_lds(hc, lds0, wave, workers);
         if (lane == 0) count_up(table_ready);
     }
     int u0 = wave;

@@ -13,7 +13,8 @@
 //   2b. bias      (optional) a bias in real units and an exclusion mask are brought to the integer
 //                 score unit of the scales just found and written in the packed layout
 //   3. attention  the usual kernel, reading its constants from the device structure of step 2
-// (The whole-compute-unit kernel, see qflash_cu.hip, takes over steps 2 and 3 from the partial maxima on.)
+// (The whole-compute-unit kernel, see qflash_cu.hip, takes over steps 2 and 3 from the partial maxima on, the
+// windowed one with a bias, see qflash_win.hip, also step 2b.)
 //
 // Steps 1 and 2 stream the float32 tensors once each and are bound by HBM: 12 B read in step 1
 // and 12 B read + 3 B written in step 2 per (q, k, v) element triple.
@@ -25,8 +26,6 @@
 #include "qflash_derive_device.h"
 
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kDynThreads = 512;
 constexpr int kDynMaxPartials = 256;     // workgroups per tensor at most: one partial maximum per thread of half a workgroup

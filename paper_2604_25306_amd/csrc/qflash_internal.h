@@ -92,12 +92,13 @@ struct QflashKernelArgs {
     const uint8_t* lut_base;                 // table slot 0
     int device;                              // the GPU of the launch (current when it is made)
     QflashHeadWords hw[kQflashMaxParamHeads];
-    // where the attention kernel itself quantises (cu_mode and hc_dev only; nullptr: it does not): Q, K and V are float32, these
+    // where the attention kernel itself quantises (cu_mode or win_mode, and hc_dev, only; nullptr: it does not): Q, K and V are float32, these
     // are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
     const float* dyn_partial;
     int dyn_partials;
     double dyn_sqrt_d;
     qflash_dynamic_info* dyn_info;           // may be null
+    const uint8_t* dyn_mask;                 // win_mode: exclusion mask or null; bias is then float32 in real units, plain layout, or null
 };
 
 // Number of bytes of a weight table that reaches down to -x_p (multiple of 16).
@@ -193,6 +194,13 @@ int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stre
 int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
 int qflash_launch_fwd_win(const QflashKernelArgs& args, int lds_limit, void* stream);
 size_t qflash_win_lds_bytes(int streams, int table_bytes);
+// The same kernel fed with float32 tensors (dynamic quantisation) and a bias in real units.
+int qflash_plan_win_dynamic(int d, int kv_tile, int lds_limit, QflashKernelArgs* args);
+size_t qflash_win_dyn_lds_bytes(int streams, int table_bytes);
+constexpr int kWinDynStreams = 3;                 // runs of pairs per workgroup, four wavefronts each
+constexpr int kWinDynSets = 4;                    // pairs in LDS per run
+constexpr int kWinDynSetBytes = 6 * 1024;         // V, K, Q: 64 rows each
+constexpr int kDynConstBytes = 44;                // constants and score unit, derived by the workgroup
 
 // The kernel for launches that leave the chip idle, whose wavefronts share out the keys of 32 query rows:
 // decides whether the launch, already planned for the other kernels, takes it, and then sets split_waves

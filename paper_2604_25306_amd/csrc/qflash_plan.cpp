@@ -286,17 +286,20 @@ size_t qflash_win_lds_bytes(int streams, int table_bytes) {
     return (((size_t)table_bytes + 1023) & ~(size_t)1023) + (size_t)streams * 2 * 2 * 5120;
 }
 
-int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+size_t qflash_win_dyn_lds_bytes(int streams, int table_bytes) {
+    return (((size_t)table_bytes + 1023) & ~(size_t)1023) + (size_t)streams * kWinDynSets * (kWinDynSetBytes + 8) + 8 + kDynConstBytes;
+}
+
+static int plan_win(int d, int kv_tile, int lds_limit, int table_bytes, int max_streams, size_t (*lds_bytes)(int, int), QflashKernelArgs* a) {
     (void)kv_tile;                      // a single KV tile either way: 64 and 128 give the same result
     a->win_mode = 0;
     if (d != 32 || a->N <= 32 || a->N > 64 || a->per_head || a->qmax) return 0;
     if (a->bias && (a->bias_B < 1 || a->bias_H < 1 || a->B % a->bias_B != 0 || a->H % a->bias_H != 0)) return 0;
     const long long T = (long long)a->B * a->H;
     const int cus = a->n_cu > 0 ? a->n_cu : 256;
-    // as many runs as there are pairs, up to eight per compute unit (fewer where the table leaves
+    // as many runs as there are pairs, up to max_streams per compute unit (fewer where the table leaves
     // less LDS); equal shares
-    int max_streams = 8;
-    while (max_streams > 0 && qflash_win_lds_bytes(max_streams, table_bytes) > (size_t)lds_limit) --max_streams;
+    while (max_streams > 0 && lds_bytes(max_streams, table_bytes) > (size_t)lds_limit) --max_streams;
     if (max_streams == 0) return 0;
     long long runs = T < (long long)max_streams * cus ? T : (long long)max_streams * cus;
     const long long chunk = (T + runs - 1) / runs;
@@ -305,13 +308,21 @@ int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKe
     if (streams > max_streams) streams = max_streams;
     const long long groups = (runs + streams - 1) / streams;
     if (chunk >= (1ll << 30) || groups >= (1ll << 30)) return 0;
-    if (qflash_win_lds_bytes(streams, table_bytes) > (size_t)lds_limit) return 0;
+    if (lds_bytes(streams, table_bytes) > (size_t)lds_limit) return 0;
     a->win_mode = 1;
     a->win_streams = streams;
     a->win_chunk = (int)chunk;
     a->win_groups = (int)groups;
     a->win_table_lds = (table_bytes + 1023) & ~1023;
     return 1;
+}
+
+int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+    return plan_win(d, kv_tile, lds_limit, table_bytes, 8, qflash_win_lds_bytes, a);
+}
+
+int qflash_plan_win_dynamic(int d, int kv_tile, int lds_limit, QflashKernelArgs* a) {
+    return plan_win(d, kv_tile, lds_limit, kTableMaxBytes, kWinDynStreams, qflash_win_dyn_lds_bytes, a);
 }
 
 // LDS bytes of the kernel that shares out the keys: the table (rounded up to 1 KiB), one part of P V
