@@ -246,7 +246,10 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 3) : a.kv_tile == 64 ? 6 : 4;   // by registers
     const long long units = (long long)a.B * a.H * *qtiles, per_cu = (units + cus - 1) / cus;
     long long fit = (long long)((size_t)lds_limit / qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d));
-    if (fit > 4 * per_simd / w) fit = 4 * per_simd / w;
+    // (with three wavefronts to a SIMD a second workgroup of five or six was not resident beside the first: 512 pairs of
+    // 302 tokens 34.0 us with five against 28.2 with four, 288 of 330 27.7 with six against 20.4)
+    const int by_registers = per_simd == 3 ? 3 / ((w + 3) / 4) : 4 * per_simd / w;
+    if (fit > by_registers) fit = by_registers;
     if (fit > per_cu) fit = per_cu;
     if (fit < 1) return 1e30;
     const double x = (double)fit * eff;
