@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void qflash_dyn_bias(const float* __restrict__
                                                       const double* __restrict__ unit_p) {
     const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
     if (t >= n_words) return;
-    const double unit = *unit_p;
+    const double unit = *unit_p, inv = 1.0 / unit;
     const int nb = (N + 31) / 32;
     const int lane = (int)(t & 63), a4 = (int)((t >> 6) & 3);
     const unsigned blk = blockIdx.x;                       // 256 words: one 32 x 32 block
@@ -156,8 +156,7 @@ __global__ __launch_bounds__(256) void qflash_dyn_bias(const float* __restrict__
     int32_t w[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const double r = floor(__dadd_rn(__ddiv_rn((double)x[b], unit), 0.5));
-        const int32_t v = (int32_t)fmin(fmax(r, -1048575.0), 1048575.0);
+        const int32_t v = bias_word(x[b], unit, inv);
         w[b] = col0 + b < N && ((mk >> (8 * b)) & 0xffu) == 0 ? v : INT32_MIN;
     }
     *(int4*)(packed + 4 * t) = int4{w[0], w[1], w[2], w[3]};

@@ -330,19 +330,6 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
 // emptied[set] the wavefronts that have read a use (2).  A use of a set begins only when its last one is
 // read by both, so neither counter can run ahead.  Those who quantise wait only for those who compute the use
 // before the last kWinDynSets - 1 pairs, those who compute only for theirs: every wavefront reaches its exit.
-// Bias words in the score unit: clip(floor(x / unit + 0.5)), in float64 with one rounding per operation.  The product
-// with the reciprocal decides unless it is within 2^-24 of the edge (its error is below 2^-29 where the
-// clip does not decide), which spares a division of 30 instructions.
-__device__ __forceinline__ int bias_word(float x, double unit, double inv) {
-    double t = __dadd_rn(__dmul_rn((double)x, inv), 0.5);
-    double f = floor(t);
-    const double frac = t - f;
-    if (!(frac > 0x1p-24 && frac < 1.0 - 0x1p-24)) {
-        t = __dadd_rn(__ddiv_rn((double)x, unit), 0.5);
-        f = floor(t);
-    }
-    return (int)fmin(fmax(f, -1048575.0), 1048575.0);
-}
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
 template <int XM>
