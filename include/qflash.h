@@ -323,7 +323,8 @@ int qflash_attention_dynamic_bias(qflash_ctx* ctx,
  *                    a single round of workgroups; assumes a weight table of 32 KiB).  For kernel 3:
  *                    wavefronts_per_pair is the number of wavefronts of a workgroup, query_blocks the
  *                    32-row blocks of a pair, units = workgroups, and workgroup w takes pairs
- *                    [w * pairs_per_workgroup, (w + 1) * pairs_per_workgroup).
+ *                    [w * pairs_per_workgroup, (w + 1) * pairs_per_workgroup).  Calls with kv_tile 128 use
+ *                    that kernel as well, and are reported as kernel 1.
  *                    4: windowed attention (33 <= N <= 64, d = 32, one KV tile, no bias or a bias
  *                    in the packed layout whose extents divide B and H, one set of constants,
  *                    Algorithm 1 only): persistent workgroups, one per compute unit, whose wavefronts

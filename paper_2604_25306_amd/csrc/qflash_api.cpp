@@ -186,6 +186,9 @@ bool table_fits(const QflashKernelArgs& a, int d, int table_bytes, int lds_limit
     return qflash_table_fits(a, d, table_bytes, lds_limit) != 0;
 }
 
+// A sequence of one KV tile gives the same result with either tile size; the smaller one's kernels need fewer registers.
+int effective_tile(int kv_tile, int N) { return N <= 64 ? 64 : kv_tile; }
+
 // Dynamic quantisation inside the attention kernel (Q, K and V of the call are float32 then): the partial maxima, and the
 // bias in real units and exclusion mask of a windowed launch.
 struct DynSource {
@@ -228,6 +231,8 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
                                          hc_dev != nullptr, qmax);
         if (rc != QFLASH_OK) return rc;
     }
+    const int asked_tile = kv_tile;
+    kv_tile = effective_tile(kv_tile, N);
     const int n_p = hc_dev ? 0 : per_head ? H : 1;
     // The entry point that allocates nothing keeps its one weight table in the static device array:
     // constants whose table is larger than that are refused, not silently run another way.
@@ -302,8 +307,14 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         qflash_plan_ring(d, lds_limit, table_hint, &a);
         if (dyn && !a.win_mode) (void)qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &a);
         else if (qmax || a.win_mode || hc_dev) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
-        else if (!qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table_hint, &a) && table_hint > 0)
-            qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, 0, &a);
+        else {
+            auto plan = [&](int table) {
+                return kv_tile == 64 ? qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table, &a) : qflash_plan_cu128(B * H, N, d, lds_limit, table, &a);
+            };
+            if (!plan(table_hint) && table_hint > 0) (void)plan(0);
+        }
+        // (one pair per compute unit, tiles of 128 and no table, see below: 192 pairs of 197 tokens 9.1 us resident, 9.6 here)
+        if (static_table && a.cu_mode && kv_tile == 128 && a.cu_heads == 1) a.cu_mode = 0;
         if (per_head && !qmax && !a.win_mode) qflash_plan_cu_heads(B * H, N, d, kv_tile, lds_limit, &a);
         // attention_static would have to build its table ahead of a launch no longer than that takes
         qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
@@ -344,7 +355,11 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
         // One table, rebuilt by every call in the static device array ahead of the attention kernel
         // on the same stream (the array keeps the last call's table and every byte the kernel
         // stages, [0, static_np), is rewritten).  No lock: nothing of the context is touched.
-        if (static_np > 0 && takes_table && table_fits(a, d, static_np, lds_limit)) {
+        // The whole-compute-unit kernel computes its weights while there are fewer than 40 K scores per workgroup: building a
+        // table first costs more (720 pairs of 130 tokens, 51 K scores: 12.9 us with a table, 14.5 without; 768 of 100,
+        // 30 K: 10.3 against 9.9; 360 of 80, 13 K: 7.8 against 6.4).
+        const bool pays = !a.cu_mode || a.split_waves || (long long)a.cu_heads * N * N >= 40000;
+        if (static_np > 0 && pays && takes_table && table_fits(a, d, static_np, lds_limit)) {
             rc = qflash_launch_build_table(scratch_ptr, static_xp + 1, static_np, static_xp, hc[0], hip_stream);
             a.lut_base = scratch_ptr;
             hc[0].lut_bytes = static_np;
@@ -457,7 +472,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             if (hc[h].lut_bytes == 0) a.hw[h] = qflash_pack_head(hc[h], 0);
         if (rc == 0) rc = launch_attention(a, d, kv_tile, lds_limit, hip_stream);
         ctx->last_mode = a.exp_mode == 2 ? QFLASH_WEIGHTS_TABLE : a.exp_mode == 3 ? QFLASH_WEIGHTS_MIXED : QFLASH_WEIGHTS_ARITHMETIC;
-        ctx->last_kernel = a.win_mode ? (a.bias && !a.bias_packed ? 1 : 4) : a.cu_mode ? 3 : !a.resident ? 0 : a.ring ? 2 : 1;   // (2 also for the direct-load ring)
+        ctx->last_kernel = a.win_mode ? (a.bias && !a.bias_packed ? 1 : 4) : a.cu_mode ? (asked_tile == 64 ? 3 : 1) : !a.resident ? 0 : a.ring ? 2 : 1;   // (2 also for the direct-load ring)
         lk.unlock();
         if (cur != device) (void)hipSetDevice(cur);
         if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }
@@ -515,6 +530,8 @@ int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, 
     if (B < 1 || H < 1 || N < 1 || N > QFLASH_MAX_N) return QFLASH_ERR_SHAPE;
     if ((int64_t)B * H * N * d >= ((int64_t)1 << 31)) return QFLASH_ERR_SHAPE;
     if (kv_tile != 64 && kv_tile != 128) return QFLASH_ERR_TILE;
+    const bool whole_cu = kv_tile == 64;       // (with tiles of 128 reported as kernel 1, see the header)
+    kv_tile = effective_tile(kv_tile, N);
     const bool has_bias = bias_B != 0 || bias_H != 0;
     if (has_bias && (bias_B < 1 || bias_H < 1)) return QFLASH_ERR_SHAPE;
     QflashKernelArgs& a = *args;
@@ -538,7 +555,7 @@ int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, 
         out->workgroups = a.win_groups;
         return QFLASH_OK;
     }
-    if (!qmax && qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, kPlanQueryTableBytes, &a)) {
+    if (!qmax && whole_cu && qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, kPlanQueryTableBytes, &a)) {
         out->kernel = 3;
         out->pairs_per_workgroup = a.cu_heads;
         out->wavefronts_per_pair = a.cu_waves;
@@ -686,6 +703,7 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
     if (((uintptr_t)Qf | (uintptr_t)Kf | (uintptr_t)Vf | (uintptr_t)O | (uintptr_t)workspace) & 15u) return QFLASH_ERR_ALIGN;
     if (bias_real && ((uintptr_t)bias_real & 3u)) return QFLASH_ERR_ALIGN;
     if (info && ((uintptr_t)info & 7u)) return QFLASH_ERR_ALIGN;
+    kv_tile = effective_tile(kv_tile, N);
     {
         // everything the attention launch would refuse is refused here, before the quantising kernels
         // are enqueued

@@ -20,6 +20,9 @@
 // wavefronts raise without waiting for anybody but their own loads, so every wavefront reaches its
 // exit.
 //
+// KV tiles of 128: 131 registers leave three wavefronts to a SIMD, so workgroups are at most twelve; still ahead of
+// the resident kernel (768 pairs of 197 tokens 22.8 -> 18.6 us, 480 of 256 19.4 -> 15.0, 720 of 130 16.8 -> 12.4).
+//
 // QF_TRACE (never defined in the library build) adds per-wavefront timestamps for timeline studies.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
@@ -52,11 +55,11 @@ template <int XM> struct WeightMode { static constexpr int value = XM; };
 // The units of a workgroup, from unit u0 of this wavefront on.  ready(pair, tile, first tile of the unit, first unit of the
 // wavefront) returns when the tile (and what goes with the first one of a unit) is in LDS; next_unit: LDS
 // address of the counter; PH: hc0 are the constants of the table's head, otherwise of the launch.
-template <int XM, bool PH, class Ready, class PairOf, class HeadOf>
+template <int XM, bool PH, int BC, class Ready, class PairOf, class HeadOf>
 __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const QflashHeadConsts& hc0, int table_head, int u0, int units,
                                          int nblk, int kv_base, int slot, int next_unit, int wave, int trace_base,
                                          Ready ready, PairOf pair_of, HeadOf head_of) {
-    constexpr int D = 64, BC = 64;
+    constexpr int D = 64;
     const int N = a.N;
     const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
@@ -95,11 +98,12 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
         }                                                                                                  \
         process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_>(                          \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,      \
-            Kb + 4096 * (J_) + sl.k_off, Vb + 4096 * (J_) + sl.v_off);                                     \
+            Kb + D * BC * (J_) + sl.k_off, Vb + D * BC * (J_) + sl.v_off);                                 \
         if (tk == 6) QF_T(9 + (J_))
-        // the ragged tile, with its number of groups of 8 keys as a compile-time constant
+        // the ragged tile, with its number of groups of 8 keys as a compile-time constant (tiles of 64)
 #define QF_RAGGED(FIRST_, J_)                                                                              \
-        switch ((rem + 7) >> 3) {                                                                          \
+        if constexpr (BC == 128) { QF_TILE(false, FIRST_, J_, rem, 0); }                                   \
+        else switch ((rem + 7) >> 3) {                                                                     \
             case 1: { QF_TILE(false, FIRST_, J_, rem, 1); } break;                                         \
             case 2: { QF_TILE(false, FIRST_, J_, rem, 2); } break;                                         \
             case 3: { QF_TILE(false, FIRST_, J_, rem, 3); } break;                                         \
@@ -154,9 +158,9 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
 // PH: one set of constants per head.  The pairs are then dealt out so that every workgroup gets its share of
 // those with a table and of those without, the former one head after the other: a workgroup stages
 // the table of its first pair's head, and a unit of a pair of another head computes its weights.
-template <int XM, bool PH>
+template <int XM, bool PH, int BC>
 __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
-    constexpr int D = 64, BC = 64;
+    constexpr int D = 64;
     const int N = a.N;
     const int rows16 = (N + 15) & ~15;
     const int slot = rows16 * D;                    // LDS bytes of one tensor of one pair
@@ -245,7 +249,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
         if (XM == kExpTable && my_group == 0)
             for (int it = member; it < nt; it += group_size)
                 load_1k_to_lds((const int8_t*)hc0.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
-        const int x0 = min(8, 2 * nb16);                            // K/V block numbers of the first tile
+        const int x0 = min(BC / 8, 2 * nb16);                       // K/V block numbers of the first tile
         auto load_q = [&](int h, int mi, int np) {
             const size_t head_off = (size_t)pair_of(h) * N * D;
             for (int b = mi; b < nb16; b += np)
@@ -299,7 +303,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 #ifndef QF_TRACE
     const int trace_base = 0;
 #endif
-    cu_units<XM, PH>(a, hc0, table_head, wave, units, nblk, kv_base, slot, cnt_base + 4 * 4 * hpw, wave, trace_base, ready,
+    cu_units<XM, PH, BC>(a, hc0, table_head, wave, units, nblk, kv_base, slot, cnt_base + 4 * 4 * hpw, wave, trace_base, ready,
                      pair_of, [&](int h) { return __builtin_amdgcn_readlane(head_l, h); });
 #ifdef QF_TRACE
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -308,9 +312,9 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 #endif
 }
 
-template <int XM, bool PH>
-__global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) {
-    cu_body<XM, PH>(a);
+template <int XM, bool PH, int BC>
+__global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu(const QflashKernelArgs a) {
+    cu_body<XM, PH, BC>(a);
 }
 
 // ---- the same from float32 tensors (dynamic quantisation): the kernel quantises on the way into LDS
@@ -328,11 +332,11 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu(const QflashKernelArgs a) 
 // the end (8 workers: with 4 to 12 of the 16 within 3 %).  Nobody waits for anything but loads, the
 // constants (wavefront 0 waits for no other) and the table and tiles that the former two lead to, so
 // every wavefront reaches its exit.
-constexpr int kCuDynWaves = 16;
 constexpr int kCuDynWorkers = 8;      // at most: wavefronts that start on the units while the others quantise
 
-__global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs a) {
-    constexpr int D = 64;
+template <int BC>
+__global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu_dyn(const QflashKernelArgs a) {
+    constexpr int D = 64, kTileBlocks = BC / 16, kWaves = qflash_cu_max_waves(BC);
     constexpr int kDepth = 2;                       // pieces in flight per wavefront
     const int N = a.N;
     const int nb16 = (N + 15) >> 4;                 // pieces per tensor of a pair
@@ -380,10 +384,10 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
         };
         auto next = [&](int x) {
             if (x < first_end) {
-                x += kCuDynWaves - 1;
+                x += kWaves - 1;
                 if (x >= first_end) x = wave >= workers ? first_end + wave - workers : end;
             } else {
-                x += kCuDynWaves - workers;
+                x += kWaves - workers;
             }
             return place(x);
         };
@@ -427,7 +431,7 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
 #pragma unroll
                     for (int u = 0; u < 4; ++u) *(lds_int*)(size_t)(dst + (w_lane ^ (16 * u)) + 256 * u) = packed[u];
                     // (the LDS serves a wavefront's requests in order: the count is seen after the bytes)
-                    if (lane == 0) count_up(cnt_base + 4 * (4 * p.h + (z < 0 ? 0 : b >> 2)));
+                    if (lane == 0) count_up(cnt_base + 4 * (4 * p.h + (z < 0 ? 0 : b / kTileBlocks)));
                 }
             }
         }
@@ -448,44 +452,49 @@ __global__ __launch_bounds__(1024) void qflash_fwd_cu_dyn(const QflashKernelArgs
     }
     auto ready = [&](int h, int j, bool first, bool first_unit) {
         if (first && first_unit && hc.lut_bytes > 0) wait_count(table_ready, workers);
-        wait_count(cnt_base + 4 * (4 * h + j), 2 * (min(4 * j + 4, nb16) - 4 * j) + (j == 0 ? nb16 : 0));
+        wait_count(cnt_base + 4 * (4 * h + j), 2 * (min(kTileBlocks * (j + 1), nb16) - kTileBlocks * j) + (j == 0 ? nb16 : 0));
     };
     auto pair_of = [&](int h) { return head0 + h; };
     auto head_of = [](int) { return 0; };
     if (hc.lut_bytes > 0)
-        cu_units<kExpTable, false>(a, hc, 0, u0, units, nblk, kv_base, slot, next_unit, wave, 0, ready, pair_of, head_of);
+        cu_units<kExpTable, false, BC>(a, hc, 0, u0, units, nblk, kv_base, slot, next_unit, wave, 0, ready, pair_of, head_of);
     else
-        cu_units<kExpShift, false>(a, hc, 0, u0, units, nblk, kv_base, slot, next_unit, wave, 0, ready, pair_of, head_of);
+        cu_units<kExpShift, false, BC>(a, hc, 0, u0, units, nblk, kv_base, slot, next_unit, wave, 0, ready, pair_of, head_of);
 }
 
-template <int XM, bool PH>
+template <int XM, bool PH, int BC>
 int launch_cu(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    return qflash_launch_kernel<qflash_fwd_cu<XM, PH>>(a, (unsigned)a.cu_groups, (unsigned)(64 * a.cu_waves), lds, lds_limit, st);
+    return qflash_launch_kernel<qflash_fwd_cu<XM, PH, BC>>(a, (unsigned)a.cu_groups, (unsigned)(64 * a.cu_waves), lds, lds_limit, st);
+}
+
+template <int BC>
+int launch_tile(const QflashKernelArgs& a, bool table, size_t lds, int lds_limit, hipStream_t st) {
+    if (a.dyn_partial)
+        return qflash_launch_kernel<qflash_fwd_cu_dyn<BC>>(a, (unsigned)a.cu_groups, 64 * qflash_cu_max_waves(BC), lds, lds_limit, st);
+    if (a.per_head) {
+        if (table) return launch_cu<kExpTable, true, BC>(a, lds, lds_limit, st);
+        if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, true, BC>(a, lds, lds_limit, st);
+        return launch_cu<kExpShift, true, BC>(a, lds, lds_limit, st);
+    }
+    if (table) return launch_cu<kExpTable, false, BC>(a, lds, lds_limit, st);
+    if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, false, BC>(a, lds, lds_limit, st);
+    return launch_cu<kExpShift, false, BC>(a, lds, lds_limit, st);
 }
 
 }  // namespace
 
-// LDS bytes of the kernel above for `heads` pairs of N rows and a table of table_bytes.
 int qflash_launch_fwd_cu(const QflashKernelArgs& a, int lds_limit, void* stream) {
     hipStream_t st = (hipStream_t)stream;
-    if (!a.cu_mode || a.cu_heads < 1 || a.cu_waves < 1 || a.cu_waves > 16 || a.N > 256 || a.bias) return (int)hipErrorInvalidValue;
-    if (a.dyn_partial) {
-        const size_t lds = qflash_cu_lds_bytes(a.N, a.cu_heads, a.cu_table_lds) + kCuDynExtraLds;
-        if (a.per_head || a.lut_bytes_max > a.cu_table_lds || a.dyn_partials > 256 || lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
-        return qflash_launch_kernel<qflash_fwd_cu_dyn>(a, (unsigned)a.cu_groups, 64 * kCuDynWaves, lds, lds_limit, st);
-    }
-    if (a.hc_dev) return (int)hipErrorInvalidValue;
-    const bool table = a.exp_mode == kExpTable || (a.exp_mode == kExpAuto && a.per_head);      // (some heads have one)
+    if (!a.cu_mode || a.cu_heads < 1 || a.cu_waves < 1 || a.cu_waves > qflash_cu_max_waves(a.kv_tile) || a.N > 256 || a.bias ||
+        (a.kv_tile != 64 && a.kv_tile != 128))
+        return (int)hipErrorInvalidValue;
+    if (a.dyn_partial && (a.per_head || a.dyn_partials > 256)) return (int)hipErrorInvalidValue;
+    if (!a.dyn_partial && a.hc_dev) return (int)hipErrorInvalidValue;
+    if (a.per_head && (a.cu_table_heads < 0 || a.cu_table_heads > a.H || a.H > kQflashMaxParamHeads)) return (int)hipErrorInvalidValue;
+    // (per-head constants, mode Auto: some heads have a table)
+    const bool table = a.dyn_partial || a.exp_mode == kExpTable || (a.exp_mode == kExpAuto && a.per_head);
     if (table && a.lut_bytes_max > a.cu_table_lds) return (int)hipErrorInvalidValue;
-    const size_t lds = qflash_cu_lds_bytes(a.N, a.cu_heads, table ? a.cu_table_lds : 0);
+    const size_t lds = qflash_cu_lds_bytes(a.N, a.cu_heads, table ? a.cu_table_lds : 0) + (a.dyn_partial ? kCuDynExtraLds : 0);
     if (lds > (size_t)lds_limit) return (int)hipErrorInvalidValue;
-    if (a.per_head) {
-        if (a.cu_table_heads < 0 || a.cu_table_heads > a.H || a.H > kQflashMaxParamHeads) return (int)hipErrorInvalidValue;
-        if (table) return launch_cu<kExpTable, true>(a, lds, lds_limit, st);
-        if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, true>(a, lds, lds_limit, st);
-        return launch_cu<kExpShift, true>(a, lds, lds_limit, st);
-    }
-    if (a.exp_mode == kExpTable) return launch_cu<kExpTable, false>(a, lds, lds_limit, st);
-    if (a.exp_mode == kExpShift0) return launch_cu<kExpShift0, false>(a, lds, lds_limit, st);
-    return launch_cu<kExpShift, false>(a, lds, lds_limit, st);
+    return a.kv_tile == 64 ? launch_tile<64>(a, table, lds, lds_limit, st) : launch_tile<128>(a, table, lds, lds_limit, st);
 }

@@ -163,6 +163,8 @@ int qflash_check_call(const void* Q, const void* K, const void* V, const void* O
 // of the whole-compute-unit kernel.
 size_t qflash_resident_lds_bytes(int N, int d, int heads, int table_bytes, int lds_limit, int ring_tile = 0);
 size_t qflash_cu_lds_bytes(int N, int heads, int table_bytes);
+// Wavefronts per workgroup of that kernel at most: with KV tiles of 128 it takes 131 registers, three wavefronts to a SIMD.
+QF_UNIT_HD constexpr int qflash_cu_max_waves(int kv_tile) { return kv_tile == 64 ? 16 : 12; }
 
 // Enqueue the forward kernel for head size d (32|64), KV tile (64|128).  Returns a hipError_t value.
 int qflash_launch_fwd(const QflashKernelArgs& args, int d, int kv_tile, int lds_limit, void* stream);
@@ -179,6 +181,8 @@ int qflash_plan_fwd(int BH, int N, int d, int kv_tile, int lds_limit, QflashKern
 // no bias, one set of constants): decides whether the launch takes it, assuming a weight table of
 // table_bytes (0: none), and fills the cu_* fields.  Reads bias, per_head, n_cu (0: 256).  Returns cu_mode.
 int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
+// The same for KV tiles of 128.
+int qflash_plan_cu128(int BH, int N, int d, int lds_limit, int table_bytes, QflashKernelArgs* args);
 // The same kernel for per-head constants: heads whose table is at most cu_table_lds bytes (what is left of LDS)
 // look their weights up, the others compute them.
 int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* args);

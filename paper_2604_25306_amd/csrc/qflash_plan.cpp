@@ -184,9 +184,9 @@ size_t qflash_cu_lds_bytes(int N, int heads, int table_bytes) {
         ;
 }
 
-int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+static int plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* a) {
     a->cu_mode = 0;
-    if (d != 64 || kv_tile != 64 || a->bias || a->per_head || N > 256) return 0;
+    if (d != 64 || a->bias || a->per_head || N > 256) return 0;
     const int cus = a->n_cu > 0 ? a->n_cu : 256;
     const int hpw = (BH + cus - 1) / cus;                 // every pair in a single round of workgroups
     if (qflash_cu_lds_bytes(N, hpw, table_bytes) > (size_t)lds_limit) return 0;
@@ -195,19 +195,34 @@ int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_b
     a->cu_mode = 1;
     a->cu_heads = hpw;
     a->cu_groups = (BH + hpw - 1) / hpw;
-    a->cu_waves = units < 16 ? units : 16;
+    const int most = qflash_cu_max_waves(kv_tile);
+    a->cu_waves = units < most ? units : most;
     a->cu_table_lds = (table_bytes + 1023) & ~1023;
     return 1;
+}
+
+int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+    a->cu_mode = 0;
+    return kv_tile == 64 ? plan_cu(BH, N, d, kv_tile, lds_limit, table_bytes, a) : 0;
+}
+
+int qflash_plan_cu128(int BH, int N, int d, int lds_limit, int table_bytes, QflashKernelArgs* a) {
+    return plan_cu(BH, N, d, 128, lds_limit, table_bytes, a);
 }
 
 int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* a) {
     QflashKernelArgs one = *a;
     one.per_head = 0;
     a->cu_mode = 0;
-    if (!a->per_head || N <= 64 || !qflash_plan_cu(BH, N, d, kv_tile, lds_limit, 0, &one)) return 0;
+    if (!a->per_head || N <= 64 || !plan_cu(BH, N, d, kv_tile, lds_limit, 0, &one)) return 0;
     // (with one pair per compute unit, or one KV tile, the resident kernel is as fast: 10.6 us for 192 pairs of
     // 197 tokens against 10.9, 7.8 for 768 pairs of 64 against 8.1; 768 pairs of 197: 24.4 against 22.7)
     if (one.cu_heads < 2) return 0;
+    // (two short pairs per compute unit likewise: 360 pairs of 80 tokens 7.1 against 7.7; 516, three per unit, 10.4 against 9.9.
+    // With twelve wavefronts, i.e. tiles of 128, it has to fill the chip: 480 pairs of 256 tokens, 240 workgroups,
+    // 19.7 against 18.5, but 416 of 197, 208 workgroups, 16.8 against 18.1.)
+    const int cus = a->n_cu > 0 ? a->n_cu : 256;
+    if (kv_tile == 64 ? one.cu_heads == 2 && N <= 128 : 10 * one.cu_groups < 9 * cus) return 0;
     a->cu_mode = 1;
     a->cu_heads = one.cu_heads;
     a->cu_groups = one.cu_groups;
@@ -218,7 +233,7 @@ int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, Qflas
 }
 
 int qflash_plan_cu_dynamic(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* a) {
-    if (!qflash_plan_cu(BH, N, d, kv_tile, lds_limit, 0, a)) return 0;
+    if (!plan_cu(BH, N, d, kv_tile, lds_limit, 0, a)) return 0;
     const int left = lds_limit - (int)qflash_cu_lds_bytes(N, a->cu_heads, 0) - kCuDynExtraLds;
     if (left < 0) { a->cu_mode = 0; return 0; }
     a->cu_table_lds = left < kTableMaxBytes ? left & ~1023 : kTableMaxBytes;

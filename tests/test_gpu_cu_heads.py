@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
     ((103, 5, 130), [0.1]),                   # none has
     ((87, 3, 200), [1.0, 0.15, 2.0]),         # last workgroup with fewer pairs
     ((100, 6, 256), [0.9, 0.3]),
-    ((300, 1, 65), [1.0])])
+    ((600, 1, 65), [1.0])])
 def test_whole_compute_unit_per_head(gpu, bhn, gains):  # noqa: F811
     torch, qf, ctx = gpu
     B, H, N = bhn
