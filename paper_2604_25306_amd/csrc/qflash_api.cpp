@@ -285,12 +285,21 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &a) != 0) return QFLASH_ERR_SHAPE;
     a.ring_table_lds = 0;
     a.split_waves = 0;
+    // Room for a table that is made on the GPU, its size unknown here (a larger one is not used then): any table, but
+    // for rings of 64 features and tile 64 24 KiB, enough for N(0,1) inputs, so that four workgroups share a compute unit, not
+    // two (128 pairs of 1025 tokens from float32 104.5 -> 92.5 us; 107 instead of 106 where the table would not fit), for
+    // rings of 32 features 32 KiB (three quarters of the variance, four workgroups), and never more than the
+    // workgroup moves anyway (1728 windows of 144 tokens 82.3 -> 77.9 us with a table of 18 KiB).
+    int dyn_room = kTableMaxBytes;
+    if (a.ring_dma) { if (kv_tile == 64) dyn_room = 24 * 1024; }
+    else if (d == 32 && N > 64 && !a.bias) dyn_room = 32 * 1024;
+    else if (a.resident && 4ll * a.heads_per_wg * N * d < dyn_room) dyn_room = 4 * a.heads_per_wg * N * d & ~1023;
     // The kernels whose plan depends on the size of the weight table the call would use: the largest of all heads
     // (the windowed and the whole-compute-unit kernel take one set of constants only).
     {
         int table_hint = 0;
         if (hc_dev) {
-            table_hint = (table_wanted && dyn_table) ? kTableMaxBytes : 0;
+            table_hint = (table_wanted && dyn_table) ? dyn_room : 0;
         } else if (table_wanted) {
             for (int h = 0; h < n_p; ++h) {
                 const int64_t x_p = table_span(p[h]);
@@ -347,9 +356,9 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             const long long pairs = a.win_mode ? (long long)a.win_streams * a.win_chunk : a.cu_heads, half = pairs * N * N / 2;
             const int room = a.win_mode ? a.win_table_lds : a.cu_table_lds;
             a.lut_bytes_max = !table_wanted ? 0 : half < room ? (int)half : room;
-        } else if (use_table && dyn_table && takes_table && table_fits(a, d, kTableMaxBytes, lds_limit)) {
+        } else if (use_table && dyn_table && takes_table && table_fits(a, d, dyn_room, lds_limit)) {
             a.exp_mode = 3;
-            a.lut_bytes_max = kTableMaxBytes;
+            a.lut_bytes_max = dyn_room;
         }
     } else if (static_table) {
         // One table, rebuilt by every call in the static device array ahead of the attention kernel

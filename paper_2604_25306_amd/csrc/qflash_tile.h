@@ -636,6 +636,7 @@ __device__ __forceinline__ QflashHeadConsts head_consts_or_dev(const QflashKerne
         // the table, if the GPU built one for these constants (lut_bytes == 0: none)
         h.lut_xp = __builtin_amdgcn_readfirstlane(g[7]);
         h.lut_bytes = __builtin_amdgcn_readfirstlane(g[8]);
+        if (h.lut_bytes > a.lut_bytes_max) h.lut_bytes = 0;      // (the launch has no room for it)
         const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane(g[10]), hi = (unsigned)__builtin_amdgcn_readfirstlane(g[11]);
         h.lut = (const uint8_t*)(((unsigned long long)hi << 32) | lo);
     }
