@@ -136,12 +136,8 @@ int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out /* host */);
  *   kv_tile  B_c of Algorithm 1: 64 or 128.  The result depends on it (the running maximum and
  *            the rescaling of past accumulators happen per KV tile); it does not depend on the
  *            query block size or on any launch parameter.
- *            Cost: 64 is the tile the kernels are tuned for.  Measured on MI355X: with short
- *            sequences (N <= 256) tile 128 takes 1.3 times the time of tile 64 (ViT-B/16
- *            B=64: 24.9 against 19.2 us; the variant runs short of registers, and the library
- *            computes its weights arithmetically there because the look-up variant is slower
- *            still); on long sequences with d = 64 the two are within 1 % (N = 577: 43.7 against
- *            43.9 us).  A d = 32 sequence
+ *            Cost on MI355X: the two are within 10 % of each other (ViT-B/16 B=64: 18.6 us both; N = 577,
+ *            d = 64: 43.0 against 42.2 us).  A d = 32 sequence
  *            with a bias that is too long for LDS (N above about 1000) takes a kernel that stages one
  *            tile at a time with two barriers per tile and computes weights arithmetically.
  *   p        host; validated on every call.
