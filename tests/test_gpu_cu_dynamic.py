@@ -1,5 +1,5 @@
 """GPU parity of the whole-compute-unit kernel that quantises float32 tensors on the way in: ragged last pieces and
-tiles, one to several pairs per workgroup, a short last workgroup, with and without a weight table, degenerate scales."""
+tiles, one to several pairs per workgroup, a short last workgroup, several rounds of workgroups, with and without a weight table, degenerate scales."""
 import numpy as np
 import pytest
 
@@ -27,6 +27,21 @@ def test_whole_compute_unit_from_floats(gpu, bhn, gains):  # noqa: F811
     out, inf, _ = run_dynamic(gpu, Qf, Kf, Vf, 64, out_round=bhn[2] % 2)
     assert inf.status == 0 and inf.params.astuple() == rinfo["params"].astuple()
     assert (inf.sQ, inf.sK, inf.sV) == (rinfo["sQ"], rinfo["sK"], rinfo["sV"])
+    assert np.array_equal(out, ref)
+
+
+@pytest.mark.parametrize("bhn,kv_tile", [
+    ((257, 3, 256), 64),             # more pairs than one round holds, by three
+    ((190, 10, 100), 128),
+    ((230, 16, 65), 64),
+    ((1360, 10, 9), 64)])            # many short pairs
+def test_several_rounds_from_floats(gpu, bhn, kv_tile):  # noqa: F811
+    shape = bhn + (64,)
+    rng = np.random.default_rng(8500 + bhn[2])
+    Qf, Kf, Vf = (rng.standard_normal(shape, dtype=np.float32) for _ in range(3))
+    ref, rinfo = oracle.qflash_attention_dynamic(Qf, Kf, Vf, kv_tile)
+    out, inf, _ = run_dynamic(gpu, Qf, Kf, Vf, kv_tile)
+    assert inf.status == 0 and inf.params.astuple() == rinfo["params"].astuple()
     assert np.array_equal(out, ref)
 
 
