@@ -192,6 +192,7 @@ def _native():
         except ImportError as e:
             raise RuntimeError("_qflash_native.so is missing or stale: build it with "
                                "`python -m paper_2604_25306_amd.build`.") from e
+        _qflash_native.bind_types(QFlashParams, ctypes.Array)
         _native_mod = _qflash_native
     return _native_mod
 

@@ -2,8 +2,9 @@
 // and calls it.  A call on a small layer takes the GPU less time than ctypes takes to marshal its
 // fifteen arguments: through ctypes and Python-level tensor checks a call cost the host 9.9 us
 // (DeiT-Tiny, one image), of which 3 us are the HIP launch; the checks below are a few loads each.
-// The module holds no state and no device code; every function returns the error code of the C ABI
-// and raises ValueError for tensors that do not have the type or shape the binding promises.
+// The module holds no device code and no state but the two types that constants come in; every function
+// returns the error code of the C ABI, raises ValueError for tensors that do not have the type or shape the
+// binding promises and TypeError for constants that are not a QFlashParams or an array of them.
 #include <Python.h>
 
 #include <c10/hip/HIPStream.h>
@@ -96,24 +97,54 @@ bool stream_arg(PyObject* o, int device, void** out) {
     return *out || !PyErr_Occurred();
 }
 
-// The qflash_params behind a ctypes structure or array of them, through the buffer protocol.
+// The types constants come in, told by the binding when it loads this module (bind_types).
+PyTypeObject* g_params_type = nullptr;     // QFlashParams
+PyTypeObject* g_array_type = nullptr;      // ctypes.Array
+
+// The qflash_params behind a QFlashParams or a ctypes array of them, through the buffer protocol.  The
+// type is checked, not only the size: with any other count than the entry point takes, or with a buffer
+// that merely is as long, the kernel would run on constants of another head or on none at all.
+enum class Constants { one, array, either };
 class Params {
 public:
     ~Params() { if (held_) PyBuffer_Release(&buf_); }
-    bool get(PyObject* o) {
+    bool get(PyObject* o, Constants want) {
+        if (!g_params_type || !g_array_type) {
+            PyErr_SetString(PyExc_RuntimeError, "bind_types has not been called");
+            return false;
+        }
+        const bool one = want != Constants::array && PyObject_TypeCheck(o, g_params_type);
+        if (!one && (want == Constants::one || !is_array(o))) {
+            if (!PyErr_Occurred())
+                PyErr_Format(PyExc_TypeError, "params must be %s, not %.200s", want == Constants::one ? "one QFlashParams" :
+                             want == Constants::array ? "an array of QFlashParams" : "one QFlashParams or an array of them",
+                             Py_TYPE(o)->tp_name);
+            return false;
+        }
         if (PyObject_GetBuffer(o, &buf_, PyBUF_SIMPLE) != 0) return false;
         held_ = true;
-        if (buf_.len < (Py_ssize_t)sizeof(qflash_params) || buf_.len % sizeof(qflash_params) != 0) {
-            PyErr_SetString(PyExc_ValueError, "params must be one QFlashParams or an array of them");
+        n_ = one ? 1 : (int)(buf_.len / (Py_ssize_t)sizeof(qflash_params));
+        if (n_ < 1 || (!one && buf_.itemsize != (Py_ssize_t)sizeof(qflash_params)) || buf_.len < (Py_ssize_t)sizeof(qflash_params)) {
+            PyErr_SetString(PyExc_ValueError, "params must hold at least one QFlashParams");
             return false;
         }
         return true;
     }
     const qflash_params* p() const { return (const qflash_params*)buf_.buf; }
-    int n() const { return (int)(buf_.len / (Py_ssize_t)sizeof(qflash_params)); }
+    int n() const { return n_; }
 
 private:
+    // A ctypes array whose elements are QFlashParams.
+    static bool is_array(PyObject* o) {
+        if (!PyObject_TypeCheck(o, g_array_type)) return false;
+        PyObject* t = PyObject_GetAttrString((PyObject*)Py_TYPE(o), "_type_");
+        if (!t) return false;
+        const bool ok = PyType_Check(t) && PyType_IsSubtype((PyTypeObject*)t, g_params_type);
+        Py_DECREF(t);
+        return ok;
+    }
     Py_buffer buf_;
+    int n_ = 0;
     bool held_ = false;
 };
 
@@ -145,7 +176,8 @@ PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Params p;
     void* stream;
     if (!count_is(n, 10) || !int_arg(a[0], &entry) || !ctx_arg(a[1], &ctx) ||
-        !layer_args(a + 2, at::kChar, "int8", kInt8Names, &L) || !p.get(a[6]) || !int_arg(a[7], &tile))
+        !p.get(a[6], entry == kPerHead ? Constants::array : Constants::one) ||
+        !layer_args(a + 2, at::kChar, "int8", kInt8Names, &L) || !int_arg(a[7], &tile))
         return nullptr;
     if (entry == kPerHead && p.n() != L.H) {
         PyErr_SetString(PyExc_ValueError, "need one QFlashParams per head");
@@ -184,8 +216,8 @@ PyObject* attention_packed_bias(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Layer L;
     Params p;
     void* stream;
-    if (!count_is(n, 11) || !ctx_arg(a[0], &ctx) || !layer_args(a + 1, at::kChar, "int8", kInt8Names, &L) || !p.get(a[5]) ||
-        !int_arg(a[6], &tile) || !int_arg(a[8], &bias_B) || !int_arg(a[9], &bias_H))
+    if (!count_is(n, 11) || !ctx_arg(a[0], &ctx) || !p.get(a[5], Constants::either) ||
+        !layer_args(a + 1, at::kChar, "int8", kInt8Names, &L) || !int_arg(a[6], &tile) || !int_arg(a[8], &bias_B) || !int_arg(a[9], &bias_H))
         return nullptr;
     const at::Tensor* t = tensor_arg(a[7], "packed");
     if (!t) return nullptr;
@@ -271,7 +303,25 @@ PyObject* attention_dynamic(PyObject*, PyObject* const* a, Py_ssize_t n) {
     QF_CATCH
 }
 
+// bind_types(QFlashParams, ctypes.Array)
+PyObject* bind_types(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!count_is(n, 2)) return nullptr;
+    if (!PyType_Check(a[0]) || !PyType_Check(a[1])) {
+        PyErr_SetString(PyExc_TypeError, "bind_types takes two types");
+        return nullptr;
+    }
+    Py_INCREF(a[0]);
+    Py_INCREF(a[1]);
+    Py_XDECREF((PyObject*)g_params_type);
+    Py_XDECREF((PyObject*)g_array_type);
+    g_params_type = (PyTypeObject*)a[0];
+    g_array_type = (PyTypeObject*)a[1];
+    Py_RETURN_NONE;
+}
+
 PyMethodDef kMethods[] = {
+    {"bind_types", (PyCFunction)(void (*)(void))bind_types, METH_FASTCALL,
+     "bind_types(QFlashParams, ctypes.Array): the types that constants are accepted in"},
     {"attention", (PyCFunction)(void (*)(void))attention, METH_FASTCALL,
      "attention(entry, ctx, Q, K, V, O, params, kv_tile, bias, stream) -> error code; entry 0: per tensor, 1: static, 2: per head"},
     {"attention_packed_bias", (PyCFunction)(void (*)(void))attention_packed_bias, METH_FASTCALL,
