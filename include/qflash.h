@@ -106,8 +106,9 @@ int qflash_configure(qflash_ctx* ctx, int key, int value);
  *   slots_total, slots_in_use, slots_pinned (read by a captured graph: never rebuilt), evictions
  *   (slots rebuilt for other constants so far); last_weight_mode: QFLASH_WEIGHTS_ARITHMETIC, _TABLE
  *   (every head read its table) or _MIXED (per-head constants of which only some had a table) of the
- *   last qflash_attention / _per_head / _packed_bias call; last_kernel: as qflash_plan_info.kernel (the
- *   family of the shape, also where qflash_plan_info.key_waves says that the keys are shared out).
+ *   last qflash_attention / _per_head / _packed_bias call; last_kernel: the kernel family that call ran, as
+ *   qflash_plan_info.kernel; last_key_waves: not 0 if it shared out the keys of 32 query rows instead, as
+ *   qflash_plan_info.key_waves (last_kernel is then the family a larger launch of the shape would run).
  * Errors: NULL, CTX.
  */
 #define QFLASH_WEIGHTS_ARITHMETIC 0
@@ -115,7 +116,7 @@ int qflash_configure(qflash_ctx* ctx, int key, int value);
 #define QFLASH_WEIGHTS_MIXED      2
 typedef struct {
     int32_t slots_total, slots_in_use, slots_pinned, evictions;
-    int32_t last_weight_mode, last_kernel, reserved[2];
+    int32_t last_weight_mode, last_kernel, last_key_waves, reserved[1];
 } qflash_cache_info;
 int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out /* host */);
 
@@ -308,26 +309,25 @@ int qflash_attention_dynamic_bias(qflash_ctx* ctx,
  * own choice and does not change a single output bit.
  *
  *   bias_B, bias_H   extents of the bias the call would be given, or 0, 0 for none.
- *   kernel           0: KV tiles streamed through LDS (d = 32: every sequence of more than 64 keys
- *                    without a bias, fed by direct global-to-LDS loads, up to 256 query rows per
- *                    workgroup; with a bias those too long for LDS, 128 query rows per workgroup);
- *                    1: K and V of a (batch, head) pair resident in LDS; 2: two KV tiles in LDS (long
- *                    sequences with d = 64; without a bias they are fed by direct global-to-LDS loads and
- *                    workgroups are four wavefronts);
+ *   kernel           0: KV tiles streamed through LDS, 128 query rows per workgroup (what fits none of the others:
+ *                    d = 32 with a bias and too long for LDS);
+ *                    1: K and V of a (batch, head) pair resident in LDS; 2: two KV tiles in LDS (without a bias:
+ *                    sequences of more than 256 keys with d = 64, of more than 64 with d = 32, the tiles fed by
+ *                    direct global-to-LDS loads; with a bias: d = 64 and more than 256 keys with kv_tile 128,
+ *                    more than about 330 with kv_tile 64);
  *                    3: one workgroup per compute unit holds Q, K, V of several pairs in LDS (short
- *                    sequences, d = 64, kv_tile 64, no bias, one set of constants, few enough pairs for
- *                    a single round of workgroups; assumes a weight table of 32 KiB).  For kernel 3:
- *                    wavefronts_per_pair is the number of wavefronts of a workgroup, query_blocks the
+ *                    sequences, d = 64, no bias, few enough pairs for a single round of workgroups).  For
+ *                    kernel 3: wavefronts_per_pair is the number of wavefronts of a workgroup, query_blocks the
  *                    32-row blocks of a pair, units = workgroups, and workgroup w takes pairs
- *                    [w * pairs_per_workgroup, (w + 1) * pairs_per_workgroup).  Calls with kv_tile 128 use
- *                    that kernel as well, and are reported as kernel 1.
- *                    4: windowed attention (33 <= N <= 64, d = 32, one KV tile, no bias or a bias
- *                    in the packed layout whose extents divide B and H, one set of constants,
- *                    Algorithm 1 only): persistent workgroups, one per compute unit, whose wavefronts
- *                    each work through a run of pairs that share a bias slice (the query assumes
- *                    that a bias would be packed).  For kernel 4: pairs_per_workgroup = pairs a
- *                    workgroup works through, wavefronts_per_pair = 2 (one per half of the rows),
- *                    units = workgroups.
+ *                    [w * pairs_per_workgroup, (w + 1) * pairs_per_workgroup).
+ *                    4: windowed attention (33 <= N <= 64, d = 32, one KV tile, no bias or a bias, packed or
+ *                    plain, whose extents divide B and H, Algorithm 1 only): persistent workgroups, one per
+ *                    compute unit, whose wavefronts each work through a run of pairs that share a bias slice.
+ *                    For kernel 4: pairs_per_workgroup = pairs a workgroup works through,
+ *                    wavefronts_per_pair = 2 (one per half of the rows), units = workgroups.
+ *                    The query assumes one set of constants and, unless the context has its tables switched
+ *                    off, a weight table of 32 KiB; a call with another table may split differently, one with
+ *                    per-head constants may take another kernel (qflash_cache_query tells afterwards).
  *   pairs_per_workgroup, wavefronts_per_pair, query_blocks (workgroups a pair is split over),
  *   units (pieces of work = workgroups that have rows), workgroups (launched; a few may be idle),
  *   tile_by_tile (1: KV tiles staged one ahead of their use), bias_period_units (0, or the number of

@@ -59,8 +59,8 @@ class DynamicInfo(ctypes.Structure):
 class CacheInfo(ctypes.Structure):
     """Mirror of ``qflash_cache_info`` (state of a context's table cache, mode of its last launch)."""
     _fields_ = [(n, ctypes.c_int32) for n in (
-        "slots_total", "slots_in_use", "slots_pinned", "evictions", "last_weight_mode", "last_kernel")] + \
-        [("reserved", ctypes.c_int32 * 2)]
+        "slots_total", "slots_in_use", "slots_pinned", "evictions", "last_weight_mode", "last_kernel",
+        "last_key_waves")] + [("reserved", ctypes.c_int32 * 1)]
 
 
 WEIGHTS_ARITHMETIC, WEIGHTS_TABLE, WEIGHTS_MIXED = 0, 1, 2

@@ -55,6 +55,7 @@ struct qflash_ctx {
     int evictions;        // slots rebuilt for other constants so far
     int last_mode;        // weight mode of the last launch through the cache: QFLASH_WEIGHTS_*
     int last_kernel;      // kernel family of the last launch (as qflash_plan_info.kernel)
+    int last_key_waves;   // and whether it shared out the keys instead (as qflash_plan_info.key_waves)
 };
 
 namespace {
@@ -99,6 +100,7 @@ extern "C" int qflash_create(qflash_ctx** out, int device_id) {
     c->evictions = 0;
     c->last_mode = QFLASH_WEIGHTS_ARITHMETIC;
     c->last_kernel = 0;
+    c->last_key_waves = 0;
     c->evict_ev = nullptr;
     int cur = -1;
     const bool switched = hipGetDevice(&cur) == hipSuccess && cur != device_id && hipSetDevice(device_id) == hipSuccess;
@@ -186,9 +188,6 @@ bool table_fits(const QflashKernelArgs& a, int d, int table_bytes, int lds_limit
     return qflash_table_fits(a, d, table_bytes, lds_limit) != 0;
 }
 
-// A sequence of one KV tile gives the same result with either tile size; the smaller one's kernels need fewer registers.
-int effective_tile(int kv_tile, int N) { return N <= 64 ? 64 : kv_tile; }
-
 // Dynamic quantisation inside the attention kernel (Q, K and V of the call are float32 then): the partial maxima, and the
 // bias in real units and exclusion mask of a windowed launch.
 struct DynSource {
@@ -231,8 +230,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
                                          hc_dev != nullptr, qmax);
         if (rc != QFLASH_OK) return rc;
     }
-    const int asked_tile = kv_tile;
-    kv_tile = effective_tile(kv_tile, N);
+    kv_tile = qflash_effective_tile(kv_tile, N);
     const int n_p = hc_dev ? 0 : per_head ? H : 1;
     // The entry point that allocates nothing keeps its one weight table in the static device array:
     // constants whose table is larger than that are refused, not silently run another way.
@@ -282,52 +280,21 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     }
     a.exp_mode = all_k0 ? 1 : 0;
     a.lut_bytes_max = 0;
-    if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &a) != 0) return QFLASH_ERR_SHAPE;
-    a.ring_table_lds = 0;
-    a.split_waves = 0;
-    // Room for a table that is made on the GPU, its size unknown here (a larger one is not used then): any table, but
-    // for rings of 64 features and tile 64 24 KiB, enough for N(0,1) inputs, so that four workgroups share a compute unit, not
-    // two (128 pairs of 1025 tokens from float32 104.5 -> 92.5 us; 107 instead of 106 where the table would not fit), for
-    // rings of 32 features 32 KiB (three quarters of the variance, four workgroups), and never more than the
-    // workgroup moves anyway (1728 windows of 144 tokens 82.3 -> 77.9 us with a table of 18 KiB).
-    int dyn_room = kTableMaxBytes;
-    if (a.ring_dma) { if (kv_tile == 64) dyn_room = 24 * 1024; }
-    else if (d == 32 && N > 64 && !a.bias) dyn_room = 32 * 1024;
-    else if (a.resident && 4ll * a.heads_per_wg * N * d < dyn_room) dyn_room = 4 * a.heads_per_wg * N * d & ~1023;
-    // The kernels whose plan depends on the size of the weight table the call would use: the largest of all heads
-    // (the windowed and the whole-compute-unit kernel take one set of constants only).
-    {
-        int table_hint = 0;
-        if (hc_dev) {
-            table_hint = (table_wanted && dyn_table) ? dyn_room : 0;
-        } else if (table_wanted) {
-            for (int h = 0; h < n_p; ++h) {
-                const int64_t x_p = table_span(p[h]);
-                if (x_p + 16 <= kTableMaxBytes && table_bytes(x_p) > table_hint) table_hint = table_bytes(x_p);
-            }
+    // The kernels whose plan depends on the size of the weight table the call would use: the largest of all heads.
+    int table_hint = 0;
+    if (hc_dev) {
+        table_hint = table_wanted && dyn_table ? kTableMaxBytes : 0;
+    } else if (table_wanted) {
+        for (int h = 0; h < n_p; ++h) {
+            const int64_t x_p = table_span(p[h]);
+            if (x_p + 16 <= kTableMaxBytes && table_bytes(x_p) > table_hint) table_hint = table_bytes(x_p);
         }
-        // a table only pays while it is smaller than the Q, K, V, O bytes of the workgroup
-        a.win_mode = 0;
-        if (dyn) {
-            if (dyn->bias || dyn->mask) (void)qflash_plan_win_dynamic(d, kv_tile, lds_limit, &a);
-        } else if (!qmax && qflash_plan_win(d, kv_tile, lds_limit, table_hint, &a) == 0 && table_hint > 0) {
-            qflash_plan_win(d, kv_tile, lds_limit, 0, &a);
-        }
-        qflash_plan_ring(d, lds_limit, table_hint, &a);
-        if (dyn && !a.win_mode) (void)qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &a);
-        else if (qmax || a.win_mode || hc_dev) a.cu_mode = 0;          // (the whole-compute-unit kernel exists for Algorithm 1 only)
-        else {
-            auto plan = [&](int table) {
-                return kv_tile == 64 ? qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, table, &a) : qflash_plan_cu128(B * H, N, d, lds_limit, table, &a);
-            };
-            if (!plan(table_hint) && table_hint > 0) (void)plan(0);
-        }
-        // (one pair per compute unit, tiles of 128 and no table, see below: 192 pairs of 197 tokens 9.1 us resident, 9.6 here)
-        if (static_table && a.cu_mode && kv_tile == 128 && a.cu_heads == 1) a.cu_mode = 0;
-        if (per_head && !qmax && !a.win_mode) qflash_plan_cu_heads(B * H, N, d, kv_tile, lds_limit, &a);
-        // attention_static would have to build its table ahead of a launch no longer than that takes
-        qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     }
+    a.ring_table_lds = 0;
+    const QflashCallKind kind = {hc_dev != nullptr, dyn != nullptr, static_table};
+    if (qflash_plan_family(d, kv_tile, lds_limit, kind, &table_hint, &a) != 0) return QFLASH_ERR_SHAPE;
+    // attention_static would have to build its table ahead of a launch no longer than that takes
+    qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     if (dyn && ((!a.cu_mode && !a.win_mode) || a.split_waves)) return QFLASH_ERR_SHAPE;    // (the caller planned the same launch)
     const bool takes_table = a.resident || a.ring_dma || a.split_waves;
     // wave priority by dispatch round: only for launches of two to four rounds (0 = off)
@@ -356,9 +323,9 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             const long long pairs = a.win_mode ? (long long)a.win_streams * a.win_chunk : a.cu_heads, half = pairs * N * N / 2;
             const int room = a.win_mode ? a.win_table_lds : a.cu_table_lds;
             a.lut_bytes_max = !table_wanted ? 0 : half < room ? (int)half : room;
-        } else if (use_table && dyn_table && takes_table && table_fits(a, d, dyn_room, lds_limit)) {
+        } else if (use_table && dyn_table && takes_table && table_fits(a, d, table_hint, lds_limit)) {
             a.exp_mode = 3;
-            a.lut_bytes_max = dyn_room;
+            a.lut_bytes_max = table_hint;
         }
     } else if (static_table) {
         // One table, rebuilt by every call in the static device array ahead of the attention kernel
@@ -481,7 +448,8 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
             if (hc[h].lut_bytes == 0) a.hw[h] = qflash_pack_head(hc[h], 0);
         if (rc == 0) rc = launch_attention(a, d, kv_tile, lds_limit, hip_stream);
         ctx->last_mode = a.exp_mode == 2 ? QFLASH_WEIGHTS_TABLE : a.exp_mode == 3 ? QFLASH_WEIGHTS_MIXED : QFLASH_WEIGHTS_ARITHMETIC;
-        ctx->last_kernel = a.win_mode ? (a.bias && !a.bias_packed ? 1 : 4) : a.cu_mode ? (asked_tile == 64 ? 3 : 1) : !a.resident ? 0 : a.ring ? 2 : 1;   // (2 also for the direct-load ring)
+        ctx->last_kernel = qflash_kernel_family(a);
+        ctx->last_key_waves = a.split_waves;
         lk.unlock();
         if (cur != device) (void)hipSetDevice(cur);
         if (rc != 0) { (void)hipGetLastError(); return QFLASH_ERR_LAUNCH; }
@@ -516,14 +484,10 @@ extern "C" int qflash_attention_per_head(qflash_ctx* ctx, const int8_t* Q, const
     return attention_impl(ctx, Q, K, V, O, bias, bias_B, bias_H, B, H, N, d, kv_tile, p, true, hip_stream);
 }
 
-namespace {
-
-// The kernel family of a shape and its decomposition (*lds_limit: 160 KiB on entry).
-int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, int bias_B, int bias_H,
-                      qflash_plan_info* out, QflashKernelArgs* args, int* lds_limit_io) {
+extern "C" int qflash_plan_query(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, int bias_B,
+                                 int bias_H, qflash_plan_info* out) {
     if (!out) return QFLASH_ERR_NULL;
-    int& lds_limit = *lds_limit_io;
-    int n_cu = 256;
+    int lds_limit = 160 * 1024, n_cu = 256, table = kPlanQueryTableBytes;
     bool qmax = false;
     if (ctx) {
         {
@@ -534,16 +498,16 @@ int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, 
         }
         std::lock_guard<std::mutex> lk(ctx->mu);
         qmax = ctx->qmax != 0;
+        if (!ctx->use_table) table = 0;
     }
     if (d != 32 && d != 64) return QFLASH_ERR_SHAPE;
     if (B < 1 || H < 1 || N < 1 || N > QFLASH_MAX_N) return QFLASH_ERR_SHAPE;
     if ((int64_t)B * H * N * d >= ((int64_t)1 << 31)) return QFLASH_ERR_SHAPE;
     if (kv_tile != 64 && kv_tile != 128) return QFLASH_ERR_TILE;
-    const bool whole_cu = kv_tile == 64;       // (with tiles of 128 reported as kernel 1, see the header)
-    kv_tile = effective_tile(kv_tile, N);
     const bool has_bias = bias_B != 0 || bias_H != 0;
     if (has_bias && (bias_B < 1 || bias_H < 1)) return QFLASH_ERR_SHAPE;
-    QflashKernelArgs& a = *args;
+    kv_tile = qflash_effective_tile(kv_tile, N);
+    QflashKernelArgs a;
     std::memset(&a, 0, sizeof a);
     static const int32_t some_bias = 0;
     a.bias = has_bias ? &some_bias : nullptr;    // the plan only asks whether there is one
@@ -552,49 +516,11 @@ int plan_query_family(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, 
     a.B = B; a.H = H; a.N = N;
     a.n_cu = n_cu;
     a.qmax = qmax ? 1 : 0;
-    if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &a) != 0) return QFLASH_ERR_SHAPE;
+    if (qflash_plan_family(d, kv_tile, lds_limit, QflashCallKind{}, &table, &a) != 0) return QFLASH_ERR_SHAPE;
     std::memset(out, 0, sizeof *out);
-    a.bias_packed = has_bias ? 1 : 0;      // (a bias is taken to be in the packed layout, the only one kernel 4 reads)
-    if (!qmax && qflash_plan_win(d, kv_tile, lds_limit, kPlanQueryTableBytes, &a)) {
-        out->kernel = 4;
-        out->pairs_per_workgroup = a.win_streams * a.win_chunk;
-        out->wavefronts_per_pair = 2;
-        out->query_blocks = 2;
-        out->units = a.win_groups;
-        out->workgroups = a.win_groups;
-        return QFLASH_OK;
-    }
-    if (!qmax && whole_cu && qflash_plan_cu(B * H, N, d, kv_tile, lds_limit, kPlanQueryTableBytes, &a)) {
-        out->kernel = 3;
-        out->pairs_per_workgroup = a.cu_heads;
-        out->wavefronts_per_pair = a.cu_waves;
-        out->query_blocks = (N + 31) / 32;
-        out->units = a.cu_groups;
-        out->workgroups = a.cu_groups;
-        return QFLASH_OK;
-    }
-    qflash_plan_ring(d, lds_limit, kPlanQueryTableBytes, &a);
-    out->kernel = !a.resident ? 0 : a.ring ? 2 : 1;
-    out->pairs_per_workgroup = a.heads_per_wg;
-    out->wavefronts_per_pair = a.waves_per_head;
-    out->query_blocks = a.n_qtiles;
-    out->units = a.n_units;
-    out->workgroups = 8 * a.units_per_xcd;
-    out->tile_by_tile = a.resident && a.pipelined && d == 64 && (kv_tile == 64 || N > 256) ? 1 : 0;
-    out->bias_period_units = a.xcd_period;
-    out->units_per_xcd = a.units_per_xcd;
+    qflash_plan_report(a, d, out);
+    out->key_waves = qflash_plan_split(d, lds_limit, table, &a);
     return QFLASH_OK;
-}
-
-}  // namespace
-
-extern "C" int qflash_plan_query(qflash_ctx* ctx, int B, int H, int N, int d, int kv_tile, int bias_B,
-                                 int bias_H, qflash_plan_info* out) {
-    QflashKernelArgs a;
-    int lds_limit = 160 * 1024;
-    const int rc = plan_query_family(ctx, B, H, N, d, kv_tile, bias_B, bias_H, out, &a, &lds_limit);
-    if (rc == QFLASH_OK) out->key_waves = qflash_plan_split(d, lds_limit, kPlanQueryTableBytes, &a);
-    return rc;
 }
 
 extern "C" int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out) {
@@ -611,6 +537,7 @@ extern "C" int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out) {
     out->evictions = ctx->evictions;
     out->last_weight_mode = ctx->last_mode;
     out->last_kernel = ctx->last_kernel;
+    out->last_key_waves = ctx->last_key_waves;
     return QFLASH_OK;
 }
 
@@ -712,7 +639,7 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
     if (((uintptr_t)Qf | (uintptr_t)Kf | (uintptr_t)Vf | (uintptr_t)O | (uintptr_t)workspace) & 15u) return QFLASH_ERR_ALIGN;
     if (bias_real && ((uintptr_t)bias_real & 3u)) return QFLASH_ERR_ALIGN;
     if (info && ((uintptr_t)info & 7u)) return QFLASH_ERR_ALIGN;
-    kv_tile = effective_tile(kv_tile, N);
+    kv_tile = qflash_effective_tile(kv_tile, N);
     {
         // everything the attention launch would refuse is refused here, before the quantising kernels
         // are enqueued

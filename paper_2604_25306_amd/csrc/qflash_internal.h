@@ -192,9 +192,8 @@ constexpr int kCuDynExtraLds = 64;           // LDS of that variant beyond qflas
 int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stream);
 
 // The persistent kernel for windowed attention (33 to 64 tokens, 32 features, one KV tile, no bias or a
-// packed bias whose extents divide B and H, one set of constants, Algorithm 1 only): decides whether
-// the launch takes it and fills the win_* fields.  Reads bias, bias_packed, bias_B, bias_H, B, H, N,
-// per_head, qmax, n_cu (0: 256).  Returns win_mode.
+// bias, packed or plain, whose extents divide B and H, one set of constants, Algorithm 1 only): decides
+// whether the launch takes it and fills the win_* fields.  Reads bias, bias_B, bias_H, B, H, N, per_head, qmax, n_cu (0: 256).  Returns win_mode.
 int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
 int qflash_launch_fwd_win(const QflashKernelArgs& args, int lds_limit, void* stream);
 size_t qflash_win_lds_bytes(int streams, int table_bytes);
@@ -214,6 +213,24 @@ constexpr int kDynConstBytes = 44;                // constants and score unit, d
 int qflash_plan_split(int d, int lds_limit, int table_bytes, QflashKernelArgs* args);
 int qflash_launch_fwd_split(const QflashKernelArgs& args, int d, int lds_limit, void* stream);
 size_t qflash_split_lds_bytes(int d, int waves, int table_bytes);
+
+// The whole choice of kernel, for a call with a->B, H, N, bias, bias_B, bias_H, per_head, qmax, dyn_mask and n_cu
+// set: tries the plans above in the order the launch does and leaves one of win_mode, cu_mode, ring and resident
+// set (none: streamed).  A launch and qflash_plan_query both go through it, so that the one cannot report what
+// the other does not run.  *table_bytes: weight table the call would use, 0 none; with constants made on the GPU
+// any positive number asks for one, and the room the launch keeps for it comes back.  qflash_plan_split decides
+// afterwards whether the launch shares out keys instead.  Returns non-zero if the launch would be too large.
+struct QflashCallKind {
+    bool on_device;       // the integer constants are made on the GPU
+    bool from_floats;     // the attention kernel itself quantises (qflash_plan_cu_dynamic, qflash_plan_win_dynamic)
+    bool static_table;    // qflash_attention_static
+};
+int qflash_plan_family(int d, int kv_tile /* effective */, int lds_limit, QflashCallKind kind, int* table_bytes, QflashKernelArgs* args);
+// Kernel family of such a plan as in qflash_plan_info.kernel, and the decomposition it stands for.
+int qflash_kernel_family(const QflashKernelArgs& args);
+void qflash_plan_report(const QflashKernelArgs& args, int d, qflash_plan_info* out);
+// A sequence of one KV tile gives the same result with either tile size; the smaller one's kernels need fewer registers.
+inline int qflash_effective_tile(int kv_tile, int N) { return N <= 64 ? 64 : kv_tile; }
 
 // The two-tile ring with direct global-to-LDS loads (long sequences, no bias, both Algorithm 1 and the
 // quantised-maximum variant; work decomposition as for the ring of the resident kernel).

@@ -387,3 +387,70 @@ int qflash_plan_split(int d, int lds_limit, int table_bytes, QflashKernelArgs* a
     a->xcd_period = 0;
     return waves;
 }
+
+// The kernel a call takes, but for launches too small to fill the chip (qflash_plan_split).
+int qflash_plan_family(int d, int kv_tile, int lds_limit, QflashCallKind kind, int* table_bytes, QflashKernelArgs* a) {
+    const int BH = a->B * a->H, N = a->N;
+    if (qflash_plan_fwd(BH, N, d, kv_tile, lds_limit, a) != 0) return -1;
+    a->split_waves = 0;
+    a->win_mode = 0;
+    a->cu_mode = 0;
+    // Room for a table that is made on the GPU, its size unknown here (a larger one is not used then): any table, but
+    // for rings of 64 features and tile 64 24 KiB, enough for N(0,1) inputs, so that four workgroups share a compute unit, not
+    // two (128 pairs of 1025 tokens from float32 104.5 -> 92.5 us; 107 instead of 106 where the table would not fit), for
+    // rings of 32 features 32 KiB (three quarters of the variance, four workgroups), and never more than the
+    // workgroup moves anyway (1728 windows of 144 tokens 82.3 -> 77.9 us with a table of 18 KiB).
+    if (kind.on_device && *table_bytes > 0) {
+        int room = kTableMaxBytes;
+        if (a->ring_dma) { if (kv_tile == 64) room = 24 * 1024; }
+        else if (d == 32 && N > 64 && !a->bias) room = 32 * 1024;
+        else if (a->resident && 4ll * a->heads_per_wg * N * d < room) room = 4 * a->heads_per_wg * N * d & ~1023;
+        *table_bytes = room;
+    }
+    const int table = *table_bytes;
+    if (kind.from_floats) {
+        if (a->bias || a->dyn_mask) (void)qflash_plan_win_dynamic(d, kv_tile, lds_limit, a);
+    } else if (!a->qmax && qflash_plan_win(d, kv_tile, lds_limit, table, a) == 0 && table > 0) {
+        (void)qflash_plan_win(d, kv_tile, lds_limit, 0, a);
+    }
+    (void)qflash_plan_ring(d, lds_limit, table, a);
+    if (kind.from_floats) {
+        if (!a->win_mode) (void)qflash_plan_cu_dynamic(BH, N, d, kv_tile, lds_limit, a);
+    } else if (!a->qmax && !a->win_mode && !kind.on_device) {          // (the whole-compute-unit kernel exists for Algorithm 1 only)
+        auto plan = [&](int bytes) {
+            return kv_tile == 64 ? qflash_plan_cu(BH, N, d, kv_tile, lds_limit, bytes, a) : qflash_plan_cu128(BH, N, d, lds_limit, bytes, a);
+        };
+        if (!plan(table) && table > 0) (void)plan(0);
+        // (one pair per compute unit, tiles of 128 and no table, see qflash_attention_static: 192 pairs of 197 tokens
+        // 9.1 us resident, 9.6 here)
+        if (kind.static_table && a->cu_mode && kv_tile == 128 && a->cu_heads == 1) a->cu_mode = 0;
+        if (a->per_head) (void)qflash_plan_cu_heads(BH, N, d, kv_tile, lds_limit, a);
+    }
+    return 0;
+}
+
+int qflash_kernel_family(const QflashKernelArgs& a) { return a.win_mode ? 4 : a.cu_mode ? 3 : a.ring ? 2 : a.resident ? 1 : 0; }
+
+void qflash_plan_report(const QflashKernelArgs& a, int d, qflash_plan_info* out) {
+    out->kernel = qflash_kernel_family(a);
+    if (out->kernel == 4) {
+        out->pairs_per_workgroup = a.win_streams * a.win_chunk;
+        out->wavefronts_per_pair = 2;
+        out->query_blocks = 2;
+        out->units = out->workgroups = a.win_groups;
+    } else if (out->kernel == 3) {
+        out->pairs_per_workgroup = a.cu_heads;
+        out->wavefronts_per_pair = a.cu_waves;
+        out->query_blocks = (a.N + 31) / 32;
+        out->units = out->workgroups = a.cu_groups;
+    } else {
+        out->pairs_per_workgroup = a.heads_per_wg;
+        out->wavefronts_per_pair = a.waves_per_head;
+        out->query_blocks = a.n_qtiles;
+        out->units = a.n_units;
+        out->workgroups = 8 * a.units_per_xcd;
+        out->tile_by_tile = a.ring_dma || (a.resident && a.pipelined && d == 64 && (a.kv_tile == 64 || a.N > 256)) ? 1 : 0;
+        out->bias_period_units = a.xcd_period;
+        out->units_per_xcd = a.units_per_xcd;
+    }
+}

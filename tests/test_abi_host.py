@@ -143,8 +143,9 @@ def test_plan_covers_every_unit_exactly_once(lib):
         pairs = c[0] * c[1]
         if plan.kernel == 3:        # one workgroup per compute unit, several whole pairs each
             assert plan.units == plan.workgroups == -(-pairs // plan.pairs_per_workgroup) <= 256, c
-            assert c[3] == 64 and c[4] == 64 and c[2] <= 256 and c[5] == 0, c
-            assert 1 <= plan.wavefronts_per_pair <= 16 and plan.query_blocks * 32 >= c[2], c
+            assert c[3] == 64 and c[2] <= 256 and c[5] == 0, c
+            most = 16 if c[4] == 64 or c[2] <= 64 else 12       # (registers of the variant for tiles of 128)
+            assert 1 <= plan.wavefronts_per_pair <= most and plan.query_blocks * 32 >= c[2], c
             continue
         if plan.kernel == 4:        # windowed attention: persistent workgroups, runs of pairs per wavefront pair
             assert plan.units == plan.workgroups <= 256 and plan.workgroups * plan.pairs_per_workgroup >= pairs, c
@@ -185,8 +186,17 @@ def test_plan_of_the_benchmark_shapes(lib):
         slices = {(qf.qflash_plan_unit(p, wg) * 4 + s) % 192 for wg in range(x, p.workgroups, 8) for s in range(4)
                   if qf.qflash_plan_unit(p, wg) >= 0}
         assert len(slices) == 24, x
-    p = qf.qflash_plan_query(None, 1, 1, 4096, 32, 64)           # too long for LDS at d = 32: streamed
+    p = qf.qflash_plan_query(None, 1, 1, 4096, 32, 64, 1, 1)     # with a bias and too long for LDS at d = 32: streamed
     assert p.kernel == 0
+    p = qf.qflash_plan_query(None, 64, 12, 197, 64, 128)         # tiles of 128: the whole-compute-unit kernel too, with fewer wavefronts
+    assert (p.kernel, p.pairs_per_workgroup, p.wavefronts_per_pair, p.units, p.query_blocks, p.key_waves) == (3, 3, 12, 256, 7, 0)
+    p = qf.qflash_plan_query(None, 150, 12, 50, 64, 128)         # a single tile: as with tiles of 64
+    assert (p.kernel, p.pairs_per_workgroup, p.wavefronts_per_pair, p.units) == (3, 8, 16, 225)
+    p = qf.qflash_plan_query(None, 84, 12, 197, 64, 64)          # four pairs leave no room for a table: without one
+    assert (p.kernel, p.pairs_per_workgroup, p.wavefronts_per_pair, p.units) == (3, 4, 16, 252)
+    p = qf.qflash_plan_query(None, 8, 8, 2100, 32, 64)           # 32 features without a bias: the direct-load ring
+    assert (p.kernel, p.pairs_per_workgroup, p.query_blocks * p.wavefronts_per_pair >= 66, p.units, p.tile_by_tile) == \
+        (2, 1, True, 64 * p.query_blocks, 1)
     assert lib.qflash_plan_query(None, 1, 1, 64, 64, 64, 0, 0, None) == qf.ERR["NULL"]
     info = qf.PlanInfo()
     assert lib.qflash_plan_query(None, 1, 1, 64, 48, 64, 0, 0, ctypes.byref(info)) == qf.ERR["SHAPE"]

@@ -18,6 +18,7 @@ def test_whole_compute_unit_tile_128(gpu, bhn, gain):  # noqa: F811
     p = oracle.derive_params(sQ * gain, sK, 64, out_round=N % 2)
     ref = oracle.qflash_attention(Q, K, V, p, 128)
     assert_same(run_gpu(gpu, Q, K, V, p, 128), ref, "whole CU, tile 128 %s" % (bhn,))
+    assert (ctx.cache_info().last_kernel, ctx.cache_info().last_key_waves) == (3, 0), bhn
     ps = [oracle.derive_params(sQ * g, sK, 64, out_round=0) for g in ([0.2, 1.0, 30.0] * H)[:H]]
     assert_same(run_gpu(gpu, Q, K, V, ps, 128), oracle.qflash_attention(Q, K, V, ps, 128), "the same, per head")
 

@@ -18,11 +18,13 @@ def test_ring32(gpu, bhn, tile):  # noqa: F811
     torch, qf, ctx = gpu
     B, H, N = bhn
     plan = qf.qflash_plan_query(ctx.handle, B, H, N, 32, tile)
-    assert plan.kernel == 0 and plan.key_waves == 0 and plan.query_blocks * plan.wavefronts_per_pair * 32 >= N, bhn
+    assert plan.kernel == 2 and plan.key_waves == 0 and plan.query_blocks * plan.wavefronts_per_pair * 32 >= N, bhn
     Q, K, V, sQ, sK, _ = rand_case((B, H, N, 32), 5000 + N, q_gain=1.0 + (N % 3) * 0.4)
     for scale in (1.0, 40.0):                                # 40: coarse scores, x_shift > 0
         p = oracle.derive_params(sQ * scale, sK * scale, 32, out_round=N % 2)
         assert_same(run_gpu(gpu, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "%s x%g" % (bhn, scale))
+        info = ctx.cache_info()
+        assert (info.last_kernel, info.last_key_waves) == (2, 0), bhn
     if N in (129, 577):
         ps = [oracle.derive_params(sQ * g, sK, 32) for g in ([0.2, 1.0, 30.0] + [1.3] * H)[:H]]
         assert_same(run_gpu(gpu, Q, K, V, ps, tile), oracle.qflash_attention(Q, K, V, ps, tile), "%s per head" % (bhn,))
