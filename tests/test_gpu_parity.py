@@ -282,7 +282,9 @@ def test_bias_period_mapping(gpu, shape, bias_bh, tile):
 @pytest.mark.parametrize("tile", [64, 128])
 def test_two_tile_ring(gpu, shape, with_bias, tile):
     """d = 64 and N > 330 or so (kv_tile 64) or N > 256 (kv_tile 128): the kernel keeps two KV tiles
-    in LDS and reuses the slots; with kv_tile 128 every staging thread carries two items."""
+    in LDS and reuses the slots; with kv_tile 128 every staging thread carries two items.  (Of these only the
+    launch of 520 pairs runs it: the small ones share out their keys, tests/test_gpu_kernel_families.py has
+    larger batches of the same lengths.)"""
     B, H, N, d = shape
     Q, K, V, sQ, sK, _ = rand_case(shape, 700 + N, q_gain=1.3)
     p = oracle.derive_params(sQ, sK, d)
@@ -377,7 +379,9 @@ def test_windowed_kernel_is_not_taken_when_the_bias_does_not_divide_the_batch(gp
 
 
 # long sequences without a bias: the two-tile ring fed by direct loads, both tile sizes, ragged last tiles,
-# one to five row blocks in the last workgroup of a pair, fewer than four wavefronts per workgroup
+# one to five row blocks in the last workgroup of a pair, fewer than four wavefronts per workgroup.  (Launches of
+# at most two row blocks per compute unit share out their keys whatever the family; the same lengths at batches
+# that do run the ring are in tests/test_gpu_kernel_families.py.)
 DIRECT_RING_SHAPES = [(2, 3, 257, 64), (3, 2, 288, 128), (1, 5, 320, 64), (2, 2, 383, 128), (1, 3, 449, 64),
                       (4, 12, 577, 64), (4, 12, 577, 128), (1, 2, 640, 64), (1, 1, 1030, 128), (1, 2, 2049, 64),
                       (1, 1, 4096, 64)]
@@ -405,8 +409,9 @@ def test_direct_load_ring(gpu, shape):
 def test_streamed_kernel_with_bias(gpu, tile):
     """d = 32 and a sequence too long for LDS: the kernel that streams KV tiles, with a bias in both
     layouts, exclusions across whole tiles and a ragged last tile."""
-    shape = (1, 2, 2100, 32)
-    assert paper_plan(shape, tile, (1, 2)).kernel == 0
+    shape = (4, 2, 2100, 32)                      # (more than two blocks of query rows per compute unit: keys not shared out)
+    plan = paper_plan(shape, tile, (1, 2))
+    assert plan.kernel == 0 and plan.key_waves == 0
     Q, K, V, sQ, sK, _ = rand_case(shape, 2100 + tile)
     p = oracle.derive_params(sQ, sK, 32)
     rng = np.random.default_rng(tile)

@@ -1,7 +1,7 @@
 """The entry point that allocates no device memory (``qflash_attention_static``) against the
 ordinary one (``qflash_attention``) and the oracle, through the C ABI: two calls in a row on one
-stream, the second with a smaller input and other constants (the static table memory keeps the
-first call's table), then the refusal of constants whose table exceeds the static memory.
+stream, the second with a smaller input and other constants, then the refusal of constants whose
+table exceeds the static memory.
 """
 import ctypes
 
@@ -53,7 +53,9 @@ def test_static_entry_point_matches_ordinary_one_twice_in_a_row():
             assert np.array_equal(a, b), "static entry point differs from qflash_attention: %s" % (shape,)
             ref = oracle.qflash_attention(Q, K, V, p, tile)
             assert np.array_equal(a, ref), "static entry point differs from the oracle: %s" % (shape,)
-        assert all(used_table), "both cases are meant to run in table mode"
+        # (constants a table would fit for; launches this small share out their keys and compute their weights, those
+        # that build the table are in tests/test_gpu_kernel_families.py)
+        assert all(used_table), "both cases have constants whose table fits"
 
 
 def test_static_entry_point_refuses_a_table_beyond_its_memory():
