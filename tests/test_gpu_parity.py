@@ -41,6 +41,9 @@ def run_gpu(gpu, Q, K, V, p, tile, bias=None, stream=None, packed=False):
     tO = torch.full(Q.shape, 0x55, dtype=torch.int8, device=dev)
     tB = torch.from_numpy(np.ascontiguousarray(bias)).to(dev) if bias is not None else None
     lp = lib_params(qf, p) if isinstance(p, OracleParams) else [lib_params(qf, x) for x in p]
+    if stream:
+        # the tensors are filled on torch's current stream: a launch on another one waits for that
+        torch.cuda.ExternalStream(stream, device=dev).wait_stream(torch.cuda.current_stream(dev))
     if packed:
         tP = ctx.pack_bias(tB, stream=stream)
         ctx.attention_packed_bias(tQ, tK, tV, tO, lp, tile, tP, bias.shape[0], bias.shape[1], stream=stream)
