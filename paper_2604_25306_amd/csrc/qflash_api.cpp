@@ -650,14 +650,7 @@ int dynamic_impl(qflash_ctx* ctx, const float* Qf, const float* Kf, const float*
         probe.bias = with_bias ? &some_bias : nullptr;
         probe.bias_B = with_bias ? bias_B : 1;
         probe.bias_H = with_bias ? bias_H : 1;
-        if (qflash_plan_fwd(B * H, N, d, kv_tile, lds_limit, &probe) != 0) return QFLASH_ERR_SHAPE;
-        // a launch whose keys are shared out computes its weights (building a table takes longer than it saves)
-        probe.bias_packed = with_bias;
-        fused = with_bias && qflash_plan_win_dynamic(d, kv_tile, lds_limit, &probe) != 0;
-        if (!fused) (void)qflash_plan_win(d, kv_tile, lds_limit, 0, &probe);
-        wants_table = qflash_plan_split(d, lds_limit, 0, &probe) == 0;
-        // Windows with a bias and short sequences (one that gives whole compute units to a workgroup) are quantised on the way in.
-        fused = fused || (wants_table && qflash_plan_cu_dynamic(B * H, N, d, kv_tile, lds_limit, &probe) != 0);
+        if (qflash_plan_dynamic(d, kv_tile, lds_limit, &probe, &fused, &wants_table) != 0) return QFLASH_ERR_SHAPE;
     }
 
     const size_t n = (size_t)B * H * N * d;        // a multiple of 32

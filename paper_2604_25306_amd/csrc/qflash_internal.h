@@ -193,7 +193,8 @@ int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stre
 
 // The persistent kernel for windowed attention (33 to 64 tokens, 32 features, one KV tile, no bias or a
 // bias, packed or plain, whose extents divide B and H, one set of constants, Algorithm 1 only): decides
-// whether the launch takes it and fills the win_* fields.  Reads bias, bias_B, bias_H, B, H, N, per_head, qmax, n_cu (0: 256).  Returns win_mode.
+// whether the launch takes it and fills the win_* fields.  Reads bias, bias_B, bias_H, B, H, N, per_head,
+// qmax, n_cu (0: 256).  Returns win_mode.
 int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
 int qflash_launch_fwd_win(const QflashKernelArgs& args, int lds_limit, void* stream);
 size_t qflash_win_lds_bytes(int streams, int table_bytes);
@@ -226,6 +227,9 @@ struct QflashCallKind {
     bool static_table;    // qflash_attention_static
 };
 int qflash_plan_family(int d, int kv_tile /* effective */, int lds_limit, QflashCallKind kind, int* table_bytes, QflashKernelArgs* args);
+// Before that, for a call from float32 tensors (a->B, H, N, n_cu and, with a bias or mask, bias, bias_B, bias_H set):
+// whether the attention kernel quantises on the way in, and whether a weight table is to be made at all.
+int qflash_plan_dynamic(int d, int kv_tile /* effective */, int lds_limit, QflashKernelArgs* args, bool* fused, bool* wants_table);
 // Kernel family of such a plan as in qflash_plan_info.kernel, and the decomposition it stands for.
 int qflash_kernel_family(const QflashKernelArgs& args);
 void qflash_plan_report(const QflashKernelArgs& args, int d, qflash_plan_info* out);

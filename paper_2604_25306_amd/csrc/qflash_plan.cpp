@@ -429,6 +429,17 @@ int qflash_plan_family(int d, int kv_tile, int lds_limit, QflashCallKind kind, i
     return 0;
 }
 
+int qflash_plan_dynamic(int d, int kv_tile, int lds_limit, QflashKernelArgs* a, bool* fused, bool* wants_table) {
+    if (qflash_plan_fwd(a->B * a->H, a->N, d, kv_tile, lds_limit, a) != 0) return -1;
+    // Windows with a bias and short sequences (one that gives whole compute units to a workgroup) are quantised on the way in.
+    *fused = a->bias && qflash_plan_win_dynamic(d, kv_tile, lds_limit, a) != 0;
+    if (!*fused) (void)qflash_plan_win(d, kv_tile, lds_limit, 0, a);
+    // a launch whose keys are shared out computes its weights (building a table takes longer than it saves)
+    *wants_table = qflash_plan_split(d, lds_limit, 0, a) == 0;
+    *fused = *fused || (*wants_table && qflash_plan_cu_dynamic(a->B * a->H, a->N, d, kv_tile, lds_limit, a) != 0);
+    return 0;
+}
+
 int qflash_kernel_family(const QflashKernelArgs& a) { return a.win_mode ? 4 : a.cu_mode ? 3 : a.ring ? 2 : a.resident ? 1 : 0; }
 
 void qflash_plan_report(const QflashKernelArgs& a, int d, qflash_plan_info* out) {

@@ -220,6 +220,141 @@ static void kernel_plans() {
     CHECK(qflash_packed_bias_words(192, 49) == 192ll * 4 * 256);
 }
 
+// What every launch relies on, for the plan the call ends with (the launchers check much of it again).
+static void check_plan(const QflashKernelArgs& a, int d, int tile, int lds, int table, QflashCallKind kind) {
+    const long long pairs = (long long)a.B * a.H;
+    const int cus = a.n_cu > 0 ? a.n_cu : 256, nblk = (a.N + 31) / 32;
+    if (a.split_waves) {
+        CHECK(!a.qmax && !a.win_mode && (a.split_waves == 4 || a.split_waves == 8) && (a.split_blocks == 1 || a.split_blocks == 2));
+        CHECK(a.n_qtiles == nblk && a.n_units == pairs * nblk && a.xcd_period == 0);
+        CHECK(a.split_table_lds % 1024 == 0 && qflash_split_lds_bytes(d, a.split_waves, a.split_table_lds) <= (size_t)lds);
+        CHECK(a.split_table_lds == 0 || a.split_table_lds >= table);
+        for (int u = 0; u < a.n_units; ++u)        // the pair of a unit by the high word, as the kernel takes it
+            CHECK((a.n_qtiles == 1 ? u : (int)(((uint64_t)(unsigned)u * a.split_qtiles_inv) >> 32)) == u / a.n_qtiles);
+        grid_covers_units(a);
+        return;
+    }
+    const int family = qflash_kernel_family(a);
+    qflash_plan_info info;
+    std::memset(&info, 0, sizeof info);
+    qflash_plan_report(a, d, &info);
+    CHECK(info.kernel == family && info.units >= 1 && info.workgroups >= info.units);
+    if (family == 4) {
+        CHECK(d == 32 && a.N > 32 && a.N <= 64 && !a.per_head && !a.qmax);
+        CHECK(!a.bias || (a.B % a.bias_B == 0 && a.H % a.bias_H == 0));
+        CHECK(a.win_streams >= 1 && a.win_streams <= (kind.from_floats ? kWinDynStreams : 8) && a.win_chunk >= 1);
+        const long long per = (long long)a.win_streams * a.win_chunk;
+        CHECK(per * a.win_groups >= pairs && per * (a.win_groups - 1) < pairs && a.win_groups <= cus);
+        CHECK(a.win_table_lds % 1024 == 0);
+        CHECK((kind.from_floats ? qflash_win_dyn_lds_bytes : qflash_win_lds_bytes)(a.win_streams, a.win_table_lds) <= (size_t)lds);
+        CHECK(info.pairs_per_workgroup == per && info.workgroups == a.win_groups);
+    } else if (family == 3) {
+        CHECK(d == 64 && a.N <= 256 && !a.bias && !a.qmax && a.kv_tile == tile);
+        CHECK(a.cu_heads >= 1 && (long long)a.cu_heads * a.cu_groups >= pairs && (long long)a.cu_heads * (a.cu_groups - 1) < pairs);
+        CHECK(a.cu_waves >= 1 && a.cu_waves <= qflash_cu_max_waves(tile) && a.cu_waves <= a.cu_heads * nblk);
+        CHECK(a.cu_table_lds % 1024 == 0 && a.cu_table_lds >= 0 && a.cu_table_lds <= kTableMaxBytes);
+        CHECK(qflash_cu_lds_bytes(a.N, a.cu_heads, a.cu_table_lds) + (kind.from_floats ? kCuDynExtraLds : 0) <= (size_t)lds);
+        if (!kind.from_floats) CHECK(a.cu_groups <= cus);        // one round of workgroups
+        if (a.per_head) CHECK(a.cu_heads >= 2 && a.N > 64);
+        if (kind.static_table && tile == 128) CHECK(a.cu_heads > 1);
+        CHECK(info.units == a.cu_groups && info.workgroups == a.cu_groups && info.query_blocks == nblk);
+    } else {
+        CHECK(!kind.from_floats);                                // (those two are the only kernels that quantise)
+        CHECK(a.kv_tile == tile && a.rows_per_wg == 32 * a.waves_per_head);
+        CHECK((long long)a.rows_per_wg * a.n_qtiles >= a.N && (long long)a.rows_per_wg * (a.n_qtiles - 1) < a.N);
+        if (a.ring_dma) {
+            CHECK(family == 2 && !a.bias && a.heads_per_wg == 1 && !a.same_head && a.N > tile / 2 && (d == 64 ? a.N > 256 : a.N > 64));
+            CHECK(a.waves_per_head >= 1 && a.waves_per_head <= kRingMaxWaves && a.resident == (d == 64));
+            CHECK(a.n_units == pairs * a.n_qtiles && qflash_ring_lds_bytes(a.waves_per_head, tile, 0, d) <= (size_t)lds);
+            if (qflash_table_fits(a, d, table, lds)) CHECK(2 * qflash_ring_lds_bytes(a.waves_per_head, tile, table, d) <= (size_t)lds);
+        } else if (a.resident) {
+            const int fits = qflash_table_fits(a, d, table, lds);
+            CHECK(qflash_resident_lds_bytes(a.N, d, a.heads_per_wg, fits ? table : 0, lds, a.ring ? tile : 0) != 0);
+        } else {
+            CHECK(family == 0 && a.rows_per_wg == kStreamRows && a.heads_per_wg == 1);
+        }
+        CHECK(info.workgroups == 8 * a.units_per_xcd && info.units == a.n_units);
+        if (a.n_units <= (1 << 14)) grid_covers_units(a);
+    }
+}
+
+// The whole choice of kernel, every kind of call: int8 tensors with one or several sets of constants, the static
+// entry point, the quantised maximum, constants made on the GPU, float32 tensors quantised on the way in.
+static void call_plans() {
+    static const int32_t some_bias = 0;
+    static const uint8_t some_mask = 0;
+    std::mt19937 rng(29);
+    long families[5] = {}, splits = 0, fused[2] = {}, rings[2] = {}, tile128 = 0, heads = 0, rounds = 0, no_table = 0;
+    auto pick = [&](std::initializer_list<int> l) { return *(l.begin() + rng() % l.size()); };
+    auto plan = [&](QflashKernelArgs a, int d, int tile, int lds, QflashCallKind kind, int table) {
+        const int asked = table;
+        if (qflash_plan_family(d, tile, lds, kind, &table, &a) != 0) return a;
+        CHECK(table >= 0 && (kind.on_device ? table <= kTableMaxBytes : table == asked));
+        const QflashKernelArgs before = a;
+        check_plan(a, d, tile, lds, table, kind);
+        ++families[qflash_kernel_family(a)];
+        if (a.ring_dma) ++rings[d == 64];
+        if (a.cu_mode && tile == 128) ++tile128;
+        if (a.cu_mode && a.per_head) ++heads;
+        if (a.cu_mode && a.cu_groups > (a.n_cu ? a.n_cu : 256)) ++rounds;
+        if (a.cu_mode && !a.per_head && !kind.from_floats && asked > 0 && a.cu_table_lds == 0) ++no_table;
+        if (qflash_plan_split(d, lds, kind.static_table ? 0 : table, &a)) {
+            ++splits;
+            CHECK(a.split_table_lds == 0 || !kind.static_table);
+            check_plan(a, d, tile, lds, table, kind);
+        } else {
+            CHECK(std::memcmp(&a, &before, sizeof a) == 0);
+        }
+        return a;
+    };
+    for (int it = 0; it < 60000; ++it) {
+        const int d = pick({32, 64}), lds = pick({160 * 1024, 160 * 1024, 64 * 1024}), n_cu = pick({256, 256, 0, 64, 1});
+        const int N = pick({1, 31, 32, 33, 49, 64, 65, 100, 128, 129, 144, 197, 256, 257, 577, 1 + (int)(rng() % 64), 1 + (int)(rng() % 300),
+                            1 + (int)(rng() % 4096)});
+        const int B = 1 + (int)std::exp2((rng() % 1000) * 0.001 * 9), H = pick({1, 2, 3, 4, 6, 8, 12, 16, 24, 64});
+        if ((int64_t)B * H * N * d >= ((int64_t)1 << 31)) continue;
+        const int tile = qflash_effective_tile(pick({64, 64, 128}), N);
+        const int table = pick({0, 16, 1040, 4096, 14 * 1024 + 16, 24 * 1024, 25024, 32 * 1024, 40 * 1024});
+        QflashKernelArgs a;
+        std::memset(&a, 0, sizeof a);
+        a.B = B; a.H = H; a.N = N; a.n_cu = n_cu;
+        const bool with_bias = rng() % 3 == 0;
+        a.bias_B = with_bias ? pick({1, 1, 2, 8, B}) : 1;
+        a.bias_H = with_bias ? pick({1, H, H}) : 1;
+        QflashKernelArgs b = a;
+        b.bias = with_bias ? &some_bias : nullptr;
+        plan(b, d, tile, lds, QflashCallKind{false, false, false}, table);
+        plan(b, d, tile, lds, QflashCallKind{false, false, true}, table < 32 * 1024 ? table : 0);
+        b.per_head = 1;
+        plan(b, d, tile, lds, QflashCallKind{false, false, false}, table);
+        b.per_head = (int)(rng() & 1);
+        b.qmax = 1;
+        const QflashKernelArgs q = plan(b, d, tile, lds, QflashCallKind{false, false, false}, table);
+        CHECK(!q.split_waves && !q.cu_mode && !q.win_mode);
+        // from float32: what is decided ahead of the quantising kernels is what the launch then does
+        QflashKernelArgs probe = a;
+        probe.bias = with_bias ? &some_bias : nullptr;
+        bool in_kernel = false, wants_table = false;
+        if (qflash_plan_dynamic(d, tile, lds, &probe, &in_kernel, &wants_table) != 0) continue;
+        QflashKernelArgs f = a;
+        if (in_kernel) {
+            const bool mask_only = with_bias && (rng() & 1);
+            f.bias = with_bias && !mask_only ? &some_bias : nullptr;
+            f.dyn_mask = with_bias ? &some_mask : nullptr;
+            const QflashKernelArgs done = plan(f, d, tile, lds, QflashCallKind{true, true, false}, 0);
+            CHECK(!done.split_waves && (with_bias ? done.win_mode : done.cu_mode));
+            ++fused[with_bias];
+        } else {
+            f.bias = probe.bias;
+            const QflashKernelArgs done = plan(f, d, tile, lds, QflashCallKind{true, false, false}, wants_table ? kTableMaxBytes : 0);
+            CHECK(wants_table == (done.split_waves == 0) && !done.cu_mode);
+        }
+    }
+    for (long n : families) CHECK(n > 100);
+    CHECK(splits > 1000 && fused[0] > 100 && fused[1] > 100 && rings[0] > 100 && rings[1] > 100 && tile128 > 100 && heads > 100);
+    CHECK(rounds > 20 && no_table > 20);
+}
+
 static void oracle_runs() {
     std::mt19937 rng(11);
     for (int it = 0; it < 40; ++it) {
@@ -266,6 +401,7 @@ int main() {
     constants_from_scales();
     argument_checks();
     kernel_plans();
+    call_plans();
     oracle_runs();
     std::printf("host_sanitize: %ld checks passed\n", g_checks);
     return 0;
