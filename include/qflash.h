@@ -138,8 +138,8 @@ int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out /* host */);
  *            the rescaling of past accumulators happen per KV tile); it does not depend on the
  *            query block size or on any launch parameter.
  *            Cost on MI355X: the two are within 10 % of each other (ViT-B/16 B=64: 18.6 us both; N = 577,
- *            d = 64: 43.0 against 42.2 us).  A d = 32 sequence
- *            with a bias that is too long for LDS (N above about 1000) takes a kernel that stages one
+ *            d = 64: 42.4 against 41.9 us).  A d = 32 sequence
+ *            with a bias that is too long for LDS (N above 2016) takes a kernel that stages one
  *            tile at a time with two barriers per tile and computes weights arithmetically.
  *   p        host; validated on every call.
  *   hip_stream  a hipStream_t of the context's device (NULL = the default stream).

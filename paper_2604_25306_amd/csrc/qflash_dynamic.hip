@@ -3,10 +3,10 @@
 //
 //   1. abs-max    max |x| over each of Q, K, V (float32): one partial maximum per workgroup (a
 //                 maximum is exact in any order, so the result does not depend on the grid)
-//   2. quantise   every workgroup finishes the reduction of its tensor; one more workgroup derives the
+//   2. quantise   every workgroup finishes the reduction of its tensor; eight more workgroups derive the
 //                 scales s_X = max|X| / 127 (double) and, from s_Q and s_K, every integer constant of
-//                 the attention kernel -- the same routine the host entry point uses -- and builds
-//                 the weight table of those constants if it is small enough.  The others compute
+//                 the attention kernel -- the same routine the host entry point uses -- and build
+//                 the weight table of those constants if it is at most 40 KiB.  The others compute
 //                 x_hat = clip(rint(x * r), -127, 127), r = float32(127) / max|x|: one float32
 //                 division per tensor, one float32 multiplication and one round-half-to-even per
 //                 element (the precision the rounding decision is defined in)

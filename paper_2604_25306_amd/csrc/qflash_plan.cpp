@@ -54,12 +54,11 @@ long long qflash_packed_bias_words(int slices, int N) {
     return (long long)slices * nb * nb * 256;
 }
 
-
-// LDS bytes of the resident kernel: K and V^T of `heads` heads of N rows (ring: of two KV tiles)
-// and the weight table; 0 if they do not fit.
 // Table size assumed when deciding whether two workgroups with the whole sequence in LDS fit a compute unit.
 constexpr int kRingTableGuess = 32 * 1024;
 
+// LDS bytes of the resident kernel: K and V^T of `heads` heads of N rows (ring: of two KV tiles)
+// and the weight table; 0 if they do not fit.
 size_t qflash_resident_lds_bytes(int N, int d, int heads, int table_bytes, int lds_limit, int ring_tile) {
     const size_t npad = (size_t)((N + 31) & ~31);
     const size_t kv = ring_tile ? 2 * ((size_t)ring_tile * (size_t)(d + 16) + (size_t)d * (size_t)(ring_tile + 16))
@@ -395,9 +394,11 @@ int qflash_plan_family(int d, int kv_tile, int lds_limit, QflashCallKind kind, i
     a->split_waves = 0;
     a->win_mode = 0;
     a->cu_mode = 0;
-    // Room for a table that is made on the GPU, its size unknown here (a larger one is not used then): any table, but
-    // for rings of 64 features and tile 64 24 KiB, enough for N(0,1) inputs, so that four workgroups share a compute unit, not
-    // two (128 pairs of 1025 tokens from float32 104.5 -> 92.5 us; 107 instead of 106 where the table would not fit), for
+    // Room for a table that is made on the GPU, its size unknown here (a larger one is not used then, although the
+    // quantising kernel has built it): any table, but for rings of 64 features and tile 64 24 KiB, so that four workgroups
+    // share a compute unit, not two (128 pairs of 1025 tokens from float32 104.5 -> 92.5 us; 107 instead of 106 where the
+    // table does not fit).  N(0,1) inputs fit it if their largest magnitudes reach 5.04 (geometric mean of Q's and K's):
+    // from about two million elements on; the finer scales of smaller tensors compute their weights.  For
     // rings of 32 features 32 KiB (three quarters of the variance, four workgroups), and never more than the
     // workgroup moves anyway (1728 windows of 144 tokens 82.3 -> 77.9 us with a table of 18 KiB).
     if (kind.on_device && *table_bytes > 0) {

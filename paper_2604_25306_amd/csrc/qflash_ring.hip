@@ -10,12 +10,18 @@
 // in the vector ALU and no LDS write instructions: about a third of that kernel's vector
 // instructions on these shapes.
 //
-// What bounds it: the LDS (a byte look-up costs the compute unit 7 cycles, its lanes meeting 3.5 to a bank)
-// and vector issue, both at two thirds to nine tenths: 290 LDS and 250 vector cycles of the compute unit
-// per KV tile of 64 and wavefront at 64 features, 340 to 414 measured, depending on how many wavefronts
-// the weight table leaves room for.  32 features against the streamed kernel that staged one tile at a
-// time through registers and computed the weights: B*H = 64, N = 2100 145.6 -> 76.0 us with tiles of 64,
-// 202 -> 79.5 us with tiles of 128; against whole sequences in LDS: B*H = 96, N = 1200 56.8 -> 39.6 us.
+// What bounds it, by counters (cycles of a compute unit at 2.2 GHz per wavefront and KV tile: a vector instruction 4 on
+// one of four SIMDs, an LDS operand read 8 or, transposing, 4, a look-up 2.5 plus the counted bank conflicts):
+//   64 features, tiny table (256 pairs of 577 tokens, tiles of 64, 26 us): 302 measured; 214 vector, 63 matrix, 130
+//     LDS, no bank conflicts.  No unit is full.  The vector and the matrix time add up: the barrier after every
+//     tile keeps the wavefronts of a workgroup in one phase.
+//   64 features, tiles of 128 (384 pairs of 577, 39 us): 604 measured; 338 vector, 125 matrix, 350 LDS (1.5 conflict
+//     cycles per look-up).  No unit is full here either: 137 registers leave three wavefronts to a SIMD.
+//   32 features (64 pairs of 2100 tokens, 73 us): 295 measured; 191 vector, 33 matrix, 251 LDS, 219 of them 28 look-ups
+//     with 5.3 conflict cycles each: here the look-ups are most of the time.
+// 32 features against the streamed kernel that staged one tile at a time through registers and computed the
+// weights: B*H = 64, N = 2100 145.6 -> 73 us with tiles of 64, 202 -> 77.5 us with tiles of 128; against whole
+// sequences in LDS: B*H = 96, N = 1200 56.8 -> 39.6 us.
 //
 // Synchronisation: the wavefronts share the loads of a tile (1 KiB pieces, dealt round robin).
 // While tile j is computed, tile j+1 lands in the other slot; after its arithmetic a wavefront waits

@@ -257,9 +257,10 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     auto grp_on = [&](int kb, int a4) { return NG ? 4 * kb + a4 < NG : 32 * kb + 8 * a4 < n_valid; };
     auto grp_cut = [&](int kb, int a4) { return NG ? 4 * kb + a4 == NG - 1 : 32 * kb + 8 * a4 + 8 > n_valid; };
     // Look-up mode with 32 features: one group of four scores in eight is computed instead of looked up.  A
-    // look-up costs the LDS of the compute unit 7 cycles (64 random bytes, two passes of 32 lanes that
-    // meet 3.5 to a bank; 2.5 cycles without conflicts), its arithmetic the vector units 5.  At 32
-    // features a tile has half the vector work per look-up and the LDS is what runs out first
+    // look-up of 64 random bytes costs the LDS of the compute unit 2.5 cycles plus its bank conflicts (counted:
+    // 5.3 cycles on the shape below, 4.6 with 64 x 12 pairs of 197 tokens and 64 features, 0 where a handful
+    // of table entries carries the weights), its arithmetic the vector units 5.  At 32 features a tile has half the
+    // vector work per look-up and the LDS is what runs out first
     // (B*H = 64, N = 2100: 88.0 us with every weight looked up, 81.2 with 7 of 8, 79.8 with 6 of 8 but
     // 105 with larger workgroups: registers); at 64 features it only costs (40.5 -> 45 us, N = 577).
     constexpr bool MIX = XM == kExpTable && D == 32 && LAY == kLaySwizzled && FULL;   // (a ragged tile would spill)

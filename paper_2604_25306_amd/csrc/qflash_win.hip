@@ -1,6 +1,6 @@
 // gfx950 kernel of the integer-only fused attention forward pass (Algorithm 1) for windowed
 // attention: sequences of 33 to 64 tokens with 32 features per head (7 x 7 windows), one KV tile, an
-// optional additive bias in the packed layout (relative-position bias, shifted-window mask).
+// optional additive bias, packed or plain (relative-position bias, shifted-window mask).
 //
 // Such a layer is thousands of tiny independent problems (6 KB of Q, K, V, O per pair, but 16 KB of
 // bias), so what matters is what is NOT done per pair.  The kernel is persistent: one workgroup of up
