@@ -99,6 +99,25 @@ def test_windows_the_bias_does_not_divide(gpu, B, H, N, bias_B):  # noqa: F811
         assert_same(run(gpu, 1, Q, K, V, p, 64, bias=bias, packed=packed), ref, "windows %s" % (Q.shape,))
 
 
+# bias slices that repeat every 8 k units of work: workgroups are dealt to the XCDs by that period; whole and partial
+# periods, one pair or several per workgroup, several query blocks per pair, one set of constants and one per head
+@pytest.mark.parametrize("shape,bias_bh,tile,kernel", [
+    ((44, 2, 197, 64), (8, 2), 64, 1), ((60, 1, 300, 64), (8, 1), 128, 2), ((18, 1, 1200, 64), (8, 1), 64, 2), ((48, 1, 353, 64), (8, 1), 64, 2),
+    ((173, 3, 49, 32), (32, 3), 64, 1), ((600, 4, 20, 64), (14, 4), 64, 1), ((18, 2, 449, 32), (4, 2), 64, 1), ((10, 2, 2060, 32), (4, 2), 64, 0)])
+def test_bias_period(gpu, shape, bias_bh, tile, kernel):  # noqa: F811
+    torch, qf, ctx = gpu
+    B, H, N, d = shape
+    plan = qf.qflash_plan_query(ctx.handle, *shape, tile, *bias_bh)
+    assert plan.bias_period_units > 0 and plan.units > plan.bias_period_units, shape
+    Q, K, V, sQ, sK, _ = rand_case(shape, 16000 + N)
+    fine, _, per_head = scale_sets(sQ, sK, d, H, N)
+    bias = random_bias(bias_bh, N, N)
+    for p, label in ((fine, "one set"), (per_head, "per head")):
+        ref = oracle.qflash_attention(Q, K, V, p, tile, bias=bias)
+        for packed in (False, True):
+            assert_same(run(gpu, kernel, Q, K, V, p, tile, bias=bias, packed=packed), ref, "%s %s packed %s" % (shape, label, packed))
+
+
 # The entry point that allocates nothing, where it builds its table: every family, one call after the other on one
 # stream, each with another table in the same memory, a launch without a table in between.
 def test_static_entry_point_with_its_table(gpu):  # noqa: F811

@@ -254,14 +254,15 @@ def test_table1_workloads(gpu, name):
     ((128, 3, 49, 32), (64, 3), 64),     # whole periods
     ((20, 2, 197, 64), (8, 2), 64),      # one pair per workgroup, 2.5 periods
     ((16, 1, 300, 64), (8, 1), 128),     # two query tiles per pair
-    ((8, 1, 1200, 64), (8, 1), 64),      # streamed kernel
+    ((8, 1, 1200, 64), (8, 1), 64),
     # last tile more than half full: with a packed bias it runs as a full tile
     ((4, 2, 120, 64), (1, 2), 64), ((2, 2, 250, 32), (2, 1), 64), ((2, 2, 230, 64), (1, 1), 128),
     ((3, 2, 33, 32), (1, 1), 64), ((3, 2, 97, 32), (3, 2), 128),
 ])
 def test_bias_period_mapping(gpu, shape, bias_bh, tile):
     """Launches whose bias repeats every 8k units of work take the bias-aware placement of
-    workgroups; the result must not depend on placement."""
+    workgroups; the result must not depend on placement.  (Launches as small as these share out their keys
+    or, as windows, take the windowed kernel; the placement itself: tests/test_gpu_kernel_families.py.)"""
     B, H, N, d = shape
     Q, K, V, sQ, sK, _ = rand_case(shape, 300 + N)
     p = oracle.derive_params(sQ, sK, d)
@@ -450,9 +451,9 @@ def check_per_head(gpu, Q, K, V, ps, tile, bias=None, label=""):
 @pytest.mark.parametrize("shape,tile", [((2, 4, 197, 64), 64), ((3, 5, 49, 32), 64), ((1, 3, 300, 64), 128),
                                         ((2, 6, 70, 32), 64), ((1, 2, 1200, 64), 64), ((1, 64, 40, 32), 64)])
 def test_per_head_constants(gpu, shape, tile):
-    """Heads with scales a factor 200 apart (some need x_shift > 0, so the launch mixes shifts),
-    every kernel family: one head per workgroup with and without tile-by-tile staging, several
-    windows per workgroup, the streamed kernel, the largest head count; with and without bias."""
+    """Heads with scales a factor 200 apart (some need x_shift > 0, so the launch mixes shifts), on the kernel that
+    shares out the keys: short and long sequences, windows, the largest head count; with and without bias.
+    (The other families with one set of constants per head: tests/test_gpu_kernel_families.py.)"""
     from workloads import quantize_per_head
     B, H, N, d = shape
     rng = np.random.default_rng(900 + N + H)
