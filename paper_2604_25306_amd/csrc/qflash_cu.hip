@@ -60,6 +60,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
                                          int nblk, int kv_base, int slot, int next_unit, int wave, int trace_base,
                                          Ready ready, PairOf pair_of, HeadOf head_of) {
     constexpr int D = 64;
+    round_down();
     const int N = a.N;
     const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
@@ -96,7 +97,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
             _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                  \
                 qreg[s] = *(lds_v4i*)(size_t)(Qb + row0 * D + (sl.k_off ^ (32 * s)));                      \
         }                                                                                                  \
-        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_>(                          \
+        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_, false, true>(                          \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,      \
             Kb + D * BC * (J_) + sl.k_off, Vb + D * BC * (J_) + sl.v_off);                                 \
         if (tk == 6) QF_T(9 + (J_))
@@ -138,7 +139,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
             // (uniform base plus a 32-bit lane offset made here: a per-lane 64-bit pointer prepared ahead of
             // the unit loop would be held in registers across all the tile code, or spilled)
             v4i w[2];
-            normalise_words<D, 16>(st, a.out_round != 0, w);
+            normalise_words<D, 16, kAccOffset>(st, a.out_round != 0, w);
             int8_t* Ob = a.O + (size_t)pair_of(h) * N * D;
             unsigned o_lane = (unsigned)(i * D + g * (D / 2));
             asm volatile("" : "+v"(o_lane));

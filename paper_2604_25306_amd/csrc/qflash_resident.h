@@ -72,6 +72,7 @@ template <int D, int BC, int BIAS, bool NARROW, int XM, bool QMAX>
 __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     constexpr int KSTEPS = D / 32;
     constexpr int KROW = D + 16;
+    if (!QMAX) round_down();
     const int N = a.N;
     const int npad = (N + 31) & ~31;
     // a.ring: LDS holds two KV tiles (the one in use and the one being staged) instead of the whole
@@ -365,7 +366,7 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     const bool ragged_as_full = bias_packed && rem > BC - 32;
 #define QF_TILE(FULL_, FIRST_, J_, NV_)                                                                      \
     if (active)                                                                                              \
-    process_tile<D, BC, BIAS, XM, SB, FULL_, FIRST_, kLayPadded, 0, QMAX>(st, qreg,                                               \
+    process_tile<D, BC, BIAS, XM, SB, FULL_, FIRST_, kLayPadded, 0, QMAX, NARROW>(st, qreg,                                               \
                                                      sK + (size_t)(ring ? (J_) & 1 : (J_)) * BC * KROW, KROW, \
                                                      ring ? sV + (size_t)((J_) & 1) * D * VROW : sV + (J_) * BC, \
                                                      VROW, NV_, hc.lut_xp,                                   \
@@ -405,8 +406,8 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     if (!active) return;
     if (i >= N) return;
     int8_t* Orow = a.O + head_off + (size_t)i * D;
-    if (NARROW) normalise_store<D, 16>(st, Orow, g, a.out_round != 0);
-    else normalise_store<D, 20>(st, Orow, g, a.out_round != 0);
+    if (NARROW) normalise_store<D, 16, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
+    else normalise_store<D, 20, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
 }
 
 // Wavefronts per SIMD the register allocation has to allow.  Short sequences (NARROW): 4, and 6
@@ -452,6 +453,7 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
     constexpr int VROW = BC + 16;
     __shared__ __align__(16) int8_t sK[BC * KROW];
     __shared__ __align__(16) int8_t sV[D * VROW];
+    if (!QMAX) round_down();
 
     const int wg = blockIdx.x;
     const int unit = qflash_unit_of_workgroup(wg, a.units_per_xcd, a.xcd_period);
@@ -513,8 +515,8 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
     }
     if (!wave_active || i >= N) return;
     int8_t* Orow = a.O + head_off + (size_t)i * D;
-    if (NARROW) normalise_store<D, 16>(st, Orow, g, a.out_round != 0);
-    else normalise_store<D, 20>(st, Orow, g, a.out_round != 0);
+    if (NARROW) normalise_store<D, 16, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
+    else normalise_store<D, 20, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
 }
 
 // ------------------------------------------------------------------------------ launchers

@@ -49,6 +49,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     constexpr int kPieces = 2 * BC / kRows;         // pieces of a tile: K, then V
     constexpr int kRowPieces = D / 16;              // 16-byte pieces of a row
     constexpr bool SB = XM == kExpTable;
+    if (!QMAX) round_down();
     const int N = a.N;
     const int unit = qflash_unit_of_workgroup(blockIdx.x, a.units_per_xcd, a.xcd_period);
     if (unit >= a.n_units) return;
@@ -58,7 +59,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, bh);
-    const ExpConst c = make_exp_const(hc);
+    const ExpConst c = make_exp_const<XM != kExpTable || D == 32>(hc);
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
 
     // ---- LDS: [weight table][slot 0][slot 1]; the dynamic LDS is the only LDS of the kernel, so the
@@ -75,15 +76,21 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int n_tiles = (N + BC - 1) / BC;
 
     // Lane part of the address of a 1 KiB piece: row lane / (D / 16), 16-byte piece lane % (D / 16) permuted
-    // by the row.  Rows beyond the sequence are clamped to the last row (what lands there is never used).
-    const int lrow = lane / kRowPieces, piece = ((lane ^ (lrow >> 2)) & (kRowPieces - 1)) << 4;
-    auto block_off = [&](int first_row) { return min(first_row + lrow, N - 1) * D + piece; };
+    // by the row.  Rows beyond the sequence are clamped to the last row (their weights are masked).
+    auto lane_row = [](int l) { return l / kRowPieces; };
+    auto lane_piece = [&](int l) { return ((l ^ (lane_row(l) >> 2)) & (kRowPieces - 1)) << 4; };
+    const int lane_off = lane_row(lane) * D + lane_piece(lane);
     // The 1 KiB pieces of tile j (the K blocks, then the V blocks), dealt round robin to the wavefronts.
     auto issue_tile = [&](int j) {
         const int slot = ring_base + kRingTileBytes * (j & 1);
-        for (int x = wave; x < kPieces; x += n_waves) {
-            const int b = x % (kPieces / 2);
-            load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, block_off(BC * j + kRows * b), slot + 1024 * x);
+        if (BC * (j + 1) <= N) {
+            for (int x = wave; x < kPieces; x += n_waves)
+                load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, lane_off + BC * D * j + 1024 * (x % (kPieces / 2)), slot + 1024 * x);
+        } else {
+            int l = (int)threadIdx.x & 63;
+            asm volatile("" : "+v"(l));
+            for (int x = wave; x < kPieces; x += n_waves)
+                load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, min(BC * j + kRows * (x % (kPieces / 2)) + lane_row(l), N - 1) * D + lane_piece(l), slot + 1024 * x);
         }
     };
 
@@ -113,31 +120,63 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     st.m = SB ? (int)((unsigned)m_init + (unsigned)kAccBias) : m_init;
 
     const int n_full = N / BC, rem = N - n_full * BC;
-#define QF_RING_TILE(FULL_, FIRST_, J_, NV_)                                                                   \
-    {                                                                                                          \
-        if ((J_) + 1 < n_tiles) issue_tile((J_) + 1);                                                          \
-        if (active) {                                                                                          \
-            const int slot = ring_base + kRingTileBytes * ((J_) & 1);                                          \
-            process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, 0, QMAX>(                            \
-                st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g,       \
-                slot + sl.k_off, slot + BC * D + sl.v_off);                                                      \
-        }                                                                                                      \
-        if ((J_) + 1 < n_tiles) {                                                                              \
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                                   \
-            __syncthreads();                                                                                   \
-        }                                                                                                      \
+#define QF_RING_COMPUTE(FULL_, FIRST_, J_, NV_, NG_, FR_)                                                          \
+    {                                                                                                              \
+        const int slot = ring_base + kRingTileBytes * ((J_) & 1);                                                  \
+        int k_off = sl.k_off, v_off = sl.v_off, g_ = 0;                                                            \
+        if (!(FULL_)) {      /* (nothing of it is to be prepared ahead of the tiles) */                            \
+            g_ = (int)threadIdx.x & 63;                                                                            \
+            asm volatile("; ragged tile %3" : "+v"(g_), "+v"(k_off), "+v"(v_off) : "i"(NG_) : "memory");           \
+            g_ >>= 5;                                                                                              \
+        }                                                                                                          \
+        process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_, QMAX, FR_>(                       \
+            st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,               \
+            slot + k_off, slot + BC * D + v_off);                                                                  \
     }
-    if (n_full > 0) {
-        QF_RING_TILE(true, true, 0, BC)
-        for (int j = 1; j < n_full; ++j) QF_RING_TILE(true, false, j, BC)
-        if (rem > 0) QF_RING_TILE(false, false, n_full, rem)
-    } else {
-        QF_RING_TILE(false, true, 0, rem)
+#define QF_RING_TILE(FIRST_, J_, FR_)                                                                              \
+    {                                                                                                              \
+        if ((J_) + 1 < n_tiles) issue_tile((J_) + 1);                                                              \
+        if (active) QF_RING_COMPUTE(true, FIRST_, J_, BC, 0, FR_)                                                  \
+        if ((J_) + 1 < n_tiles) {                                                                                  \
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                                       \
+            __syncthreads();                                                                                       \
+        }                                                                                                          \
     }
-#undef QF_RING_TILE
+#define QF_RING_LAST(FIRST_, J_, NV_, NG_, FR_) { QF_RING_COMPUTE(false, FIRST_, J_, NV_, NG_, FR_) }
+    constexpr bool kFloats = XM == kExpTable && !QMAX;
+    // (N >= BC but for 32 features and tiles of 128)
+    if (D == 64 || BC == 64 || n_full > 0) {
+        QF_RING_TILE(true, 0, true)
+        int j = 1;
+        // (every wavefront passes the barrier of every tile in one of the two loops)
+        for (; j < n_full && __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0; ++j) {
+            QF_RING_TILE(false, j, true)
+        }
+        for (; j < n_full; ++j) QF_RING_TILE(false, j, false)
+        if (!active) return;
+        if (rem == 0) {
+        } else if (!kFloats || (BC == 64 && rem > 16) || __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) != 0) {
+            if (kFloats && D == 32 && __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0) QF_RING_LAST(false, n_full, rem, 0, true)
+            else QF_RING_LAST(false, n_full, rem, 0, false)
+        } else if constexpr (kFloats) {
+            const int ng = (rem + 7) >> 3;
+            if (ng == 1) QF_RING_LAST(false, n_full, rem, -1, true)
+            else if (ng == 2) QF_RING_LAST(false, n_full, rem, -2, true)
+            else if constexpr (BC == 128) {
+                if (ng <= 4) QF_RING_LAST(false, n_full, rem, -4, true)
+                else if (ng <= 8) QF_RING_LAST(false, n_full, rem, -8, true)
+                else QF_RING_LAST(false, n_full, rem, -BC / 8, true)
+            }
+        }
+    } else if constexpr (D == 32 && BC == 128) {
+        if (!active) return;
+        QF_RING_LAST(true, 0, rem, 0, true)
+    }
     const int i = row0 + li;
-    if (!active || i >= N) return;
-    normalise_store<D, 20>(st, a.O + head_off + (size_t)i * D, g, a.out_round != 0);
+    if (i < N) normalise_store<D, 20, acc_offset<QMAX>()>(st, a.O + head_off + (size_t)i * D, g, a.out_round != 0);
+#undef QF_RING_LAST
+#undef QF_RING_COMPUTE
+#undef QF_RING_TILE
 }
 
 // Wavefronts per SIMD the register allocation has to allow.  64 features: with KV tiles of 64, 5 for the

@@ -74,25 +74,70 @@ __device__ __forceinline__ int release_acc(int y, const ReleaseConst& r) { retur
 // Denominator: 0 <= l < 2^20, floor(l * alpha16 / 2^16) = ((l << 2) * (alpha16 << 14)) >> 32.
 __device__ __forceinline__ int release_l(int l, const ReleaseConst& r) { return __mulhi(l << 2, r.alpha14); }
 
-constexpr int kAccBias = 0x40000000;   // offset carried by numerator accumulators and biased scores
+// The same for accumulators offset by 2^23 (kAccOffset), in one instruction: seen as a float, an integer below
+// 2^24 is that many units of 2^-149, denormal or not, so that a fused multiply-add that rounds toward minus
+// infinity (round_down) is floor(x alpha16 / 2^16) + 2^23, y = x + 2^23, with the addend 2^23 - 2^7 alpha16, as
+// long as -2^23 <= x < 2^23.  |x| <= 128 l + 129 per tile, so l < 65000 (kFloatReleaseMaxL) keeps it there; always
+// where N <= 256.  Beyond it the integer form above takes over, between two changes of offset.
+//
+// Why floats: of the vector units of a SIMD, one instruction in four cycles is all that integer work gets
+// (4.1 cycles measured with four wavefronts for any mix of multiplies, maxima, permutes, subtractions), but
+// fused multiply-adds issue beside it (2.2 to 2.4 cycles per instruction for a mix of half and half).  A
+// v_dot4 or a 24-bit multiply among them stops that for some forty instructions (4.1 cycles with one in
+// sixteen), which is why neither is used in the loop over the tiles.
+constexpr int kAccOffset = 1 << 23;
+constexpr int kFloatReleaseMaxL = 65000;
+__device__ __forceinline__ void round_down() { __builtin_amdgcn_s_setreg(1 | (0 << 6) | (1 << 11), 2); }   // MODE.round, single precision
+struct FloatRelease { float alpha, add; };
+__device__ __forceinline__ FloatRelease make_float_release(unsigned alpha16) {
+    return FloatRelease{(float)alpha16 * 0x1p-16f, __int_as_float(kAccOffset - (int)(alpha16 << 7))};
+}
+__device__ __forceinline__ int release_acc(int y, const FloatRelease& r) { return __float_as_int(__builtin_fmaf(__int_as_float(y), r.alpha, r.add)); }
+__device__ __forceinline__ int release_l(int l, const FloatRelease& r) { return __float_as_int(__int_as_float(l) * r.alpha); }
+
+// Four weights below 128, one to a register, to the bytes of one: the first three as floats (integers below 2^24,
+// exact in any rounding), see above.
+__device__ __forceinline__ unsigned pack_weights(unsigned p0, unsigned p1, unsigned p2, unsigned p3) {
+    const float w = __builtin_fmaf(__builtin_fmaf(__uint_as_float(p2), 256.0f, __uint_as_float(p1)), 256.0f, __uint_as_float(p0));
+    return (p3 << 24) | __float_as_uint(w);
+}
+// Mask of the first n bytes (n <= 0: none, n >= 4: all).
+__device__ __forceinline__ unsigned first_bytes(int n) { return (unsigned)(0xffffffffull >> (8 * (4 - min(max(n, 0), 4)))); }
+// Sum of the four bytes of w, added to sum.
+__device__ __forceinline__ int add_bytes(unsigned w, int sum) { return (int)__builtin_amdgcn_sad_u8(w, 0u, (unsigned)sum); }
+
+constexpr int kAccBias = 0x40000000;   // offset carried by biased scores, and by the numerator accumulators of QMAX
 // A result block full of the offset (the compiler turns it into the inline constant).
+template <int OFFSET = kAccBias>
 __device__ __forceinline__ v16i offset_block() {
     v16i z;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) z[v] = kAccBias;
+    for (int v = 0; v < 16; ++v) z[v] = OFFSET;
     return z;
 }
 // Offset of the biased scores of 32-key block kb of a tile, relative to kAccBias.  A matrix
 // instruction takes a constant as its addend only if the constant is one of the few the instruction
-// set has built in (here the bit patterns of 2.0, 4.0, 1.0 and 0.5: 2^30, 2^30 + 2^23, 2^30 - 2^23,
-// 2^30 - 2^24) and, with this compiler, only if no other instruction shares it; a block of sixteen
-// registers filled with the constant costs eight vector and sixteen scalar instructions per tile
-// otherwise.  So each block of a tile gets a constant of its own, and the two places that compare
-// scores across blocks (the row maximum, the table index) take the difference out again.
+// set has built in (here the bit patterns of 1 / (2 pi), 2.0, 4.0 and 1.0) and, with this compiler, only if no other
+// instruction shares it; a block of sixteen registers filled with the constant costs eight vector and
+// sixteen scalar instructions per tile otherwise.  So each block of a tile gets a constant of its own, and the
+// two places that compare scores across blocks (the row maximum, the table index) take the difference out again.
+// Block 0 has the only one of them around which 2^21 integers either way lie in one binade, [1/8, 1/4): its scores
+// are floats 2^-26 apart, and a fused multiply-add makes the table index of them (float_index).
+constexpr int kScoreOffset0 = 0x3E22F983;
 __device__ __forceinline__ constexpr int score_offset_delta(int kb) {
-    return kb == 0 ? 0 : kb == 1 ? (1 << 23) : kb == 2 ? -(1 << 23) : -(1 << 24);
+    return kb == 0 ? kScoreOffset0 - kAccBias : kb == 1 ? 0 : kb == 2 ? (1 << 23) : -(1 << 23);
 }
-constexpr int kMaskedBiased = 1 << 24;   // a key beyond the sequence, as a biased score at the common offset
+// A key beyond the sequence, as a biased score at the common offset: below every real score and every table edge
+// (which are at least -2^21 - 40960), and still in the binade of block 0.
+constexpr int kMaskedBiased = kAccBias - (kScoreOffset0 - 0x3E000000);
+// max(0, s - edge) for a score s of block 0 and the edge -- the score of table index 0 -- at the common offset:
+// s 2^-123 is s - 0x3E000000 + 2^23 units of 2^-149, and so is the addend; the clamp to [0, 1] is the maximum.
+__device__ __forceinline__ float index_addend(unsigned edge) {
+    return __uint_as_float(edge + ((unsigned)score_offset_delta(0) - 0x3E000000u + 0x800000u + 0x80000000u));
+}
+__device__ __forceinline__ unsigned float_index(int s, float scale /* 2^-123 */, float addend) {
+    return __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(__int_as_float(s), scale, addend), 0.0f, 1.0f));
+}
 template <int KBI>
 __device__ __forceinline__ v16i score_offset_block() {
     v16i z;
@@ -169,6 +214,10 @@ enum { kBiasNone = 0, kBiasPlain = 1, kBiasPacked = 2 };
 template <int D, int BC, int BIAS, bool NARROW, int XM>
 constexpr bool score_biased() { return XM == kExpTable && !BIAS; }
 
+// Offset of the numerator accumulators.
+template <bool QMAX>
+constexpr int acc_offset() { return QMAX ? kAccBias : kAccOffset; }
+
 template <bool SB>
 __device__ __forceinline__ int smax(int a, int b) { return SB ? (int)max((unsigned)a, (unsigned)b) : max(a, b); }
 template <bool SB>
@@ -235,27 +284,32 @@ __device__ __forceinline__ SwizzledLane swizzled_lane_offsets(int lane) {
 }
 
 // NG: 0, or the number of groups of 8 keys the (ragged) tile has, known at compile time: the tests
-// "does this group exist" then cost nothing; n_valid_rt still tells which keys of the last group exist.
-template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false>
+// "does this group exist" then cost nothing; n_valid_rt still tells which keys of the last group exist.  NG < 0: at
+// most -NG groups and more than -NG / 2 of them; what is in LDS for keys beyond the sequence is then the last key again
+// (the maximum stays what it is), and their weights are masked.
+template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, bool FLOAT_RELEASE = false>
 __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, const int8_t* sK, int KROW,
                                             const int8_t* sV, int VROW, int n_valid_rt, int x_p,
                                             const int32_t* bias_row /* + c0 */,
                                             const v4i* bpre /* packed bias of this tile already in registers, or null */,
                                             const ExpConst& c, int a_mul, int li, int g,
                                             int kx = 0, int vx = 0) {
-    const v16i zb = offset_block();
+    const v16i zb = offset_block<acc_offset<QMAX>()>();
     constexpr int KSTEPS = D / 32, TB = D / 32, KB = BC / 32;
     constexpr bool KZ = XM == kExpShift0;
     static_assert(!SB || (XM == kExpTable && !BIAS), "biased scores: table mode without bias only");
-    static_assert(KB <= 4, "one built-in constant per 32-key block");
+    static_assert(KB >= 2 && KB <= 4, "one built-in constant per 32-key block");
     // FULL: the tile has all BC kv rows, every "is this group inside the sequence" test below is
     // true at compile time and the tile is one straight line of code.
-    static_assert(NG >= 0 && NG <= BC / 8 && !(FULL && NG != 0), "groups of a ragged tile");
+    constexpr int NGA = NG < 0 ? -NG : NG;
+    static_assert(NGA <= BC / 8 && !(FULL && NG != 0), "groups of a ragged tile");
     const int n_valid = FULL ? BC : n_valid_rt;
     // does the 32-key block kb / the group a4 of it exist; does that group reach beyond the sequence
-    auto blk_on = [&](int kb) { return NG ? 4 * kb < NG : 32 * kb < n_valid; };
-    auto grp_on = [&](int kb, int a4) { return NG ? 4 * kb + a4 < NG : 32 * kb + 8 * a4 < n_valid; };
-    auto grp_cut = [&](int kb, int a4) { return NG ? 4 * kb + a4 == NG - 1 : 32 * kb + 8 * a4 + 8 > n_valid; };
+    auto blk_on = [&](int kb) { return NG ? 4 * kb < NGA : 32 * kb < n_valid; };
+    auto grp_on = [&](int kb, int a4) { return NG ? 4 * kb + a4 < NGA : 32 * kb + 8 * a4 < n_valid; };
+    auto grp_cut = [&](int kb, int a4) {
+        return NG > 0 ? 4 * kb + a4 == NG - 1 : NG == 0 && 32 * kb + 8 * a4 + 8 > n_valid;
+    };
     // Look-up mode with 32 features: one group of four scores in eight is computed instead of looked up.  A
     // look-up of 64 random bytes costs the LDS of the compute unit 2.5 cycles plus its bank conflicts (counted:
     // 5.3 cycles on the shape below, 4.6 with 64 x 12 pairs of 197 tokens and 64 features, 0 where a handful
@@ -335,10 +389,11 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     // (three-operand maxima, one chain per score block so that they can overlap)
     int m_new = st.m;
     {
+        constexpr int BASE = SB ? 1 : 0;             // a block at the common offset
         int mk[KB];
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            mk[kb] = kb == 0 ? st.m : (SB ? kMaskedBiased + score_offset_delta(kb) : INT32_MIN);
+            mk[kb] = kb == BASE ? st.m : (SB ? kMaskedBiased + score_offset_delta(kb) : INT32_MIN);
 #pragma unroll
             for (int a4 = 0; a4 < 4; ++a4)
                 if (grp_on(kb, a4)) {
@@ -346,9 +401,10 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                     mk[kb] = smax3<SB>(mk[kb], s[kb][4 * a4 + 2], s[kb][4 * a4 + 3]);
                 }
         }
-        m_new = mk[0];
+        m_new = mk[BASE];
 #pragma unroll
-        for (int kb = 1; kb < KB; ++kb) {
+        for (int kb = 0; kb < KB; ++kb) {
+            if (kb == BASE) continue;
             if (SB) {
                 // (a block that does not exist has no maximum to bring to the common offset)
                 if (blk_on(kb)) m_new = smax<SB>(m_new, (int)((unsigned)mk[kb] - (unsigned)score_offset_delta(kb)));
@@ -377,10 +433,10 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     const int lo = m_new + c.x_floor;
     const int m2 = m_new - 2 * c.s_inv;
     // ---- step 4: max-offset factor alpha, brought to 16 fractional bits
-    ReleaseConst rel;
+    unsigned alpha16 = 0;
     if (!FIRST && !QMAX) {
         const int a_hat = shift_exp2<KZ>(smax<SB>(st.m, lo), m_new, m2, c);
-        rel = make_release(min(((unsigned)a_hat * (unsigned)a_mul) >> 14, 65536u));
+        alpha16 = min(((unsigned)a_hat * (unsigned)a_mul) >> 14, 65536u);
     }
     // ---- steps 9,10 (the part that concerns the past): ScaleRelease of denominator and numerator.
     //      QMAX: alpha = 2^-n, an arithmetic shift; on the offset representation
@@ -395,12 +451,20 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
             for (int t = 0; t < TB; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) st.acc[t][v] = (int)(((unsigned)st.acc[t][v] >> n) + addc);
-        } else {
-            st.l = release_l(st.l, rel);
+        } else if (!FLOAT_RELEASE) {
+            const ReleaseConst ri = make_release(alpha16);
+            st.l = release_l(st.l, ri);
 #pragma unroll
             for (int t = 0; t < TB; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) st.acc[t][v] = release_acc(st.acc[t][v], rel);
+                for (int v = 0; v < 16; ++v) st.acc[t][v] = release_acc(st.acc[t][v] + (kAccBias - kAccOffset), ri) - (kAccBias - kAccOffset);
+        } else {
+            const FloatRelease rf = make_float_release(alpha16);
+            st.l = release_l(st.l, rf);
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) st.acc[t][v] = release_acc(st.acc[t][v], rf);
         }
     };
     v4i pk[KB];
@@ -411,6 +475,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
         //      or below -x_p (excluded scores included).
         const unsigned x_p_v = (unsigned)to_vgpr(x_p);
         const unsigned edge = (unsigned)m_new - x_p_v;       // score_biased: m + 2^30 - x_p > 0
+        const float addend0 = index_addend(edge), scale0 = __int_as_float(to_vgpr(0x02000000));   // 2^-123
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
             const unsigned edge_kb = edge + (unsigned)score_offset_delta(kb);   // (the block's own offset)
@@ -422,7 +487,8 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                         // Saturating subtractions are fast-class instructions; as builtins, because
                         // they read MFMA results.
                         const unsigned sv = (unsigned)s[kb][4 * a4 + b];
-                        const unsigned idx = SB ? __builtin_elementwise_sub_sat(sv, edge_kb)
+                        const unsigned idx = SB && kb == 0 && (FULL || NG) ? float_index((int)sv, scale0, addend0)
+                                           : SB ? __builtin_elementwise_sub_sat(sv, edge_kb)
                                                 : __builtin_elementwise_sub_sat(x_p_v, (unsigned)m_new - sv);
                         s[kb][4 * a4 + b] = computed(kb, a4) ? (int)idx : table_weight(idx);
                     }
@@ -440,8 +506,8 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                         for (int b = 0; b < 4; ++b) {
                             const int xs = (s[kb][4 * a4 + b] << c.k) - xpk, xs2 = xs + c.two_s_inv_v;
                             const int q = mulhi24(xs, c.M_v);
-                            const int y = (int)((unsigned)(__mul24(q, c.s_inv) + xs2) >> (q + 1));
-                            s[kb][4 * a4 + b] = __mul24(y, c.p_mul_hi_v);
+                            const int y = (int)((unsigned)(q * c.s_inv + xs2) >> (q + 1));
+                            s[kb][4 * a4 + b] = y * c.p_mul_hi_v;
                         }
                     }
         }
@@ -455,9 +521,11 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                 if (grp_on(kb, a4)) {
                     const unsigned p0 = (unsigned)s[kb][4 * a4], p1 = (unsigned)s[kb][4 * a4 + 1];
                     const unsigned p2 = (unsigned)s[kb][4 * a4 + 2], p3 = (unsigned)s[kb][4 * a4 + 3];
-                    const unsigned w = computed(kb, a4) ? pack_byte3(p0, p1, p2, p3) : pack_byte<0>(p0, p1, p2, p3);
+                    unsigned w = computed(kb, a4) ? pack_byte3(p0, p1, p2, p3)
+                                                : FULL || NG ? pack_weights(p0, p1, p2, p3) : pack_byte<0>(p0, p1, p2, p3);
+                    if (NG < 0 && 4 * kb + a4 >= NGA / 2) w &= first_bytes(n_valid - (32 * kb + 8 * a4 + 4 * g));
                     pk[kb][a4] = (int)w;
-                    rowsum = __builtin_amdgcn_sdot4((int)w, 0x01010101, rowsum, false);   // step 7
+                    rowsum = add_bytes(w, rowsum);   // step 7
                 }
         }
         {
@@ -477,11 +545,11 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
                         const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m2, c);
-                        pr[b] = (unsigned)__mul24(y, c.p_mul_hi_v);       // Eq. 10, result in byte 3
+                        pr[b] = (unsigned)(y * c.p_mul_hi_v);       // Eq. 10, result in byte 3
                     }
                     const unsigned w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
                     pk[kb][a4] = (int)w;
-                    rowsum = __builtin_amdgcn_sdot4((int)w, 0x01010101, rowsum, false);
+                    rowsum = add_bytes(w, rowsum);
                 }
         }
         {
@@ -539,7 +607,8 @@ __device__ __forceinline__ int clamp_0(int u, int hi) {
 
 // normalise_words leaves the lane's contiguous half of the output row (D / 2 bytes: lane g = 0 the
 // first half, g = 1 the second) in out[0 .. D/32); normalise_store also writes it.
-template <int D, int L>
+// OFFSET: the offset the accumulators carry.
+template <int D, int L, int OFFSET>
 __device__ __forceinline__ void normalise_words(const RowState<D>& st, bool round_nearest, v4i* out) {
     constexpr int TB = D / 32;
     static_assert(L == 16 || L == 20, "quotient must be byte aligned");
@@ -553,7 +622,7 @@ __device__ __forceinline__ void normalise_words(const RowState<D>& st, bool roun
     const int zz = z + rs;
     // The accumulators carry their offset (ReleaseConst); it is taken out, modulo 2^32, together
     // with the addition of 128 l.
-    int bias_z = (int)(((128u * dsafe + (round_nearest ? (unsigned)st.l : 0u)) << z) - ((unsigned)kAccBias << zz));
+    int bias_z = (int)(((128u * dsafe + (round_nearest ? (unsigned)st.l : 0u)) << z) - ((unsigned)OFFSET << zz));
     asm volatile("" : "+v"(bias_z));     // (kept as one addend: otherwise the offset is subtracted from every element first)
     // word[j]: features 8 j + 4 g + (0..3) of this lane's row, j = 4 t + a4
     unsigned word[4 * TB];
@@ -609,10 +678,10 @@ __device__ __forceinline__ void normalise_quads(const v4i* acc, int l, bool roun
     }
 }
 
-template <int D, int L>
+template <int D, int L, int OFFSET>
 __device__ __forceinline__ void normalise_store(const RowState<D>& st, int8_t* Orow, int g, bool round_nearest) {
     v4i w[D / 32];
-    normalise_words<D, L>(st, round_nearest, w);
+    normalise_words<D, L, OFFSET>(st, round_nearest, w);
     int8_t* dst = Orow + g * (D / 2);
 #pragma unroll
     for (int q = 0; q < D / 32; ++q) *(v4i*)(dst + 16 * q) = w[q];

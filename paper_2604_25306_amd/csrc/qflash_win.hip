@@ -131,7 +131,7 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
     }
     // ---- step 11
     v4i o;
-    normalise_words<D, 16>(st, out_round, &o);
+    normalise_words<D, 16, kAccBias>(st, out_round, &o);
     return o;
 }
 

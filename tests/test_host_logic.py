@@ -174,3 +174,52 @@ def test_inline_assembly_never_has_a_vector_register_as_a_pure_output():
             statements += 1
             assert '"=v"' not in stmt and '"=&v"' not in stmt, "%s: %s" % (os.path.basename(path), stmt.strip()[:120])
     assert statements > 10
+
+
+def round_down_to_float(num, shift):
+    """The float32 nearest below num / 2^shift among the integers (units of 2^-149) under 2^24: floor."""
+    v = num >> shift
+    assert 0 <= v < 1 << 24                      # integers below 2^24 are floats, denormal or not, one unit apart
+    return v
+
+
+def test_float_release_is_the_integer_one():
+    """fma(x + 2^23, alpha16 2^-16, 2^23 - 2^7 alpha16), rounded toward minus infinity, in units of 2^-149."""
+    rng = np.random.default_rng(6)
+    x = rng.integers(-(1 << 23), 1 << 23, size=40000).astype(object)
+    x[:6] = [0, 1, -1, (1 << 23) - 1, -(1 << 23), 12345]
+    a = rng.integers(0, 65537, size=40000).astype(object)
+    a[:8] = [0, 65536, 1, 65535, 32768, 32767, 65536, 65536]
+    for xi, ai in zip(x, a):
+        y, add = xi + (1 << 23), (1 << 23) - (ai << 7)
+        assert 0 <= y < 1 << 24 and 0 <= add < 1 << 24 and ai < 1 << 24
+        assert round_down_to_float(y * ai + (add << 16), 16) == ((xi * ai) >> 16) + (1 << 23)
+
+
+def test_float_release_range_of_the_numerator():
+    """|x| <= 128 l + 129 per tile, whatever the weights, values and factors; 65000 keeps it below 2^23 over 64 tiles."""
+    assert 128 * 65000 + 129 * 64 < 1 << 23 and 128 * 127 * 256 < 1 << 23
+    rng = np.random.default_rng(7)
+    for _ in range(300):
+        l = x = 0
+        for t in range(64):
+            a = int(rng.integers(0, 65537)) if rng.random() < 0.5 else 65536 - int(rng.integers(0, 4))
+            s = int(rng.integers(0, 127 * 64 + 1))
+            v = int(rng.choice([-128, 127, int(rng.integers(-128, 128))]))
+            l, x = ((l * a) >> 16) + s, ((x * a) >> 16) + s * v
+            assert abs(x) <= 128 * l + 129 * (t + 1)
+
+
+def test_float_index_of_block_0():
+    """(bits of a score around 1 / (2 pi)) 2^-123 - edge, in units of 2^-149: max(0, score - edge)."""
+    off = 0x3E22F983
+    assert np.array([off], np.uint32).view(np.float32)[0] == np.float32(0.15915494)
+    lo, hi = off - (1 << 21) - 40960, off + (1 << 21)
+    assert 0x3E000000 <= lo and hi < 0x3E800000                 # one binade, 2^-26 apart: bits b stand for (b - 0x3E000000 + 2^23) 2^-26
+    scale = np.array([0x02000000], np.uint32).view(np.float32)[0]
+    assert scale == np.float32(2.0) ** -123
+    masked = (1 << 30) - (off - 0x3E000000)                     # a key beyond the sequence, at the common offset
+    assert masked < (1 << 30) - (1 << 21) - 40960
+    for b in (lo, off - 1, off, off + 1, hi):
+        v = np.array([b], np.uint32).view(np.float32)[0]
+        assert float(v) == (b - 0x3E000000 + (1 << 23)) * 2.0 ** -26
