@@ -70,6 +70,7 @@ struct QflashKernelArgs {
     // two-tile ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
     int ring_dma;
     int ring_table_lds;      // LDS bytes reserved for the weight table (a multiple of 1 KiB)
+    int ring_even_from;      // workgroups from this index on give way to those behind them (qflash_plan_ring)
     // windowed-attention kernel (qflash_plan_win): 1 if the launch takes it
     int win_mode;
     int win_streams;         // pairs of wavefronts (one per half of the query rows) per workgroup, at most 8

@@ -258,7 +258,7 @@ size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
 // 20: DeiT-B/384, N(0,1), 12 resident: 414; N(0,1.5^2), small table, 20 resident: 341), x limited by LDS and
 // registers.  Measured against the fixed four (us): d = 64, 96 pairs of 1025 tokens 47.4 -> 39.7 (seven),
 // 32 features, 64 pairs of 2100 tokens 81.2 -> 76.9 (six), 96 pairs of 1200 tokens 41.2 -> 39.9 (three).
-static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKernelArgs& a, int want, int* waves, int* qtiles) {
+static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKernelArgs& a, int want, int* waves, int* qtiles, int* resident) {
     const int nblk = (a.N + 31) / 32, cus = a.n_cu > 0 ? a.n_cu : 256;
     *qtiles = (nblk + want - 1) / want;
     const int w = *waves = (nblk + *qtiles - 1) / *qtiles;                        // balanced
@@ -272,6 +272,7 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     const int by_registers = per_simd == 3 ? 3 / ((w + 3) / 4) : 4 * per_simd / w;
     if (fit > by_registers) fit = by_registers;
     if (fit > per_cu) fit = per_cu;
+    *resident = (int)fit;
     if (fit < 1) return 1e30;
     const double x = (double)fit * eff;
     return (double)per_cu * eff * (2200.0 + 230.0 * x) / x;
@@ -281,11 +282,11 @@ int qflash_plan_ring(int d, int lds_limit, int table_bytes, QflashKernelArgs* a)
     if (a->bias || a->win_mode || (!a->ring_dma && (d != 32 || a->N <= 64))) return 0;
     const int wants[2][3] = {{4, 8, 4}, {4, 3, 6}};
     double best = 0.0;
-    int waves = 0, qtiles = 0;
+    int waves = 0, qtiles = 0, resident = 0;
     for (int i = 0; i < 3; ++i) {
-        int w, t;
-        const double cost = ring_cost(d, lds_limit, table_bytes, *a, wants[d == 32][i], &w, &t);
-        if (waves == 0 || cost < 0.97 * best) { best = cost; waves = w; qtiles = t; }
+        int w, t, r;
+        const double cost = ring_cost(d, lds_limit, table_bytes, *a, wants[d == 32][i], &w, &t, &r);
+        if (waves == 0 || cost < 0.97 * best) { best = cost; waves = w; qtiles = t; resident = r; }
     }
     const long long units = (long long)a->B * a->H * qtiles;
     if (units >= (1ll << 30)) return 0;
@@ -301,6 +302,14 @@ int qflash_plan_ring(int d, int lds_limit, int table_bytes, QflashKernelArgs* a)
     a->n_units = (int)units;
     a->units_per_xcd = (a->n_units + 7) / 8;
     a->xcd_period = 0;
+    // Of the workgroups that share a compute unit the oldest goes first, so that the last ones of a launch would end
+    // alone, at the pace of a single wavefront (1 us per tile; 19 wavefronts on a unit do a tile in 0.09).  From this
+    // workgroup on, the last that fit the chip together, wavefronts give way the further they have come (the kernel's
+    // s_setprio): 256 pairs of 577 tokens 22.6 -> 20.9 us, 64 pairs of 2100 with 32 features 69.8 -> 64.0.  Not for
+    // all of several rounds: 64 pairs of 2100, tiles of 128, 71.0 -> 78.3; nor for fewer than three wavefronts to a
+    // SIMD, where there is nothing to share (32 pairs of 768 tokens, 32 features, 12.1 -> 12.4).
+    const long long grid = 8ll * a->units_per_xcd, last = (long long)resident * (a->n_cu > 0 ? a->n_cu : 256);
+    a->ring_even_from = resident * waves < 9 ? (int)grid : grid > last ? (int)(grid - last) : 0;
     return 1;
 }
 

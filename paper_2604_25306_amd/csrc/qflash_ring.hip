@@ -146,10 +146,17 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     constexpr bool kFloats = XM == kExpTable && !QMAX;
     // (N >= BC but for 32 features and tiles of 128)
     if (D == 64 || BC == 64 || n_full > 0) {
+        // wavefronts of the last workgroups give way the further they have come (qflash_plan_ring)
+        const bool even = (int)blockIdx.x >= a.ring_even_from;
+        const int p2 = even ? n_tiles / 2 : n_tiles, p1 = even ? (3 * n_tiles) / 4 : n_tiles, p0 = even ? (7 * n_tiles) / 8 : n_tiles;
+        if (a.ring_even_from < (int)gridDim.x) __builtin_amdgcn_s_setprio(3);
         QF_RING_TILE(true, 0, true)
         int j = 1;
         // (every wavefront passes the barrier of every tile in one of the two loops)
         for (; j < n_full && __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0; ++j) {
+            if (j == p2) __builtin_amdgcn_s_setprio(2);
+            if (j == p1) __builtin_amdgcn_s_setprio(1);
+            if (j == p0) __builtin_amdgcn_s_setprio(0);
             QF_RING_TILE(false, j, true)
         }
         for (; j < n_full; ++j) QF_RING_TILE(false, j, false)
