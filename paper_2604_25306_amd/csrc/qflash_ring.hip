@@ -42,7 +42,10 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_ring[];
 
-template <int D, int BC, int XM, bool QMAX>
+// Weight tables of 32 features from this size on: part of the weights is computed (MIXED of process_tile).
+constexpr int kRingMixedBytes = 7 * 1024;
+
+template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
 __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     constexpr int kRingTileBytes = 2 * BC * D;      // one KV tile in LDS: K (BC rows of D bytes), then V
     constexpr int kRows = 1024 / D;                 // rows of a 1 KiB piece
@@ -59,7 +62,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, bh);
-    const ExpConst c = make_exp_const<XM != kExpTable || D == 32>(hc);
+    const ExpConst c = make_exp_const<XM != kExpTable || MIXED>(hc);
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
 
     // ---- LDS: [weight table][slot 0][slot 1]; the dynamic LDS is the only LDS of the kernel, so the
@@ -129,7 +132,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
             asm volatile("; ragged tile %3" : "+v"(g_), "+v"(k_off), "+v"(v_off) : "i"(NG_) : "memory");           \
             g_ >>= 5;                                                                                              \
         }                                                                                                          \
-        process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_, QMAX, FR_>(                       \
+        process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_, QMAX, FR_, MIXED>(                \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,               \
             slot + k_off, slot + BC * D + v_off);                                                                  \
     }
@@ -197,21 +200,23 @@ constexpr int ring_min_waves() {
 }
 
 // QMAX: the quantised-maximum variant (not Algorithm 1 as printed; see process_tile).
-template <int D, int BC, int XM, bool QMAX>
+template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
 __global__ __launch_bounds__(64 * kRingMaxWaves, (ring_min_waves<D, BC, XM>())) void qflash_fwd_ring(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
         const int unit = qflash_unit_of_workgroup(blockIdx.x, a.units_per_xcd, a.xcd_period);
         if (unit >= a.n_units) return;
-        if (head_consts(a, unit / a.n_qtiles).lut_bytes > 0) ring_body<D, BC, kExpTable, QMAX>(a);
+        const int table = head_consts(a, unit / a.n_qtiles).lut_bytes;
+        if (D == 32 && table >= kRingMixedBytes) ring_body<D, BC, kExpTable, QMAX, D == 32>(a);
+        else if (table > 0) ring_body<D, BC, kExpTable, QMAX>(a);
         else ring_body<D, BC, kExpShift, QMAX>(a);
     } else {
-        ring_body<D, BC, XM, QMAX>(a);
+        ring_body<D, BC, XM, QMAX, MIXED>(a);
     }
 }
 
-template <int D, int BC, int XM, bool QMAX>
+template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
 int launch_ring(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    return qflash_launch_kernel<qflash_fwd_ring<D, BC, XM, QMAX>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)(64 * a.waves_per_head), lds, lds_limit, st);
+    return qflash_launch_kernel<qflash_fwd_ring<D, BC, XM, QMAX, MIXED>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)(64 * a.waves_per_head), lds, lds_limit, st);
 }
 
 }  // namespace
@@ -220,6 +225,7 @@ namespace {
 template <int D, int BC, bool QMAX>
 int launch_mode(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
     if (a.exp_mode == kExpAuto) return launch_ring<D, BC, kExpAuto, QMAX>(a, lds, lds_limit, st);
+    if (D == 32 && a.exp_mode == kExpTable && a.lut_bytes_max >= kRingMixedBytes) return launch_ring<D, BC, kExpTable, QMAX, D == 32>(a, lds, lds_limit, st);
     if (a.exp_mode == kExpTable) return launch_ring<D, BC, kExpTable, QMAX>(a, lds, lds_limit, st);
     if (a.exp_mode == kExpShift0) return launch_ring<D, BC, kExpShift0, QMAX>(a, lds, lds_limit, st);
     return launch_ring<D, BC, kExpShift, QMAX>(a, lds, lds_limit, st);
@@ -238,6 +244,7 @@ int qflash_launch_fwd_ring(const QflashKernelArgs& a, int d, int lds_limit, void
         return (int)hipErrorInvalidValue;
     if (a.waves_per_head < 1 || a.waves_per_head > kRingMaxWaves || a.rows_per_wg != 32 * a.waves_per_head) return (int)hipErrorInvalidValue;
     if ((long long)a.rows_per_wg * a.n_qtiles < a.N) return (int)hipErrorInvalidValue;
+    if (a.N < a.kv_tile && (d == 64 || a.kv_tile == 64)) return (int)hipErrorInvalidValue;
     const bool table = a.exp_mode == kExpTable || a.exp_mode == kExpAuto;
     if (table && a.lut_bytes_max > a.ring_table_lds) return (int)hipErrorInvalidValue;
     const size_t lds = qflash_ring_lds_bytes(a.waves_per_head, a.kv_tile, table ? a.ring_table_lds : 0, d);

@@ -287,7 +287,7 @@ __device__ __forceinline__ SwizzledLane swizzled_lane_offsets(int lane) {
 // "does this group exist" then cost nothing; n_valid_rt still tells which keys of the last group exist.  NG < 0: at
 // most -NG groups and more than -NG / 2 of them; what is in LDS for keys beyond the sequence is then the last key again
 // (the maximum stays what it is), and their weights are masked.
-template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, bool FLOAT_RELEASE = false>
+template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, bool FLOAT_RELEASE = false, bool MIXED = false>
 __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, const int8_t* sK, int KROW,
                                             const int8_t* sV, int VROW, int n_valid_rt, int x_p,
                                             const int32_t* bias_row /* + c0 */,
@@ -310,15 +310,16 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     auto grp_cut = [&](int kb, int a4) {
         return NG > 0 ? 4 * kb + a4 == NG - 1 : NG == 0 && 32 * kb + 8 * a4 + 8 > n_valid;
     };
-    // Look-up mode with 32 features: one group of four scores in eight is computed instead of looked up.  A
-    // look-up of 64 random bytes costs the LDS of the compute unit 2.5 cycles plus its bank conflicts (counted:
-    // 5.3 cycles on the shape below, 4.6 with 64 x 12 pairs of 197 tokens and 64 features, 0 where a handful
-    // of table entries carries the weights), its arithmetic the vector units 5.  At 32 features a tile has half the
-    // vector work per look-up and the LDS is what runs out first
-    // (B*H = 64, N = 2100: 88.0 us with every weight looked up, 81.2 with 7 of 8, 79.8 with 6 of 8 but
-    // 105 with larger workgroups: registers); at 64 features it only costs (40.5 -> 45 us, N = 577).
-    constexpr bool MIX = XM == kExpTable && D == 32 && LAY == kLaySwizzled && FULL;   // (a ragged tile would spill)
-    auto computed = [&](int kb, int a4) { return MIX && (kb & 1) == 1 && a4 == 3; };
+    // MIXED (look-up mode, 32 features): two groups of four scores in eight are computed instead of looked up.  A
+    // look-up of 64 random bytes costs the LDS of the compute unit 2.1 cycles where they fall into few words, 7.5 where
+    // they are spread over a large table (measured: 2.1 and 7.5), its arithmetic nine vector instructions.  At 32
+    // features a tile has half the vector work per look-up and the LDS is what runs out first.  us with none, one,
+    // two and three groups computed, 96 pairs of 1200 tokens, inputs N(0, sigma^2): sigma 1.0 (table of 12 KB) 36.4 34.2
+    // 32.5 32.9, 1.2 (8.5 KB) 32.0 30.6 29.9 31.9, 1.35 (6.7 KB) 28.2 27.9 28.6 31.4, 1.6 (4.8 KB) 24.5 25.8 28.0 31.2: see
+    // kRingMixedBytes.  At 64 features computing only costs (40.5 -> 45 us, N = 577).
+    static_assert(!MIXED || (XM == kExpTable && D == 32 && LAY == kLaySwizzled), "computed weights beside look-ups");
+    constexpr bool MIX = MIXED && FULL;                    // (a ragged tile would spill)
+    auto computed = [&](int kb, int a4) { return MIX && a4 == 3; };
     // ---- step 1: S^T blocks (32 kv rows x 32 queries each)
     v16i s[KB];
 #pragma unroll
@@ -496,7 +497,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
         }
         __builtin_amdgcn_sched_barrier(0);
         if (MIX) {
-            const int xpk = x_p << c.k;
+            const unsigned neg_xpk = (unsigned)to_vgpr(-(x_p << c.k));
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -504,7 +505,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                     if (computed(kb, a4) && grp_on(kb, a4)) {
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
-                            const int xs = (s[kb][4 * a4 + b] << c.k) - xpk, xs2 = xs + c.two_s_inv_v;
+                            const int xs = (int)(((unsigned)s[kb][4 * a4 + b] << c.k) + neg_xpk), xs2 = xs + c.two_s_inv_v;
                             const int q = mulhi24(xs, c.M_v);
                             const int y = (int)((unsigned)(q * c.s_inv + xs2) >> (q + 1));
                             s[kb][4 * a4 + b] = y * c.p_mul_hi_v;

@@ -28,3 +28,15 @@ def test_ring32(gpu, bhn, tile):  # noqa: F811
     if N in (129, 577):
         ps = [oracle.derive_params(sQ * g, sK, 32) for g in ([0.2, 1.0, 30.0] + [1.3] * H)[:H]]
         assert_same(run_gpu(gpu, Q, K, V, ps, tile), oracle.qflash_attention(Q, K, V, ps, tile), "%s per head" % (bhn,))
+
+
+# weight tables on either side of the size from which part of the weights is computed, full tiles and a ragged one
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("gain", [1.0, 2.6, 2.74, 2.85, 3.5])
+def test_ring32_mixed_weights(gpu, gain, tile):  # noqa: F811
+    torch, qf, ctx = gpu
+    Q, K, V, sQ, sK, _ = rand_case((12, 4, 420, 32), 6000, q_gain=1.0)
+    p = oracle.derive_params(sQ * gain, sK, 32)
+    assert_same(run_gpu(gpu, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "gain %g" % gain)
+    info = ctx.cache_info()
+    assert (info.last_kernel, info.last_key_waves) == (2, 0)
