@@ -242,6 +242,8 @@ inline int qflash_effective_tile(int kv_tile, int N) { return N <= 64 ? 64 : kv_
 constexpr int kRingMaxWaves = 8;
 int qflash_launch_fwd_ring(const QflashKernelArgs& args, int d, int lds_limit, void* stream);
 size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d = 64);
+// Slots in its LDS, each of one tile of K or V.
+constexpr int qflash_ring_slots(int d) { return d == 64 ? 3 : 4; }
 // Completes the plan of qflash_plan_fwd for that kernel: takes every sequence of 32 features without a bias and
 // with more than one KV tile (planned as resident or streamed so far), and chooses the number of wavefronts
 // per workgroup for a weight table of table_bytes.  Returns ring_dma.

@@ -249,7 +249,7 @@ int qflash_plan_cu_dynamic(int BH, int N, int d, int kv_tile, int lds_limit, Qfl
 // LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and two KV tiles of K and V.
 size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
     (void)waves;
-    return (((size_t)table_bytes + 1023) & ~(size_t)1023) + 2 * (size_t)kv_tile * 2 * (size_t)d;
+    return (((size_t)table_bytes + 1023) & ~(size_t)1023) + (size_t)qflash_ring_slots(d) * (size_t)kv_tile * (size_t)d;
 }
 
 // Wavefronts per workgroup of the ring.  More of them share one weight table and one staged tile, fewer
@@ -257,30 +257,36 @@ size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
 // of them adds, (2200 + 230 x) / x cycles per KV tile with x wavefronts on the unit (fitted to 12 to
 // 20: DeiT-B/384, N(0,1), 12 resident: 414; N(0,1.5^2), small table, 20 resident: 341), x limited by LDS and
 // registers.  Measured against the fixed four (us): d = 64, 96 pairs of 1025 tokens 47.4 -> 39.7 (seven),
-// 32 features, 64 pairs of 2100 tokens 81.2 -> 76.9 (six), 96 pairs of 1200 tokens 41.2 -> 39.9 (three).
+// 36 pairs of 1000 25.2 -> 21.7, 56 of 577 16.7 -> 14.6 (three), 32 features, 64 pairs of 2100 tokens 81.2 -> 76.9 (six), 96
+// pairs of 1200 tokens 41.2 -> 39.9 (three).
 static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKernelArgs& a, int want, int* waves, int* qtiles, int* resident) {
     const int nblk = (a.N + 31) / 32, cus = a.n_cu > 0 ? a.n_cu : 256;
     *qtiles = (nblk + want - 1) / want;
     const int w = *waves = (nblk + *qtiles - 1) / *qtiles;                        // balanced
+    *resident = 1;
     // (at 64 features the SIMDs are busy enough for an uneven workgroup to cost part of its fullest SIMD's share)
     const double eff = d == 64 ? 0.5 * (w + ((w + 3) & ~3)) : w;
-    const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 3) : a.kv_tile == 64 ? 6 : 4;   // by registers
+    const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 4) : a.kv_tile == 64 ? 6 : 4;   // by registers
     const long long units = (long long)a.B * a.H * *qtiles, per_cu = (units + cus - 1) / cus;
     long long fit = (long long)((size_t)lds_limit / qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d));
-    // (with three wavefronts to a SIMD a second workgroup of five or six was not resident beside the first: 512 pairs of
-    // 302 tokens 34.0 us with five against 28.2 with four, 288 of 330 27.7 with six against 20.4)
-    const int by_registers = per_simd == 3 ? 3 / ((w + 3) / 4) : 4 * per_simd / w;
+    // (Tiles of 128: workgroups of five to seven wavefronts, which do not share the SIMDs evenly, are never better: 384 pairs
+    // of 577 tokens 47.2 us with five and 40.6 with seven against 38.8 with four, 192 of 640 27.6 with seven against 22.6;
+    // eight are, where they even out the rounds: 120 pairs of 900 32.2 -> 29.5.  Three only where the launch does not
+    // share out its keys, qflash_plan_split.)
+    if (d == 64 && a.kv_tile == 128 && w > 4 && w < 8) return 1e30;
+    if (d == 64 && want == 3 && (long long)a.B * a.H * nblk <= 2ll * cus) return 1e30;
+    const int by_registers = d == 64 && a.kv_tile == 128 ? per_simd / ((w + 3) / 4) : 4 * per_simd / w;
     if (fit > by_registers) fit = by_registers;
     if (fit > per_cu) fit = per_cu;
-    *resident = (int)fit;
     if (fit < 1) return 1e30;
+    *resident = (int)fit;
     const double x = (double)fit * eff;
     return (double)per_cu * eff * (2200.0 + 230.0 * x) / x;
 }
 
 int qflash_plan_ring(int d, int lds_limit, int table_bytes, QflashKernelArgs* a) {
     if (a->bias || a->win_mode || (!a->ring_dma && (d != 32 || a->N <= 64))) return 0;
-    const int wants[2][3] = {{4, 8, 4}, {4, 3, 6}};
+    const int wants[2][3] = {{4, 8, 3}, {4, 3, 6}};
     double best = 0.0;
     int waves = 0, qtiles = 0, resident = 0;
     for (int i = 0; i < 3; ++i) {

@@ -2,32 +2,28 @@
 // without a bias: the two-tile ring, fed by direct global-to-LDS loads.
 //
 // A workgroup of up to 8 wavefronts serves 32 query rows per wavefront of one (batch, head) pair and
-// walks over all KV tiles of the pair.  LDS holds the weight table and two KV tiles: the one in use
-// and the one on its way.  K and V tiles arrive row-major as they lie in memory (16-byte pieces
-// permuted by the row so that operand reads are free of bank conflicts), put there by `global_load_lds_dwordx4`; the K/Q operands are plain 16-byte LDS reads
-// and the V^T operand is read with the transposing 8-bit LDS read (see qflash_tile.h).  Compared with
-// staging through registers (qflash_resident.h) there are no staging registers, no byte transposes
-// in the vector ALU and no LDS write instructions: about a third of that kernel's vector
-// instructions on these shapes.
+// walks over all KV tiles of the pair.  LDS holds the weight table and three (64 features) or four slots, each
+// of one tile of K or V.  The tiles arrive row-major as they lie in memory (16-byte pieces permuted by the row so
+// that operand reads are free of bank conflicts), put there by `global_load_lds_dwordx4`; the K/Q operands are
+// plain 16-byte LDS reads and the V^T operand is read with the transposing 8-bit LDS read (see qflash_tile.h).
+// Compared with staging through registers (qflash_resident.h) there are no staging registers, no byte transposes
+// in the vector ALU and no LDS write instructions: about a third of that kernel's vector instructions on these shapes.
 //
-// What bounds it, by counters (cycles of a compute unit at 2.2 GHz per wavefront and KV tile: a vector instruction 4 on
-// one of four SIMDs, an LDS operand read 8 or, transposing, 4, a look-up 2.5 plus the counted bank conflicts):
-//   64 features, tiny table (256 pairs of 577 tokens, tiles of 64, 26 us): 302 measured; 214 vector, 63 matrix, 130
-//     LDS, no bank conflicts.  No unit is full.  The vector and the matrix time add up: the barrier after every
-//     tile keeps the wavefronts of a workgroup in one phase.
-//   64 features, tiles of 128 (384 pairs of 577, 39 us): 604 measured; 338 vector, 125 matrix, 350 LDS (1.5 conflict
-//     cycles per look-up).  No unit is full here either: 137 registers leave three wavefronts to a SIMD.
-//   32 features (64 pairs of 2100 tokens, 73 us): 295 measured; 191 vector, 33 matrix, 251 LDS, 219 of them 28 look-ups
-//     with 5.3 conflict cycles each: here the look-ups are most of the time.
-// 32 features against the streamed kernel that staged one tile at a time through registers and computed the
-// weights: B*H = 64, N = 2100 145.6 -> 73 us with tiles of 64, 202 -> 77.5 us with tiles of 128; against whole
-// sequences in LDS: B*H = 96, N = 1200 56.8 -> 39.6 us.
+// What bounds it (cycles at 2.2 GHz, per wavefront and KV tile of 64):
+//   64 features, tiny table (256 pairs of 577 tokens, tiles of 64, 26.1 -> 20.4 us): in steady state (four times the
+//     pairs) 770 cycles of a SIMD for 146 vector instructions and 8 matrix instructions of 32 cycles, during which hardly
+//     any float instruction issues; a lone wavefront takes 2300.  5 of the 20 us are the start (first loads, 2 us) and the end.
+//   64 features, tiles of 128 (384 pairs of 577, 39.1 -> 33.8 us): four wavefronts to a SIMD instead of three, as far
+//     as registers (128) and LDS (three slots, not four: 35 KiB with the table) go; then the same.
+//   32 features (64 pairs of 2100 tokens, 73.0 -> 59.7 us): LDS, 24 look-ups with 5.3 conflict cycles each, against the
+//     eight computed weights on the vector units (MIXED of process_tile).
+// 32 features against the streamed kernel that staged one tile at a time through registers and computed the weights:
+// B*H = 64, N = 2100 145.6 -> 59.7 us with tiles of 64, 202 -> 61 us with tiles of 128.
 //
-// Synchronisation: the wavefronts share the loads of a tile (1 KiB pieces, dealt round robin).
-// While tile j is computed, tile j+1 lands in the other slot; after its arithmetic a wavefront waits
-// for its own loads (vmcnt) and then for the others at a workgroup barrier, which also says that
-// everybody is done with tile j, whose slot the loads of tile j+2 may now overwrite.  Every
-// wavefront of a workgroup executes every barrier, with or without query rows of its own.
+// Synchronisation: the wavefronts share the loads of a tile (1 KiB pieces, dealt round robin), wait for their own (vmcnt)
+// and then for the others at a barrier; see QF_RING_TILE.  Every wavefront of a workgroup executes every barrier, with
+// or without query rows of its own.  (Three slots: V of a tile is requested behind the tile before it, when its place,
+// the one of that tile's K, is free; requested at the start of its own tile the last, short one waited for it.)
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -42,14 +38,15 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_ring[];
 
+template <int V> struct RingInt { static constexpr int value = V; };
+
 // Weight tables of 32 features from this size on: part of the weights is computed (MIXED of process_tile).
 constexpr int kRingMixedBytes = 7 * 1024;
 
 template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
 __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
-    constexpr int kRingTileBytes = 2 * BC * D;      // one KV tile in LDS: K (BC rows of D bytes), then V
     constexpr int kRows = 1024 / D;                 // rows of a 1 KiB piece
-    constexpr int kPieces = 2 * BC / kRows;         // pieces of a tile: K, then V
+    constexpr int kPieces = BC / kRows;             // pieces of K, or V, of a tile
     constexpr int kRowPieces = D / 16;              // 16-byte pieces of a row
     constexpr bool SB = XM == kExpTable;
     if (!QMAX) round_down();
@@ -63,7 +60,13 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, bh);
     const ExpConst c = make_exp_const<XM != kExpTable || MIXED>(hc);
-    const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
+    // (made anew where the compiler would otherwise hold, or spill, them through a tile)
+    auto lane_offsets = [&]() {
+        int l = (int)threadIdx.x & 63;
+        asm volatile("" : "+v"(l));
+        return swizzled_lane_offsets<D>(l);
+    };
+    SwizzledLane sl = lane_offsets();
 
     // ---- LDS: [weight table][slot 0][slot 1]; the dynamic LDS is the only LDS of the kernel, so the
     //      table index is its address
@@ -83,18 +86,48 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     auto lane_row = [](int l) { return l / kRowPieces; };
     auto lane_piece = [&](int l) { return ((l ^ (lane_row(l) >> 2)) & (kRowPieces - 1)) << 4; };
     const int lane_off = lane_row(lane) * D + lane_piece(lane);
-    // The 1 KiB pieces of tile j (the K blocks, then the V blocks), dealt round robin to the wavefronts.
-    auto issue_tile = [&](int j) {
-        const int slot = ring_base + kRingTileBytes * (j & 1);
-        if (BC * (j + 1) <= N) {
-            for (int x = wave; x < kPieces; x += n_waves)
-                load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, lane_off + BC * D * j + 1024 * (x % (kPieces / 2)), slot + 1024 * x);
+    // LDS slots of one tile of K or V each.  With 32 features two of K and two of V; with 64 three that change places:
+    // V of tile j + 1 goes where K of tile j was, K of tile j + 2 where V of tile j was.
+    constexpr int kSlot = BC * D;
+    constexpr bool kThree = qflash_ring_slots(D) == 3;
+    int k_slot = ring_base, v_slot = ring_base + kSlot, k_next = ring_base + 2 * kSlot, v_next = kThree ? k_slot : ring_base + 3 * kSlot;
+    auto next_slots = [&]() {
+        if (kThree) {
+            const int free = v_slot;
+            v_slot = k_slot;
+            k_slot = k_next;
+            k_next = free;
+            v_next = k_slot;
         } else {
-            int l = (int)threadIdx.x & 63;
-            asm volatile("" : "+v"(l));
-            for (int x = wave; x < kPieces; x += n_waves)
-                load_1k_to_lds(x < kPieces / 2 ? Kh : Vh, min(BC * j + kRows * (x % (kPieces / 2)) + lane_row(l), N - 1) * D + lane_piece(l), slot + 1024 * x);
+            const int k = k_slot, v = v_slot;
+            k_slot = k_next;
+            v_slot = v_next;
+            k_next = k;
+            v_next = v;
         }
+    };
+    // Requests the 1 KiB pieces of tile j, dealt round robin to the wavefronts: FROM 0 to TO 1: K, 1 to 2: V, 0 to 2: both.
+    // EDGE: the tile may reach beyond the sequence, or not exist.
+    auto request = [&](int j, int k_lds, int v_lds, auto from, auto to, auto edge) {
+        constexpr int X0 = decltype(from)::value * kPieces, X1 = decltype(to)::value * kPieces;
+        constexpr bool EDGE = decltype(edge)::value != 0;
+        [[maybe_unused]] int l = 0;
+        if (EDGE) {
+            if (j >= n_tiles) return;
+            l = (int)threadIdx.x & 63;
+            asm volatile("" : "+v"(l));
+        }
+        for (int x = X0 + wave; x < X1; x += n_waves) {
+            const bool is_k = x < kPieces;
+            const int b = is_k ? x : x - kPieces;
+            const int8_t* Th = is_k ? Kh : Vh;
+            const int lds = (is_k ? k_lds : v_lds) + 1024 * b;
+            load_1k_to_lds(Th, EDGE ? min(BC * j + kRows * b + lane_row(l), N - 1) * D + lane_piece(l) : lane_off + kSlot * j + 1024 * b, lds);
+        }
+    };
+    auto request_next = [&](int j, auto from, auto to) {
+        if (__builtin_expect(BC * (j + 1) <= N, 1)) request(j, k_next, v_next, from, to, RingInt<0>{});
+        else request(j, k_next, v_next, from, to, RingInt<1>{});
     };
 
     // ---- prologue: table (shared), first tile, this lane's query row (straight to its operand
@@ -105,7 +138,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     if (XM == kExpTable)
         for (int it = wave; it < ((hc.lut_bytes + 1023) >> 10); it += n_waves)
             load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
-    issue_tile(0);
+    request(0, k_slot, v_slot, RingInt<0>{}, RingInt<2>{}, RingInt<1>{});
     v4i qreg[D / 32];
     {
         const int8_t* Qrow = a.Q + head_off + (size_t)min(row0 + li, N - 1) * D + 16 * g;
@@ -123,80 +156,114 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     st.m = SB ? (int)((unsigned)m_init + (unsigned)kAccBias) : m_init;
 
     const int n_full = N / BC, rem = N - n_full * BC;
-#define QF_RING_COMPUTE(FULL_, FIRST_, J_, NV_, NG_, FR_)                                                          \
+    // The next tile lands while this one is computed.  Four slots: one barrier behind the tile, after every wavefront has
+    // waited for its own loads, publishes the next tile and frees the slots of this one.  Three: K of the next tile is
+    // requested ahead of this one and V behind it; a barrier between the weights and the first read of V
+    // publishes and frees the slot of K, one behind the tile frees that of V.
+    auto publish = [&]() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    int jt = 0;                                          // the tile
+    auto before_v = [&]() {
+        if (kThree) publish();
+    };
+#define QF_RING_COMPUTE(FULL_, FIRST_, NV_, NG_, FR_)                                                              \
     {                                                                                                              \
-        const int slot = ring_base + kRingTileBytes * ((J_) & 1);                                                  \
-        int k_off = sl.k_off, v_off = sl.v_off, g_ = 0;                                                            \
+        int g_ = 0;                                                                                                \
         if (!(FULL_)) {      /* (nothing of it is to be prepared ahead of the tiles) */                            \
             g_ = (int)threadIdx.x & 63;                                                                            \
-            asm volatile("; ragged tile %3" : "+v"(g_), "+v"(k_off), "+v"(v_off) : "i"(NG_) : "memory");           \
+            asm volatile("; ragged tile %1" : "+v"(g_) : "i"(NG_) : "memory");                                     \
+            sl = swizzled_lane_offsets<D>(g_);                                                                     \
             g_ >>= 5;                                                                                              \
         }                                                                                                          \
         process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_, QMAX, FR_, MIXED>(                \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,               \
-            slot + k_off, slot + BC * D + v_off);                                                                  \
+            k_slot + sl.k_off, v_slot + sl.v_off, before_v);                                                       \
     }
-#define QF_RING_TILE(FIRST_, J_, FR_)                                                                              \
+#define QF_RING_TILE(FIRST_, FR_)                                                                                  \
     {                                                                                                              \
-        if ((J_) + 1 < n_tiles) issue_tile((J_) + 1);                                                              \
-        if (active) QF_RING_COMPUTE(true, FIRST_, J_, BC, 0, FR_)                                                  \
-        if ((J_) + 1 < n_tiles) {                                                                                  \
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                                       \
+        request_next(jt + 1, RingInt<0>{}, RingInt<kThree ? 1 : 2>{});                                             \
+        if (active) QF_RING_COMPUTE(true, FIRST_, BC, 0, FR_)                                                      \
+        else before_v();                                                                                           \
+        if (kThree) {                                                                                              \
+            request_next(jt + 1, RingInt<1>{}, RingInt<2>{});                                                      \
             __syncthreads();                                                                                       \
+        } else {                                                                                                   \
+            publish();                                                                                             \
         }                                                                                                          \
+        next_slots();                                                                                              \
+        ++jt;                                                                                                      \
     }
-#define QF_RING_LAST(FIRST_, J_, NV_, NG_, FR_) { QF_RING_COMPUTE(false, FIRST_, J_, NV_, NG_, FR_) }
+#define QF_RING_LAST(FIRST_, NG_, FR_) QF_RING_COMPUTE(false, FIRST_, rem, NG_, FR_)
     constexpr bool kFloats = XM == kExpTable && !QMAX;
+    // up to this many keys, the last tile takes code for (twice) the groups there are; as many kinds of it as registers allow
+    constexpr int kPartial = D == 32 && BC == 128 ? 128 : 16;
     // (N >= BC but for 32 features and tiles of 128)
     if (D == 64 || BC == 64 || n_full > 0) {
         // wavefronts of the last workgroups give way the further they have come (qflash_plan_ring)
-        const bool even = (int)blockIdx.x >= a.ring_even_from;
-        const int p2 = even ? n_tiles / 2 : n_tiles, p1 = even ? (3 * n_tiles) / 4 : n_tiles, p0 = even ? (7 * n_tiles) / 8 : n_tiles;
+        int give_way = (int)blockIdx.x >= a.ring_even_from ? n_tiles / 2 : n_tiles;
         if (a.ring_even_from < (int)gridDim.x) __builtin_amdgcn_s_setprio(3);
-        QF_RING_TILE(true, 0, true)
-        int j = 1;
+        QF_RING_TILE(true, true)
+        sl = lane_offsets();
         // (every wavefront passes the barrier of every tile in one of the two loops)
-        for (; j < n_full && __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0; ++j) {
-            if (j == p2) __builtin_amdgcn_s_setprio(2);
-            if (j == p1) __builtin_amdgcn_s_setprio(1);
-            if (j == p0) __builtin_amdgcn_s_setprio(0);
-            QF_RING_TILE(false, j, true)
+        while (jt < n_full && __builtin_expect(__builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0, 1)) {
+            if (__builtin_expect(jt == give_way, 0)) {           // at a half, three quarters and seven eighths of the tiles
+                if (give_way == n_tiles / 2) {
+                    __builtin_amdgcn_s_setprio(2);
+                    give_way = (3 * n_tiles) / 4;
+                } else if (give_way == (3 * n_tiles) / 4) {
+                    __builtin_amdgcn_s_setprio(1);
+                    give_way = (7 * n_tiles) / 8;
+                } else {
+                    __builtin_amdgcn_s_setprio(0);
+                }
+            }
+            QF_RING_TILE(false, true)
         }
-        for (; j < n_full; ++j) QF_RING_TILE(false, j, false)
-        if (!active) return;
+        while (jt < n_full) QF_RING_TILE(false, false)
+        if (!active) {
+            if (rem > 0) before_v();
+            return;
+        }
         if (rem == 0) {
-        } else if (!kFloats || (BC == 64 && rem > 16) || __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) != 0) {
-            if (kFloats && D == 32 && __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0) QF_RING_LAST(false, n_full, rem, 0, true)
-            else QF_RING_LAST(false, n_full, rem, 0, false)
+        } else if (!kFloats || (rem > kPartial) || __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) != 0) {
+            if (kFloats && (D == 32 || BC == 128) && __builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0) QF_RING_LAST(false, 0, true)
+            else QF_RING_LAST(false, 0, false)
         } else if constexpr (kFloats) {
             const int ng = (rem + 7) >> 3;
-            if (ng == 1) QF_RING_LAST(false, n_full, rem, -1, true)
-            else if (ng == 2) QF_RING_LAST(false, n_full, rem, -2, true)
-            else if constexpr (BC == 128) {
-                if (ng <= 4) QF_RING_LAST(false, n_full, rem, -4, true)
-                else if (ng <= 8) QF_RING_LAST(false, n_full, rem, -8, true)
-                else QF_RING_LAST(false, n_full, rem, -BC / 8, true)
+            if (ng == 1) QF_RING_LAST(false, -1, true)
+            else if constexpr (kPartial >= 16) {
+                if (ng == 2) QF_RING_LAST(false, -2, true)
+                else if constexpr (kPartial == 128) {
+                if (ng <= 4) QF_RING_LAST(false, -4, true)
+                else if (ng <= 8) QF_RING_LAST(false, -8, true)
+                else QF_RING_LAST(false, -BC / 8, true)
+                }
             }
         }
     } else if constexpr (D == 32 && BC == 128) {
         if (!active) return;
-        QF_RING_LAST(true, 0, rem, 0, true)
+        QF_RING_LAST(true, 0, true)
     }
-    const int i = row0 + li;
-    if (i < N) normalise_store<D, 20, acc_offset<QMAX>()>(st, a.O + head_off + (size_t)i * D, g, a.out_round != 0);
+    int lane_ = (int)threadIdx.x & 63;              // (made anew: no register is held for it through the tiles)
+    asm volatile("" : "+v"(lane_));
+    const int i = row0 + (lane_ & 31);
+    if (i < N) normalise_store<D, 20, acc_offset<QMAX>()>(st, a.O + head_off + (size_t)i * D, lane_ >> 5, a.out_round != 0);
 #undef QF_RING_LAST
 #undef QF_RING_COMPUTE
 #undef QF_RING_TILE
 }
 
-// Wavefronts per SIMD the register allocation has to allow.  64 features: with KV tiles of 64, 5 for the
-// look-up variant (94 registers) and 4 for the others (which would spill at 96); 3 with tiles of 128 (137
-// registers; held to 128 it spills a dozen and is a sixth slower).  32 features: 5 and 4 (72 and 104
-// registers).
+// Wavefronts per SIMD the register allocation has to allow (a single spilled register costs microseconds: every
+// wavefront's scratch goes through memory).  64 features: with KV tiles of 64, 5 for the look-up variant (91 registers)
+// and 4 for the others; 4 with tiles of 128 (128 registers; three wavefronts, 137 registers: 384 pairs of 577 tokens
+// 36.6 us instead of 33.8, also because an odd number of wavefronts does not share a SIMD evenly: 5.3 cycles per integer
+// instruction with three, 4.1 with two or four).  32 features: 5 and 4 (78 and 111 registers).
 template <int D, int BC, int XM>
 constexpr int ring_min_waves() {
     if (D == 32) return BC == 128 ? 4 : 5;
-    return BC == 128 ? 3 : XM == kExpTable ? 5 : 4;
+    return BC == 128 ? (XM == kExpAuto ? 3 : 4) : XM == kExpTable ? 5 : 4;
 }
 
 // QMAX: the quantised-maximum variant (not Algorithm 1 as printed; see process_tile).

@@ -191,6 +191,9 @@ struct RowState {
     int m;              // running maximum
 };
 
+// What a kernel does ahead of the first read of the tile's V (before_v of process_tile).
+struct NothingBeforeV { __device__ __forceinline__ void operator()() const {} };
+
 // One KV tile for one wavefront.  sK: K rows of the tile (row pitch KROW), sV: V^T with the tile's
 // columns starting at column 0 (row pitch VROW).  n_valid = number of real kv rows in the tile.
 // QMAX selects the quantised-maximum variant, which is NOT Algorithm 1 as printed: RowState::m is
@@ -287,13 +290,14 @@ __device__ __forceinline__ SwizzledLane swizzled_lane_offsets(int lane) {
 // "does this group exist" then cost nothing; n_valid_rt still tells which keys of the last group exist.  NG < 0: at
 // most -NG groups and more than -NG / 2 of them; what is in LDS for keys beyond the sequence is then the last key again
 // (the maximum stays what it is), and their weights are masked.
-template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, bool FLOAT_RELEASE = false, bool MIXED = false>
+template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, bool FLOAT_RELEASE = false, bool MIXED = false,
+          class BeforeV = NothingBeforeV>
 __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, const int8_t* sK, int KROW,
                                             const int8_t* sV, int VROW, int n_valid_rt, int x_p,
                                             const int32_t* bias_row /* + c0 */,
                                             const v4i* bpre /* packed bias of this tile already in registers, or null */,
                                             const ExpConst& c, int a_mul, int li, int g,
-                                            int kx = 0, int vx = 0) {
+                                            int kx = 0, int vx = 0, BeforeV before_v = BeforeV()) {
     const v16i zb = offset_block<acc_offset<QMAX>()>();
     constexpr int KSTEPS = D / 32, TB = D / 32, KB = BC / 32;
     constexpr bool KZ = XM == kExpShift0;
@@ -569,6 +573,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
         }
     }
     __builtin_amdgcn_sched_barrier(0);
+    before_v();
     // ---- step 8: O^T += V_j^T P^T (the first tile starts the accumulators at their offset 2^30)
 #pragma unroll
     for (int t = 0; t < TB; ++t)
