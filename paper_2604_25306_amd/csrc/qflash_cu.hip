@@ -64,7 +64,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
     const int N = a.N;
     const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
-    const ExpConst c0 = make_exp_const(hc0);
+    const ExpConst c0 = make_exp_const<XM != kExpTable || PH>(hc0);
     const int n_tiles = (N + BC - 1) / BC;
     [[maybe_unused]] int tk = 3;
 
@@ -139,7 +139,8 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
             // (uniform base plus a 32-bit lane offset made here: a per-lane 64-bit pointer prepared ahead of
             // the unit loop would be held in registers across all the tile code, or spilled)
             v4i w[2];
-            normalise_words<D, 16, kAccOffset>(st, a.out_round != 0, w);
+            if (a.out_round == 0) float_normalise_words<D, kAccOffset>(st, w);
+            else normalise_words<D, 16, kAccOffset>(st, true, w);
             int8_t* Ob = a.O + (size_t)pair_of(h) * N * D;
             unsigned o_lane = (unsigned)(i * D + g * (D / 2));
             asm volatile("" : "+v"(o_lane));

@@ -263,7 +263,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
 template <int D, int BC, int XM>
 constexpr int ring_min_waves() {
     if (D == 32) return BC == 128 ? 4 : 5;
-    return BC == 128 ? (XM == kExpAuto ? 3 : 4) : XM == kExpTable ? 5 : 4;
+    return BC == 128 ? 4 : XM == kExpTable ? 5 : 4;
 }
 
 // QMAX: the quantised-maximum variant (not Algorithm 1 as printed; see process_tile).

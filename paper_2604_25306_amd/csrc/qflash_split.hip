@@ -271,18 +271,18 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
                 for (int a4 = 0; a4 < 4; ++a4) {
                     unsigned w;
                     if (XM == kExpTable) {
-                        w = pack_byte<0>((unsigned)s[kb][4 * a4], (unsigned)s[kb][4 * a4 + 1], (unsigned)s[kb][4 * a4 + 2], (unsigned)s[kb][4 * a4 + 3]);
+                        w = pack_weights((unsigned)s[kb][4 * a4], (unsigned)s[kb][4 * a4 + 1], (unsigned)s[kb][4 * a4 + 2], (unsigned)s[kb][4 * a4 + 3]);
                     } else {
                         unsigned pr[4];
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
                             const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m2, c);
-                            pr[b] = (unsigned)__mul24(y, c.p_mul_hi_v);
+                            pr[b] = (unsigned)(y * c.p_mul_hi_v);
                         }
                         w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
                     }
                     pk[kb][a4] = (int)w;
-                    rowsum = __builtin_amdgcn_sdot4((int)w, 0x01010101, rowsum, false);
+                    rowsum = add_bytes(w, rowsum);
                 }
             const HalfPair hp = both_halves(rowsum);
             rowsum = hp.x + hp.y;

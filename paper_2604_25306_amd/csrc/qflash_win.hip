@@ -85,10 +85,10 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int a4 = 0; a4 < 4; ++a4) {
-                const unsigned w = pack_byte<0>((unsigned)s[kb][4 * a4], (unsigned)s[kb][4 * a4 + 1],
+                const unsigned w = pack_weights((unsigned)s[kb][4 * a4], (unsigned)s[kb][4 * a4 + 1],
                                                 (unsigned)s[kb][4 * a4 + 2], (unsigned)s[kb][4 * a4 + 3]);
                 pk[kb][a4] = (int)w;
-                rowsum = __builtin_amdgcn_sdot4((int)w, 0x01010101, rowsum, false);
+                rowsum = add_bytes(w, rowsum);
             }
     } else {
         const int lo = m_new + c.x_floor;
@@ -101,11 +101,11 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m2, c);
-                    pr[b] = (unsigned)__mul24(y, c.p_mul_hi_v);
+                    pr[b] = (unsigned)(y * c.p_mul_hi_v);
                 }
                 const unsigned w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
                 pk[kb][a4] = (int)w;
-                rowsum = __builtin_amdgcn_sdot4((int)w, 0x01010101, rowsum, false);
+                rowsum = add_bytes(w, rowsum);
             }
     }
     RowState<D> st;
@@ -116,7 +116,7 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
     st.m = m_new;
     // ---- step 8: O^T = V^T P^T, the V^T operand read transposed from the row-major V in LDS
     {
-        v16i acc = offset_block();
+        v16i acc = offset_block<kScoreOffset0>();
         v4i va[2];
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
@@ -131,7 +131,8 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
     }
     // ---- step 11
     v4i o;
-    normalise_words<D, 16, kAccBias>(st, out_round, &o);
+    if (!out_round) float_normalise_words<D, kScoreOffset0>(st, &o);
+    else normalise_words<D, 16, kScoreOffset0>(st, true, &o);
     return o;
 }
 
@@ -187,13 +188,14 @@ __device__ __forceinline__ int win_v_lane(int lane) {
 template <int XM, bool PLAIN>
 __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     constexpr int D = 32;
+    round_down();
     const int N = a.N;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, 0);
-    const ExpConst c = make_exp_const(hc);
+    const ExpConst c = make_exp_const<XM != kExpTable>(hc);
 
     // ---- LDS: [weight table, a.win_table_lds bytes][wavefront w: two sets of V (2 KiB), K (2 KiB),
     //      Q (1 KiB)]; the dynamic LDS is the only LDS of the kernel, so the table index is its address
@@ -336,6 +338,7 @@ template <int XM>
 __device__ __forceinline__ void win_dyn_compute(const QflashKernelArgs& a, const QflashHeadConsts& hc, double unit, const WinOrder& order,
                                                 int t0, int t1, int half, int ring, int filled, int emptied) {
     constexpr int D = 32;
+    round_down();                  // (single precision only: the bias is converted in double precision)
     const int N = a.N;
     const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
     const int row = 32 * half + li;

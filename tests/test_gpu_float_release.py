@@ -1,5 +1,5 @@
-"""GPU parity where the float form of ScaleRelease meets its limit and where the last tile of the direct-load ring takes
-another variant: sums of weights that pass 65000 in the middle of a sequence (the integer form takes over), numerators
+"""GPU parity where the float form of ScaleRelease meets its limit, where the last tile of the direct-load ring takes
+another variant and where quotients of the normalisation are whole numbers: sums of weights that pass 65000 in the middle of a sequence (the integer form takes over), numerators
 beyond 2^23, and sequences with every kind of remainder."""
 import numpy as np
 import pytest
@@ -49,3 +49,23 @@ def test_last_tile_of_the_ring(gpu, d, tile, full, rem):  # noqa: F811
         for scale in (1.0, 40.0):                                # 40: coarse scores, x_shift > 0
             p = oracle.derive_params(sQ * scale, sK * scale, d, out_round=rem % 2)
             assert_same(run(gpu, 2, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "%s x%g" % (shape, scale))
+
+
+# Every value of V in turn for a whole column, so that the quotient is that integer exactly, and columns one weight above
+# and below it; equal weights (the largest denominators) and random ones; a batch per kernel.
+@pytest.mark.parametrize("kernel,B,H,N,d,tile", [
+    (4, 64, 6, 49, 32, 64), (4, 64, 6, 64, 32, 64), (3, 64, 6, 197, 64, 64), (3, 48, 6, 256, 64, 64), (3, 64, 6, 197, 64, 128),
+    (1, 200, 6, 256, 64, 64), (2, 12, 6, 257, 64, 64), (2, 12, 6, 259, 64, 128), (2, 4, 6, 700, 64, 64), (2, 30, 6, 200, 32, 64)])
+def test_whole_quotients(gpu, kernel, B, H, N, d, tile):  # noqa: F811
+    rng = np.random.default_rng(N + d)
+    shape = (B, H, N, d)
+    level = ((np.arange(B * H * d) * 3) // 2 % 256 - 128).astype(np.int64).reshape(B, H, 1, d)
+    V = np.repeat(level, N, axis=2)
+    V[:, :, N // 3, 1::3] += 1
+    V[:, :, N // 2, 2::3] -= 1
+    V = np.clip(V, -128, 127).astype(np.int8)
+    K = rng.integers(-127, 128, shape).astype(np.int8)
+    for Q in (np.zeros(shape, np.int8), rng.integers(-127, 128, shape).astype(np.int8)):
+        for out_round in (0, 1):
+            p = oracle.derive_params(0.02, 0.02, d, out_round=out_round)
+            assert_same(run(gpu, kernel, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "%s %d" % (shape, out_round))
