@@ -10,15 +10,11 @@
 
 namespace {
 
-// (a * b) >> 32.  The operands here fit 24 signed bits, but a 24-bit multiply is no faster and, like v_dot4, keeps
-// the float instructions of other wavefronts from issuing beside integer ones (see FloatRelease).
-__device__ __forceinline__ int mulhi24(int a, int b) { return __mulhi(a, b); }
-
 // Loop-invariant constants of Algorithm 2 / Eq. 10 kept in registers.
 struct ExpConst {
     int k, s_inv, x_floor;   // uniform (scalar registers)
     int M_v;                 // exp_mul, in a vector register
-    int two_s_inv_v;         // 2 * s_inv, in a vector register
+    int s_inv_v;             // s_inv, in a vector register
     int p_mul_hi_v;          // p_mul << (24 - p_shift): the requantised weight lands in byte 3
 };
 
@@ -42,27 +38,33 @@ __device__ __forceinline__ int to_vgpr(int v) {
     return r;
 }
 
+// The same from x' and x' + s_inv.  MAD: one instruction for q + 1, with a pair of registers for its result.
+template <bool MAD = true>
+__device__ __forceinline__ int shift_exp2_shifted(int xs, int xs1, const ExpConst& c) {
+    const int q1 = MAD ? (int)(((long long)xs * c.M_v + (1ll << 32)) >> 32) : __mulhi(xs, c.M_v) + 1;
+    return (int)((unsigned)(q1 * c.s_inv + xs1) >> q1);
+}
+
 // Algorithm 2 for a score t already clamped from below to (m + x_floor).
 //   x' = (t - m) << k,  q = (x' * M) >> 32,  r = x' + q * s_inv,  y = ((r >> 1) + s_inv) >> q.
 // (r >> 1) + s_inv = floor((r + 2 s_inv) / 2) and nested floors of divisions by powers of two
 // compose, so y = (r + 2 s_inv) >> (q + 1).  In the clamped range x' fits 24 bits, 0 <= q <= 28
-// and r + 2 s_inv is positive, so the logical shift is exact.
-// KZ (k == 0): x' = t - m and x' + 2 s_inv = t - (m - 2 s_inv) are two cheap subtractions.
-template <bool KZ>
-__device__ __forceinline__ int shift_exp2(int t, int m, int m2 /* m - 2 s_inv */, const ExpConst& c) {
-    int xs, xs2;
+// and r + 2 s_inv is positive, so the logical shift is exact.  One instruction makes q + 1, the upper half of
+// x' M + 2^32, and r + 2 s_inv = (q + 1) s_inv + (x' + s_inv).
+// KZ (k == 0): x' = t - m and x' + s_inv = t - (m - s_inv) are two cheap subtractions.
+template <bool KZ, bool MAD = true>
+__device__ __forceinline__ int shift_exp2(int t, int m, int m1 /* m - s_inv */, const ExpConst& c) {
+    int xs, xs1;
     if (KZ) {
         xs = t - m;
-        xs2 = t - m2;
+        xs1 = t - m1;
     } else {
         const int neg_m = -m;
         xs = t;                                      // (output tied to an input, see above)
         asm("v_add_lshl_u32 %0, %0, %1, %2" : "+v"(xs) : "v"(neg_m), "s"(c.k));
-        xs2 = xs + c.two_s_inv_v;
+        xs1 = xs + c.s_inv_v;
     }
-    const int q = mulhi24(xs, c.M_v);
-    const int r2 = q * c.s_inv + xs2;
-    return (int)((unsigned)r2 >> (q + 1));
+    return shift_exp2_shifted<MAD>(xs, xs1, c);
 }
 
 // PIN: keep the multipliers in vector registers (not where one exponential per tile is all that is computed).
@@ -71,11 +73,11 @@ __device__ __forceinline__ ExpConst make_exp_const(const QflashHeadConsts& h) {
     ExpConst c;
     c.k = h.x_shift; c.s_inv = h.s_inv; c.x_floor = h.x_floor;
     c.M_v = h.exp_mul;
-    c.two_s_inv_v = 2 * h.s_inv;
+    c.s_inv_v = h.s_inv;
     c.p_mul_hi_v = h.p_mul << (24 - h.p_shift);
     if (PIN) {
         c.M_v = to_vgpr(c.M_v);
-        c.two_s_inv_v = to_vgpr(c.two_s_inv_v);
+        c.s_inv_v = to_vgpr(c.s_inv_v);
         c.p_mul_hi_v = to_vgpr(c.p_mul_hi_v);
     }
     return c;
@@ -86,7 +88,7 @@ __device__ __forceinline__ ExpConst make_exp_const(const QflashHeadConsts& h) {
 // like x_floor itself.
 __device__ __forceinline__ unsigned table_entry(int i, int x_p, const QflashHeadConsts& h, const ExpConst& c) {
     const int x = max(i - x_p, h.x_floor);
-    const int y = shift_exp2<false>(x, 0, -2 * h.s_inv, c);
+    const int y = shift_exp2<false>(x, 0, -h.s_inv, c);
     return ((unsigned)__mul24(y, c.p_mul_hi_v)) >> 24;
 }
 

@@ -33,11 +33,10 @@
 // The element-wise integer softmax is what takes the time (about six VALU instructions per score
 // a lane handles, against 256 MFMA operations and 1.3 HBM bytes per score), so the per-element
 // path is kept short: where the constants allow it the int8 weight of a score comes from a table
-// in LDS (one saturating subtraction and one byte read); otherwise Algorithm 2 runs on the
-// 24-bit multiplier (v_mul_hi_i32_i24), leaves its int8 result in the top byte of a product, and
-// four of them are gathered with v_perm_b32.  Accumulators (and, where registers allow, scores)
-// carry an offset of 2^30 that turns the rescale into a multiply-high and an add and the table
-// index into a single subtraction.  Inline assembly never reads a register written by an MFMA:
+// in LDS (one saturating subtraction and one byte read); otherwise Algorithm 2 leaves its int8 result
+// in the top byte of a product, and four of them are gathered with v_perm_b32.  Accumulators and scores
+// carry offsets that turn the rescale into one fused multiply-add and the table index into a
+// single subtraction or multiply-add (FloatRelease, float_index).  Inline assembly never reads a register written by an MFMA:
 // the compiler only places the wait states of the matrix pipeline for reads it can see.
 #include <hip/hip_runtime.h>
 #include <stddef.h>

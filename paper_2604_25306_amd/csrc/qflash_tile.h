@@ -438,11 +438,11 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
         m_new = st.m + n_oct * c.s_inv;
     }
     const int lo = m_new + c.x_floor;
-    const int m2 = m_new - 2 * c.s_inv;
+    const int m1 = m_new - c.s_inv;
     // ---- step 4: max-offset factor alpha, brought to 16 fractional bits
     unsigned alpha16 = 0;
     if (!FIRST && !QMAX) {
-        const int a_hat = shift_exp2<KZ>(smax<SB>(st.m, lo), m_new, m2, c);
+        const int a_hat = shift_exp2<KZ, XM != kExpTable>(smax<SB>(st.m, lo), m_new, m1, c);   // (registers are short there)
         alpha16 = min(((unsigned)a_hat * (unsigned)a_mul) >> 14, 65536u);
     }
     // ---- steps 9,10 (the part that concerns the past): ScaleRelease of denominator and numerator.
@@ -511,9 +511,8 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                     if (computed(kb, a4) && grp_on(kb, a4)) {
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
-                            const int xs = (int)(((unsigned)s[kb][4 * a4 + b] << c.k) + neg_xpk), xs2 = xs + c.two_s_inv_v;
-                            const int q = mulhi24(xs, c.M_v);
-                            const int y = (int)((unsigned)(q * c.s_inv + xs2) >> (q + 1));
+                            const int xs = (int)(((unsigned)s[kb][4 * a4 + b] << c.k) + neg_xpk);
+                            const int y = shift_exp2_shifted(xs, xs + c.s_inv_v, c);
                             s[kb][4 * a4 + b] = y * c.p_mul_hi_v;
                         }
                     }
@@ -551,7 +550,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                     unsigned pr[4];
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
-                        const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m2, c);
+                        const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m1, c);
                         pr[b] = (unsigned)(y * c.p_mul_hi_v);       // Eq. 10, result in byte 3
                     }
                     const unsigned w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);

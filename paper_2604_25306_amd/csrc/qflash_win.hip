@@ -92,7 +92,7 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
             }
     } else {
         const int lo = m_new + c.x_floor;
-        const int m2 = m_new - 2 * c.s_inv;
+        const int m1 = m_new - c.s_inv;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -100,7 +100,7 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
                 unsigned pr[4];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m2, c);
+                    const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m1, c);
                     pr[b] = (unsigned)(y * c.p_mul_hi_v);
                 }
                 const unsigned w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
