@@ -20,7 +20,11 @@
 // wavefronts raise without waiting for anybody but their own loads, so every wavefront reaches its
 // exit.
 //
-// KV tiles of 128: 131 registers leave three wavefronts to a SIMD, so workgroups are at most twelve; still ahead of
+// 64 features, 768 pairs of 197 tokens: 16.9 -> 15.6 us with ScaleRelease, packing and normalisation on the float units
+// (qflash_tile.h), per head 21.7 -> 18.9.  What is left: LDS 9 us of look-ups and operand reads, vector issue 7, 3 us until
+// every wavefront has data, five units for sixteen wavefronts at the end.
+//
+// KV tiles of 128: more than 128 registers leave three wavefronts to a SIMD, so workgroups are at most twelve; still ahead of
 // the resident kernel (768 pairs of 197 tokens 22.8 -> 18.6 us, 480 of 256 19.4 -> 15.0, 720 of 130 16.8 -> 12.4).
 //
 // QF_TRACE (never defined in the library build) adds per-wavefront timestamps for timeline studies.

@@ -67,7 +67,7 @@ struct QflashKernelArgs {
     int cu_table_lds;        // LDS bytes reserved for the weight table (a multiple of 1 KiB)
     int cu_table_heads;      // per-head constants: number of heads with a table, and
     uint8_t cu_order[kQflashMaxParamHeads];   // the heads, those with a table first
-    // two-tile ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
+    // ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
     int ring_dma;
     int ring_table_lds;      // LDS bytes reserved for the weight table (a multiple of 1 KiB)
     int ring_even_from;      // workgroups from this index on give way to those behind them (qflash_plan_ring)
@@ -237,7 +237,7 @@ void qflash_plan_report(const QflashKernelArgs& args, int d, qflash_plan_info* o
 // A sequence of one KV tile gives the same result with either tile size; the smaller one's kernels need fewer registers.
 inline int qflash_effective_tile(int kv_tile, int N) { return N <= 64 ? 64 : kv_tile; }
 
-// The two-tile ring with direct global-to-LDS loads (long sequences, no bias, both Algorithm 1 and the
+// The ring with direct global-to-LDS loads (long sequences, no bias, both Algorithm 1 and the
 // quantised-maximum variant; work decomposition as for the ring of the resident kernel).
 constexpr int kRingMaxWaves = 8;
 int qflash_launch_fwd_ring(const QflashKernelArgs& args, int d, int lds_limit, void* stream);

@@ -1,5 +1,5 @@
 // gfx950 kernel of the integer-only fused attention forward pass (Algorithm 1) for long sequences
-// without a bias: the two-tile ring, fed by direct global-to-LDS loads.
+// without a bias: the ring fed by direct global-to-LDS loads.
 //
 // A workgroup of up to 8 wavefronts serves 32 query rows per wavefront of one (batch, head) pair and
 // walks over all KV tiles of the pair.  LDS holds the weight table and three (64 features) or four slots, each

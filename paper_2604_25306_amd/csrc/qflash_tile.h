@@ -49,7 +49,7 @@ __device__ __forceinline__ unsigned pack_byte(unsigned p0, unsigned p1, unsigned
 
 // ScaleRelease with alpha in 16 fractional bits, floor(x * alpha16 / 2^16), 0 <= alpha16 <= 2^16.
 //
-// Numerator accumulators are kept with an offset, y = x + 2^30 > 0 (the MFMA adds products modulo
+// Integer form.  Numerator accumulators are kept with an offset, y = x + 2^30 > 0 (the MFMA adds products modulo
 // 2^32, so the offset rides along).  With A = alpha16 << 16:
 //   mul_hi_u32(y, A) = floor((x A + 2^30 A) / 2^32) = floor(x alpha16 / 2^16) + A/4   (A is a multiple of 4)
 // so the rescaled accumulator, again offset by 2^30, is mul_hi_u32(y, A) + (2^30 - A/4): one
@@ -205,11 +205,11 @@ struct NothingBeforeV { __device__ __forceinline__ void operator()() const {} };
 // ALUs, any x_shift), kExpShift0 (the same, x_shift == 0) or kExpTable (one LDS look-up in a table
 // of the same function, see qflash_build_table).
 //
-// Offsets.  Numerator accumulators always carry +2^30 (see ReleaseConst).  In table mode without
+// Offsets.  Numerator accumulators always carry one, 2^23 (see FloatRelease; QMAX: 2^30).  In table mode without
 // bias the scores can carry it too (SB): the first MFMA of a score block starts from a
 // block of the offset instead of zeros, which costs nothing, and then
 //   table index = max(0, s - m + x_p) = (s + 2^30) -sat- (m + 2^30 - x_p)
-// is a single unsigned saturating subtraction per score (both operands are positive: |s| < 2^21);
+// is a single unsigned saturating subtraction per score (both operands are positive: |s| < 2^21; block 0: float_index);
 // RowState::m holds m + 2^30.  Algorithm 2 for alpha only sees differences, which are unchanged.
 enum { kExpShift = 0, kExpShift0 = 1, kExpTable = 2, kExpAuto = 3 };   // kExpAuto: per workgroup, table if its head has one
 // Bias of a kernel variant: none, the plain [N,N] layout, or the lane-major packed layout.
@@ -575,7 +575,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     }
     __builtin_amdgcn_sched_barrier(0);
     before_v();
-    // ---- step 8: O^T += V_j^T P^T (the first tile starts the accumulators at their offset 2^30)
+    // ---- step 8: O^T += V_j^T P^T (the first tile starts the accumulators at their offset)
 #pragma unroll
     for (int t = 0; t < TB; ++t)
 #pragma unroll
