@@ -72,7 +72,6 @@ template <int D, int BC, int BIAS, bool NARROW, int XM, bool QMAX>
 __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     constexpr int KSTEPS = D / 32;
     constexpr int KROW = D + 16;
-    if (!QMAX) round_down();
     const int N = a.N;
     const int npad = (N + 31) & ~31;
     // a.ring: LDS holds two KV tiles (the one in use and the one being staged) instead of the whole
@@ -296,6 +295,7 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     const int32_t* bias_row = nullptr;
     constexpr bool bias_packed = BIAS == kBiasPacked;
     if (BIAS) bias_row = bias_lane_base(a, bh_safe, row0, i, li, g);
+    if (!QMAX) round_down();                                  // (behind the divisions of bias_lane_base)
     constexpr bool BPRE_OK = bias_packed && D == 32 && BC == 64;
     v4i bpre[BPRE_OK ? 4 * (BC / 32) : 1];
     if (BPRE_OK) {
@@ -453,7 +453,6 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
     constexpr int VROW = BC + 16;
     __shared__ __align__(16) int8_t sK[BC * KROW];
     __shared__ __align__(16) int8_t sV[D * VROW];
-    if (!QMAX) round_down();
 
     const int wg = blockIdx.x;
     const int unit = qflash_unit_of_workgroup(wg, a.units_per_xcd, a.xcd_period);
@@ -476,6 +475,7 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
     const int32_t* bias_row = nullptr;
     constexpr bool bias_packed = BIAS == kBiasPacked;
     if (BIAS) bias_row = bias_lane_base(a, bh, row0, i, li, g);
+    if (!QMAX) round_down();                                  // (behind the divisions of bias_lane_base)
     v4i qreg[KSTEPS];
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {

@@ -87,8 +87,11 @@ __device__ __forceinline__ int release_l(int l, const ReleaseConst& r) { return 
 // sixteen), which is why neither is used in the loop over the tiles.
 constexpr int kAccOffset = 1 << 23;
 constexpr int kFloatReleaseMaxL = 65000;
-// (After the scales of a dynamic call: those round to nearest.  Integer divisions, which the compiler makes of v_rcp and
-// products of floats, only get smaller first guesses, corrected as ever: their divisors are below 2^24.)
+// The rest of a kernel behind this call rounds single precision down.  Ahead of it: the scales of a dynamic call, which
+// round to nearest, and integer divisions by numbers that may exceed 2^24 (bias_lane_base: heads and bias extents of
+// one-token sequences).  The compiler makes a division of v_rcp and products of floats and relies on a first guess that
+// is not too large; a divisor cut down to 24 bits makes it larger.  Behind it divisors are small, exact as floats, and
+// rounding down only makes the guess smaller, corrected as ever.
 __device__ __forceinline__ void round_down() { __builtin_amdgcn_s_setreg(1 | (0 << 6) | (1 << 11), 2); }   // MODE.round, single precision
 struct FloatRelease { float alpha, add; };
 __device__ __forceinline__ FloatRelease make_float_release(unsigned alpha16) {
@@ -782,7 +785,9 @@ static_assert(offsetof(QflashHeadConsts, x_floor) == 24 && offsetof(QflashHeadCo
 __device__ __forceinline__ const int32_t* bias_lane_base(const QflashKernelArgs& a, int bh, int row0, int i,
                                                         int li, int g) {
     const int b = bh / a.H, h = bh % a.H, N = a.N;
-    const size_t slice = (size_t)(b % a.bias_B) * a.bias_H + (size_t)(h % a.bias_H);
+    const unsigned slice32 = (unsigned)(b % a.bias_B) * (unsigned)a.bias_H + (unsigned)(h % a.bias_H);   // (below 2^31)
+    asm volatile("" :: "s"(slice32));                     // (made here, ahead of a change of the rounding mode: round_down)
+    const size_t slice = slice32;
     if (a.bias_packed) {
         const int nb = (N + 31) / 32;
         return a.bias + ((slice * nb + (size_t)min(row0 / 32, nb - 1)) * nb) * 1024 + 4 * (32 * g + li);
