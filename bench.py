@@ -39,7 +39,7 @@ PEAK_ALU_TOPS = CUS * LANES_PER_CU_CLK * CLOCK_GHZ / 1000.0    # 39.3 T integer 
 ALU_OPS_PER_SCORE = 14.0         # algorithmic integer lane-operations per score element (the paper's steps)
 LLC_BYTES = 256 << 20
 KERNEL_SOURCES = ["qflash_kernels.hip", "qflash_split.hip", "qflash_resident.h", "qflash_cu.hip", "qflash_win.hip", "qflash_ring.hip", "qflash_qmax.hip",
-                  "qflash_tile.h", "qflash_device.h", "qflash_launch.h", "qflash_internal.h", "qflash_dynamic.hip", "qflash_api.cpp",
+                  "qflash_tile.h", "qflash_float_units.h", "qflash_device.h", "qflash_launch.h", "qflash_internal.h", "qflash_dynamic.hip", "qflash_api.cpp",
                   "qflash_plan.cpp", "qflash_derive.h", "qflash_derive_device.h", "qflash_counters.h"]
 
 

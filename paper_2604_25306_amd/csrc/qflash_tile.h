@@ -9,16 +9,13 @@
 
 #include "qflash_internal.h"
 #include "qflash_device.h"
+#include "qflash_float_units.h"
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 namespace {
-
-constexpr int kNegBig = -(1 << 30);   // stands for "excluded": far below any clamp point (so is
-                                      // anything a saturating add of INT32_MIN produces)
-constexpr int kMInit = -(1 << 21);    // initial running maximum (Algorithm 1)
 
 // ------------------------------------------------------------------ scalar building blocks
 
@@ -47,71 +44,17 @@ __device__ __forceinline__ unsigned pack_byte(unsigned p0, unsigned p1, unsigned
     return __builtin_amdgcn_perm(p3, w, (h << 24) | 0x020100u);
 }
 
-// ScaleRelease with alpha in 16 fractional bits, floor(x * alpha16 / 2^16), 0 <= alpha16 <= 2^16.
-//
-// Integer form.  Numerator accumulators are kept with an offset, y = x + 2^30 > 0 (the MFMA adds products modulo
-// 2^32, so the offset rides along).  With A = alpha16 << 16:
-//   mul_hi_u32(y, A) = floor((x A + 2^30 A) / 2^32) = floor(x alpha16 / 2^16) + A/4   (A is a multiple of 4)
-// so the rescaled accumulator, again offset by 2^30, is mul_hi_u32(y, A) + (2^30 - A/4): one
-// multiply-high and one add, no shift.  alpha16 = 2^16 (identity) does not fit A; there
-// A = 2^32 - 1 gives mul_hi_u32(y, A) = y - 1 for every 1 <= y < 2^32, and the addend is 1.
-// (|x| < 2^26 always.)  The offset is 2^30 because that bit pattern (the float 2.0) is an inline
-// constant of the instruction set: a matrix instruction can start from a block of it without a
-// single register being set aside for it.
-struct ReleaseConst {
-    unsigned A, C;       // accumulator: y <- mul_hi_u32(y, A) + C
-    int alpha14;         // alpha16 << 14, for the (unbiased, non-negative) denominator
-};
-__device__ __forceinline__ ReleaseConst make_release(unsigned alpha16) {
-    ReleaseConst r;
-    const unsigned one = alpha16 >> 16;   // 1 only for the identity
-    r.A = (alpha16 << 16) - one;
-    r.C = 0x40000000u - (alpha16 << 14) + one;
-    r.alpha14 = (int)(alpha16 << 14);
-    return r;
-}
-__device__ __forceinline__ int release_acc(int y, const ReleaseConst& r) { return (int)(__umulhi((unsigned)y, r.A) + r.C); }
-// Denominator: 0 <= l < 2^20, floor(l * alpha16 / 2^16) = ((l << 2) * (alpha16 << 14)) >> 32.
-__device__ __forceinline__ int release_l(int l, const ReleaseConst& r) { return __mulhi(l << 2, r.alpha14); }
-
-// The same for accumulators offset by 2^23 (kAccOffset), in one instruction: seen as a float, an integer below
-// 2^24 is that many units of 2^-149, denormal or not, so that a fused multiply-add that rounds toward minus
-// infinity (round_down) is floor(x alpha16 / 2^16) + 2^23, y = x + 2^23, with the addend 2^23 - 2^7 alpha16, as
-// long as -2^23 <= x < 2^23.  |x| <= 128 l + 129 per tile, so l < 65000 (kFloatReleaseMaxL) keeps it there; always
-// where N <= 256.  Beyond it the integer form above takes over, between two changes of offset.
-//
-// Why floats: of the vector units of a SIMD, one instruction in four cycles is all that integer work gets
-// (4.1 cycles measured with four wavefronts for any mix of multiplies, maxima, permutes, subtractions), but
-// fused multiply-adds issue beside it (2.2 to 2.4 cycles per instruction for a mix of half and half).  A
-// v_dot4 or a 24-bit multiply among them stops that for some forty instructions (4.1 cycles with one in
-// sixteen), which is why neither is used in the loop over the tiles.
-constexpr int kAccOffset = 1 << 23;
-constexpr int kFloatReleaseMaxL = 65000;
 // The rest of a kernel behind this call rounds single precision down.  Ahead of it: the scales of a dynamic call, which
 // round to nearest, and integer divisions by numbers that may exceed 2^24 (bias_lane_base: heads and bias extents of
 // one-token sequences).  The compiler makes a division of v_rcp and products of floats and relies on a first guess that
 // is not too large; a divisor cut down to 24 bits makes it larger.  Behind it divisors are small, exact as floats, and
 // rounding down only makes the guess smaller, corrected as ever.
 __device__ __forceinline__ void round_down() { __builtin_amdgcn_s_setreg(1 | (0 << 6) | (1 << 11), 2); }   // MODE.round, single precision
-struct FloatRelease { float alpha, add; };
-__device__ __forceinline__ FloatRelease make_float_release(unsigned alpha16) {
-    return FloatRelease{(float)alpha16 * 0x1p-16f, __int_as_float(kAccOffset - (int)(alpha16 << 7))};
-}
-__device__ __forceinline__ int release_acc(int y, const FloatRelease& r) { return __float_as_int(__builtin_fmaf(__int_as_float(y), r.alpha, r.add)); }
-__device__ __forceinline__ int release_l(int l, const FloatRelease& r) { return __float_as_int(__int_as_float(l) * r.alpha); }
-
-// Four weights below 128, one to a register, to the bytes of one: the first three as floats (integers below 2^24,
-// exact in any rounding), see above.
-__device__ __forceinline__ unsigned pack_weights(unsigned p0, unsigned p1, unsigned p2, unsigned p3) {
-    const float w = __builtin_fmaf(__builtin_fmaf(__uint_as_float(p2), 256.0f, __uint_as_float(p1)), 256.0f, __uint_as_float(p0));
-    return (p3 << 24) | __float_as_uint(w);
-}
 // Mask of the first n bytes (n <= 0: none, n >= 4: all).
 __device__ __forceinline__ unsigned first_bytes(int n) { return (unsigned)(0xffffffffull >> (8 * (4 - min(max(n, 0), 4)))); }
 // Sum of the four bytes of w, added to sum.
 __device__ __forceinline__ int add_bytes(unsigned w, int sum) { return (int)__builtin_amdgcn_sad_u8(w, 0u, (unsigned)sum); }
 
-constexpr int kAccBias = 0x40000000;   // offset carried by biased scores, and by the numerator accumulators of QMAX
 // A result block full of the offset (the compiler turns it into the inline constant).
 template <int OFFSET = kAccBias>
 __device__ __forceinline__ v16i offset_block() {
@@ -119,29 +62,6 @@ __device__ __forceinline__ v16i offset_block() {
 #pragma unroll
     for (int v = 0; v < 16; ++v) z[v] = OFFSET;
     return z;
-}
-// Offset of the biased scores of 32-key block kb of a tile, relative to kAccBias.  A matrix
-// instruction takes a constant as its addend only if the constant is one of the few the instruction
-// set has built in (here the bit patterns of 1 / (2 pi), 2.0, 4.0 and 1.0) and, with this compiler, only if no other
-// instruction shares it; a block of sixteen registers filled with the constant costs eight vector and
-// sixteen scalar instructions per tile otherwise.  So each block of a tile gets a constant of its own, and the
-// two places that compare scores across blocks (the row maximum, the table index) take the difference out again.
-// Block 0 has the only one of them around which 2^21 integers either way lie in one binade, [1/8, 1/4): its scores
-// are floats 2^-26 apart, and a fused multiply-add makes the table index of them (float_index).
-constexpr int kScoreOffset0 = 0x3E22F983;
-__device__ __forceinline__ constexpr int score_offset_delta(int kb) {
-    return kb == 0 ? kScoreOffset0 - kAccBias : kb == 1 ? 0 : kb == 2 ? (1 << 23) : -(1 << 23);
-}
-// A key beyond the sequence, as a biased score at the common offset: below every real score and every table edge
-// (which are at least -2^21 - 40960), and still in the binade of block 0.
-constexpr int kMaskedBiased = kAccBias - (kScoreOffset0 - 0x3E000000);
-// max(0, s - edge) for a score s of block 0 and the edge -- the score of table index 0 -- at the common offset:
-// s 2^-123 is s - 0x3E000000 + 2^23 units of 2^-149, and so is the addend; the clamp to [0, 1] is the maximum.
-__device__ __forceinline__ float index_addend(unsigned edge) {
-    return __uint_as_float(edge + ((unsigned)score_offset_delta(0) - 0x3E000000u + 0x800000u + 0x80000000u));
-}
-__device__ __forceinline__ unsigned float_index(int s, float scale /* 2^-123 */, float addend) {
-    return __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf(__int_as_float(s), scale, addend), 0.0f, 1.0f));
 }
 template <int KBI>
 __device__ __forceinline__ v16i score_offset_block() {
@@ -387,8 +307,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                         const int bv = beyond ? INT32_MIN : bias_row[col];
                         val = __builtin_elementwise_add_sat(val, bv);
                     } else if (beyond) {
-                        // below every real score in either representation (biased: 2^24 at the
-                        // common offset, so that taking the block's own offset out cannot wrap)
+                        // below every real score in either representation
                         val = SB ? kMaskedBiased + score_offset_delta(kb) : kNegBig;
                     }
                     s[kb][4 * a4 + b] = val;
@@ -485,7 +404,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
         //      or below -x_p (excluded scores included).
         const unsigned x_p_v = (unsigned)to_vgpr(x_p);
         const unsigned edge = (unsigned)m_new - x_p_v;       // score_biased: m + 2^30 - x_p > 0
-        const float addend0 = index_addend(edge), scale0 = __int_as_float(to_vgpr(0x02000000));   // 2^-123
+        const float addend0 = index_addend(edge), scale0 = __int_as_float(to_vgpr((int)kIndexScale));
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
             const unsigned edge_kb = edge + (unsigned)score_offset_delta(kb);   // (the block's own offset)
@@ -667,24 +586,14 @@ __device__ __forceinline__ void normalise_words(const RowState<D>& st, bool roun
         out[q] = v4i{(int)ev[2 * q], (int)od[2 * q], (int)ev[2 * q + 1], (int)od[2 * q + 1]};
 }
 
-// The same (rounding down, denominators up to kFloatNormaliseMaxL) with floats: three instructions per element, two of
-// which issue beside integer ones, instead of nearly four, and no Newton iteration: 768 pairs of 197 tokens 16.1 -> 15.6 us,
-// 256 of 577 20.4 -> 19.7, windows (12288 pairs of 49) 19.2 -> 17.9.  x / l + 128 is taken as (x + 1/2) R + 128 with R = v_rcp(l), at
-// most 1.49 2^-24 off in relative terms (enumerated up to 2^20): (x + 1/2) / l is at least 1 / (2 l) from any integer,
-// and where it matters, |x / l| <= 128, off by less than 128 * 1.5 * 2^-24 < 1 / (2 * 32768).  v_cvt_pk_u8_f32 floors, saturates to
-// [0, 255] and packs.  OFFSET kAccOffset: y = x + 2^23 as a float is (x + 2^23) 2^-149, so y 2^126 - (1 - 2^-24) is (x + 1/2) 2^-23.
-// OFFSET kScoreOffset0 (one KV tile of at most 64 keys: |x| < 2^20, l <= 8128): y is (x + 10680707) 2^-26 and the half goes to the
-// addend, 128 + 1 / (2 l) rounded down to a multiple of 2^-16 < 1 / (4 l).
-constexpr int kFloatNormaliseMaxL = 32768;
+// The same (rounding down, denominators up to kFloatNormaliseMaxL) with floats, see FloatQuotient: three instructions per element,
+// two of which issue beside integer ones, instead of nearly four, and no Newton iteration: 768 pairs of 197 tokens 16.1 -> 15.6 us,
+// 256 of 577 20.4 -> 19.7, windows (12288 pairs of 49) 19.2 -> 17.9.  v_cvt_pk_u8_f32 floors, saturates to [0, 255] and packs.
 template <int D, int OFFSET>
 __device__ __forceinline__ void float_normalise_words(const RowState<D>& st, v4i* out) {
     constexpr int TB = D / 32, HALF = 2 * TB;
-    static_assert(OFFSET == kAccOffset || OFFSET == kScoreOffset0, "the offsets whose bits are evenly spaced floats");
-    const float r = st.l == 0 ? 0.0f : __builtin_amdgcn_rcpf((float)st.l);        // (no key: 128 -> output 0)
-    const float R = r * 0x1p23f;
-    const float c = OFFSET == kAccOffset ? 128.0f : __builtin_fmaf(r, 0.5f, 128.0f);
-    const float scale = __int_as_float(to_vgpr(OFFSET == kAccOffset ? 0x7e800000 /* 2^126 */ : 0x41000000 /* 8 */));
-    constexpr float base = OFFSET == kAccOffset ? -1.0f + 0x1p-24f : -10680707.0f * 0x1p-23f;
+    const FloatQuotient<OFFSET> quotient(st.l == 0 ? 0.0f : __builtin_amdgcn_rcpf((float)st.l));
+    const float scale = __int_as_float(to_vgpr((int)FloatQuotient<OFFSET>::kScale));
     unsigned word[4 * TB];
 #pragma unroll
     for (int t = 0; t < TB; ++t)
@@ -692,10 +601,7 @@ __device__ __forceinline__ void float_normalise_words(const RowState<D>& st, v4i
         for (int a4 = 0; a4 < 4; ++a4) {
             unsigned w = 0;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const float x = __builtin_fmaf(__int_as_float(st.acc[t][4 * a4 + b]), scale, base);
-                w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(x, R, c), b, w);
-            }
+            for (int b = 0; b < 4; ++b) w = __builtin_amdgcn_cvt_pk_u8_f32(quotient(st.acc[t][4 * a4 + b], scale), b, w);
             word[4 * t + a4] = w ^ 0x80808080u;
         }
 #pragma unroll
