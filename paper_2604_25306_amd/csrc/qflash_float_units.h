@@ -104,13 +104,13 @@ QF_UNIT_HD inline unsigned float_index(int s, float scale /* kIndexScale */, flo
 }
 
 // Normalisation with floats, floor(x / l) + 128 before the saturation to a byte, for l <= kFloatNormaliseMaxL:
-// (x + 1/2) R + 128 rounded down, with R = v_rcp(l), at most 1.49 2^-24 off in relative terms (enumerated up to 2^20):
-// (x + 1/2) / l is at least 1 / (2 l) from any integer, and where it matters, |x / l| <= 128, off by less than
-// 128 * 1.5 * 2^-24 < 1 / (2 * 32768).
+// (x + 1/2) R + 128 rounded down, with R = v_rcp(l).  (x + 1/2) / l is at least 1 / (2 l) from any integer, and where it
+// matters, |x / l| <= 128, off by 128 2^-23 at most if v_rcp is off by one unit in the last place at most, which is what
+// the instruction promises: less than 1 / (2 l) for l < 32768.  The limit is the largest l of 256 keys.
 // OFFSET kAccOffset: y = x + 2^23 as a float is (x + 2^23) 2^-149, so y 2^126 - (1 - 2^-24) is (x + 1/2) 2^-23.
 // OFFSET kScoreOffset0 (one KV tile of at most 64 keys: |x| < 2^20, l <= 8128): y is (x + 10680707) 2^-26 and the half goes
 // to the addend, 128 + 1 / (2 l) rounded down to a multiple of 2^-16: both errors together stay below 1 / (2 l).
-constexpr int kFloatNormaliseMaxL = 32768;
+constexpr int kFloatNormaliseMaxL = 127 * 256;
 template <int OFFSET>
 struct FloatQuotient {
     static_assert(OFFSET == kAccOffset || OFFSET == kScoreOffset0, "the offsets whose bits are evenly spaced floats");

@@ -190,6 +190,9 @@ def reciprocals(l):
 def test_normalisation(units, window):
     """floor(x / l) saturated, for every l the float form is used for and every reciprocal within one unit in the last place,
     at every whole quotient and one off it, and at the largest numerators."""
+    # a reciprocal off by 2^-23 moves a quotient of 128 by less than its distance from an integer, 1 / (2 l); sequences of
+    # 256 keys are never tested for the limit
+    assert 127 * 256 <= units.normalise_max_l and 2 * units.normalise_max_l * 128 < 1 << 23
     l = np.arange(1, (64 * 127 if window else units.normalise_max_l) + 1, dtype=np.int64)
     top = (1 << 20) - 1 if window else units.acc_offset - 1
     for k in [-129, -128, -127, -126, -65, -64, -63, -33, -2, -1, 0, 1, 2, 31, 63, 64, 65, 95, 125, 126, 127, 128, 129]:
