@@ -68,7 +68,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
     const int N = a.N;
     const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
     const SwizzledLane sl = swizzled_lane_offsets<D>(lane);
-    const ExpConst c0 = make_exp_const<XM != kExpTable || PH>(hc0);
+    const ExpConst<> c0 = make_exp_const<XM != kExpTable || PH>(hc0);
     const int n_tiles = (N + BC - 1) / BC;
     [[maybe_unused]] int tk = 3;
 
@@ -93,7 +93,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
         st.l = 0;
         v4i qreg[2];
         const QflashHeadConsts hc = PH ? head_consts(a, head_of(h)) : hc0;
-        const ExpConst c = PH ? make_exp_const(hc) : c0;
+        const ExpConst<> c = PH ? make_exp_const(hc) : c0;
 #define QF_TILE(FULL_, FIRST_, J_, NV_, NG_)                                                               \
         ready(h, J_, FIRST_, first_unit);                                                                  \
         if (FIRST_) QF_T(tk);                                                                              \
@@ -101,7 +101,7 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
             _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                  \
                 qreg[s] = *(lds_v4i*)(size_t)(Qb + row0 * D + (sl.k_off ^ (32 * s)));                      \
         }                                                                                                  \
-        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_, false, true>(                          \
+        process_tile<D, BC, kBiasNone, UM, UM == kExpTable, FULL_, FIRST_, kLaySwizzled, NG_, false, kReleaseFloat>(                 \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,      \
             Kb + D * BC * (J_) + sl.k_off, Vb + D * BC * (J_) + sl.v_off);                                 \
         if (tk == 6) QF_T(9 + (J_))

@@ -134,7 +134,7 @@ __device__ __forceinline__ double unit_from_lds(int hc_base) {
 }
 // Share `part` of `parts` wavefronts in the weight table of hc, at LDS address lds0.
 __device__ __forceinline__ void table_to_lds(const QflashHeadConsts& hc, int lds0, int part, int parts) {
-    const ExpConst c = make_exp_const(hc);
+    const ExpConst<> c = make_exp_const(hc);
     for (int i = 4 * (64 * part + (int)(threadIdx.x & 63)); i < hc.lut_bytes; i += 4 * 64 * parts) {
         unsigned w = 0;
 #pragma unroll

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kDynThreads) void qflash_dyn_quantize(const float* 
         __syncthreads();
         if (sh_hc.lut_bytes > 0) {
             const QflashHeadConsts h = sh_hc;
-            const ExpConst c = make_exp_const(h);
+            const ExpConst<> c = make_exp_const(h);
             for (int i = part * kDynThreads + (int)threadIdx.x; i < h.lut_bytes; i += parts * kDynThreads)
                 table[i] = (uint8_t)(i <= h.lut_xp ? table_entry(i, h.lut_xp, h, c) : 0u);
         }

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void qflash_build_table(uint8_t* tbl, int n, i
                                                           const QflashHeadConsts a) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n_padded) return;
-    const ExpConst c = make_exp_const(a);
+    const ExpConst<> c = make_exp_const(a);
     tbl[i] = (uint8_t)(i < n ? table_entry(i, x_p, a, c) : 0u);
 }
 

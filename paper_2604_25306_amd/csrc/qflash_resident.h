@@ -68,10 +68,22 @@ extern __shared__ __align__(16) int8_t smem[];
 template <bool NARROW>
 constexpr int resident_max_waves() { return NARROW ? kResidentMaxWavesNarrow : kResidentMaxWavesWide; }
 
+// The float form of ScaleRelease where a sequence cannot leave its range (kFloatReleaseMaxL).
+template <bool NARROW, bool QMAX>
+constexpr int resident_release() { return NARROW && !QMAX ? kReleaseFloat : kReleaseInt; }
+
+// Computed weights with 24-bit multiplies (ExpConst), by measurement (us, 24 and 32 bits): 64 features, 96 pairs of 577 tokens
+// with a packed bias, tiles of 64 47.1 and 53.8, of 128 37.2 and 39.5; 32 features, 192 pairs of 400 24.2 and 23.4.  Table modes,
+// which compute one exponential per row and tile: plain bias, tiles of 64 57.2 and 53.9.  Without a bias (quantised maximum,
+// 768 pairs of 197) 24.0 and 23.2.
+template <int D, int BIAS, bool NARROW, int XM>
+constexpr bool resident_mul24() { return D == 64 && BIAS != kBiasNone && !NARROW && XM != kExpTable; }
+
 template <int D, int BC, int BIAS, bool NARROW, int XM, bool QMAX>
 __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     constexpr int KSTEPS = D / 32;
     constexpr int KROW = D + 16;
+    constexpr int RELEASE = resident_release<NARROW, QMAX>();
     const int N = a.N;
     const int npad = (N + 31) & ~31;
     // a.ring: LDS holds two KV tiles (the one in use and the one being staged) instead of the whole
@@ -295,7 +307,7 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     const int32_t* bias_row = nullptr;
     constexpr bool bias_packed = BIAS == kBiasPacked;
     if (BIAS) bias_row = bias_lane_base(a, bh_safe, row0, i, li, g);
-    if (!QMAX) round_down();                                  // (behind the divisions of bias_lane_base)
+    if (RELEASE == kReleaseFloat) round_down();               // (behind the divisions of bias_lane_base)
     constexpr bool BPRE_OK = bias_packed && D == 32 && BC == 64;
     v4i bpre[BPRE_OK ? 4 * (BC / 32) : 1];
     if (BPRE_OK) {
@@ -304,7 +316,7 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
             if (32 * (q / 4) < N) bpre[q] = *(const v4i*)(bias_row + q * 256);
     }
     // ---- loop-invariant registers, set up before any K/V tile is in flight
-    const ExpConst c = make_exp_const(hc);
+    const auto c = make_exp_const<true, resident_mul24<D, BIAS, NARROW, XM>()>(hc);
     constexpr bool SB = score_biased<D, BC, BIAS, NARROW, XM>();
     RowState<D> st;
     st.l = 0;
@@ -366,7 +378,7 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     const bool ragged_as_full = bias_packed && rem > BC - 32;
 #define QF_TILE(FULL_, FIRST_, J_, NV_)                                                                      \
     if (active)                                                                                              \
-    process_tile<D, BC, BIAS, XM, SB, FULL_, FIRST_, kLayPadded, 0, QMAX, NARROW>(st, qreg,                                               \
+    process_tile<D, BC, BIAS, XM, SB, FULL_, FIRST_, kLayPadded, 0, QMAX, RELEASE>(st, qreg,                                              \
                                                      sK + (size_t)(ring ? (J_) & 1 : (J_)) * BC * KROW, KROW, \
                                                      ring ? sV + (size_t)((J_) & 1) * D * VROW : sV + (J_) * BC, \
                                                      VROW, NV_, hc.lut_xp,                                   \
@@ -406,8 +418,8 @@ __device__ __forceinline__ void resident_body(const QflashKernelArgs& a) {
     if (!active) return;
     if (i >= N) return;
     int8_t* Orow = a.O + head_off + (size_t)i * D;
-    if (NARROW) normalise_store<D, 16, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
-    else normalise_store<D, 20, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
+    if (NARROW) normalise_store<D, 16, acc_offset<RELEASE>()>(st, Orow, g, a.out_round != 0);
+    else normalise_store<D, 20, acc_offset<RELEASE>()>(st, Orow, g, a.out_round != 0);
 }
 
 // Wavefronts per SIMD the register allocation has to allow.  Short sequences (NARROW): 4, and 6
@@ -447,7 +459,6 @@ constexpr int kStreamThreads = kStreamWaves * 64;
 
 template <int D, int BC, int BIAS, bool QMAX>
 __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const QflashKernelArgs a) {
-    constexpr bool NARROW = false;   // long sequences only
     constexpr int KSTEPS = D / 32;
     constexpr int KROW = D + 16;
     constexpr int VROW = BC + 16;
@@ -475,7 +486,6 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
     const int32_t* bias_row = nullptr;
     constexpr bool bias_packed = BIAS == kBiasPacked;
     if (BIAS) bias_row = bias_lane_base(a, bh, row0, i, li, g);
-    if (!QMAX) round_down();                                  // (behind the divisions of bias_lane_base)
     v4i qreg[KSTEPS];
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {
@@ -483,7 +493,7 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
         if (i < N) qreg[s] = *(const v4i*)(Qh + (size_t)i * D + 32 * s + 16 * g);
     }
     const QflashHeadConsts hc = head_consts(a, bh);
-    const ExpConst c = make_exp_const(hc);
+    const auto c = make_exp_const<true, true>(hc);
     RowState<D> st;
     st.l = 0;
     st.m = QMAX ? qmax_initial_reference(hc.s_inv, hc.a_mul) : kMInit;
@@ -515,8 +525,7 @@ __global__ __launch_bounds__(kStreamThreads) void qflash_fwd_stream(const Qflash
     }
     if (!wave_active || i >= N) return;
     int8_t* Orow = a.O + head_off + (size_t)i * D;
-    if (NARROW) normalise_store<D, 16, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
-    else normalise_store<D, 20, acc_offset<QMAX>()>(st, Orow, g, a.out_round != 0);
+    normalise_store<D, 20, acc_offset<kReleaseInt>()>(st, Orow, g, a.out_round != 0);
 }
 
 // ------------------------------------------------------------------------------ launchers

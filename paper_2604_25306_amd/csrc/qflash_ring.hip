@@ -38,6 +38,10 @@ namespace {
 
 extern __shared__ __align__(1024) int8_t smem_ring[];
 
+// ScaleRelease: the float form, and beyond its range the integer form on the same accumulators.
+template <bool QMAX>
+constexpr int ring_release(bool in_range) { return QMAX ? kReleaseInt : in_range ? kReleaseFloat : kReleaseMoved; }
+
 template <int V> struct RingInt { static constexpr int value = V; };
 
 // Weight tables of 32 features from this size on: part of the weights is computed (MIXED of process_tile).
@@ -59,7 +63,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, bh);
-    const ExpConst c = make_exp_const<XM != kExpTable || MIXED>(hc);
+    const auto c = make_exp_const<XM != kExpTable || MIXED>(hc);
     // (made anew where the compiler would otherwise hold, or spill, them through a tile)
     auto lane_offsets = [&]() {
         int l = (int)threadIdx.x & 63;
@@ -177,7 +181,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
             sl = swizzled_lane_offsets<D>(g_);                                                                     \
             g_ >>= 5;                                                                                              \
         }                                                                                                          \
-        process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_, QMAX, FR_, MIXED>(                \
+        process_tile<D, BC, kBiasNone, XM, SB, FULL_, FIRST_, kLaySwizzled, NG_, QMAX, ring_release<QMAX>(FR_), MIXED>( \
             st, qreg, nullptr, 0, nullptr, 0, NV_, hc.lut_xp, nullptr, nullptr, c, hc.a_mul, li, g_,               \
             k_slot + sl.k_off, v_slot + sl.v_off, before_v);                                                       \
     }
@@ -249,7 +253,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     int lane_ = (int)threadIdx.x & 63;              // (made anew: no register is held for it through the tiles)
     asm volatile("" : "+v"(lane_));
     const int i = row0 + (lane_ & 31);
-    if (i < N) normalise_store<D, 20, acc_offset<QMAX>()>(st, a.O + head_off + (size_t)i * D, lane_ >> 5, a.out_round != 0);
+    if (i < N) normalise_store<D, 20, acc_offset<ring_release<QMAX>(true)>()>(st, a.O + head_off + (size_t)i * D, lane_ >> 5, a.out_round != 0);
 #undef QF_RING_LAST
 #undef QF_RING_COMPUTE
 #undef QF_RING_TILE

@@ -115,7 +115,7 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
         load_v(KB * wave);
     }
     const QflashHeadConsts hc = head_consts(a, bh);
-    const ExpConst c = make_exp_const(hc);
+    const ExpConst<> c = make_exp_const(hc);
     // ---- LDS: [weight table][one part per wavefront: V, then its part of P V][row maxima][row sums][alpha];
     //      the dynamic LDS is the only LDS of the kernel, so the table index is its address
     const int lds0 = (int)(size_t)(lds_void)smem_split;
@@ -248,10 +248,10 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
         if (active) {
             store_v();
             if (more) load_v(blk + KB * W);
-            const int lo = m_new + c.x_floor, m1 = m_new - c.s_inv;
+            const int lo = m_new + c.x_floor, ml = m_new - c.lead;
             // ---- step 4 (one wavefront per tile)
             if (wave % WPT == 0) {
-                const int a_hat = shift_exp2<KZ>(max(m_old, lo), m_new, m1, c);
+                const int a_hat = shift_exp2<KZ>(max(m_old, lo), m_new, ml, c);
                 if (g == 0) alphas[li * kRowPitch + t_mine] = (int)min(((unsigned)a_hat * (unsigned)hc.a_mul) >> 14, 65536u);
             }
             // ---- steps 5 to 7
@@ -276,8 +276,8 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
                         unsigned pr[4];
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
-                            const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m1, c);
-                            pr[b] = (unsigned)(y * c.p_mul_hi_v);
+                            const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, ml, c);
+                            pr[b] = c.weight(y);
                         }
                         w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
                     }

@@ -128,7 +128,7 @@ struct NothingBeforeV { __device__ __forceinline__ void operator()() const {} };
 // ALUs, any x_shift), kExpShift0 (the same, x_shift == 0) or kExpTable (one LDS look-up in a table
 // of the same function, see qflash_build_table).
 //
-// Offsets.  Numerator accumulators always carry one, 2^23 (see FloatRelease; QMAX: 2^30).  In table mode without
+// Offsets.  Numerator accumulators always carry one, which depends on how they are rescaled (kRelease...).  In table mode without
 // bias the scores can carry it too (SB): the first MFMA of a score block starts from a
 // block of the offset instead of zeros, which costs nothing, and then
 //   table index = max(0, s - m + x_p) = (s + 2^30) -sat- (m + 2^30 - x_p)
@@ -142,9 +142,13 @@ enum { kBiasNone = 0, kBiasPlain = 1, kBiasPacked = 2 };
 template <int D, int BC, int BIAS, bool NARROW, int XM>
 constexpr bool score_biased() { return XM == kExpTable && !BIAS; }
 
-// Offset of the numerator accumulators.
-template <bool QMAX>
-constexpr int acc_offset() { return QMAX ? kAccBias : kAccOffset; }
+// How the numerator accumulators are rescaled, and with it the offset they carry: the integer form (ReleaseConst) on 2^30;
+// the float form (FloatRelease) on 2^23; or the integer form on 2^23, for what a kernel that uses the float form has to do beyond
+// its range.  Moving the offset there and back costs two additions per accumulator and tile (577 tokens with a bias, computed
+// weights, tiles of 64: 48.6 us against 54.7), so a kernel that never uses the float form takes the first.
+enum { kReleaseInt = 0, kReleaseFloat = 1, kReleaseMoved = 2 };
+template <int RELEASE>
+constexpr int acc_offset() { return RELEASE == kReleaseInt ? kAccBias : kAccOffset; }
 
 template <bool SB>
 __device__ __forceinline__ int smax(int a, int b) { return SB ? (int)max((unsigned)a, (unsigned)b) : max(a, b); }
@@ -215,15 +219,16 @@ __device__ __forceinline__ SwizzledLane swizzled_lane_offsets(int lane) {
 // "does this group exist" then cost nothing; n_valid_rt still tells which keys of the last group exist.  NG < 0: at
 // most -NG groups and more than -NG / 2 of them; what is in LDS for keys beyond the sequence is then the last key again
 // (the maximum stays what it is), and their weights are masked.
-template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, bool FLOAT_RELEASE = false, bool MIXED = false,
-          class BeforeV = NothingBeforeV>
+template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, int RELEASE = kReleaseInt, bool MIXED = false,
+          class BeforeV = NothingBeforeV, bool MUL24 = false>
 __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, const int8_t* sK, int KROW,
                                             const int8_t* sV, int VROW, int n_valid_rt, int x_p,
                                             const int32_t* bias_row /* + c0 */,
                                             const v4i* bpre /* packed bias of this tile already in registers, or null */,
-                                            const ExpConst& c, int a_mul, int li, int g,
+                                            const ExpConst<MUL24>& c, int a_mul, int li, int g,
                                             int kx = 0, int vx = 0, BeforeV before_v = BeforeV()) {
-    const v16i zb = offset_block<acc_offset<QMAX>()>();
+    const v16i zb = offset_block<acc_offset<RELEASE>()>();
+    static_assert(!QMAX || RELEASE == kReleaseInt, "its shifts take the offset 2^30");
     constexpr int KSTEPS = D / 32, TB = D / 32, KB = BC / 32;
     constexpr bool KZ = XM == kExpShift0;
     static_assert(!SB || (XM == kExpTable && !BIAS), "biased scores: table mode without bias only");
@@ -360,11 +365,11 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
         m_new = st.m + n_oct * c.s_inv;
     }
     const int lo = m_new + c.x_floor;
-    const int m1 = m_new - c.s_inv;
+    const int ml = m_new - c.lead;
     // ---- step 4: max-offset factor alpha, brought to 16 fractional bits
     unsigned alpha16 = 0;
     if (!FIRST && !QMAX) {
-        const int a_hat = shift_exp2<KZ, XM != kExpTable>(smax<SB>(st.m, lo), m_new, m1, c);   // (registers are short there)
+        const int a_hat = shift_exp2<KZ, XM != kExpTable>(smax<SB>(st.m, lo), m_new, ml, c);   // (registers are short there)
         alpha16 = min(((unsigned)a_hat * (unsigned)a_mul) >> 14, 65536u);
     }
     // ---- steps 9,10 (the part that concerns the past): ScaleRelease of denominator and numerator.
@@ -380,13 +385,14 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
             for (int t = 0; t < TB; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) st.acc[t][v] = (int)(((unsigned)st.acc[t][v] >> n) + addc);
-        } else if (!FLOAT_RELEASE) {
+        } else if (RELEASE != kReleaseFloat) {
+            constexpr int kMove = kAccBias - acc_offset<RELEASE>();
             const ReleaseConst ri = make_release(alpha16);
             st.l = release_l(st.l, ri);
 #pragma unroll
             for (int t = 0; t < TB; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) st.acc[t][v] = release_acc(st.acc[t][v] + (kAccBias - kAccOffset), ri) - (kAccBias - kAccOffset);
+                for (int v = 0; v < 16; ++v) st.acc[t][v] = release_acc(st.acc[t][v] + kMove, ri) - kMove;
         } else {
             const FloatRelease rf = make_float_release(alpha16);
             st.l = release_l(st.l, rf);
@@ -434,8 +440,7 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
                             const int xs = (int)(((unsigned)s[kb][4 * a4 + b] << c.k) + neg_xpk);
-                            const int y = shift_exp2_shifted(xs, xs + c.s_inv_v, c);
-                            s[kb][4 * a4 + b] = y * c.p_mul_hi_v;
+                            s[kb][4 * a4 + b] = (int)c.weight(shift_exp2_shifted(xs, xs + c.lead_v, c));
                         }
                     }
         }
@@ -472,8 +477,8 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
                     unsigned pr[4];
 #pragma unroll
                     for (int b = 0; b < 4; ++b) {
-                        const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m1, c);
-                        pr[b] = (unsigned)(y * c.p_mul_hi_v);       // Eq. 10, result in byte 3
+                        const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, ml, c);
+                        pr[b] = c.weight(y);
                     }
                     const unsigned w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
                     pk[kb][a4] = (int)w;

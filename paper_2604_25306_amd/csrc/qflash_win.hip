@@ -45,7 +45,7 @@ constexpr int kWinExcluded = -(1 << 29);   // stands for "takes no part" in the 
 // rows; cb: accumulator input; operands_read() is called when the last LDS read of the pair has been issued.
 template <int XM, class Done>
 __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, const v16i (&cb)[2], const QflashHeadConsts& hc,
-                                        const ExpConst& c, bool out_round, Done operands_read) {
+                                        const ExpConst<>& c, bool out_round, Done operands_read) {
     constexpr int D = 32;
     constexpr bool KZ = XM == kExpShift0;
     // ---- step 1: S^T + bias (two blocks of 32 keys x 32 queries)
@@ -93,7 +93,7 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
             }
     } else {
         const int lo = m_new + c.x_floor;
-        const int m1 = m_new - c.s_inv;
+        const int ml = m_new - c.lead;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -101,8 +101,8 @@ __device__ __forceinline__ v4i win_half(int q_addr, int k_addr, int v_addr, cons
                 unsigned pr[4];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, m1, c);
-                    pr[b] = (unsigned)(y * c.p_mul_hi_v);
+                    const int y = shift_exp2<KZ>(max(s[kb][4 * a4 + b], lo), m_new, ml, c);
+                    pr[b] = c.weight(y);
                 }
                 const unsigned w = pack_byte3(pr[0], pr[1], pr[2], pr[3]);
                 pk[kb][a4] = (int)w;
@@ -196,7 +196,7 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, 0);
-    const ExpConst c = make_exp_const<XM != kExpTable>(hc);
+    const ExpConst<> c = make_exp_const<XM != kExpTable>(hc);
 
     // ---- LDS: [weight table, a.win_table_lds bytes][wavefront w: two sets of V (2 KiB), K (2 KiB),
     //      Q (1 KiB)]; the dynamic LDS is the only LDS of the kernel, so the table index is its address
@@ -343,7 +343,7 @@ __device__ __forceinline__ void win_dyn_compute(const QflashKernelArgs& a, const
     const int N = a.N;
     const int lane = threadIdx.x & 63, g = lane >> 5, li = lane & 31;
     const int row = 32 * half + li;
-    const ExpConst c = make_exp_const(hc);
+    const ExpConst<> c = make_exp_const(hc);
     const int op_lane = 32 * li + 16 * g, v_lane = win_v_lane(lane);
     const double inv = 1.0 / unit;
     v16i cb[2];
