@@ -252,6 +252,12 @@ size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
     return (((size_t)table_bytes + 1023) & ~(size_t)1023) + (size_t)qflash_ring_slots(d) * (size_t)kv_tile * (size_t)d;
 }
 
+// LDS a workgroup takes on a compute unit of gfx950, which hands it out in pieces of 1280 bytes.  Five workgroups of 32 KiB are
+// 160 KiB, all there is, but only four of them are resident; planned as five, with the wrong workgroups giving way, 96 pairs of
+// 1200 tokens with 32 features and tiles of 128 took 44.0 us, 32.1 now, 64 of 2100 73.5 and 65.1, 384 of 577 with 64 features
+// and tiles of 64 46.3 and 42.1 (256 of 400 with 32 features and tiles of 128 the other way, 17.0 and 18.4).
+static size_t qflash_lds_allocated(size_t bytes) { return (bytes + 1279) / 1280 * 1280; }
+
 // Wavefronts per workgroup of the ring.  More of them share one weight table and one staged tile, fewer
 // are dealt out more evenly.  Cost of a choice: wavefronts on the busiest compute unit times the time each
 // of them adds, (2200 + 230 x) / x cycles per KV tile with x wavefronts on the unit (fitted to 12 to
@@ -268,7 +274,7 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     const double eff = d == 64 ? 0.5 * (w + ((w + 3) & ~3)) : w;
     const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 4) : a.kv_tile == 64 ? 6 : 4;   // by registers
     const long long units = (long long)a.B * a.H * *qtiles, per_cu = (units + cus - 1) / cus;
-    long long fit = (long long)((size_t)lds_limit / qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d));
+    long long fit = (long long)((size_t)lds_limit / qflash_lds_allocated(qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d)));
     // (Tiles of 128: workgroups of five to seven wavefronts, which do not share the SIMDs evenly, are never better: 384 pairs
     // of 577 tokens 47.2 us with five and 40.6 with seven against 38.8 with four, 192 of 640 27.6 with seven against 22.6;
     // eight are, where they even out the rounds: 120 pairs of 900 32.2 -> 29.5.  Three only where the launch does not
