@@ -208,10 +208,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
         // wavefronts of the last workgroups give way the further they have come (qflash_plan_ring)
         int give_way = (int)blockIdx.x >= a.ring_even_from ? n_tiles / 2 : n_tiles;
         if (a.ring_even_from < (int)gridDim.x) __builtin_amdgcn_s_setprio(3);
-        QF_RING_TILE(true, true)
-        sl = lane_offsets();
-        // (every wavefront passes the barrier of every tile in one of the two loops)
-        while (jt < n_full && __builtin_expect(__builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0, 1)) {
+        auto priority = [&]() {
             if (__builtin_expect(jt == give_way, 0)) {           // at a half, three quarters and seven eighths of the tiles
                 if (give_way == n_tiles / 2) {
                     __builtin_amdgcn_s_setprio(2);
@@ -223,9 +220,18 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
                     __builtin_amdgcn_s_setprio(0);
                 }
             }
+        };
+        QF_RING_TILE(true, true)
+        sl = lane_offsets();
+        // (every wavefront passes the barrier of every tile in one of the two loops)
+        while (jt < n_full && __builtin_expect(__builtin_amdgcn_ballot_w64(st.l >= kFloatReleaseMaxL) == 0, 1)) {
+            priority();
             QF_RING_TILE(false, true)
         }
-        while (jt < n_full) QF_RING_TILE(false, false)
+        while (jt < n_full) {
+            priority();
+            QF_RING_TILE(false, false)
+        }
         if (!active) {
             if (rem > 0) before_v();
             return;
