@@ -13,6 +13,7 @@ SHIM = """
 #include <cstring>
 #include "qflash_derive.h"
 #include "qflash_internal.h"
+extern "C" int table_span(int s_inv, int x_shift, int p_mul, int p_shift) { return (int)qflash_table_span(s_inv, x_shift, p_mul, p_shift); }
 extern "C" int table_bytes(int s_inv, int x_shift, int p_mul, int p_shift) {
     const long long x_p = qflash_table_span(s_inv, x_shift, p_mul, p_shift);
     return x_p + 16 <= kTableMaxBytes ? qflash_table_bytes((int)x_p) : 0;
@@ -43,6 +44,11 @@ def _library():
         subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC, src,
                                os.path.join(CSRC, "qflash_plan.cpp"), "-o", out])
         return ctypes.CDLL(out)
+
+
+def table_span(params):
+    """Score difference to the running maximum at which the table begins: its entry 0, of weight 0."""
+    return _library().table_span(params.s_inv, params.x_shift, params.p_mul, params.p_shift)
 
 
 def table_bytes(params):
