@@ -6,6 +6,10 @@
 
 #include "qflash_internal.h"
 
+#if defined(__FAST_MATH__) || __FINITE_MATH_ONLY__
+#error "every float operation here is meant exactly as written, denormals and the sign of zero included"
+#endif
+
 namespace {
 
 QF_UNIT_HD inline float qf_as_float(uint32_t bits) { return __builtin_bit_cast(float, bits); }

@@ -49,6 +49,9 @@ __device__ __forceinline__ unsigned pack_byte(unsigned p0, unsigned p1, unsigned
 // one-token sequences).  The compiler makes a division of v_rcp and products of floats and relies on a first guess that
 // is not too large; a divisor cut down to 24 bits makes it larger.  Behind it divisors are small, exact as floats, and
 // rounding down only makes the guess smaller, corrected as ever.
+// The compiler does not know what the call does.  What keeps arithmetic on its side of it is data: the floats behind it come of
+// products of LDS contents read behind a barrier further on, and what has to round to nearest has gone to LDS, or to a scalar
+// register by an assembly statement (bias_lane_base), ahead of it.  tests/test_rounding_mode.py reads that from the built code.
 __device__ __forceinline__ void round_down() { __builtin_amdgcn_s_setreg(1 | (0 << 6) | (1 << 11), 2); }   // MODE.round, single precision
 // Mask of the first n bytes (n <= 0: none, n >= 4: all).
 __device__ __forceinline__ unsigned first_bytes(int n) { return (unsigned)(0xffffffffull >> (8 * (4 - min(max(n, 0), 4)))); }
