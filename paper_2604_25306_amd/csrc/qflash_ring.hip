@@ -47,7 +47,7 @@ template <int V> struct RingInt { static constexpr int value = V; };
 // Weight tables of 32 features from this size on: part of the weights is computed (MIXED of process_tile).
 constexpr int kRingMixedBytes = 7 * 1024;
 
-template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
+template <int D, int BC, int XM, bool QMAX, int MIXED = 0>
 __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     constexpr int kRows = 1024 / D;                 // rows of a 1 KiB piece
     constexpr int kPieces = BC / kRows;             // pieces of K, or V, of a tile
@@ -63,7 +63,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     const int n_waves = (int)(blockDim.x >> 6);
     const int g = lane >> 5, li = lane & 31;
     const QflashHeadConsts hc = head_consts(a, bh);
-    const auto c = make_exp_const<XM != kExpTable || MIXED>(hc);
+    const auto c = make_exp_const<XM != kExpTable || MIXED != 0>(hc);
     // (made anew where the compiler would otherwise hold, or spill, them through a tile)
     auto lane_offsets = [&]() {
         int l = (int)threadIdx.x & 63;
@@ -277,13 +277,13 @@ constexpr int ring_min_waves() {
 }
 
 // QMAX: the quantised-maximum variant (not Algorithm 1 as printed; see process_tile).
-template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
+template <int D, int BC, int XM, bool QMAX, int MIXED = 0>
 __global__ __launch_bounds__(64 * kRingMaxWaves, (ring_min_waves<D, BC, XM>())) void qflash_fwd_ring(const QflashKernelArgs a) {
     if constexpr (XM == kExpAuto) {
         const int unit = qflash_unit_of_workgroup(blockIdx.x, a.units_per_xcd, a.xcd_period);
         if (unit >= a.n_units) return;
         const int table = head_consts(a, unit / a.n_qtiles).lut_bytes;
-        if (D == 32 && table >= kRingMixedBytes) ring_body<D, BC, kExpTable, QMAX, D == 32>(a);
+        if (D == 32 && table >= kRingMixedBytes) ring_body<D, BC, kExpTable, QMAX, D == 32 ? 2 : 0>(a);
         else if (table > 0) ring_body<D, BC, kExpTable, QMAX>(a);
         else ring_body<D, BC, kExpShift, QMAX>(a);
     } else {
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * kRingMaxWaves, (ring_min_waves<D, BC, XM>())) 
     }
 }
 
-template <int D, int BC, int XM, bool QMAX, bool MIXED = false>
+template <int D, int BC, int XM, bool QMAX, int MIXED = 0>
 int launch_ring(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
     return qflash_launch_kernel<qflash_fwd_ring<D, BC, XM, QMAX, MIXED>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)(64 * a.waves_per_head), lds, lds_limit, st);
 }
@@ -302,7 +302,11 @@ namespace {
 template <int D, int BC, bool QMAX>
 int launch_mode(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
     if (a.exp_mode == kExpAuto) return launch_ring<D, BC, kExpAuto, QMAX>(a, lds, lds_limit, st);
-    if (D == 32 && a.exp_mode == kExpTable && a.lut_bytes_max >= kRingMixedBytes) return launch_ring<D, BC, kExpTable, QMAX, D == 32>(a, lds, lds_limit, st);
+    if (D == 32 && a.exp_mode == kExpTable && a.lut_bytes_max >= kRingMixedBytes) {
+        // (at most one workgroup to a compute unit; measured to make no difference where the kernel chooses, kExpAuto)
+        if (a.n_units <= (a.n_cu > 0 ? a.n_cu : 256)) return launch_ring<D, BC, kExpTable, QMAX, D == 32 ? 1 : 0>(a, lds, lds_limit, st);
+        return launch_ring<D, BC, kExpTable, QMAX, D == 32 ? 2 : 0>(a, lds, lds_limit, st);
+    }
     if (a.exp_mode == kExpTable) return launch_ring<D, BC, kExpTable, QMAX>(a, lds, lds_limit, st);
     if (a.exp_mode == kExpShift0) return launch_ring<D, BC, kExpShift0, QMAX>(a, lds, lds_limit, st);
     return launch_ring<D, BC, kExpShift, QMAX>(a, lds, lds_limit, st);

@@ -222,7 +222,7 @@ __device__ __forceinline__ SwizzledLane swizzled_lane_offsets(int lane) {
 // "does this group exist" then cost nothing; n_valid_rt still tells which keys of the last group exist.  NG < 0: at
 // most -NG groups and more than -NG / 2 of them; what is in LDS for keys beyond the sequence is then the last key again
 // (the maximum stays what it is), and their weights are masked.
-template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, int RELEASE = kReleaseInt, bool MIXED = false,
+template <int D, int BC, int BIAS, int XM, bool SB, bool FULL, bool FIRST, int LAY = kLayPadded, int NG = 0, bool QMAX = false, int RELEASE = kReleaseInt, int MIXED = 0,
           class BeforeV = NothingBeforeV, bool MUL24 = false>
 __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, const int8_t* sK, int KROW,
                                             const int8_t* sV, int VROW, int n_valid_rt, int x_p,
@@ -247,16 +247,19 @@ __device__ __forceinline__ void process_tile(RowState<D>& st, const v4i* qreg, c
     auto grp_cut = [&](int kb, int a4) {
         return NG > 0 ? 4 * kb + a4 == NG - 1 : NG == 0 && 32 * kb + 8 * a4 + 8 > n_valid;
     };
-    // MIXED (look-up mode, 32 features): two groups of four scores in eight are computed instead of looked up.  A
+    // MIXED (look-up mode, 32 features): so many groups of four scores in eight are computed instead of looked up.  A
     // look-up of 64 random bytes costs the LDS of the compute unit 2.1 cycles where they fall into few words, 7.5 where
     // they are spread over a large table (measured: 2.1 and 7.5), its arithmetic nine vector instructions.  At 32
     // features a tile has half the vector work per look-up and the LDS is what runs out first.  us with none, one,
     // two and three groups computed, 96 pairs of 1200 tokens, inputs N(0, sigma^2): sigma 1.0 (table of 12 KB) 36.4 34.2
     // 32.5 32.9, 1.2 (8.5 KB) 32.0 30.6 29.9 31.9, 1.35 (6.7 KB) 28.2 27.9 28.6 31.4, 1.6 (4.8 KB) 24.5 25.8 28.0 31.2: see
-    // kRingMixedBytes.  At 64 features computing only costs (40.5 -> 45 us, N = 577).
+    // kRingMixedBytes.  Where a compute unit has one workgroup one group is best, the arithmetic being a longer chain: none, one and
+    // two 12.2 12.0 12.3 (32 pairs of 768, tiles of 64), 10.9 10.65 10.75 (of 128); with two workgroups two are (32 of 1600, tiles of
+    // 64: 33.5 31.0 30.1).
+    // At 64 features computing only costs (40.5 -> 45 us, N = 577).
     static_assert(!MIXED || (XM == kExpTable && D == 32 && LAY == kLaySwizzled), "computed weights beside look-ups");
-    constexpr bool MIX = MIXED && FULL;                    // (a ragged tile would spill)
-    auto computed = [&](int kb, int a4) { return MIX && a4 == 3; };
+    constexpr bool MIX = MIXED != 0 && FULL;                    // (a ragged tile would spill)
+    auto computed = [&](int kb, int a4) { return MIX && a4 == 3 && (MIXED == 2 || (kb & 1)); };
     // ---- step 1: S^T blocks (32 kv rows x 32 queries each)
     v16i s[KB];
 #pragma unroll
