@@ -275,12 +275,18 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     const int per_simd = d == 64 ? (a.kv_tile == 64 ? 5 : 4) : a.kv_tile == 64 ? 6 : 4;   // by registers
     const long long units = (long long)a.B * a.H * *qtiles, per_cu = (units + cus - 1) / cus;
     long long fit = (long long)((size_t)lds_limit / qflash_lds_allocated(qflash_ring_lds_bytes(w, a.kv_tile, table_bytes, d)));
-    // (Tiles of 128: workgroups of five to seven wavefronts, which do not share the SIMDs evenly, are never better: 384 pairs
-    // of 577 tokens 47.2 us with five and 40.6 with seven against 38.8 with four, 192 of 640 27.6 with seven against 22.6;
-    // eight are, where they even out the rounds: 120 pairs of 900 32.2 -> 29.5.  Three only where the launch does not
-    // share out its keys, qflash_plan_split.)
-    if (d == 64 && a.kv_tile == 128 && w > 4 && w < 8) return 1e30;
-    if (d == 64 && want == 3 && (long long)a.B * a.H * nblk <= 2ll * cus) return 1e30;
+    // Workgroups of five to seven wavefronts do not share the SIMDs evenly, and wait for one another twice a tile.  Tiles of 64: five
+    // and six only alone on their compute unit (60 pairs of 513 tokens 14.2 us with six, 15.1 with four; but 384 of 380 26.9 and
+    // 21.5, 360 of 330 24.7 and 20.5, 600 of 300 26.5 with five and 23.3); seven and eight even out the rounds (120 of 770 28.3 with
+    // seven, 33.3 with four).  Tiles of 128: 384 pairs of 577 47.2 with five and 40.6 with seven, 38.8 with four, 192 of 640 27.6
+    // with seven and 22.6; six and seven are better all the same where LDS holds two workgroups only, tables of 30 KiB and more
+    // (96 of 1025 34.5 with seven, 46.8 with four, 96 of 800 28.4 and 35.4, 240 of 400 16.7 and 22.4, 360 of 330 21.5 with six and
+    // 25.0; five 480 of 257 25.6 and 22.4), unless some heads compute their weights (per head, 192 of 350 19.9 with six, 16.7 with
+    // four, nor three then: 18.3, 288 of 300 24.7 and 20.4).  Three only where the launch does not share out its keys,
+    // qflash_plan_split.
+    if (d == 64 && a.kv_tile == 64 && (w == 5 || w == 6) && per_cu > 1) return 1e30;
+    if (d == 64 && a.kv_tile == 128 && (w == 5 || ((w == 6 || w == 7) && (fit > 2 || a.per_head)))) return 1e30;
+    if (d == 64 && want == 3 && ((long long)a.B * a.H * nblk <= 2ll * cus || (a.kv_tile == 128 && a.per_head))) return 1e30;
     const int by_registers = d == 64 && a.kv_tile == 128 ? per_simd / ((w + 3) / 4) : 4 * per_simd / w;
     if (fit > by_registers) fit = by_registers;
     if (fit > per_cu) fit = per_cu;

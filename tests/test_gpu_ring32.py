@@ -3,6 +3,7 @@ workgroup size the plan can choose, look-ups mixed with computed weights (full t
 import pytest
 
 import oracle
+from tests.ring_plan import ring_plan, table_bytes
 from tests.test_gpu_parity import gpu, rand_case, run_gpu, assert_same  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -38,5 +39,20 @@ def test_ring32_mixed_weights(gpu, gain, tile):  # noqa: F811
     Q, K, V, sQ, sK, _ = rand_case((12, 4, 420, 32), 6000, q_gain=1.0)
     p = oracle.derive_params(sQ * gain, sK, 32)
     assert_same(run_gpu(gpu, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "gain %g" % gain)
+    info = ctx.cache_info()
+    assert (info.last_kernel, info.last_key_waves) == (2, 0)
+
+
+# one workgroup to a compute unit, where another share of the weights is computed: full tiles only, and a ragged one
+@pytest.mark.parametrize("tile", [64, 128])
+@pytest.mark.parametrize("bhn", [(9, 4, 512), (9, 4, 642)])
+def test_ring32_alone_on_a_compute_unit(gpu, bhn, tile):  # noqa: F811
+    torch, qf, ctx = gpu
+    shape = bhn + (32,)
+    Q, K, V, sQ, sK, _ = rand_case(shape, 6100 + bhn[2])
+    p = oracle.derive_params(sQ, sK, 32)
+    plan = ring_plan(shape, tile, table_bytes(p))
+    assert plan.ring and plan.units <= 256 and table_bytes(p) >= 7 * 1024
+    assert_same(run_gpu(gpu, Q, K, V, p, tile), oracle.qflash_attention(Q, K, V, p, tile), "%s" % (shape,))
     info = ctx.cache_info()
     assert (info.last_kernel, info.last_key_waves) == (2, 0)

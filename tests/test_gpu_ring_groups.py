@@ -20,7 +20,7 @@ CASES = [(22, 4, 700, 64, 64, 0.09, 3, 2, ONE), (22, 4, 770, 64, 64, 0.06, 4, 3,
          (20, 12, 400, 64, 64, 0.2, 7, 1, ONE), (10, 12, 770, 64, 64, 0.06, 7, 3, ONE), (20, 12, 450, 64, 64, 0.033, 8, 1, ONE),
          (43, 3, 700, 64, 64, 0.033, 8, 2, ONE),
          (22, 4, 700, 64, 128, 0.09, 3, 2, ONE), (22, 4, 770, 64, 128, 0.06, 4, 3, ONE), (40, 4, 705, 64, 128, 0.06, 4, 1, ONE),
-         (20, 12, 450, 64, 128, 0.036, 8, 1, ONE), (22, 12, 450, 64, 128, 0.033, 8, 1, MORE), (36, 3, 900, 64, 128, 0.036, 8, 3, ONE),
+         (30, 12, 330, 64, 128, 0.033, 6, 1, MORE), (8, 12, 1025, 64, 128, 0.033, 7, 2, ONE), (20, 12, 450, 64, 128, 0.036, 8, 1, ONE), (22, 12, 450, 64, 128, 0.033, 8, 1, MORE), (36, 3, 900, 64, 128, 0.036, 8, 3, ONE),
          (22, 4, 700, 32, 64, 0.06, 3, 2, ONE), (36, 3, 705, 32, 64, 0.2, 4, 1, ONE), (32, 12, 257, 32, 64, 0.0292, 5, 1, ONE),
          (43, 4, 513, 32, 64, 0.028, 6, 1, ONE), (12, 12, 700, 32, 64, 0.028, 6, 2, ONE),
          (22, 4, 700, 32, 128, 0.06, 3, 2, ONE), (8, 12, 1200, 32, 128, 0.0412, 4, 2, ONE), (32, 12, 257, 32, 128, 0.036, 5, 1, ONE),

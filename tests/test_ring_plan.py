@@ -28,3 +28,25 @@ def test_wavefronts_that_give_way_are_those_of_the_last_resident_workgroups():
         sizes |= 1 << plan.waves
     assert shares > 2000 and five > 100
     assert sizes & 0b111111000 == 0b111111000        # three to eight wavefronts
+
+
+def test_workgroups_that_do_not_share_the_simds_evenly():
+    """64 features: five and six wavefronts with tiles of 64 only alone on a compute unit; with tiles of 128 six and seven only where
+    LDS holds two workgroups and all heads have a table, and three not with one set of constants per head."""
+    rng = random.Random(4)
+    met = set()
+    for _ in range(30000):
+        tile, H, per_head = rng.choice((64, 128)), rng.choice((1, 3, 4, 6, 8, 12, 16)), rng.random() < 0.3
+        N = rng.randint(257, 1400)
+        plan = ring_plan((rng.randint(1, 64), H, N, 64), tile, rng.choice((0, 9600, 20 * 1024, 24160, 36000, 40960)),
+                         per_head=per_head)
+        if not plan.ring:
+            continue
+        met.add((tile, plan.waves, per_head))
+        if tile == 64:
+            assert plan.waves not in (5, 6) or plan.units <= CUS, plan
+        else:
+            assert plan.waves != 5 and (plan.waves not in (6, 7) or (not per_head and 3 * plan.lds > LDS)), plan
+            blocks = -(-N // 32)
+            assert plan.waves != 3 or not per_head or -(-blocks // -(-blocks // 4)) == 3, plan      # (nine: three times three)
+    assert {w for t, w, h in met if t == 64} == {3, 4, 5, 6, 7, 8} and {w for t, w, h in met if t == 128 and not h} == {3, 4, 6, 7, 8}
