@@ -137,8 +137,8 @@ int qflash_cache_query(qflash_ctx* ctx, qflash_cache_info* out /* host */);
  *   kv_tile  B_c of Algorithm 1: 64 or 128.  The result depends on it (the running maximum and
  *            the rescaling of past accumulators happen per KV tile); it does not depend on the
  *            query block size or on any launch parameter.
- *            Cost on MI355X: the two are within 10 % of each other (ViT-B/16 B=64: 18.6 us both; N = 577,
- *            d = 64: 42.4 against 41.9 us).  A d = 32 sequence
+ *            Cost on MI355X: close to each other (ViT-B/16 B=64, input in cache: 15.2 us with 64, 17.0 with 128;
+ *            384 pairs of N = 577, d = 64: 34 us both).  A d = 32 sequence
  *            with a bias that is too long for LDS (N above 2016) takes a kernel that stages one
  *            tile at a time with two barriers per tile and computes weights arithmetically.
  *   p        host; validated on every call.

@@ -164,7 +164,7 @@ int qflash_check_call(const void* Q, const void* K, const void* V, const void* O
 // of the whole-compute-unit kernel.
 size_t qflash_resident_lds_bytes(int N, int d, int heads, int table_bytes, int lds_limit, int ring_tile = 0);
 size_t qflash_cu_lds_bytes(int N, int heads, int table_bytes);
-// Wavefronts per workgroup of that kernel at most: with KV tiles of 128 it takes 131 registers, three wavefronts to a SIMD.
+// Wavefronts per workgroup of that kernel at most: with KV tiles of 128 it takes more than 128 registers, three wavefronts to a SIMD.
 QF_UNIT_HD constexpr int qflash_cu_max_waves(int kv_tile) { return kv_tile == 64 ? 16 : 12; }
 
 // Enqueue the forward kernel for head size d (32|64), KV tile (64|128).  Returns a hipError_t value.

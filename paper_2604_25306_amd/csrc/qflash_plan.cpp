@@ -85,9 +85,7 @@ int qflash_plan_fwd(int BH, int N, int d, int kv_tile, int lds_limit, QflashKern
         const int cus = a->n_cu > 0 ? a->n_cu : 256;
         int waves;
         // Without a bias the ring is fed by direct global-to-LDS loads (qflash_fwd_ring): no wavefront
-        // stages anything, registers allow five (tile 64) or three (tile 128) wavefronts per SIMD, and
-        // workgroups of four wavefronts, one per SIMD, measured best (DeiT-B/384: 45.3 us against
-        // 50.9 with seven or eight and 54.6 with five or six).
+        // stages anything, and workgroups of four wavefronts, one per SIMD, are where qflash_plan_ring starts from.
         a->ring_dma = !a->bias ? 1 : 0;
         if (a->ring_dma) {
             const int tiles = (nblk + 3) / 4;
@@ -246,7 +244,7 @@ int qflash_plan_cu_dynamic(int BH, int N, int d, int kv_tile, int lds_limit, Qfl
     return 0;
 }
 
-// LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and two KV tiles of K and V.
+// LDS bytes of the direct-load ring kernel: table (rounded up to 1 KiB) and the slots, each of one tile of K or V.
 size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
     (void)waves;
     return (((size_t)table_bytes + 1023) & ~(size_t)1023) + (size_t)qflash_ring_slots(d) * (size_t)kv_tile * (size_t)d;
@@ -324,8 +322,12 @@ int qflash_plan_ring(int d, int lds_limit, int table_bytes, QflashKernelArgs* a)
     // alone, at the pace of a single wavefront (1 us per tile; 19 wavefronts on a unit do a tile in 0.09).  From this
     // workgroup on, the last that fit the chip together, wavefronts give way the further they have come (the kernel's
     // s_setprio): 256 pairs of 577 tokens 22.6 -> 20.9 us, 64 pairs of 2100 with 32 features 69.8 -> 64.0.  Not for
-    // all of several rounds: 64 pairs of 2100, tiles of 128, 71.0 -> 78.3; nor for fewer than three wavefronts to a
+    // all of several rounds: 64 pairs of 2100, tiles of 128, 65.1 -> 76.8; nor for fewer than three wavefronts to a
     // SIMD, where there is nothing to share (32 pairs of 768 tokens, 32 features, 12.1 -> 12.4).
+    // (To step down, wavefronts have to start above the default: for its whole length such a launch is issued ahead of what other
+    // streams have on the same compute units.  Two layers at a time on two streams gain all the same: 64 pairs of 2100 beside 768 of
+    // 197 63.7 us a pair of launches, 71.9 without priorities, 384 of 577 beside them 48.4 and 50.0; a 16 MiB elementwise kernel
+    // beside 256 of 577 8.7 to 9.5 us both ways, beside 64 of 2100 10.7 to 11.7 and 7.8 to 10.1.)
     const long long grid = 8ll * a->units_per_xcd, last = (long long)resident * (a->n_cu > 0 ? a->n_cu : 256);
     a->ring_even_from = resident * waves < 9 ? (int)grid : grid > last ? (int)(grid - last) : 0;
     return 1;

@@ -16,9 +16,9 @@
 //   64 features, tiles of 128 (384 pairs of 577, 39.1 -> 33.8 us): four wavefronts to a SIMD instead of three, as far
 //     as registers (128) and LDS (three slots, not four: 35 KiB with the table) go; then the same.
 //   32 features (64 pairs of 2100 tokens, 73.0 -> 59.7 us): LDS, 24 look-ups with 5.3 conflict cycles each, against the
-//     eight computed weights on the vector units (MIXED of process_tile).
+//     eight computed weights in thirty-two on the vector units (MIXED of process_tile).
 // 32 features against the streamed kernel that staged one tile at a time through registers and computed the weights:
-// B*H = 64, N = 2100 145.6 -> 59.7 us with tiles of 64, 202 -> 61 us with tiles of 128.
+// B*H = 64, N = 2100 145.6 -> 59.7 us with tiles of 64, 202 -> 65 us with tiles of 128.
 //
 // Synchronisation: the wavefronts share the loads of a tile (1 KiB pieces, dealt round robin), wait for their own (vmcnt)
 // and then for the others at a barrier; see QF_RING_TILE.  Every wavefront of a workgroup executes every barrier, with
@@ -72,7 +72,7 @@ __device__ __forceinline__ void ring_body(const QflashKernelArgs& a) {
     };
     SwizzledLane sl = lane_offsets();
 
-    // ---- LDS: [weight table][slot 0][slot 1]; the dynamic LDS is the only LDS of the kernel, so the
+    // ---- LDS: [weight table][three or four slots]; the dynamic LDS is the only LDS of the kernel, so the
     //      table index is its address
     const int lds0 = (int)(size_t)(lds_void)smem_ring;
     const int tbytes = XM == kExpTable ? a.ring_table_lds : 0;
