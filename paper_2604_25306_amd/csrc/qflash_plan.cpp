@@ -253,7 +253,7 @@ size_t qflash_ring_lds_bytes(int waves, int kv_tile, int table_bytes, int d) {
 // LDS a workgroup takes on a compute unit of gfx950, which hands it out in pieces of 1280 bytes.  Five workgroups of 32 KiB are
 // 160 KiB, all there is, but only four of them are resident; planned as five, with the wrong workgroups giving way, 96 pairs of
 // 1200 tokens with 32 features and tiles of 128 took 44.0 us, 32.1 now, 64 of 2100 73.5 and 65.1, 384 of 577 with 64 features
-// and tiles of 64 46.3 and 42.1 (256 of 400 with 32 features and tiles of 128 the other way, 17.0 and 18.4).
+// and tiles of 64 46.3 and 42.1.
 static size_t qflash_lds_allocated(size_t bytes) { return (bytes + 1279) / 1280 * 1280; }
 
 // Wavefronts per workgroup of the ring.  More of them share one weight table and one staged tile, fewer
@@ -261,8 +261,7 @@ static size_t qflash_lds_allocated(size_t bytes) { return (bytes + 1279) / 1280 
 // of them adds, (2200 + 230 x) / x cycles per KV tile with x wavefronts on the unit (fitted to 12 to
 // 20: DeiT-B/384, N(0,1), 12 resident: 414; N(0,1.5^2), small table, 20 resident: 341), x limited by LDS and
 // registers.  Measured against the fixed four (us): d = 64, 96 pairs of 1025 tokens 47.4 -> 39.7 (seven),
-// 36 pairs of 1000 25.2 -> 21.7, 56 of 577 16.7 -> 14.6 (three), 32 features, 64 pairs of 2100 tokens 81.2 -> 76.9 (six), 96
-// pairs of 1200 tokens 41.2 -> 39.9 (three).
+// 36 pairs of 1000 25.2 -> 21.7, 56 of 577 16.7 -> 14.6 (three), 32 features, 96 pairs of 1200 tokens 41.2 -> 39.9 (three).
 static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKernelArgs& a, int want, int* waves, int* qtiles, int* resident) {
     const int nblk = (a.N + 31) / 32, cus = a.n_cu > 0 ? a.n_cu : 256;
     *qtiles = (nblk + want - 1) / want;
@@ -284,6 +283,12 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     // qflash_plan_split.
     if (d == 64 && a.kv_tile == 64 && (w == 5 || w == 6) && per_cu > 1) return 1e30;
     if (d == 64 && a.kv_tile == 128 && (w == 5 || ((w == 6 || w == 7) && (fit > 2 || a.per_head)))) return 1e30;
+    // 32 features, tiles of 64: six where a compute unit gets three at most (96 of 1025 with a table of 33 KiB 33.1 us with six, 34.9
+    // with four; 144 of 1300 65.9 and 51.5, 288 of 530 28.2 and 25.3).  Tiles of 128: six never (240 of 350 12.3 and 11.6, 144 of 1300
+    // with a table of 26 KiB 74.6 and 60.7), five where it gets two (160 of 400 11.1 with five, 12.1 with four; 256 of 400 18.3 and
+    // 13.9, 128 of 790 29.5 and 22.6, 320 of 410 with a table of 26 KiB 25.0 and 19.2).
+    if (d == 32 && a.kv_tile == 64 && w == 6 && per_cu > 3) return 1e30;
+    if (d == 32 && a.kv_tile == 128 && (w == 6 || (w == 5 && per_cu > 2))) return 1e30;
     if (d == 64 && want == 3 && ((long long)a.B * a.H * nblk <= 2ll * cus || (a.kv_tile == 128 && a.per_head))) return 1e30;
     const int by_registers = d == 64 && a.kv_tile == 128 ? per_simd / ((w + 3) / 4) : 4 * per_simd / w;
     if (fit > by_registers) fit = by_registers;

@@ -23,8 +23,8 @@ CASES = [(22, 4, 700, 64, 64, 0.09, 3, 2, ONE), (22, 4, 770, 64, 64, 0.06, 4, 3,
          (30, 12, 330, 64, 128, 0.033, 6, 1, MORE), (8, 12, 1025, 64, 128, 0.033, 7, 2, ONE), (20, 12, 450, 64, 128, 0.036, 8, 1, ONE), (22, 12, 450, 64, 128, 0.033, 8, 1, MORE), (36, 3, 900, 64, 128, 0.036, 8, 3, ONE),
          (22, 4, 700, 32, 64, 0.06, 3, 2, ONE), (36, 3, 705, 32, 64, 0.2, 4, 1, ONE), (32, 12, 257, 32, 64, 0.0292, 5, 1, ONE),
          (43, 4, 513, 32, 64, 0.028, 6, 1, ONE), (12, 12, 700, 32, 64, 0.028, 6, 2, ONE),
-         (22, 4, 700, 32, 128, 0.06, 3, 2, ONE), (8, 12, 1200, 32, 128, 0.0412, 4, 2, ONE), (32, 12, 257, 32, 128, 0.036, 5, 1, ONE),
-         (43, 4, 700, 32, 128, 0.028, 6, 2, MORE)]
+         (22, 4, 700, 32, 128, 0.06, 3, 2, ONE), (8, 12, 1200, 32, 128, 0.0412, 4, 2, ONE), (20, 8, 400, 32, 128, 0.0412, 5, 2, ONE),
+         (43, 4, 700, 32, 128, 0.028, 4, 2, MORE)]
 
 
 def planned(shape, tile, p):
@@ -54,7 +54,8 @@ def test_workgroups_of_every_size(gpu, request, B, H, N, d, tile, scale, waves, 
 
 
 # Scores exactly on the lowest entry of the weight table, one above and one below it, in every 32-key block of a tile: the
-# first block's index is a fused multiply-add whose result is then a zero, the others' a saturating subtraction.
+# first block's index is a fused multiply-add whose result is then a zero, of either sign ahead of its clamp, the others' a
+# saturating subtraction.
 @pytest.mark.parametrize("kernel,B,H,N,d,tile", [(2, 60, 3, 300, 64, 64), (2, 60, 3, 300, 64, 128), (2, 60, 3, 200, 32, 64), (2, 60, 3, 200, 32, 128),
                                                  (3, 64, 12, 197, 64, 64), (3, 64, 12, 197, 64, 128), (1, 135, 6, 256, 64, 64)])
 def test_scores_on_the_edge_of_the_table(gpu, request, kernel, B, H, N, d, tile):  # noqa: F811

@@ -30,6 +30,21 @@ def test_wavefronts_that_give_way_are_those_of_the_last_resident_workgroups():
     assert sizes & 0b111111000 == 0b111111000        # three to eight wavefronts
 
 
+def test_workgroups_of_32_features():
+    """Tiles of 64: six wavefronts where a compute unit gets three workgroups at most; of 128: five where it gets two, never six."""
+    rng = random.Random(5)
+    met = set()
+    for _ in range(20000):
+        tile = rng.choice((64, 128))
+        plan = ring_plan((rng.randint(1, 64), rng.choice((1, 3, 4, 6, 8, 12, 16)), rng.randint(65, 2100), 32), tile,
+                         rng.choice((0, 9600, 16 * 1024, 20 * 1024, 30 * 1024, 36000, 40960)))
+        if plan.ring:
+            met.add((tile, plan.waves))
+            assert plan.waves != 6 or (tile == 64 and plan.units <= 3 * CUS), plan
+            assert plan.waves != 5 or tile == 64 or plan.units <= 2 * CUS, plan
+    assert met >= {(64, 3), (64, 4), (64, 5), (64, 6), (128, 3), (128, 4), (128, 5)}
+
+
 def test_workgroups_that_do_not_share_the_simds_evenly():
     """64 features: five and six wavefronts with tiles of 64 only alone on a compute unit; with tiles of 128 six and seven only where
     LDS holds two workgroups and all heads have a table, and three not with one set of constants per head."""
