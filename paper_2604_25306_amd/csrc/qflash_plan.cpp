@@ -276,13 +276,13 @@ static double ring_cost(int d, int lds_limit, int table_bytes, const QflashKerne
     // and six only alone on their compute unit (60 pairs of 513 tokens 14.2 us with six, 15.1 with four; but 384 of 380 26.9 and
     // 21.5, 360 of 330 24.7 and 20.5, 600 of 300 26.5 with five and 23.3); seven and eight even out the rounds (120 of 770 28.3 with
     // seven, 33.3 with four).  Tiles of 128: 384 pairs of 577 47.2 with five and 40.6 with seven, 38.8 with four, 192 of 640 27.6
-    // with seven and 22.6; six and seven are better all the same where LDS holds two workgroups only, tables of 30 KiB and more
-    // (96 of 1025 34.5 with seven, 46.8 with four, 96 of 800 28.4 and 35.4, 240 of 400 16.7 and 22.4, 360 of 330 21.5 with six and
-    // 25.0; five 480 of 257 25.6 and 22.4), unless some heads compute their weights (per head, 192 of 350 19.9 with six, 16.7 with
-    // four, nor three then: 18.3, 288 of 300 24.7 and 20.4).  Three only where the launch does not share out its keys,
-    // qflash_plan_split.
+    // with seven and 22.6; six, and seven in one round, are better all the same where LDS holds two workgroups only, tables of
+    // 30 KiB and more (96 of 1025 34.5 with seven, 46.8 with four, 96 of 800 28.4 and 35.4, 240 of 400 16.7 and 22.4, 360 of 330
+    // 21.5 with six and 25.0; five 480 of 257 25.6 and 22.4), unless some heads compute their weights (per head, 192 of 350 19.9
+    // with six, 16.7 with four, nor three then: 18.3, 288 of 300 24.7 and 20.4).  Three only where the launch does not share out its
+    // keys, qflash_plan_split.
     if (d == 64 && a.kv_tile == 64 && (w == 5 || w == 6) && per_cu > 1) return 1e30;
-    if (d == 64 && a.kv_tile == 128 && (w == 5 || ((w == 6 || w == 7) && (fit > 2 || a.per_head)))) return 1e30;
+    if (d == 64 && a.kv_tile == 128 && (w == 5 || ((w == 6 || w == 7) && (fit > 2 || a.per_head)) || (w == 7 && per_cu > fit))) return 1e30;
     // 32 features, tiles of 64: six where a compute unit gets three at most (96 of 1025 with a table of 33 KiB 33.1 us with six, 34.9
     // with four; 144 of 1300 65.9 and 51.5, 288 of 530 28.2 and 25.3).  Tiles of 128: six never (240 of 350 12.3 and 11.6, 144 of 1300
     // with a table of 26 KiB 74.6 and 60.7), five where it gets two (160 of 400 11.1 with five, 12.1 with four; 256 of 400 18.3 and

@@ -46,8 +46,8 @@ def test_workgroups_of_32_features():
 
 
 def test_workgroups_that_do_not_share_the_simds_evenly():
-    """64 features: five and six wavefronts with tiles of 64 only alone on a compute unit; with tiles of 128 six and seven only where
-    LDS holds two workgroups and all heads have a table, and three not with one set of constants per head."""
+    """64 features: five and six wavefronts with tiles of 64 only alone on a compute unit; with tiles of 128 six, and seven in
+    one round, only where LDS holds two workgroups and all heads have a table, and three not with one set of constants per head."""
     rng = random.Random(4)
     met = set()
     for _ in range(30000):
@@ -62,6 +62,7 @@ def test_workgroups_that_do_not_share_the_simds_evenly():
             assert plan.waves not in (5, 6) or plan.units <= CUS, plan
         else:
             assert plan.waves != 5 and (plan.waves not in (6, 7) or (not per_head and 3 * plan.lds > LDS)), plan
+            assert plan.waves != 7 or plan.units <= 2 * CUS, plan
             blocks = -(-N // 32)
             assert plan.waves != 3 or not per_head or -(-blocks // -(-blocks // 4)) == 3, plan      # (nine: three times three)
     assert {w for t, w, h in met if t == 64} == {3, 4, 5, 6, 7, 8} and {w for t, w, h in met if t == 128 and not h} == {3, 4, 6, 7, 8}
