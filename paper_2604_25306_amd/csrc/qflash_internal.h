@@ -77,6 +77,8 @@ struct QflashKernelArgs {
     int win_chunk;           // consecutive pairs (in slice-major order) each pair of wavefronts works through
     int win_groups;          // workgroups
     int win_table_lds;       // LDS bytes reserved for the weight table (a multiple of 1 KiB)
+    int win_rb, win_rh;      // replicas of a bias slice in batch and heads, and the reciprocals of their
+    unsigned win_inv_r, win_inv_rh, win_inv_bh;   // product, the second and bias_H (qflash_win_order, qflash_divide)
     // kernel that shares out the keys of 32 query rows (qflash_plan_split): wavefronts per workgroup, 0 if not taken
     int split_waves;
     int split_blocks;        // 32-key blocks per wavefront: 1 or 2
@@ -101,6 +103,16 @@ struct QflashKernelArgs {
     qflash_dynamic_info* dyn_info;           // may be null
     const uint8_t* dyn_mask;                 // win_mode: exclusion mask or null; bias is then float32 in real units, plain layout, or null
 };
+
+// n / d and n % d for 0 <= n < 2^32, d >= 1, with the reciprocal inv = floor((2^32 - 1) / d): the high word of n inv is the
+// quotient or one less.  (Uniform in the kernels: five scalar instructions, where the division is two dozen vector ones in a chain.)
+QF_UNIT_HD inline unsigned qflash_reciprocal(unsigned d) { return 0xffffffffu / d; }
+QF_UNIT_HD inline unsigned qflash_divide(unsigned n, unsigned d, unsigned inv, unsigned* rest) {
+    unsigned q = (unsigned)(((unsigned long long)n * inv) >> 32), r = n - q * d;
+    if (r >= d) { q += 1; r -= d; }
+    *rest = r;
+    return q;
+}
 
 // Number of bytes of a weight table that reaches down to -x_p (multiple of 16).
 QF_UNIT_HD inline int qflash_table_bytes(int x_p) { return (x_p + 1 + 15) & ~15; }
@@ -197,6 +209,7 @@ int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stre
 // whether the launch takes it and fills the win_* fields.  Reads bias, bias_B, bias_H, B, H, N, per_head,
 // qmax, n_cu (0: 256).  Returns win_mode.
 int qflash_plan_win(int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* args);
+void qflash_win_order(QflashKernelArgs* args);      // fills win_rb .. win_inv_bh of such a launch (reads bias, dyn_mask, bias_B, bias_H, B, H)
 int qflash_launch_fwd_win(const QflashKernelArgs& args, int lds_limit, void* stream);
 size_t qflash_win_lds_bytes(int streams, int table_bytes);
 // The same kernel fed with float32 tensors (dynamic quantisation) and a bias in real units.

@@ -383,6 +383,16 @@ int qflash_plan_win_dynamic(int d, int kv_tile, int lds_limit, QflashKernelArgs*
     return plan_win(d, kv_tile, lds_limit, kTableMaxBytes, kWinDynStreams, qflash_win_dyn_lds_bytes, a);
 }
 
+void qflash_win_order(QflashKernelArgs* a) {
+    const bool has_bias = a->bias || a->dyn_mask;
+    const int bias_B = has_bias ? a->bias_B : 1, bias_H = has_bias ? a->bias_H : 1;
+    a->win_rb = a->B / bias_B;
+    a->win_rh = a->H / bias_H;
+    a->win_inv_r = qflash_reciprocal((unsigned)a->win_rb * (unsigned)a->win_rh);
+    a->win_inv_rh = qflash_reciprocal((unsigned)a->win_rh);
+    a->win_inv_bh = qflash_reciprocal((unsigned)bias_H);
+}
+
 // LDS bytes of the kernel that shares out the keys: the table (rounded up to 1 KiB), one part of P V
 // per wavefront, row maxima, row sums and alpha (32 x 20 words each).
 size_t qflash_split_lds_bytes(int d, int waves, int table_bytes) {
