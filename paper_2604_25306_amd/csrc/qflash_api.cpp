@@ -170,6 +170,7 @@ int table_bytes(int64_t x_p) { return qflash_table_bytes((int)x_p); }
 
 // The kernel family the plan chose.
 int launch_attention(QflashKernelArgs& a, int d, int kv_tile, int lds_limit, void* hip_stream) {
+    a.one = a.hw[0];
     if (a.split_waves) return qflash_launch_fwd_split(a, d, lds_limit, hip_stream);
     if (a.win_mode) return qflash_launch_fwd_win(a, lds_limit, hip_stream);
     if (a.cu_mode) return qflash_launch_fwd_cu(a, lds_limit, hip_stream);

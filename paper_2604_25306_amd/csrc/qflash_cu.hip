@@ -32,6 +32,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "qflash_counters.h"
 #include "qflash_derive_device.h"
 #include "qflash_launch.h"
@@ -59,8 +61,8 @@ template <int XM> struct WeightMode { static constexpr int value = XM; };
 // The units of a workgroup, from unit u0 of this wavefront on.  ready(pair, tile, first tile of the unit, first unit of the
 // wavefront) returns when the tile (and what goes with the first one of a unit) is in LDS; next_unit: LDS
 // address of the counter; PH: hc0 are the constants of the table's head, otherwise of the launch.
-template <int XM, bool PH, int BC, class Ready, class PairOf, class HeadOf>
-__device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const QflashHeadConsts& hc0, int table_head, int u0, int units,
+template <int XM, bool PH, int BC, class Args, class Ready, class PairOf, class HeadOf>
+__device__ __forceinline__ void cu_units(const Args& a, const QflashHeadConsts& hc0, int table_head, int u0, int units,
                                          int nblk, int kv_base, int slot, int next_unit, int wave, int trace_base,
                                          Ready ready, PairOf pair_of, HeadOf head_of) {
     constexpr int D = 64;
@@ -164,8 +166,10 @@ __device__ __forceinline__ void cu_units(const QflashKernelArgs& a, const Qflash
 // PH: one set of constants per head.  The pairs are then dealt out so that every workgroup gets its share of
 // those with a table and of those without, the former one head after the other: a workgroup stages
 // the table of its first pair's head, and a unit of a pair of another head computes its weights.
+template <bool PH> using CuArgs = std::conditional_t<PH, QflashKernelArgs, QflashLaunchArgs>;
+
 template <int XM, bool PH, int BC>
-__device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
+__device__ __forceinline__ void cu_body(const CuArgs<PH>& a) {
     constexpr int D = 64;
     const int N = a.N;
     const int rows16 = (N + 15) & ~15;
@@ -319,7 +323,7 @@ __device__ __forceinline__ void cu_body(const QflashKernelArgs& a) {
 }
 
 template <int XM, bool PH, int BC>
-__global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu(const QflashKernelArgs a) {
+__global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu(const CuArgs<PH> a) {
     cu_body<XM, PH, BC>(a);
 }
 
@@ -341,7 +345,7 @@ __global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu(co
 constexpr int kCuDynWorkers = 8;      // at most: wavefronts that start on the units while the others quantise
 
 template <int BC>
-__global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu_dyn(const QflashKernelArgs a) {
+__global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu_dyn(const QflashLaunchArgs a) {
     constexpr int D = 64, kTileBlocks = BC / 16, kWaves = qflash_cu_max_waves(BC);
     constexpr int kDepth = 2;                       // pieces in flight per wavefront
     const int N = a.N;

@@ -72,7 +72,7 @@ __device__ __forceinline__ int bias_word(float x, double unit, double inv) {
 // are needed.  Every wavefront does this for itself.
 struct PartialMaxima {
     float part[3][4];
-    __device__ __forceinline__ void load(const QflashKernelArgs& a) {
+    __device__ __forceinline__ void load(const QflashLaunchArgs& a) {
         const int lane = threadIdx.x & 63;
 #pragma unroll
         for (int t = 0; t < 3; ++t)
@@ -107,7 +107,7 @@ __device__ __forceinline__ int quantise4(v4f x, float r) {
 
 // One lane: constants and score unit from the maxima, to LDS at hc_base (kDynConstBytes).
 typedef __attribute__((address_space(3))) int dyn_lds_int;
-__device__ __forceinline__ void derive_to_lds(const QflashKernelArgs& a, const float (&am)[3], int hc_base) {
+__device__ __forceinline__ void derive_to_lds(const QflashLaunchArgs& a, const float (&am)[3], int hc_base) {
     QflashHeadConsts h;
     double unit;
     derive_on_device(am, a.dyn_sqrt_d, a.out_round, &h, blockIdx.x == 0 ? a.dyn_info : nullptr, &unit);

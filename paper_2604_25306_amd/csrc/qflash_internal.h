@@ -32,7 +32,8 @@ struct QflashHeadWords {
     uint32_t w[5];   // s_inv | x_shift << 18 | p_shift << 22 | has table << 27; exp_mul; p_mul; a_mul; table slot | lut_xp << 8
 };
 
-struct QflashKernelArgs {
+// Arguments of a launch with one set of constants.
+struct QflashLaunchArgs {
     const int8_t* Q;
     const int8_t* K;
     const int8_t* V;
@@ -65,8 +66,7 @@ struct QflashKernelArgs {
     int cu_groups;           // workgroups
     int cu_waves;            // wavefronts per workgroup (at most 16)
     int cu_table_lds;        // LDS bytes reserved for the weight table (a multiple of 1 KiB)
-    int cu_table_heads;      // per-head constants: number of heads with a table, and
-    uint8_t cu_order[kQflashMaxParamHeads];   // the heads, those with a table first
+    int cu_table_heads;      // per-head constants: number of heads with a table
     // ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
     int ring_dma;
     int ring_table_lds;      // LDS bytes reserved for the weight table (a multiple of 1 KiB)
@@ -88,13 +88,13 @@ struct QflashKernelArgs {
     unsigned long long* trace;   // instrumented builds only: [workgroup][wavefront][16] timestamps
 #endif
     int qmax;                // 1: the quantised-maximum variant (not Algorithm 1 as printed; every x_shift must be 0)
-    int per_head;            // 0: hw[0] serves every head; 1: head h uses hw[h] (H <= kQflashMaxParamHeads)
+    int per_head;            // 0: `one` serves every head; 1: head h uses hw[h] of QflashKernelArgs (H <= kQflashMaxParamHeads)
     // Constants computed on the GPU (dynamic quantisation): if set, the kernel reads this device
-    // structure instead of hw[]; exp_mode is then 0 (the host does not know the constants).
+    // structure instead of those words; exp_mode is then 0 (the host does not know the constants).
     const QflashHeadConsts* hc_dev;
     const uint8_t* lut_base;                 // table slot 0
     int device;                              // the GPU of the launch (current when it is made)
-    QflashHeadWords hw[kQflashMaxParamHeads];
+    QflashHeadWords one;
     // where the attention kernel itself quantises (cu_mode or win_mode, and hc_dev, only; nullptr: it does not): Q, K and V are float32, these
     // are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
     const float* dyn_partial;
@@ -102,6 +102,13 @@ struct QflashKernelArgs {
     double dyn_sqrt_d;
     qflash_dynamic_info* dyn_info;           // may be null
     const uint8_t* dyn_mask;                 // win_mode: exclusion mask or null; bias is then float32 in real units, plain layout, or null
+};
+
+// Arguments of any launch: what the host plans and fills, and what kernels that serve per-head constants take.  Kernels
+// that never do take the first part alone, since the host copies the arguments on every launch (1.7 KB and 0.4: 0.2 us a call).
+struct QflashKernelArgs : QflashLaunchArgs {
+    uint8_t cu_order[kQflashMaxParamHeads];   // cu_mode: the heads, those with a table first
+    QflashHeadWords hw[kQflashMaxParamHeads];
 };
 
 // n / d and n % d for 0 <= n < 2^32, d >= 1, with the reciprocal inv = floor((2^32 - 1) / d): the high word of n inv is the

@@ -49,13 +49,13 @@ constexpr int kRowPitch = 20;      // words per query row of the tables of row m
 __device__ __forceinline__ int part_offset(int q, int g, int row) { return 1024 * q + 512 * g + 16 * (row ^ ((q + 4 * g) & 7)); }
 
 // (batch, head) pair of a unit = unit / n_qtiles, with the reciprocal made on the host.
-__device__ __forceinline__ int split_pair(const QflashKernelArgs& a, int unit) {
+__device__ __forceinline__ int split_pair(const QflashLaunchArgs& a, int unit) {
     return a.n_qtiles == 1 ? unit : (int)__umulhi((unsigned)unit, a.split_qtiles_inv);
 }
 
 // KB: 32-key blocks per wavefront (1 or 2).
-template <int D, int BC, int BIAS, int XM, int KB>
-__device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
+template <int D, int BC, int BIAS, int XM, int KB, class Args>
+__device__ __forceinline__ void split_body(const Args& a) {
     constexpr bool KZ = XM == kExpShift0;
     constexpr bool SB = XM == kExpTable && !BIAS;   // scores (and maxima) carry the offset 2^30
     constexpr int kExcluded = SB ? kMaskedBiased : kNegBig;
@@ -358,8 +358,8 @@ __device__ __forceinline__ void split_body(const QflashKernelArgs& a) {
 }
 
 // kExpAuto: per workgroup, table if the constants of its head have one (a.exp_mode of the launch).
-template <int D, int BC, int BIAS, int XM, int KB>
-__global__ __launch_bounds__(KB == 1 ? 1024 : 512) void qflash_fwd_split(const QflashKernelArgs a) {
+template <int D, int BC, int BIAS, int XM, int KB, class Args>
+__global__ __launch_bounds__(KB == 1 ? 1024 : 512) void qflash_fwd_split(const Args a) {
     if constexpr (XM == kExpAuto) {
         const int unit = (int)(blockIdx.x & 7) * a.units_per_xcd + (int)(blockIdx.x >> 3);
         if (unit >= a.n_units) return;
@@ -372,7 +372,9 @@ __global__ __launch_bounds__(KB == 1 ? 1024 : 512) void qflash_fwd_split(const Q
 
 template <int D, int BC, int BIAS, int XM, int KB>
 int launch_split(const QflashKernelArgs& a, size_t lds, int lds_limit, hipStream_t st) {
-    return qflash_launch_kernel<qflash_fwd_split<D, BC, BIAS, XM, KB>>(a, (unsigned)(8 * a.units_per_xcd), (unsigned)(64 * a.split_waves), lds, lds_limit, st);
+    const unsigned grid = (unsigned)(8 * a.units_per_xcd), threads = (unsigned)(64 * a.split_waves);
+    if (a.per_head) return qflash_launch_kernel<qflash_fwd_split<D, BC, BIAS, XM, KB, QflashKernelArgs>>(a, grid, threads, lds, lds_limit, st);
+    return qflash_launch_kernel<qflash_fwd_split<D, BC, BIAS, XM, KB, QflashLaunchArgs>>(a, grid, threads, lds, lds_limit, st);
 }
 
 template <int D, int BC, int BIAS, int KB>

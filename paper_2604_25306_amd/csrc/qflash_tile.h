@@ -669,7 +669,7 @@ __device__ __forceinline__ void normalise_store(const RowState<D>& st, int8_t* O
 // With dynamic quantisation they were computed on the GPU and live in device memory: read field
 // by field into scalar registers (selecting between the two structures by pointer would turn every
 // access, the table loads included, into generic-address loads).
-__device__ __forceinline__ QflashHeadConsts head_consts_or_dev(const QflashKernelArgs& a, QflashHeadConsts h) {
+__device__ __forceinline__ QflashHeadConsts head_consts_or_dev(const QflashLaunchArgs& a, QflashHeadConsts h) {
     if (a.hc_dev) {
         const int* g = (const int*)a.hc_dev;     // x_shift, s_inv, exp_mul, p_mul, p_shift, a_mul, x_floor
         h.x_shift = __builtin_amdgcn_readfirstlane(g[0]);
@@ -688,6 +688,9 @@ __device__ __forceinline__ QflashHeadConsts head_consts_or_dev(const QflashKerne
     }
     return h;
 }
+__device__ __forceinline__ QflashHeadConsts head_consts(const QflashLaunchArgs& a, int) {
+    return head_consts_or_dev(a, qflash_unpack_head(a.one, a.lut_base));
+}
 __device__ __forceinline__ QflashHeadConsts head_consts(const QflashKernelArgs& a, int bh) {
     return head_consts_or_dev(a, qflash_unpack_head(a.hw[a.per_head ? bh % a.H : 0], a.lut_base));
 }
@@ -701,7 +704,7 @@ static_assert(offsetof(QflashHeadConsts, x_floor) == 24 && offsetof(QflashHeadCo
 // 16-byte word of lane (li, g) in group a4 of column block cb holds
 // bias[32*rb + li][32*cb + 8*a4 + 4*g + 0..3], which is exactly what the lane adds to its four
 // scores of that group, so one instruction of the wavefront reads 1 KiB in a row.
-__device__ __forceinline__ const int32_t* bias_lane_base(const QflashKernelArgs& a, int bh, int row0, int i,
+__device__ __forceinline__ const int32_t* bias_lane_base(const QflashLaunchArgs& a, int bh, int row0, int i,
                                                         int li, int g) {
     const int b = bh / a.H, h = bh % a.H, N = a.N;
     const unsigned slice32 = (unsigned)(b % a.bias_B) * (unsigned)a.bias_H + (unsigned)(h % a.bias_H);   // (below 2^31)

@@ -147,7 +147,7 @@ struct WinPair {      // where a run stands: pair t of the launch order
 struct WinOrder {
     int H, bias_B, bias_H, Rb, Rh;      // Rb, Rh: replicas of a slice (the host checked divisibility)
     unsigned inv_R, inv_Rh, inv_bH;
-    __device__ __forceinline__ explicit WinOrder(const QflashKernelArgs& a, bool has_bias) {
+    __device__ __forceinline__ explicit WinOrder(const QflashLaunchArgs& a, bool has_bias) {
         H = a.H;
         bias_B = has_bias ? a.bias_B : 1;
         bias_H = has_bias ? a.bias_H : 1;
@@ -190,7 +190,7 @@ __device__ __forceinline__ int win_v_lane(int lane) {
 }
 
 template <int XM, bool PLAIN>
-__device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
+__device__ __forceinline__ void win_body(const QflashLaunchArgs& a) {
     constexpr int D = 32;
     round_down();
     const int N = a.N;
@@ -355,7 +355,7 @@ __device__ __forceinline__ void win_body(const QflashKernelArgs& a) {
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
 template <int XM>
-__device__ __forceinline__ void win_dyn_compute(const QflashKernelArgs& a, const QflashHeadConsts& hc, double unit, const WinOrder& order,
+__device__ __forceinline__ void win_dyn_compute(const QflashLaunchArgs& a, const QflashHeadConsts& hc, double unit, const WinOrder& order,
                                                 int t0, int t1, int half, int ring, int filled, int emptied) {
     constexpr int D = 32;
     round_down();                  // (single precision only: the bias is converted in double precision)
@@ -408,7 +408,7 @@ __device__ __forceinline__ void win_dyn_compute(const QflashKernelArgs& a, const
     }
 }
 
-__global__ __launch_bounds__(256 * kWinDynStreams) void qflash_fwd_win_dyn(const QflashKernelArgs a) {
+__global__ __launch_bounds__(256 * kWinDynStreams) void qflash_fwd_win_dyn(const QflashLaunchArgs a) {
     constexpr int D = 32;
     constexpr int kDepth = 1;                     // tensors in flight per quantising wavefront
     const int N = a.N;
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(256 * kWinDynStreams) void qflash_fwd_win_dyn(const
 
 // PLAIN: a bias in the plain [N,N] layout; else a packed one or none.
 template <int XM, bool PLAIN>
-__global__ __launch_bounds__(1024) void qflash_fwd_win(const QflashKernelArgs a) {
+__global__ __launch_bounds__(1024) void qflash_fwd_win(const QflashLaunchArgs a) {
     if constexpr (XM == kExpAuto) {
         if (head_consts(a, 0).lut_bytes > 0) win_body<kExpTable, PLAIN>(a);
         else win_body<kExpShift, PLAIN>(a);
