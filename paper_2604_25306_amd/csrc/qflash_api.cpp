@@ -298,6 +298,7 @@ int attention_impl(qflash_ctx* ctx, const int8_t* Q, const int8_t* K, const int8
     qflash_plan_split(d, lds_limit, static_table ? 0 : table_hint, &a);
     if (dyn && ((!a.cu_mode && !a.win_mode) || a.split_waves)) return QFLASH_ERR_SHAPE;    // (the caller planned the same launch)
     if (a.win_mode) qflash_win_order(&a);
+    if (a.cu_mode) qflash_cu_reciprocals(&a);
     const bool takes_table = a.resident || a.ring_dma || a.split_waves;
     // wave priority by dispatch round: only for launches of two to four rounds (0 = off)
     if (a.n_units <= n_cu || a.n_units > 4 * n_cu) a.n_cu = 0;

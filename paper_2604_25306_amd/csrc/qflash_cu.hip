@@ -24,6 +24,10 @@
 // (qflash_tile.h), per head 21.7 -> 18.9.  What is left: LDS 9 us of look-ups and operand reads, vector issue 7, 3 us until
 // every wavefront has data, five units for sixteen wavefronts at the end.
 //
+// A workgroup requests its first tile when a wavefront has found out what to request; the quotients it needs for that are made with reciprocals
+// from the host (or counted up), not by division: 768 pairs of 197 tokens 15.0 -> 14.7 us, per head, where two were of 64 bits, 18.7 -> 18.0
+// and 20.8 -> 19.4 with tiles of 128, 180 of 256 from the static entry point 9.6 -> 8.9.
+//
 // KV tiles of 128: more than 128 registers leave three wavefronts to a SIMD, so workgroups are at most twelve; still ahead of
 // the resident kernel (768 pairs of 197 tokens 22.8 -> 18.6 us, 480 of 256 19.4 -> 15.0, 720 of 130 16.8 -> 12.4).
 //
@@ -88,13 +92,14 @@ __device__ __forceinline__ void cu_units(const Args& a, const QflashHeadConsts& 
         int g_ = g;
         asm volatile("" : "+v"(g_));
         const int n_full = N_ / BC, rem = N_ - n_full * BC;
-        const int h = u / nblk, blk = u - h * nblk;
+        const int h = qflash_small_quotient(u, a.cu_inv_nblk), blk = u - h * nblk;
         const int Kb = kv_base + 3 * h * slot, Vb = Kb + slot, Qb = Vb + slot;
         const int row0 = 32 * blk, i = row0 + li;
         RowState<D> st;
         st.l = 0;
         v4i qreg[2];
-        const QflashHeadConsts hc = PH ? head_consts(a, head_of(h)) : hc0;
+        QflashHeadConsts hc = hc0;
+        if constexpr (PH) hc = own_head_consts(a, head_of(h));
         const ExpConst<> c = PH ? make_exp_const(hc) : c0;
 #define QF_TILE(FULL_, FIRST_, J_, NV_, NG_)                                                               \
         ready(h, J_, FIRST_, first_unit);                                                                  \
@@ -183,11 +188,13 @@ __device__ __forceinline__ void cu_body(const CuArgs<PH>& a) {
     [[maybe_unused]] int pair_l = 0, head_l = 0, table_head = -1;
     if constexpr (PH) {
         const int P = a.B * a.H, T = a.cu_table_heads * a.B;
-        const int t0 = (int)((long long)head0 * T / P), n_t = (int)((long long)(head0 + n_heads) * T / P) - t0;
+        unsigned rest, batch;
+        const int t0 = (int)qflash_divide((unsigned)head0 * (unsigned)T, (unsigned)P, a.cu_inv_pairs, &rest);
+        const int n_t = (int)qflash_divide((unsigned)(head0 + n_heads) * (unsigned)T, (unsigned)P, a.cu_inv_pairs, &rest) - t0;
         const int h = min((int)(threadIdx.x & 63), n_heads - 1);
         const int x = h < n_t ? t0 + h : T + (head0 - t0) + (h - n_t);          // position in head order
-        head_l = a.cu_order[x / a.B];
-        pair_l = (x % a.B) * a.H + head_l;
+        head_l = a.cu_order[qflash_divide((unsigned)x, (unsigned)a.B, a.cu_inv_b, &batch)];
+        pair_l = (int)batch * a.H + head_l;
         if (n_t > 0) table_head = __builtin_amdgcn_readfirstlane(head_l);
     }
     auto pair_of = [&](int h) { return PH ? __builtin_amdgcn_readlane(pair_l, h) : head0 + h; };
@@ -216,7 +223,9 @@ __device__ __forceinline__ void cu_body(const CuArgs<PH>& a) {
     QF_T(1);
 
     // constants of the launch; PH: of the table's head, each unit then takes those of its own
-    const QflashHeadConsts hc0 = PH ? head_consts(a, max(table_head, 0)) : head_consts(a, 0);
+    QflashHeadConsts hc0;
+    if constexpr (PH) hc0 = own_head_consts(a, max(table_head, 0));
+    else hc0 = head_consts(a, 0);
 
     // ---- loop-invariant registers
     const int nb16 = rows16 >> 4;                   // 1 KiB loads per tensor of a pair
@@ -234,8 +243,8 @@ __device__ __forceinline__ void cu_body(const CuArgs<PH>& a) {
     //      loads (they have had a whole tile's time) and adds 1 to the counters of all other tiles.
     //      Before any tile of any unit a wavefront waits until the counter of (pair, tile) has reached
     //      the size of the group.
-    const int last_group = (n_waves - 1) / nblk;
-    const int my_group = wave / nblk;
+    const int last_group = qflash_small_quotient(n_waves - 1, a.cu_inv_nblk);
+    const int my_group = qflash_small_quotient(wave, a.cu_inv_nblk);
     const int group_size = min(nblk, n_waves - my_group * nblk);
     const int member = wave - my_group * nblk;
     const int n_extra = my_group == last_group ? n_heads - 1 - my_group : 0;     // whole pairs
@@ -268,8 +277,9 @@ __device__ __forceinline__ void cu_body(const CuArgs<PH>& a) {
         };
         auto load_kv = [&](int h, int x_lo, int x_hi, int mi, int np) {
             const size_t head_off = (size_t)pair_of(h) * N * D;
-            const int first = x_lo + ((mi - x_lo) % np + np) % np;
-            for (int x = first; x < x_hi; x += np) {
+            int x = mi;                                             // (mi < np; counted up: a division takes longer)
+            while (x < x_lo) x += np;
+            for (; x < x_hi; x += np) {
                 const int b = x >> 1;
                 load_1k_to_lds(((x & 1) ? a.V : a.K) + head_off + 1024 * b, b == nb16 - 1 ? off_last : off_norm,
                                kv_base + (3 * h + (x & 1)) * slot + 1024 * b);
@@ -358,7 +368,7 @@ __global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu_dy
     const int units = n_heads * nblk;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int early = min(n_heads, max(1, kCuDynWorkers / nblk));     // pairs that everybody quantises first
+    const int early = min(n_heads, max(1, qflash_small_quotient(kCuDynWorkers, a.cu_inv_nblk)));     // pairs that everybody quantises first
     const int workers = min(early * nblk, kCuDynWorkers);
 
     // LDS map: as above, then [constants ready][wavefronts done with the table][the constants]
@@ -382,13 +392,12 @@ __global__ __launch_bounds__(64 * qflash_cu_max_waves(BC)) void qflash_fwd_cu_dy
         // ---- pieces: index x of the launch's share -> pair x / per; inside a pair the blocks of Q, then
         //      those of K and V in turn
         const int per = 3 * nb16;
-        const unsigned per_inv = (unsigned)(0x100000000ull / (unsigned)per) + 1u;
         struct Piece { int x, h, y; };               // h < 0: none left
         const int first_end = early * per, end = n_heads * per;
         auto place = [&](int x) {
             Piece p;
             p.x = x;
-            p.h = x < end ? (int)__umulhi((unsigned)x, per_inv) : -1;
+            p.h = x < end ? (int)__umulhi((unsigned)x, a.cu_inv_per) : -1;
             p.y = x - p.h * per;
             return p;
         };
@@ -498,6 +507,9 @@ int qflash_launch_fwd_cu(const QflashKernelArgs& a, int lds_limit, void* stream)
     if (!a.cu_mode || a.cu_heads < 1 || a.cu_waves < 1 || a.cu_waves > qflash_cu_max_waves(a.kv_tile) || a.N > 256 || a.bias ||
         (a.kv_tile != 64 && a.kv_tile != 128))
         return (int)hipErrorInvalidValue;
+    // (what qflash_small_quotient is exact for; products of two numbers of pairs, per head, in 32 bits)
+    const long long nblk = (a.N + 31) / 32;
+    if (a.cu_heads * nblk * nblk >= 65536 || (a.per_head && (long long)a.B * a.H >= 65536)) return (int)hipErrorInvalidValue;
     if (a.dyn_partial && (a.per_head || a.dyn_partials > 256)) return (int)hipErrorInvalidValue;
     if (!a.dyn_partial && a.hc_dev) return (int)hipErrorInvalidValue;
     if (a.per_head && (a.cu_table_heads < 0 || a.cu_table_heads > a.H || a.H > kQflashMaxParamHeads)) return (int)hipErrorInvalidValue;

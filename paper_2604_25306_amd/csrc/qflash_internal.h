@@ -67,6 +67,7 @@ struct QflashLaunchArgs {
     int cu_waves;            // wavefronts per workgroup (at most 16)
     int cu_table_lds;        // LDS bytes reserved for the weight table (a multiple of 1 KiB)
     int cu_table_heads;      // per-head constants: number of heads with a table
+    unsigned cu_inv_nblk, cu_inv_per, cu_inv_pairs, cu_inv_b;   // reciprocals (qflash_cu_reciprocals)
     // ring fed by direct global-to-LDS loads (no bias; set by qflash_plan_fwd and qflash_plan_ring): 1 if the launch takes it
     int ring_dma;
     int ring_table_lds;      // LDS bytes reserved for the weight table (a multiple of 1 KiB)
@@ -87,19 +88,19 @@ struct QflashLaunchArgs {
 #ifdef QF_TRACE
     unsigned long long* trace;   // instrumented builds only: [workgroup][wavefront][16] timestamps
 #endif
+    int device;              // the GPU of the launch (current when it is made)
+    // where the attention kernel itself quantises (cu_mode or win_mode, and hc_dev, only; nullptr: it does not): Q, K and V are float32, these
+    // are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
+    const float* dyn_partial;
+    double dyn_sqrt_d;
     int qmax;                // 1: the quantised-maximum variant (not Algorithm 1 as printed; every x_shift must be 0)
     int per_head;            // 0: `one` serves every head; 1: head h uses hw[h] of QflashKernelArgs (H <= kQflashMaxParamHeads)
     // Constants computed on the GPU (dynamic quantisation): if set, the kernel reads this device
     // structure instead of those words; exp_mode is then 0 (the host does not know the constants).
     const QflashHeadConsts* hc_dev;
     const uint8_t* lut_base;                 // table slot 0
-    int device;                              // the GPU of the launch (current when it is made)
     QflashHeadWords one;
-    // where the attention kernel itself quantises (cu_mode or win_mode, and hc_dev, only; nullptr: it does not): Q, K and V are float32, these
-    // are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
-    const float* dyn_partial;
     int dyn_partials;
-    double dyn_sqrt_d;
     qflash_dynamic_info* dyn_info;           // may be null
     const uint8_t* dyn_mask;                 // win_mode: exclusion mask or null; bias is then float32 in real units, plain layout, or null
 };
@@ -107,9 +108,14 @@ struct QflashLaunchArgs {
 // Arguments of any launch: what the host plans and fills, and what kernels that serve per-head constants take.  Kernels
 // that never do take the first part alone, since the host copies the arguments on every launch (1.7 KB and 0.4: 0.2 us a call).
 struct QflashKernelArgs : QflashLaunchArgs {
-    uint8_t cu_order[kQflashMaxParamHeads];   // cu_mode: the heads, those with a table first
     QflashHeadWords hw[kQflashMaxParamHeads];
+    uint8_t cu_order[kQflashMaxParamHeads];   // cu_mode: the heads, those with a table first
 };
+
+#ifndef QF_TRACE
+// What is read to find the constants lies in one line of memory (`one` across two: 0.2 us on every launch of the ring).
+static_assert(offsetof(QflashLaunchArgs, per_head) / 64 == (offsetof(QflashLaunchArgs, one) + sizeof(QflashHeadWords) - 1) / 64, "order of the fields");
+#endif
 
 // n / d and n % d for 0 <= n < 2^32, d >= 1, with the reciprocal inv = floor((2^32 - 1) / d): the high word of n inv is the
 // quotient or one less.  (Uniform in the kernels: five scalar instructions, where the division is two dozen vector ones in a chain.)
@@ -120,6 +126,10 @@ QF_UNIT_HD inline unsigned qflash_divide(unsigned n, unsigned d, unsigned inv, u
     *rest = r;
     return q;
 }
+
+// n / d for n d < 2^16, with the reciprocal inv = 2^16 / d + 1 (floor): two instructions.
+QF_UNIT_HD inline unsigned qflash_small_reciprocal(unsigned d) { return 65536u / d + 1u; }
+QF_UNIT_HD inline int qflash_small_quotient(int n, unsigned inv) { return (int)(((unsigned)n * inv) >> 16); }
 
 // Number of bytes of a weight table that reaches down to -x_p (multiple of 16).
 QF_UNIT_HD inline int qflash_table_bytes(int x_p) { return (x_p + 1 + 15) & ~15; }
@@ -209,6 +219,9 @@ int qflash_plan_cu_heads(int BH, int N, int d, int kv_tile, int lds_limit, Qflas
 // The same kernel fed with float32 tensors (dynamic quantisation).
 int qflash_plan_cu_dynamic(int BH, int N, int d, int kv_tile, int lds_limit, QflashKernelArgs* args);
 constexpr int kCuDynExtraLds = 64;           // LDS of that variant beyond qflash_cu_lds_bytes
+// Fills the reciprocals of such a launch: of the query blocks of a pair (qflash_small_quotient), of the 16-row pieces of a pair's three
+// tensors (its kernel from float32), and, for qflash_divide, of the pairs and of B (its kernel for per-head constants).
+void qflash_cu_reciprocals(QflashKernelArgs* args);
 int qflash_launch_fwd_cu(const QflashKernelArgs& args, int lds_limit, void* stream);
 
 // The persistent kernel for windowed attention (33 to 64 tokens, 32 features, one KV tile, no bias or a

@@ -198,6 +198,13 @@ static int plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_b
     return 1;
 }
 
+void qflash_cu_reciprocals(QflashKernelArgs* a) {
+    a->cu_inv_nblk = qflash_small_reciprocal((unsigned)((a->N + 31) / 32));
+    a->cu_inv_per = (unsigned)(0x100000000ull / (unsigned)(3 * ((a->N + 15) / 16))) + 1u;
+    a->cu_inv_pairs = qflash_reciprocal((unsigned)a->B * (unsigned)a->H);
+    a->cu_inv_b = qflash_reciprocal((unsigned)a->B);
+}
+
 int qflash_plan_cu(int BH, int N, int d, int kv_tile, int lds_limit, int table_bytes, QflashKernelArgs* a) {
     a->cu_mode = 0;
     return kv_tile == 64 ? plan_cu(BH, N, d, kv_tile, lds_limit, table_bytes, a) : 0;

@@ -692,7 +692,11 @@ __device__ __forceinline__ QflashHeadConsts head_consts(const QflashLaunchArgs& 
     return head_consts_or_dev(a, qflash_unpack_head(a.one, a.lut_base));
 }
 __device__ __forceinline__ QflashHeadConsts head_consts(const QflashKernelArgs& a, int bh) {
-    return head_consts_or_dev(a, qflash_unpack_head(a.hw[a.per_head ? bh % a.H : 0], a.lut_base));
+    return head_consts_or_dev(a, qflash_unpack_head(a.per_head ? a.hw[bh % a.H] : a.one, a.lut_base));
+}
+// Of head h of a launch with per-head constants.
+__device__ __forceinline__ QflashHeadConsts own_head_consts(const QflashKernelArgs& a, int h) {
+    return qflash_unpack_head(a.hw[h], a.lut_base);
 }
 static_assert(offsetof(QflashHeadConsts, x_floor) == 24 && offsetof(QflashHeadConsts, lut_xp) == 28 &&
               offsetof(QflashHeadConsts, lut_bytes) == 32 && offsetof(QflashHeadConsts, lut) == 40,

@@ -1,5 +1,5 @@
-"""The order in which windowed launches take their pairs: the quotients that the kernel makes of reciprocals from the host,
-against Python integers, and every pair once."""
+"""The quotients that kernels make of reciprocals from the host, against Python integers, and the order in which windowed launches
+take their pairs with them: every pair once."""
 import ctypes
 import os
 import shutil
@@ -13,6 +13,8 @@ SHIM = """
 #include <cstring>
 #include "qflash_internal.h"
 extern "C" unsigned divide(unsigned n, unsigned d, unsigned* rest) { return qflash_divide(n, d, qflash_reciprocal(d), rest); }
+extern "C" int small(int n, unsigned d) { return qflash_small_quotient(n, qflash_small_reciprocal(d)); }
+extern "C" unsigned pieces(int N) { static QflashKernelArgs a; a.N = N; a.B = a.H = 1; qflash_cu_reciprocals(&a); return a.cu_inv_per; }
 extern "C" void order(int bias, int mask, int bias_B, int bias_H, int B, int H, unsigned* out) {
     static QflashKernelArgs a;
     std::memset(&a, 0, sizeof a);
@@ -48,6 +50,17 @@ def test_quotients(lib):
         near = {m * d + e for m in (0, 1, 2, 3, 1000, top // d - 1, top // d) for e in (-1, 0, 1, d - 1)}
         for n in sorted(x for x in near | {0, 1, 2 ** 16, 2 ** 31, top} if 0 <= x <= top):
             assert (lib.divide(n, d, ctypes.byref(rest)), rest.value) == divmod(n, d), (n, d)
+
+
+def test_small_quotients(lib):
+    for d in range(1, 9):                          # query blocks of at most 256 tokens
+        for n in range(65536 // d):
+            assert lib.small(n, d) == n // d
+    lib.pieces.restype = ctypes.c_uint
+    for N in range(1, 257):                        # pieces of sixteen rows of a pair's three tensors: the high word of the product
+        per = 3 * ((N + 15) // 16)
+        inv = lib.pieces(N)
+        assert all(x * inv >> 32 == x // per for x in list(range(64 * per)) + [2 ** 24])
 
 
 @pytest.mark.parametrize("bias,mask,bias_B,bias_H,B,H", [(1, 0, 4, 3, 12, 6), (0, 1, 4, 1, 4, 5), (1, 1, 1, 6, 7, 6), (0, 0, 1, 1, 5, 3), (0, 0, 9, 9, 5, 3)])
