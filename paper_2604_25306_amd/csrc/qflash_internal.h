@@ -50,10 +50,10 @@ struct QflashLaunchArgs {
     int waves_per_head;      // wavefronts that serve one (batch, head) pair inside a workgroup
     int heads_per_wg;        // > 1 only when a pair fits one workgroup (n_qtiles == 1)
     int same_head;           // heads_per_wg > 1: the pairs of a workgroup are one head of consecutive batch elements
-    int resident;            // 1: whole K/V of a head staged in LDS, 0: streamed per KV tile
+    unsigned split_qtiles_inv;   // kernel that shares out the keys of 32 query rows: ceil(2^32 / n_qtiles), unit / n_qtiles is the high word of the product
     int pipelined;           // resident only: K/V tiles are staged one ahead of their use
     int ring;                // pipelined only: LDS holds two KV tiles (in use / being staged), not the whole sequence
-    int kv_tile;             // KV tile size the plan was made for
+    int split_table_lds;     // that kernel: LDS bytes reserved for the weight table (a multiple of 1 KiB)
     int n_cu;                // compute units of the device if wave priority alternates by dispatch round, else 0
     // weight mode of the launch (uniform over heads): 2 = every head reads its table,
     // 1 = arithmetic with x_shift == 0 for every head, 0 = arithmetic, 3 = per workgroup: table if the
@@ -80,41 +80,47 @@ struct QflashLaunchArgs {
     int win_table_lds;       // LDS bytes reserved for the weight table (a multiple of 1 KiB)
     int win_rb, win_rh;      // replicas of a bias slice in batch and heads, and the reciprocals of their
     unsigned win_inv_r, win_inv_rh, win_inv_bh;   // product, the second and bias_H (qflash_win_order, qflash_divide)
-    // kernel that shares out the keys of 32 query rows (qflash_plan_split): wavefronts per workgroup, 0 if not taken
-    int split_waves;
-    int split_blocks;        // 32-key blocks per wavefront: 1 or 2
-    unsigned split_qtiles_inv;   // ceil(2^32 / n_qtiles): unit / n_qtiles is the high word of the product
-    int split_table_lds;     // LDS bytes reserved for the weight table (a multiple of 1 KiB)
+    // where the attention kernel itself quantises (cu_mode or win_mode, and hc_dev, only; dyn_partial nullptr: it does not): Q, K and V are
+    // float32, dyn_partial are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
+    int dyn_partials;
+    const float* dyn_partial;
+    double dyn_sqrt_d;
+    qflash_dynamic_info* dyn_info;           // may be null
+    const uint8_t* dyn_mask;                 // win_mode: exclusion mask or null; bias is then float32 in real units, plain layout, or null
 #ifdef QF_TRACE
     unsigned long long* trace;   // instrumented builds only: [workgroup][wavefront][16] timestamps
 #endif
-    int device;              // the GPU of the launch (current when it is made)
-    // where the attention kernel itself quantises (cu_mode or win_mode, and hc_dev, only; nullptr: it does not): Q, K and V are float32, these
-    // are the partial maxima of their magnitudes, dyn_partials per tensor, and the kernel derives the constants
-    const float* dyn_partial;
-    double dyn_sqrt_d;
-    int qmax;                // 1: the quantised-maximum variant (not Algorithm 1 as printed; every x_shift must be 0)
-    int per_head;            // 0: `one` serves every head; 1: head h uses hw[h] of QflashKernelArgs (H <= kQflashMaxParamHeads)
     // Constants computed on the GPU (dynamic quantisation): if set, the kernel reads this device
-    // structure instead of those words; exp_mode is then 0 (the host does not know the constants).
+    // structure instead of the words below; exp_mode is then 0 (the host does not know the constants).
     const QflashHeadConsts* hc_dev;
     const uint8_t* lut_base;                 // table slot 0
-    QflashHeadWords one;
-    int dyn_partials;
-    qflash_dynamic_info* dyn_info;           // may be null
-    const uint8_t* dyn_mask;                 // win_mode: exclusion mask or null; bias is then float32 in real units, plain layout, or null
+    QflashHeadWords one;     // the constants if one set serves every head (hw[0] of QflashKernelArgs holds it too)
+    int per_head;            // 0: it does; 1: head h uses hw[h] (H <= kQflashMaxParamHeads)
 };
 
 // Arguments of any launch: what the host plans and fills, and what kernels that serve per-head constants take.  Kernels
-// that never do take the first part alone, since the host copies the arguments on every launch (1.7 KB and 0.4: 0.2 us a call).
+// that never do take the first part alone, since the host copies the arguments on every launch (1.7 KB and 0.3: 0.2 us a call).
 struct QflashKernelArgs : QflashLaunchArgs {
     QflashHeadWords hw[kQflashMaxParamHeads];
     uint8_t cu_order[kQflashMaxParamHeads];   // cu_mode: the heads, those with a table first
+    // read by the host alone
+    int resident;            // 1: whole K/V of a head staged in LDS, 0: streamed per KV tile
+    int kv_tile;             // KV tile size the plan was made for
+    int qmax;                // 1: the quantised-maximum variant (not Algorithm 1 as printed; every x_shift must be 0)
+    // kernel that shares out the keys of 32 query rows (qflash_plan_split): wavefronts per workgroup, 0 if not taken
+    int split_waves;
+    int split_blocks;        // 32-key blocks per wavefront: 1 or 2
+    int device;              // the GPU of the launch (current when it is made)
 };
 
 #ifndef QF_TRACE
-// What is read to find the constants lies in one line of memory (`one` across two: 0.2 us on every launch of the ring).
-static_assert(offsetof(QflashLaunchArgs, per_head) / 64 == (offsetof(QflashLaunchArgs, one) + sizeof(QflashHeadWords) - 1) / 64, "order of the fields");
+// What is read to find the constants lies in one line of 64 bytes, for either kind of arguments, and what the kernel that shares out
+// keys needs to find its unit in the line of n_qtiles.  Each line more is waited for at the start, 0.1 us with the arguments in L2 and
+// 0.3 when the host has just written them.  hw[0] apart from per_head: per-head launches of the ring (78 pairs of 618 tokens) 19.9 us a
+// call against 19.7; split_qtiles_inv apart too: 3 pairs of 197 per head 4.75 and 6.1 a call against 4.64 and 5.7, 16 of 50 3.75 and 5.4
+// against 3.65 and 5.1; `one` across two lines: 0.2 on every launch of the ring.
+static_assert(offsetof(QflashLaunchArgs, hc_dev) % 64 == 0 && sizeof(QflashLaunchArgs) - offsetof(QflashLaunchArgs, hc_dev) + sizeof(QflashHeadWords) <= 64 &&
+              offsetof(QflashLaunchArgs, split_table_lds) / 64 == offsetof(QflashLaunchArgs, n_qtiles) / 64, "order of the fields");
 #endif
 
 // n / d and n % d for 0 <= n < 2^32, d >= 1, with the reciprocal inv = floor((2^32 - 1) / d): the high word of n inv is the
