@@ -209,13 +209,18 @@ __device__ __forceinline__ void win_body(const QflashLaunchArgs& a) {
         for (int it = wave; it < ((hc.lut_bytes + 1023) >> 10); it += n_waves)
             load_1k_to_lds((const int8_t*)hc.lut + 1024 * it, 16 * lane, lds0 + 1024 * it);
     }
-    // The only barrier: the table is in place.  The first pair's five loads are requested ahead of it, behind those of the table, and
-    // stay in flight across it; the table's latency, the pair's and (before the host made the reciprocals) six integer
-    // divisions used to follow one another: 384 pairs with a packed bias 3.73 -> 3.36 us, 768 with a plain one 4.35 -> 3.88,
-    // 12288 17.9 -> 17.4.  (The bias ahead of the barrier too: 5472 pairs 10.6 -> 11.3, every wavefront then waits for the last of all loads.)
-    auto table_in_place = [] {
+    // The only barrier: the table is in place.  The first pair's five loads are requested ahead of it, behind those of the table, and stay in
+    // flight across it: 384 pairs with a packed bias 3.73 -> 3.36 us, 4608 of 64 tokens 12.5 -> 12.1.  Behind it (late) where a compute
+    // unit has more than eight wavefronts and their bias would come behind the K and V of all of them: with a plain bias, as
+    // many bytes in scattered pieces, and where every wavefront has one pair only.  By turns as well, with a plain bias: that of the first
+    // wavefronts then comes ahead of the K and V of the last.  Inputs from memory: 1632 pairs of 64 tokens, plain, 9.26 us, late 8.97, by
+    // turns 8.62; 4608 13.3, 13.3, 12.9; packed, 1632 of 64 7.84, late 7.59, 1536 of 64 equal.  (128 to 450 cycles a turn measured the
+    // same.  The bias ahead of the barrier as well: 5472 pairs 10.6 -> 11.3, every wavefront then waits for the last of all loads.)
+    const bool late = a.win_streams > 4 && (PLAIN || a.win_chunk == 1);
+    auto table_in_place = [late] {
         if (XM != kExpTable) return;
-        asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+        if (late) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
         __syncthreads();
     };
 
@@ -225,7 +230,7 @@ __device__ __forceinline__ void win_body(const QflashLaunchArgs& a) {
     const int T = a.B * a.H;
     const int t0 = sid * a.win_chunk, t1 = min(t0 + a.win_chunk, T);
     if ((wave >> 1) >= a.win_streams || t0 >= t1) {
-        if (XM == kExpTable) {
+        if (XM == kExpTable) {            // (its share of the table, none of the five)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
         }
@@ -304,16 +309,20 @@ __device__ __forceinline__ void win_body(const QflashLaunchArgs& a) {
     //      pair late, right after the only wait of the iteration, so that neither the loads nor the
     //      store are waited for while they are young.  Pairs of one bias slice form the inner loop:
     //      the accumulator input is invariant there.
+    if (late) {
+        table_in_place();
+        if (PLAIN)
+            for (int k = 0; k < (wave >> 2); ++k) __builtin_amdgcn_s_sleep(3);
+    }
     issue_loads(p, 0);
+    if (!late) table_in_place();
     int parity = 0;
     v4i o_prev = v4i{0, 0, 0, 0};
     size_t o_prev_off = 0;
     bool have_prev = false;
     const unsigned o_lane = (unsigned)(row * D + 16 * g);
     int t = t0;
-    table_in_place();
-    load_slice(p.s_idx);
-    for (;;) {
+    auto run_slice = [&] {
         const int t_end = min(t1, t + order.left_in_slice(p));       // pairs of this slice from here on
         for (; t < t_end; ++t) {
             // everything in flight belongs to this pair (or is the store of the one before the last)
@@ -329,8 +338,22 @@ __device__ __forceinline__ void win_body(const QflashLaunchArgs& a) {
             have_prev = true;
             parity ^= 1;
         }
-        if (t >= t1) break;
+    };
+    // (Two places that load a plain bias: in one, inside the loop, what every slice has in common is computed ahead of the first loads, 768 pairs
+    // of 49 tokens 4.56 us a call against 4.31, 3072 of 64 9.40 and 9.12.  A packed one has little of that and is better off with the shorter
+    // code: 2304 of 49 6.77 against 7.25, 3072 7.42 and 7.77.)
+    if (PLAIN) {
         load_slice(p.s_idx);
+        for (;;) {
+            run_slice();
+            if (t >= t1) break;
+            load_slice(p.s_idx);
+        }
+    } else {
+        while (t < t1) {
+            load_slice(p.s_idx);
+            run_slice();
+        }
     }
     if (have_prev && row < N) *(v4i*)(a.O + o_prev_off + o_lane) = o_prev;
 }
