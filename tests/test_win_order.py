@@ -11,11 +11,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2604_25306_amd", "csrc")
 SHIM = """
 #include <cstring>
-#include "qflash_internal.h"
+#include "qflash_win_order.h"
 extern "C" unsigned divide(unsigned n, unsigned d, unsigned* rest) { return qflash_divide(n, d, qflash_reciprocal(d), rest); }
 extern "C" int small(int n, unsigned d) { return qflash_small_quotient(n, qflash_small_reciprocal(d)); }
 extern "C" unsigned pieces(int N) { static QflashKernelArgs a; a.N = N; a.B = a.H = 1; qflash_cu_reciprocals(&a); return a.cu_inv_per; }
-extern "C" void order(int bias, int mask, int bias_B, int bias_H, int B, int H, unsigned* out) {
+static QflashKernelArgs launch(int bias, int mask, int bias_B, int bias_H, int B, int H) {
     static QflashKernelArgs a;
     std::memset(&a, 0, sizeof a);
     static const int32_t some_bias = 0;
@@ -23,8 +23,17 @@ extern "C" void order(int bias, int mask, int bias_B, int bias_H, int B, int H, 
     a.bias = bias ? &some_bias : nullptr; a.dyn_mask = mask ? &some_mask : nullptr;
     a.bias_B = bias_B; a.bias_H = bias_H; a.B = B; a.H = H;
     qflash_win_order(&a);
-    const unsigned all[] = {(unsigned)a.win_rb, (unsigned)a.win_rh, a.win_inv_r, a.win_inv_rh, a.win_inv_bh};
-    std::memcpy(out, all, sizeof all);
+    return a;
+}
+// pair, slice and pairs left in the slice of position t, as a run finds them that starts there (from = t) or earlier
+extern "C" void walk(int bias, int mask, int bias_B, int bias_H, int B, int H, int from, int n, long long* out) {
+    const QflashKernelArgs a = launch(bias, mask, bias_B, bias_H, B, H);
+    const WinOrder order(a, bias || mask);
+    WinPair p = order.at(from);
+    for (int k = 0; k < n; ++k, out += 3) {
+        out[0] = order.pair_index(p); out[1] = p.s_idx; out[2] = order.left_in_slice(p);
+        if (k + 1 < n) order.advance(p);
+    }
 }
 """
 
@@ -63,24 +72,42 @@ def test_small_quotients(lib):
         assert all(x * inv >> 32 == x // per for x in list(range(64 * per)) + [2 ** 24])
 
 
-@pytest.mark.parametrize("bias,mask,bias_B,bias_H,B,H", [(1, 0, 4, 3, 12, 6), (0, 1, 4, 1, 4, 5), (1, 1, 1, 6, 7, 6), (0, 0, 1, 1, 5, 3), (0, 0, 9, 9, 5, 3)])
-def test_every_pair_once(lib, bias, mask, bias_B, bias_H, B, H):
-    out = (ctypes.c_uint * 5)()
-    lib.order(bias, mask, bias_B, bias_H, B, H, out)
+def walk(lib, launch, start, n):
+    out = (ctypes.c_longlong * (3 * n))()
+    lib.walk(*launch, start, n, out)
+    return [tuple(out[3 * k:3 * k + 3]) for k in range(n)]
+
+
+def expected(bias, mask, bias_B, bias_H, B, H, t):
+    """Position t of the order, from what it is meant to be: by slice (window, head of the bias), then batch step, then head step."""
     if not (bias or mask):
         bias_B = bias_H = 1                        # (extents of no bias count for nothing)
-    rb, rh = B // bias_B, H // bias_H
-    assert list(out) == [rb, rh] + [(2 ** 32 - 1) // d for d in (rb * rh, rh, bias_H)]
-    rest, seen = ctypes.c_uint(), []
+    rh, r = H // bias_H, (B // bias_B) * (H // bias_H)
+    s, k = divmod(t, r)
+    b, h = s // bias_H + k // rh * bias_B, s % bias_H + k % rh * bias_H
+    return b * H + h, s, r - k
 
-    def divide(n, d):
-        return lib.divide(n, d, ctypes.byref(rest)), rest.value
 
-    for t in range(B * H):
-        s, r = divide(t, rb * rh)
-        i, j = divide(r, rh)
-        wb, hb = divide(s, bias_H)
-        b, h = wb + i * bias_B, hb + j * bias_H
-        assert (b % bias_B) * bias_H + h % bias_H == s       # pairs of a slice one after the other
-        seen.append(b * H + h)
-    assert sorted(seen) == list(range(B * H))
+CASES = [(1, 0, 4, 3, 12, 6), (0, 1, 4, 1, 4, 5), (1, 1, 1, 6, 7, 6), (0, 0, 1, 1, 5, 3), (0, 0, 9, 9, 5, 3), (1, 0, 1, 1, 1, 1), (1, 0, 8, 2, 8, 2),
+         (1, 0, 3, 2, 9, 8)]
+
+
+@pytest.mark.parametrize("launch", CASES)
+def test_every_pair_once(lib, launch):
+    B, H = launch[4:]
+    want = [expected(*launch, t) for t in range(B * H)]
+    assert sorted(w[0] for w in want) == list(range(B * H))
+    if launch[0] or launch[1]:
+        for pair, s, _ in want:                    # the slice is the one the pair's bias lies in
+            b, h = divmod(pair, H)
+            assert (b % launch[2]) * launch[3] + h % launch[3] == s
+    for start in range(B * H):                     # a run may start anywhere, and goes on over the ends of slices
+        assert walk(lib, launch, start, B * H - start) == want[start:]
+
+
+@pytest.mark.parametrize("launch", [(1, 0, 64, 3, 64 * 170000, 24), (1, 0, 65536, 1, 65536 * 16, 30), (0, 0, 0, 0, 2 ** 26 - 5, 31), (1, 0, 1, 7, 3 ** 17, 14)])
+def test_positions_of_the_largest_launches(lib, launch):
+    T = launch[4] * launch[5]
+    assert T < 2 ** 31
+    for start in (0, 1, T // 3, T // 2 - 2, T - 9):
+        assert walk(lib, launch, start, 9) == [expected(*launch, t) for t in range(start, start + 9)]
