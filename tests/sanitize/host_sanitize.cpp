@@ -256,6 +256,8 @@ static void check_plan(const QflashKernelArgs& a, int d, int tile, int lds, int 
         CHECK(qflash_cu_lds_bytes(a.N, a.cu_heads, a.cu_table_lds) + (kind.from_floats ? kCuDynExtraLds : 0) <= (size_t)lds);
         if (!kind.from_floats) CHECK(a.cu_groups <= cus);        // one round of workgroups
         if (a.per_head) CHECK(a.cu_heads >= 2 && a.N > 64);
+        // (what the launch asks for: the reciprocal of nblk exact for every unit, products of two numbers of pairs in 32 bits)
+        CHECK((long long)a.cu_heads * nblk * nblk < 65536 && (!a.per_head || pairs < 65536));
         if (kind.static_table && tile == 128) CHECK(a.cu_heads > 1);
         CHECK(info.units == a.cu_groups && info.workgroups == a.cu_groups && info.query_blocks == nblk);
     } else {
