@@ -124,7 +124,8 @@ static_assert(offsetof(QflashLaunchArgs, hc_dev) % 64 == 0 && sizeof(QflashLaunc
 #endif
 
 // n / d and n % d for 0 <= n < 2^32, d >= 1, with the reciprocal inv = floor((2^32 - 1) / d): the high word of n inv is the
-// quotient or one less.  (Uniform in the kernels: five scalar instructions, where the division is two dozen vector ones in a chain.)
+// quotient or one less.  (Where n is the same for a wavefront nine scalar instructions, otherwise, as where the whole-compute-unit kernel
+// deals out the pairs of heads, as many vector ones; the division is two dozen vector ones in a chain.)
 QF_UNIT_HD inline unsigned qflash_reciprocal(unsigned d) { return 0xffffffffu / d; }
 QF_UNIT_HD inline unsigned qflash_divide(unsigned n, unsigned d, unsigned inv, unsigned* rest) {
     unsigned q = (unsigned)(((unsigned long long)n * inv) >> 32), r = n - q * d;
