@@ -25,8 +25,8 @@
 // every wavefront has data, five units for sixteen wavefronts at the end.
 //
 // A workgroup requests its first tile when a wavefront has found out what to request; the quotients it needs for that are made with reciprocals
-// from the host (or counted up), not by division: 768 pairs of 197 tokens 15.0 -> 14.7 us, per head, where two were of 64 bits, 18.7 -> 18.0
-// and 20.8 -> 19.4 with tiles of 128, 180 of 256 from the static entry point 9.6 -> 8.9.
+// from the host (or counted up), not by division: 768 pairs of 197 tokens 15.55 -> 15.2 us a call, per head, where two were of 64 bits, 18.9 -> 18.5
+// and 21.0 -> 19.7 with tiles of 128, 180 of 256 from the static entry point 9.55 -> 9.35.
 //
 // KV tiles of 128: more than 128 registers leave three wavefronts to a SIMD, so workgroups are at most twelve; still ahead of
 // the resident kernel (768 pairs of 197 tokens 22.8 -> 18.6 us, 480 of 256 19.4 -> 15.0, 720 of 130 16.8 -> 12.4).

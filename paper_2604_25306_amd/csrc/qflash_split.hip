@@ -25,7 +25,7 @@
 // of P V takes afterwards.  Two 32-key blocks per wavefront rather than one: a tile of 64 keys is then
 // local to a wavefront and the chain reads half as many parts.  The weight table, where it is used,
 // lands in LDS by direct loads beside the operands (four to a setting of M0: +0.1 us instead of +0.3).
-// Measured (us per launch, HIP graph, before -> after): N = 197, 3 pairs 7.9 -> 4.5, 48 pairs 8.1 -> 5.7;
+// Measured (us per launch, HIP graph, before -> after): N = 197, 3 pairs 7.9 -> 4.5 (4.2 with the short arguments), 48 pairs 8.1 -> 5.7;
 // N = 577, 12 pairs 12.6 -> 7.4; N = 1025, 3 pairs 19.7 -> 10.0; d = 32, N = 1000, 4 pairs 25 -> 7.7.
 #include <hip/hip_runtime.h>
 #include <stddef.h>

@@ -20,8 +20,8 @@
 // Keys beyond the sequence and excluded pairs carry a large negative accumulator input
 // (-2^29 before the offset), far below every real score, so they fall out of the maximum and get
 // weight 0 without a test.  Scores carry the offset 2^30 (see qflash_tile.h), which turns the
-// table index into one saturating subtraction.  12288 pairs of 49 tokens, bias packed: 19.2 -> 17.8 us with the
-// normalisation and packing on the float units; 77 MB, 14.9 us at the rate of a copy.
+// table index into one saturating subtraction.  12288 pairs of 49 tokens, bias packed, a call: 19.2 -> 18.1 us with
+// the normalisation and packing on the float units, 17.5 with the first requests early (below); 77 MB, 14.9 at the rate of a copy.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
